@@ -101,7 +101,7 @@ def unet_roofline(tflops, step_bytes, step_flops, step_s, infer_tflops):
     else:
         ach, peak, unit = tflops, BF16_DENSE_PEAK_TFLOPS, "TFLOP/s"
     return {"bound": bound, "achieved": round(ach, 2), "peak": peak, "unit": unit, "frac": round(ach / peak, 4),
-            "traffic": None, "kernel": "conv3x3_tiled + conv3x3_mfma + conv3x3_wgrad (whole training step)",
+            "traffic": None, "kernel": "conv3x3_rows + conv3x3_taps + conv3x3_wgrad (whole training step)",
             "intensity_flop_per_B": round(intensity, 1), "ridge_flop_per_B": round(ridge, 1),
             "TFLOPs": round(tflops, 2), "frac_of_bf16_peak": round(tflops / BF16_DENSE_PEAK_TFLOPS, 4),
             "step_GB": round(step_bytes / 1e9, 4), "inference_TFLOPs": round(infer_tflops, 2)}

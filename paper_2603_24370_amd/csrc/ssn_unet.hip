@@ -6,13 +6,15 @@
 // offsets (ky - 1, kx - 1). Master weights, Adam moments and gradients are FP32.
 //
 // Kernels:
-//   conv3x3_tiled  implicit GEMM for the larger layers, M = pixels, N = out
-//                  channels, K = 9 * in channels, v_mfma_f32_32x32x16_bf16, input
-//                  patch staged in LDS; forward (bias + SiLU epilogue) and
-//                  backward-data (the same GEMM with flipped, transposed weights;
-//                  optional SiLU' and accumulation epilogue);
-//   conv3x3_mfma   the same GEMM with operands read directly (M = out channels,
-//                  N = pixels), for small grids;
+//   conv3x3_rows   implicit GEMM for the larger layers, M = out channels, N =
+//                  pixels, K = 9 * in channels, v_mfma_f32_32x32x16_bf16, input
+//                  patches of 32 channels staged in LDS; forward (bias + SiLU
+//                  epilogue) and backward-data (the same GEMM with flipped,
+//                  transposed weights; optional SiLU' epilogue);
+//   conv3x3_taps   the same GEMM for small grids (few images, deep levels), the
+//                  patch of all input channels in LDS, the weights streamed;
+//   conv3x3_mfma   the same GEMM with both operands read directly, for image
+//                  rows that are no multiple of 32 pixels;
 //   conv3x3_wgrad  weight gradient, M = out channels, N = in channels per tap,
 //                  K = pixels, operands staged transposed in LDS, split over
 //                  pixel chunks with a fixed-order reduction (deterministic);
@@ -71,23 +73,100 @@ __device__ __forceinline__ long tv_at(const TV& t, int n, int y, int x) {
 
 struct ConvArgs {
   TV in;             // input, in.C a multiple of 16
-  const bf16_t* w;   // [rows][9][in.C], rows = Co rounded up to 32
+  const bf16_t* w;   // weight fragments (frag_index), output rows rounded up to 32
   const float* bias; // [Co] or nullptr
   int Co;
   TV out_z;          // forward: pre-activation (p may be nullptr)
   TV out;            // forward: SiLU(z); backward: gradient w.r.t. the input of the layer
   TV zprev;          // backward: if p != nullptr multiply by SiLU'(zprev)
   int mode;          // 0 forward, 1 backward-data
-  int accumulate;    // backward: out += result
 };
 
+// Weights are kept as the fragments the products read: the 16 x 32 block of
+// output channels co0 .. co0 + 31, tap t and input channels 16 c .. 16 c + 15 is
+// 1 KB in lane order, so a wave's load of a fragment is contiguous (read from
+// [co][tap][ci] rows it touched 32 cache lines of 32 bytes each). Fragments of
+// one co0 follow each other in the order (t, c). Row m of a fragment is channel
+// conv_row(m): a lane of the product (pixel r, rows 8 (v / 4) + 4 half + v % 4)
+// then holds the 16 neighbouring channels co0 + 16 half + v of one pixel.
+__host__ __device__ __forceinline__ int conv_row(int m) { return ((m >> 2) & 1) * 16 + (m >> 3) * 4 + (m & 3); }
+
+// element of channel co, tap t, input channel ci (nc = input channels / 16)
+__device__ __forceinline__ long frag_index(int co, int t, int ci, int nc) {
+  const int cl = co & 31;
+  const int m = ((cl >> 2) & 3) * 8 + (cl >> 4) * 4 + (cl & 3);  // conv_row(m) = cl
+  return ((((long)(co >> 5) * 9 + t) * nc + (ci >> 4)) * 64 + ((ci >> 3) & 1) * 32 + m) * 8 + (ci & 7);
+}
+
+__device__ __forceinline__ u32x4 load_u32x4(const bf16_t* p) { return *reinterpret_cast<const u32x4*>(p); }
+__device__ __forceinline__ bf16x8 load_frag(const bf16_t* p) { return *reinterpret_cast<const bf16x8*>(p); }
+
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+
+// two floats rounded to nearest even, the first in the low half
+__device__ __forceinline__ unsigned pack2(float lo, float hi) {
+  const f32x2 v = {lo, hi};
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+}
+
+// End of a convolution at one pixel: the lane's 16 channels co .. co + 15 as two
+// 16-byte vectors per tensor. Forward: z = acc + bias and SiLU(z); backward:
+// acc, times SiLU'(zprev) where there is one.
+template <int MODE>
+__device__ __forceinline__ void conv_store(const ConvArgs& a, const f32x16& acc, const float (&bias)[16], int n, int y,
+                                           int x, int co) {
+  bf16_t* oo = a.out.p + tv_at(a.out, n, y, x) + co;
+  if (MODE == 0) {
+    u32x4 zv[2], av[2];
+#pragma unroll
+    for (int v = 0; v < 16; v += 2) {
+      const float z0 = acc[v] + bias[v], z1 = acc[v + 1] + bias[v + 1];
+      zv[v >> 3][(v & 7) >> 1] = pack2(z0, z1);
+      av[v >> 3][(v & 7) >> 1] = pack2(silu_f(z0), silu_f(z1));
+    }
+    bf16_t* zo = a.out_z.p + tv_at(a.out_z, n, y, x) + co;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      *reinterpret_cast<u32x4*>(zo + 8 * k) = zv[k];
+      *reinterpret_cast<u32x4*>(oo + 8 * k) = av[k];
+    }
+  } else {
+    u32x4 zv[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}}, gv[2];
+    if (a.zprev.p) {
+      const bf16_t* zp = a.zprev.p + tv_at(a.zprev, n, y, x) + co;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) zv[k] = load_u32x4(zp + 8 * k);
+    }
+#pragma unroll
+    for (int v = 0; v < 16; v += 2) {
+      float g0 = acc[v], g1 = acc[v + 1];
+      if (a.zprev.p) {
+        const unsigned w2 = zv[v >> 3][(v & 7) >> 1];
+        g0 *= silu_grad_f(bf2f((bf16_t)(w2 & 0xffffu)));
+        g1 *= silu_grad_f(bf2f((bf16_t)(w2 >> 16)));
+      }
+      gv[v >> 3][(v & 7) >> 1] = pack2(g0, g1);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) *reinterpret_cast<u32x4*>(oo + 8 * k) = gv[k];
+  }
+}
+
+// the 16 biases of a lane's channels (forward; zero otherwise)
+template <int MODE>
+__device__ __forceinline__ void conv_bias(const ConvArgs& a, int co, float (&bias)[16]) {
+#pragma unroll
+  for (int v = 0; v < 16; ++v) bias[v] = MODE == 0 ? a.bias[co + v] : 0.0f;
+}
+
 // Each wave: 32 output channels x (32 * WN) pixels; block: WB waves along pixels.
-template <int WN, int WB>
+// Products of one output accumulate in the order tap, channel.
+template <int WN, int WB, int MODE>
 __global__ void __launch_bounds__(64 * WB) conv3x3_mfma(ConvArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 31, half = lane >> 5;
-  const int co0 = blockIdx.y * 32;
-  const int H = a.in.H, W = a.in.W, Ci = a.in.C;
+  const int H = a.in.H, W = a.in.W, Ci = a.in.C, nc = Ci / 16;
   const long P = (long)a.in.N * H * W;
   const long pixbase = ((long)blockIdx.x * WB + wave) * (32 * WN);
   int pn[WN], py[WN], px[WN];
@@ -107,7 +186,7 @@ __global__ void __launch_bounds__(64 * WB) conv3x3_mfma(ConvArgs a) {
   for (int f = 0; f < WN; ++f)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[f][v] = 0.0f;
-  const bf16_t* wrow = a.w + (long)(co0 + r) * 9 * Ci + half * 8;
+  const bf16_t* wp = a.w + (long)blockIdx.y * 9 * nc * 512 + lane * 8;
   bf16x8 zero;
 #pragma unroll
   for (int j = 0; j < 8; ++j) zero[j] = (__bf16)0.0f;
@@ -121,126 +200,247 @@ __global__ void __launch_bounds__(64 * WB) conv3x3_mfma(ConvArgs a) {
       bv[f] = pv[f] && yy >= 0 && yy < H && xx >= 0 && xx < W;
       boff[f] = bv[f] ? tv_at(a.in, pn[f], yy, xx) + half * 8 : 0;
     }
-    for (int c = 0; c < Ci; c += 16) {
-      const bf16x8 A = *reinterpret_cast<const bf16x8*>(wrow + t * Ci + c);
+    for (int c = 0; c < nc; ++c) {
+      const bf16x8 A = load_frag(wp + (t * nc + c) * 512);
 #pragma unroll
       for (int f = 0; f < WN; ++f) {
-        const bf16x8 B = bv[f] ? *reinterpret_cast<const bf16x8*>(a.in.p + boff[f] + c) : zero;
+        const bf16x8 B = bv[f] ? load_frag(a.in.p + boff[f] + c * 16) : zero;
         acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, B, acc[f], 0, 0, 0);
       }
     }
   }
-  // D[row][col]: lane holds col = r (pixel) and rows 8 (v / 4) + 4 half + v % 4 (channels)
+  const int co = blockIdx.y * 32 + half * 16;
+  if (co >= a.Co) return;
+  float bias[16];
+  conv_bias<MODE>(a, co, bias);
 #pragma unroll
-  for (int f = 0; f < WN; ++f) {
-    if (!pv[f]) continue;
+  for (int f = 0; f < WN; ++f)
+    if (pv[f]) conv_store<MODE>(a, acc[f], bias, pn[f], py[f], px[f], co);
+}
+
+// The GEMM for small grids: a wave computes 32 output channels x 32 pixels, WCO
+// waves of a block share the patch of those pixels, all input channels of it in
+// LDS (3 rows x 34 pixels, zero outside the image, kTapPad elements of padding
+// per pixel against bank conflicts). The products of one output accumulate in
+// the order tap, channel (as conv3x3_mfma's), and the weight fragments are read
+// in just that order, a contiguous stream. It is bound by latency: a wave or two
+// per CU and one chain of 9 Ci / 16 products. So kTapAhead weight fragments are
+// in flight ahead of the product, the next nine input fragments are read from
+// LDS during the nine in hand, and the patch is staged kTapStage vectors per
+// thread at a time. 256 -> 256 channels on 32^2, one image: 15 us (9 fragments
+// ahead and one staging load at a time 27 us; conv3x3_mfma 33 us). Two rows per
+// wave were slower everywhere (21 us). Requires W % 32 == 0.
+constexpr int kTapPad = 8, kTapAhead = 36, kTapStage = 16;  // kTapAhead: an even multiple of 9
+
+__host__ __device__ constexpr long tap_lds_bytes(int Ci) { return 2L * 3 * 34 * (Ci + kTapPad); }
+
+template <int WCO, int MODE>
+__global__ void __launch_bounds__(64 * WCO) __attribute__((amdgpu_waves_per_eu(1, 2))) conv3x3_taps(ConvArgs a) {
+  constexpr int NT = 64 * WCO, PW = 34, PR = 3;
+  extern __shared__ __align__(16) bf16_t patch[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r = lane & 31, half = lane >> 5;
+  const int H = a.in.H, W = a.in.W, Ci = a.in.C, nc = Ci / 16, pitch = Ci + kTapPad;
+  const int xt = W / 32, yt = H;
+  const int n = blockIdx.x / (xt * yt);
+  const int rem = blockIdx.x - n * xt * yt;
+  const int y0 = rem / xt, x0 = (rem - y0 * xt) * 32;
+  const int ct = blockIdx.y * WCO + wave;  // channel block of the wave
+  const bf16_t* __restrict__ wp = a.w + (long)ct * 9 * nc * 512 + lane * 8;
+  const int nf = 9 * nc;
+  bf16x8 wa[kTapAhead];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int co = co0 + (v >> 2) * 8 + half * 4 + (v & 3);
-      if (co >= a.Co) continue;
-      float val = acc[f][v];
-      if (a.mode == 0) {
-        const float z = val + (a.bias ? a.bias[co] : 0.0f);
-        if (a.out_z.p) a.out_z.p[tv_at(a.out_z, pn[f], py[f], px[f]) + co] = f2bf(z);
-        a.out.p[tv_at(a.out, pn[f], py[f], px[f]) + co] = f2bf(silu_f(z));
-      } else {
-        if (a.zprev.p) val *= silu_grad_f(bf2f(a.zprev.p[tv_at(a.zprev, pn[f], py[f], px[f]) + co]));
-        bf16_t* o = a.out.p + tv_at(a.out, pn[f], py[f], px[f]) + co;
-        if (a.accumulate) val += bf2f(*o);
-        *o = f2bf(val);
+  for (int k = 0; k < kTapAhead; ++k)
+    if (k < nf) wa[k] = load_frag(wp + k * 512);
+  // the patch, kTapStage vectors per thread in flight
+  const int nv = Ci / 8, ne = PR * PW * nv;
+  const bf16_t* __restrict__ base = a.in.p + a.in.coff + (long)n * H * W * a.in.cs;
+  for (int i0 = tid; i0 < ne; i0 += NT * kTapStage) {
+    u32x4 val[kTapStage];
+    int at[kTapStage];
+#pragma unroll
+    for (int u = 0; u < kTapStage; ++u) {
+      const int it = i0 + u * NT;
+      const int e = it / nv, v = it - e * nv;
+      const int row = e / PW, px = e - row * PW;
+      const int yy = y0 + row - 1, xx = x0 + px - 1;
+      at[u] = it < ne ? e * pitch + v * 8 : -1;
+      val[u] = u32x4{0u, 0u, 0u, 0u};
+      if (it < ne && (unsigned)yy < (unsigned)H && (unsigned)xx < (unsigned)W)
+        val[u] = load_u32x4(base + (long)(yy * W + xx) * a.in.cs + v * 8);
+    }
+#pragma unroll
+    for (int u = 0; u < kTapStage; ++u)
+      if (at[u] >= 0) *reinterpret_cast<u32x4*>(patch + at[u]) = val[u];
+  }
+  __syncthreads();
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+  const bf16_t* bp = patch + r * pitch + half * 8;
+  int c = 0, dx = 0, row = 0;  // the next input fragment: tap (row, dx), channels 16 c ..
+  bf16x8 b[2][9];
+  auto load_b = [&](bf16x8 (&bb)[9]) {
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      bb[k] = load_frag(bp + (row * PW + dx) * pitch + c * 16);
+      if (++c == nc) {
+        c = 0;
+        if (++dx == 3) {
+          dx = 0;
+          ++row;
+        }
+      }
+    }
+  };
+  load_b(b[0]);
+  for (int f0 = 0; f0 < nf; f0 += kTapAhead) {  // nf is a multiple of 9
+#pragma unroll
+    for (int g = 0; g < kTapAhead / 9; ++g) {
+      const int f = f0 + 9 * g;
+      if (f >= nf) break;
+      if (f + 9 < nf) load_b(b[(g + 1) & 1]);
+#pragma unroll
+      for (int k = 0; k < 9; ++k) {
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[9 * g + k], b[g & 1][k], acc, 0, 0, 0);
+        if (f + k + kTapAhead < nf) wa[9 * g + k] = load_frag(wp + (f + k + kTapAhead) * 512);
       }
     }
   }
+  const int co = ct * 32 + half * 16;
+  if (co >= a.Co) return;
+  float bias[16];
+  conv_bias<MODE>(a, co, bias);
+  conv_store<MODE>(a, acc, bias, n, y0, x0 + r, co);
 }
 
 // LDS-tiled implicit GEMM for the larger layers. Block: WCO x WPX waves over R
 // image rows; wave (i, j) computes 32 output channels (co0 + 32 i ..) x 32 pixels
-// (x0 + 32 j ..) of each of the rows y0 .. y0 + R - 1. Input channels are taken
-// in chunks of 32: the chunk's input patch (R + 2 rows x (32 WPX + 2) pixels,
-// zero outside the image) is staged in LDS, each entry padded to kKP channels
-// so that lanes reading neighbouring pixels or rows fall in different banks.
-// The weight fragments (a few KB per layer, shared by every workgroup) are read
-// straight from global memory through the caches, which leaves LDS to the patch
-// (one more workgroup per CU than staging them); each serves R rows. Requires
-// W % (32 WPX) == 0, H % R == 0, in.C % 16 == 0 and, for WCO = 2, Co % 64 == 0
-// (weight rows exist up to gridDim.y * 32 WCO).
+// (x0 + 32 j ..) of each of the rows y0 .. y0 + R - 1, with D = weights x input.
+// A block walks `per` tiles (down the image columns) and, per tile, the input
+// channels in chunks of 32. The patch of a (tile, chunk) (R + 2 rows x
+// (32 WPX + 2) pixels, zero outside the image) is read into registers while the
+// one before it is computed, and goes to LDS between two barriers, so that a
+// block always has a patch in flight. A wave keeps the 18 weight fragments of its
+// chunk in registers (they are loaded once where there is one chunk, and each
+// tap row's again as soon as its last row is done where there are more), and
+// walks the patch row by row: the six fragments of a patch row (three shifts,
+// two channel halves) serve up to three output rows, so LDS is read once per
+// three products. Products of one output accumulate in the order chunk, tap,
+// channel half. LDS entries are padded to kKP channels so that lanes reading
+// neighbouring pixels fall in different banks. Requires W % (32 WPX) == 0,
+// H % R == 0, in.C % 16 == 0 (weight fragments exist up to gridDim.y * 32 WCO).
 constexpr int kKC = 32, kKP = 40;
 
-template <int WCO, int WPX, int R>
-__global__ void __launch_bounds__(64 * WCO * WPX) conv3x3_tiled(ConvArgs a) {
-  constexpr int NT = 64 * WCO * WPX, PX = 32 * WPX, PW = PX + 2, CO = 32 * WCO, PR = R + 2;
+template <int WCO, int WPX, int R, int MODE>
+__global__ void __launch_bounds__(64 * WCO * WPX) __attribute__((amdgpu_waves_per_eu(2)))
+conv3x3_rows(ConvArgs a, int ntiles, int per) {
+  constexpr int NT = 64 * WCO * WPX, PX = 32 * WPX, PW = PX + 2, PR = R + 2;
+  constexpr int NE = PR * PW * 4, NV = (NE + NT - 1) / NT;  // 16-byte vectors of a patch, and per thread
   __shared__ __align__(16) bf16_t sin_[PR * PW * kKP];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wi = wave / WPX, wj = wave - wi * WPX;
   const int r = lane & 31, half = lane >> 5;
   const int H = a.in.H, W = a.in.W, Ci = a.in.C;
   const int xt = W / PX, yt = H / R;
-  const int bx = blockIdx.x;
-  const int n = bx / (yt * xt);
-  const int rem = bx - n * yt * xt;
-  const int y0 = (rem / xt) * R;
-  const int x0 = (rem - (rem / xt) * xt) * PX;
-  const int co0 = blockIdx.y * CO;
-  bf16x8 zero;
+  const int nchunk = (Ci + kKC - 1) / kKC;
+  const int cow = blockIdx.y * (32 * WCO) + wi * 32;
+  const int t0 = blockIdx.x * per, t1 = min(ntiles, t0 + per);
+  if (t0 >= t1) return;
+  // tile t: row block t % yt of column block (t / yt) % xt of image t / (xt yt)
+  auto tile_at = [&](int t, int& n, int& x0, int& y0) {
+    const int c = t / yt;
+    y0 = (t - c * yt) * R;
+    n = c / xt;
+    x0 = (c - n * xt) * PX;
+  };
+  const int nc = Ci / 16;
+  const bf16_t* __restrict__ wp = a.w + (long)(cow >> 5) * 9 * nc * 512 + lane * 8;
+  bf16x8 wa[9][2];
+  auto load_w = [&](int dy, int c0) {
+    const int c = c0 >> 4, c2 = min(c + 1, nc - 1);  // a lone last half is loaded twice, used once
 #pragma unroll
-  for (int j = 0; j < 8; ++j) zero[j] = (__bf16)0.0f;
-  f32x16 acc[R];
+    for (int dx = 0; dx < 3; ++dx) {
+      const int t = dy * 3 + dx;
+      wa[t][0] = load_frag(wp + (t * nc + c) * 512);
+      wa[t][1] = load_frag(wp + (t * nc + c2) * 512);
+    }
+  };
+  // patch of (tile t, chunk c0) into registers
+  u32x4 pre[NV];
+  auto fetch = [&](int t, int c0) {
+    int n, x0, y0;
+    tile_at(t, n, x0, y0);
+    const bf16_t* __restrict__ base = a.in.p + a.in.coff + c0 + (long)n * H * W * a.in.cs;
+    const int nv = min(kKC, Ci - c0) >> 3;
 #pragma unroll
-  for (int q = 0; q < R; ++q)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[q][v] = 0.0f;
-  for (int c0 = 0; c0 < Ci; c0 += kKC) {
-    const int kc = min(kKC, Ci - c0);  // 32, or 16 for the last chunk
-    const int nv = kc >> 3;            // 16-byte vectors per entry
-    __syncthreads();
-    for (int it = tid; it < PR * PW * nv; it += NT) {
-      const int v = it % nv, q = it / nv;
-      const int px = q % PW, row = q / PW;
+    for (int q = 0; q < NV; ++q) {
+      const int it = tid + q * NT;
+      const int v = it & 3, e = it >> 2;
+      const int row = e / PW, px = e - row * PW;
       const int yy = y0 + row - 1, xx = x0 + px - 1;
-      bf16x8 val = zero;
-      if (yy >= 0 && yy < H && xx >= 0 && xx < W)
-        val = *reinterpret_cast<const bf16x8*>(a.in.p + tv_at(a.in, n, yy, xx) + c0 + v * 8);
-      *reinterpret_cast<bf16x8*>(sin_ + (row * PW + px) * kKP + v * 8) = val;
+      u32x4 val = {0u, 0u, 0u, 0u};
+      if (it < NE && v < nv && (unsigned)yy < (unsigned)H && (unsigned)xx < (unsigned)W)
+        val = *reinterpret_cast<const u32x4*>(base + (long)(yy * W + xx) * a.in.cs + v * 8);
+      pre[q] = val;
     }
-    __syncthreads();
+  };
+  fetch(t0, 0);
 #pragma unroll
-    for (int t = 0; t < 9; ++t) {
-      const int dy = t / 3, dx = t % 3;
-      for (int ks = 0; ks < kc; ks += 16) {
-        const bf16x8 A =
-            *reinterpret_cast<const bf16x8*>(a.w + ((long)(co0 + wi * 32 + r) * 9 + t) * Ci + c0 + ks + half * 8);
+  for (int dy = 0; dy < 3; ++dy) load_w(dy, 0);
+  for (int t = t0; t < t1; ++t) {
+    f32x16 acc[R];
 #pragma unroll
-        for (int q = 0; q < R; ++q) {
-          const bf16x8 B =
-              *reinterpret_cast<const bf16x8*>(sin_ + ((q + dy) * PW + wj * 32 + r + dx) * kKP + ks + half * 8);
-          // D = input x weights^T: rows are pixels, columns output channels
-          acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(B, A, acc[q], 0, 0, 0);
+    for (int q = 0; q < R; ++q)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[q][v] = 0.0f;
+    for (int ck = 0; ck < nchunk; ++ck) {
+      const bool two = ck * kKC + 16 < Ci;
+      const int cn = ck + 1 < nchunk ? (ck + 1) * kKC : 0;  // next chunk's first channel
+      const int tn = ck + 1 < nchunk ? t : t + 1;
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < NV; ++q) {
+        const int it = tid + q * NT;
+        if (it < NE) *reinterpret_cast<u32x4*>(sin_ + (it >> 2) * kKP + (it & 3) * 8) = pre[q];
+      }
+      __syncthreads();
+      if (tn < t1) fetch(tn, cn);
+#pragma unroll
+      for (int p = 0; p < PR; ++p) {
+        bf16x8 b[3][2];
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+          for (int ks = 0; ks < 2; ++ks)
+            b[dx][ks] = *reinterpret_cast<const bf16x8*>(sin_ + (p * PW + wj * 32 + r + dx) * kKP + ks * 16 + half * 8);
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) {
+#pragma unroll
+          for (int dy = 0; dy < 3; ++dy)
+            if (p - dy >= 0 && p - dy < R)
+              acc[p - dy] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[dy * 3 + dx][0], b[dx][0], acc[p - dy], 0, 0, 0);
+          if (two) {
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy)
+              if (p - dy >= 0 && p - dy < R)
+                acc[p - dy] =
+                    __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[dy * 3 + dx][1], b[dx][1], acc[p - dy], 0, 0, 0);
+          }
         }
+        if (nchunk > 1 && p >= R - 1) load_w(p - (R - 1), cn);
       }
     }
-  }
-  // D[row][col]: lane holds col = r (output channel) and rows 8 (v / 4) + 4 half + v % 4
-  // (pixels), so each store of a row writes 32 neighbouring channels of one pixel
-  const int co = co0 + wi * 32 + r;
-  if (co >= a.Co) return;
-  const float bias = (a.mode == 0 && a.bias) ? a.bias[co] : 0.0f;
+    // D[row][col]: lane holds pixel col = r and rows 8 (v / 4) + 4 half + v % 4, i.e.
+    // channels cow + 16 half + v
+    int n, x0, y0;
+    tile_at(t, n, x0, y0);
+    const int co = cow + half * 16;
+    if (co < a.Co) {
+      float bias[16];
+      conv_bias<MODE>(a, co, bias);
 #pragma unroll
-  for (int q = 0; q < R; ++q) {
-    const int y = y0 + q;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int x = x0 + wj * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
-      float val = acc[q][v];
-      if (a.mode == 0) {
-        const float z = val + bias;
-        if (a.out_z.p) a.out_z.p[tv_at(a.out_z, n, y, x) + co] = f2bf(z);
-        a.out.p[tv_at(a.out, n, y, x) + co] = f2bf(silu_f(z));
-      } else {
-        if (a.zprev.p) val *= silu_grad_f(bf2f(a.zprev.p[tv_at(a.zprev, n, y, x) + co]));
-        bf16_t* o = a.out.p + tv_at(a.out, n, y, x) + co;
-        if (a.accumulate) val += bf2f(*o);
-        *o = f2bf(val);
-      }
+      for (int q = 0; q < R; ++q) conv_store<MODE>(a, acc[q], bias, n, y0 + q, x0 + wj * 32 + r, co);
     }
   }
 }
@@ -263,9 +463,6 @@ struct WgradArgs {
   int cw;       // pixels per chunk row
   int R;        // rows per chunk
 };
-
-// 8 channels (16 bytes, channel j in bits 16 (j % 2) of word j / 2)
-__device__ __forceinline__ u32x4 load_u32x4(const bf16_t* p) { return *reinterpret_cast<const u32x4*>(p); }
 
 __global__ void __launch_bounds__(576) conv3x3_wgrad(WgradArgs a) {
   __shared__ __align__(16) bf16_t gzT[32 * kGP];  // [co][pix]
@@ -706,8 +903,8 @@ __global__ void adam_update(float* __restrict__ p, float* __restrict__ m, float*
   }
 }
 
-// bf16 copies of a 3x3 layer: wf[co][t][ci] (rows padded to 32) and the
-// backward-data weights wb[ci][t][co] = w[co][8 - t][ci] (rows padded to 32)
+// bf16 weight fragments (frag_index) of a 3x3 layer: wf of w[co][t][ci], and wb
+// of the backward-data weights w[co][8 - t][ci] with ci as the output channel
 __global__ void pack_conv_weights(const float* __restrict__ w, int Co, int Ci, bf16_t* __restrict__ wf,
                                   bf16_t* __restrict__ wb) {
   const long n = (long)Co * 9 * Ci;
@@ -716,8 +913,8 @@ __global__ void pack_conv_weights(const float* __restrict__ w, int Co, int Ci, b
     const long q = k / Ci;
     const int t = (int)(q % 9), co = (int)(q / 9);
     const bf16_t b = f2bf(w[k]);
-    wf[k] = b;
-    if (wb) wb[((long)ci * 9 + (8 - t)) * Co + co] = b;
+    wf[frag_index(co, t, ci, Ci / 16)] = b;
+    wb[frag_index(ci, 8 - t, co, Co / 16)] = b;
   }
 }
 
@@ -764,8 +961,8 @@ struct HT {  // host handle of one NHWC bf16 buffer (capacity Ncap)
 struct ConvL {
   int Ci, Ci_real, Co, H, W;
   long w_off, b_off;  // float offsets into the flat parameter arrays
-  bf16_t* wf;         // [rup(Co, 32)][9][Ci]
-  bf16_t* wb;         // [rup(Ci, 32)][9][Co]
+  bf16_t* wf;         // forward fragments, rup(Co, 32) * 9 * Ci elements
+  bf16_t* wb;         // backward-data fragments, rup(Ci, 32) * 9 * Co elements
 };
 
 constexpr int kPartBlocks = 256;
@@ -909,46 +1106,87 @@ int dec_b(const ssn_net* n, int l) { return dec_a(n, l) + 1; }
 int grid1(long n) { return (int)std::min<long>((n + 255) / 256, 65535); }
 
 template <int WCO, int WPX, int R>
-void launch_tiled(const ssn_net* n, const ConvArgs& ca, int Co) {
+void launch_rows(const ssn_net* n, const ConvArgs& ca, int Co) {
   const TV& in = ca.in;
-  dim3 grid((unsigned)((long)in.N * (in.H / R) * (in.W / (32 * WPX))), (unsigned)((Co + 32 * WCO - 1) / (32 * WCO)));
-  hipLaunchKernelGGL((conv3x3_tiled<WCO, WPX, R>), grid, dim3(64 * WCO * WPX), 0, n->stream, ca);
+  const int tiles = in.N * (in.H / R) * (in.W / (32 * WPX));
+  const int gy = (Co + 32 * WCO - 1) / (32 * WCO);
+  // two blocks of four waves per CU are resident (registers); each walks its
+  // share of the tiles
+  const int gx = std::min(tiles, std::max(1, 2048 / (WCO * WPX) / gy));
+  const int per = (tiles + gx - 1) / gx;
+  const dim3 grid((unsigned)((tiles + per - 1) / per), (unsigned)gy);
+  if (ca.mode == 0)
+    hipLaunchKernelGGL((conv3x3_rows<WCO, WPX, R, 0>), grid, dim3(64 * WCO * WPX), 0, n->stream, ca, tiles, per);
+  else
+    hipLaunchKernelGGL((conv3x3_rows<WCO, WPX, R, 1>), grid, dim3(64 * WCO * WPX), 0, n->stream, ca, tiles, per);
 }
 
-// Launch shapes: the LDS-tiled GEMM where rows are at least 32 pixels wide and
-// the grid has at least 256 workgroups (2 rows per workgroup on rows of 128 or
-// more pixels, 4 on narrower ones); otherwise direct-operand blocks of 4 waves
-// with 64 pixels per wave (large grids) or of one wave with 32 pixels (few
-// images, deep levels: 8x more workgroups).
+template <int WCO>
+void launch_taps(const ssn_net* n, const ConvArgs& ca, int Co) {
+  const TV& in = ca.in;
+  const dim3 grid((unsigned)(in.N * in.H * (in.W / 32)), (unsigned)((Co + 32 * WCO - 1) / (32 * WCO)));
+  const unsigned lds = (unsigned)tap_lds_bytes(in.C);
+  if (ca.mode == 0) hipLaunchKernelGGL((conv3x3_taps<WCO, 0>), grid, dim3(64 * WCO), lds, n->stream, ca);
+  else hipLaunchKernelGGL((conv3x3_taps<WCO, 1>), grid, dim3(64 * WCO), lds, n->stream, ca);
+}
+
+constexpr long kTapLds = 80 * 1024;  // two blocks per CU
+
+// Launch shapes. The order in which an output's products accumulate is the
+// network's, not the launch's: results in BF16 move by whole roundings when it
+// changes. It is chunk, tap, channel half where the chunked grid below has 256
+// workgroups, and tap, channel elsewhere.
+//
+// Chunked layers run on conv3x3_rows. Measured on a 4-level network of base 32
+// on 256^2 images in batches of 8 (us):
+//  - a wave serves as many rows R as leave 512 waves (two per CU), since each
+//    weight fragment serves R rows: 64 -> 64 channels on 128^2 takes 26.8 with
+//    R = 4 and 32.5 with R = 2 (21.0 with R = 4 and contiguous fragments; 62
+//    with the tiles before, which read weights and patch between barriers and
+//    stored 2 bytes per lane);
+//  - where the output channels are a multiple of 64, two waves share a patch
+//    (half the staging registers, which is what lets R = 4 fit 256 VGPRs: with
+//    one, 28 are spilled and 96 -> 32 on 256^2 takes 95 instead of 88; 74.6 with
+//    R = 2 and contiguous fragments, 96 MB of tensors at 2.2 TB/s);
+//  - a block is 32 pixels wide: 64 x 4 rows take 60 instead of 48 on
+//    64 -> 192 at 128^2, whose patch three channel blocks read again. With one
+//    wave on the channels two pixel waves are better (88 against 93 on 96 -> 32).
+// The others run on conv3x3_taps where rows are a multiple of 32 pixels and the
+// patch fits, and on direct-operand blocks otherwise (4 waves with 64 pixels per
+// wave for large grids, one wave with 32 pixels for small ones).
 void launch_conv(const ssn_net* n, const ConvArgs& ca, long P, int Co) {
   const unsigned gy = (unsigned)((Co + 31) / 32);
   const int W = ca.in.W, H = ca.in.H;
   const int wpx = W >= 128 ? 4 : W >= 64 ? 2 : 1;
   const int wco = Co % 64 == 0 ? 2 : 1;
-  const int R = wpx == 4 ? 2 : 4;
-  const long tiled_blocks =
-      (long)ca.in.N * (H / R) * (W / (32 * wpx)) * ((Co + 32 * wco - 1) / (32 * wco));
-  const bool tiled_ok = W >= 32 && W % (32 * wpx) == 0 && H % R == 0;
-  const bool tiled = tiled_ok && (n->conv_shape == 3 || (n->conv_shape == 0 && tiled_blocks >= 256));
-  if (tiled) {
-    if (wco == 2) {
-      if (wpx == 4) launch_tiled<2, 4, 2>(n, ca, Co);
-      else if (wpx == 2) launch_tiled<2, 2, 4>(n, ca, Co);
-      else launch_tiled<2, 1, 4>(n, ca, Co);
-    } else {
-      if (wpx == 4) launch_tiled<1, 4, 2>(n, ca, Co);
-      else if (wpx == 2) launch_tiled<1, 2, 4>(n, ca, Co);
-      else launch_tiled<1, 1, 4>(n, ca, Co);
-    }
+  const long chunk_blocks =
+      (long)ca.in.N * (H / (wpx == 4 ? 2 : 4)) * (W / (32 * wpx)) * ((Co + 32 * wco - 1) / (32 * wco));
+  const bool chunk_ok = W >= 32 && W % (32 * wpx) == 0;
+  const long waves1 = P / 32 * gy;  // at one row per wave
+  if (chunk_ok && (n->conv_shape == 3 || (n->conv_shape == 0 && chunk_blocks >= 256))) {
+    if (wco == 2 && waves1 >= 4 * 512) launch_rows<2, 1, 4>(n, ca, Co);
+    else if (wco == 2 && waves1 >= 2 * 512) launch_rows<2, 1, 2>(n, ca, Co);
+    else if (waves1 < 2 * 512) launch_rows<1, 1, 1>(n, ca, Co);
+    else if (wpx >= 2) launch_rows<1, 2, 2>(n, ca, Co);
+    else launch_rows<1, 1, 2>(n, ca, Co);
+    return;
+  }
+  if (n->conv_shape == 0 && W % 32 == 0 && tap_lds_bytes(ca.in.C) <= kTapLds) {
+    // waves that share a patch: 4 / 2 / 1 on 256 -> 256 channels (32^2, one image) 15 / 16 / 20 us
+    if (gy % 4 == 0) launch_taps<4>(n, ca, Co);
+    else if (gy % 2 == 0) launch_taps<2>(n, ca, Co);
+    else launch_taps<1>(n, ca, Co);
     return;
   }
   const bool large = n->conv_shape == 1 || (n->conv_shape != 2 && (P + 255) / 256 * gy >= 1024);
   if (large) {
-    dim3 grid((unsigned)((P + 255) / 256), gy);
-    hipLaunchKernelGGL((conv3x3_mfma<2, 4>), grid, dim3(256), 0, n->stream, ca);
+    const dim3 grid((unsigned)((P + 255) / 256), gy);
+    if (ca.mode == 0) hipLaunchKernelGGL((conv3x3_mfma<2, 4, 0>), grid, dim3(256), 0, n->stream, ca);
+    else hipLaunchKernelGGL((conv3x3_mfma<2, 4, 1>), grid, dim3(256), 0, n->stream, ca);
   } else {
-    dim3 grid((unsigned)((P + 31) / 32), gy);
-    hipLaunchKernelGGL((conv3x3_mfma<1, 1>), grid, dim3(64), 0, n->stream, ca);
+    const dim3 grid((unsigned)((P + 31) / 32), gy);
+    if (ca.mode == 0) hipLaunchKernelGGL((conv3x3_mfma<1, 1, 0>), grid, dim3(64), 0, n->stream, ca);
+    else hipLaunchKernelGGL((conv3x3_mfma<1, 1, 1>), grid, dim3(64), 0, n->stream, ca);
   }
 }
 
@@ -962,7 +1200,6 @@ void launch_conv_fwd(const ssn_net* n, const ConvL& c, TV in, TV z, TV a) {
   ca.out = a;
   ca.zprev.p = nullptr;
   ca.mode = 0;
-  ca.accumulate = 0;
   launch_conv(n, ca, (long)in.N * in.H * in.W, c.Co);
 }
 
@@ -978,7 +1215,6 @@ void launch_conv_bwd_data(const ssn_net* n, const ConvL& c, TV gz, TV out, const
   if (zprev) ca.zprev = *zprev;
   else ca.zprev.p = nullptr;
   ca.mode = 1;
-  ca.accumulate = 0;
   launch_conv(n, ca, (long)gz.N * gz.H * gz.W, c.Ci);
 }
 
