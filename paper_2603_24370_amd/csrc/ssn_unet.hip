@@ -16,10 +16,12 @@
 //   conv3x3_mfma   the same GEMM with both operands read directly, for image
 //                  rows that are no multiple of 32 pixels;
 //   conv3x3_wgrad  weight gradient, M = out channels, N = in channels per tap,
-//                  K = pixels, operands staged transposed in LDS, split over
-//                  pixel chunks with a fixed-order reduction (deterministic);
-//   pool / upsample / head 1x1 / SiLU' / MSE / bias sums / Adam (optionally
-//   with global-norm gradient clipping): kernels on 8-channel vectors.
+//                  K = pixels, operands read from LDS with transposing loads,
+//                  split over pixel chunks with a fixed-order reduction
+//                  (deterministic); its launch also sums the bias gradient;
+//   pool / upsample (their backward passes with SiLU') / head 1x1 with the MSE /
+//   Adam (optionally with global-norm gradient clipping) with the packing of the
+//   BF16 weights: kernels on 8-channel vectors.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
@@ -446,122 +448,232 @@ conv3x3_rows(ConvArgs a, int ntiles, int per) {
 }
 
 // Weight gradient: part[split][co][t][ci] = sum over this split's pixel chunks of
-// gz[pix][co] * x[pix + d_t][ci]. Block = 9 waves (one per tap), tile 32 co x 32 ci.
-// A chunk is R image rows of cw pixels (R * cw <= kChunk): its gz pixels and the
-// R + 2 x rows around them (cw + 2 pixels wide) are read as 16-byte vectors of 8
-// channels and staged transposed in LDS, then every wave runs R * cw / 16 MFMAs
-// on them. Requires 16-byte aligned channel vectors (cs, coff, C multiples of 8),
-// cw % 16 == 0, W % cw == 0, H % R == 0 and (R + 2) * 32 * (cw + 8) <= kXLds.
+// gz[pix][co] * x[pix + d_t][ci]. A block takes a tile of 32 co x 32 ci; its waves
+// 0 .. 2 one row of taps each (three accumulators), all four stage. A chunk is R
+// image rows of CW pixels (R * CW <= kChunk): its gz pixels and the R + 2 x rows
+// around them (CW + 2 pixels wide) go to LDS as they lie in memory, 32 channels
+// (64 bytes) per pixel, in 16-byte vectors; the next chunk's are read into
+// registers meanwhile. The products need both operands with the pixels of a
+// channel in a lane, which is what the transposing LDS read gives: four pixels x
+// sixteen channels per sixteen lanes, so a tap's shift is an offset of whole
+// pixels. The gz fragment of 16 pixels serves a wave's three taps. Every tap sums
+// its chunks' rows in 16-pixel steps, in order. Requires channel vectors of 8
+// (cs, coff, C multiples of 8), W % CW == 0, H % R == 0, (R + 2)(CW + 2) <= kXPix.
+// Bound by LDS reads (8 transposing reads of 512 bytes per 3 products) and by the
+// latency of its loads at 1.5 blocks per CU. 96 -> 32 channels on 256^2, batch 8,
+// with the bias sums: 68 us; storing every channel of a vector separately to
+// transpose, and reading three 16-byte words per product: 105 + 13 us.
 constexpr int kChunk = 256;         // pixels per chunk
-constexpr int kGP = kChunk + 8;     // gzT row pitch (elements)
-constexpr int kXLds = 13824;        // xT elements: (R + 2) * 32 rows of pitch cw + 8
+constexpr int kXPix = 396;          // staged x pixels: (R + 2)(CW + 2)
 struct WgradArgs {
   TV gz;        // gradient w.r.t. the layer's pre-activation (C = Co)
   TV x;         // layer input (C = Ci)
   float* part;  // [nsplit][Co][9][Ci]
   int nsplit;
-  int cw;       // pixels per chunk row
   int R;        // rows per chunk
+  float* cpart; // per-block channel sums of gz ([kPartBlocks][Co])
 };
 
-__global__ void __launch_bounds__(576) conv3x3_wgrad(WgradArgs a) {
-  __shared__ __align__(16) bf16_t gzT[32 * kGP];  // [co][pix]
-  __shared__ __align__(16) bf16_t xT[kXLds];      // [row][ci][pix + 1]
-  const int lane = threadIdx.x & 63, tap = threadIdx.x >> 6;
-  const int r = lane & 31, half = lane >> 5;
-  const int ci0 = blockIdx.x * 32, co0 = blockIdx.y * 32, split = blockIdx.z;
-  const int H = a.x.H, W = a.x.W, Ci = a.x.C, Co = a.gz.C, cw = a.cw, R = a.R;
-  const int XP = cw + 8;
-  const int cpr = W / cw, rpi = H / R;
-  const long nchunks = (long)a.x.N * rpi * cpr;
-  const int dy = tap / 3 - 1, dx = tap % 3 - 1;
-  f32x16 acc;
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+
+// 16 channels x 8 pixels per 16 lanes: p points at the lane's (pixel, four
+// channels) of the first four pixels, 64 bytes per pixel
+__device__ __forceinline__ bf16x8 load_tr(const bf16_t* p) {
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)p);
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(p + 4 * 32));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+constexpr int kPartBlocks = 256;
+
+__device__ __forceinline__ void unpack8(const u32x4 v, float (&x)[8]);
+
+// Block b of kPartBlocks per 256 channels: channel sums of a bf16 NHWC view into
+// fp32 partials [kPartBlocks][C]. Block (b, y) takes channels [256 y, 256 y + Cc),
+// Cc = min(C - 256 y, 256), a multiple of 8: thread t sums the 8-channel group
+// t % G (G = Cc / 8) over the pixels b0 + t / G, step 256 / G, of the block's pixel
+// range; the lane sums of each channel are then added in lane order. red: 2048
+// floats of LDS.
+__device__ __forceinline__ void channel_sums(const TV& g, int b, int y, float* __restrict__ part, float* red) {
+  const int t = threadIdx.x, C = g.C;
+  const long npix = (long)g.N * g.H * g.W;
+  const int c0 = 256 * y;
+  const int Cc = min(C - c0, 256);
+  const long per = (npix + kPartBlocks - 1) / kPartBlocks;
+  const long b0 = b * per, b1 = std::min(npix, b0 + per);
+  const int G = Cc / 8, L = 256 / G;
+  const int e = t % G, l = t / G;
+  float s[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+  if (l < L) {
+    const bf16_t* gp = g.p + g.coff + c0 + 8 * e;
+    long p = b0 + l;
+    constexpr int U = 8;  // loads in flight
+    for (; p + (U - 1) * L < b1; p += U * L) {
+      u32x4 raw[U];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-  for (long ch = split; ch < nchunks; ch += a.nsplit) {
-    const int n = (int)(ch / ((long)rpi * cpr));
-    const int rem = (int)(ch - (long)n * rpi * cpr);
-    const int y0 = (rem / cpr) * R, x0 = (rem - (rem / cpr) * cpr) * cw;
-    // gz: R * cw pixels, 4 vectors of 8 channels each
-    for (int e = threadIdx.x; e < R * cw * 4; e += 576) {
-      const int p = e >> 2, v = e & 3;
-      const int py = p / cw, px = p - py * cw;
-      u32x4 val = {0u, 0u, 0u, 0u};
-      if (co0 + 8 * v < Co) val = load_u32x4(a.gz.p + tv_at(a.gz, n, y0 + py, x0 + px) + co0 + 8 * v);
+      for (int u = 0; u < U; ++u) raw[u] = load_u32x4(gp + (p + u * L) * g.cs);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        gzT[(8 * v + 2 * j) * kGP + p] = (bf16_t)(val[j] & 0xffffu);
-        gzT[(8 * v + 2 * j + 1) * kGP + p] = (bf16_t)(val[j] >> 16);
+      for (int u = 0; u < U; ++u) {
+        float v[8];
+        unpack8(raw[u], v);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s[j] += v[j];
       }
     }
-    // x: rows y0 - 1 .. y0 + R, pixels x0 - 1 .. x0 + cw, 4 vectors of 8 channels each
-    for (int e = threadIdx.x; e < (R + 2) * (cw + 2) * 4; e += 576) {
-      const int v = e & 3, k = e >> 2;
-      const int rr = k / (cw + 2), px = k - rr * (cw + 2);
-      const int yy = y0 + rr - 1, xx = x0 + px - 1;
-      const bool in = yy >= 0 && yy < H && xx >= 0 && xx < W && ci0 + 8 * v < Ci;
-      u32x4 val = {0u, 0u, 0u, 0u};
-      if (in) val = load_u32x4(a.x.p + tv_at(a.x, n, yy, xx) + ci0 + 8 * v);
+    for (; p < b1; p += L) {
+      float v[8];
+      unpack8(load_u32x4(gp + p * g.cs), v);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        xT[(rr * 32 + 8 * v + 2 * j) * XP + px] = (bf16_t)(val[j] & 0xffffu);
-        xT[(rr * 32 + 8 * v + 2 * j + 1) * XP + px] = (bf16_t)(val[j] >> 16);
-      }
+      for (int j = 0; j < 8; ++j) s[j] += v[j];
     }
-    __syncthreads();
-    if (tap < 9) {
-      // B of tap (dy, dx) starts dx + 1 elements past a 16-byte boundary: it is
-      // read as two aligned 16-byte words and shifted by whole elements, so
-      // every vector LDS read is aligned
-      const int sh = dx + 1;
-      for (int rr = 0; rr < R; ++rr) {
-        const u32x4* ap = reinterpret_cast<const u32x4*>(gzT + r * kGP + rr * cw + half * 8);
-        const u32x4* bp = reinterpret_cast<const u32x4*>(xT + ((rr + dy + 1) * 32 + r) * XP + half * 8);
-        for (int kk = 0; kk < cw; kk += 16) {
-          const u32x4 a4 = ap[kk >> 3];
-          const u32x4 w0 = bp[kk >> 3], w1 = bp[(kk >> 3) + 1];
-          u32x4 b4 = w0;
-          if (sh == 1) {
-            b4.x = __builtin_amdgcn_alignbit(w0.y, w0.x, 16);
-            b4.y = __builtin_amdgcn_alignbit(w0.z, w0.y, 16);
-            b4.z = __builtin_amdgcn_alignbit(w0.w, w0.z, 16);
-            b4.w = __builtin_amdgcn_alignbit(w1.x, w0.w, 16);
-          } else if (sh == 2) {
-            b4.x = w0.y;
-            b4.y = w0.z;
-            b4.z = w0.w;
-            b4.w = w1.x;
-          }
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a4), __builtin_bit_cast(bf16x8, b4),
-                                                         acc, 0, 0, 0);
-        }
-      }
-    }
-    __syncthreads();
   }
-  if (tap < 9) {
-    const int ci = ci0 + r;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int co = co0 + (v >> 2) * 8 + half * 4 + (v & 3);
-      if (co < Co && ci < Ci) a.part[(((long)split * Co + co) * 9 + tap) * Ci + ci] = acc[v];
-    }
+  for (int j = 0; j < 8; ++j) red[t * 8 + j] = s[j];
+  __syncthreads();
+  if (t < Cc) {
+    float a = 0.0f;
+    for (int k = 0; k < L; ++k) a += red[(k * G + t / 8) * 8 + t % 8];
+    part[(long)b * C + c0 + t] = a;
   }
 }
 
-// out[k] = sum over s of part[s][k]. A block takes 32 outputs; its 8 groups of
-// 32 lanes each sum a contiguous eighth of the splits in order, and the eight
-// sums are added in group order (fixed order: deterministic).
-__global__ void __launch_bounds__(256) reduce_splits(const float* __restrict__ part, int nsplit, long n,
-                                                     float* __restrict__ out) {
+// Blocks 0 .. tiles * nsplit - 1 form the weight gradient, the rest the channel
+// sums of gz (the bias gradient).
+template <int CW>
+__global__ void __launch_bounds__(256) conv3x3_wgrad(WgradArgs a) {
+  __shared__ __align__(16) bf16_t gzs[kChunk * 32];  // [pixel][co]
+  __shared__ __align__(16) bf16_t xs[kXPix * 32];    // [row][pixel + 1][ci]
+  constexpr int XW = CW + 2;
+  constexpr int NG = kChunk * 4 / 256, NX = (kXPix * 4 + 255) / 256;
+  const int lane = threadIdx.x & 63, dy = threadIdx.x >> 6;
+  const int H = a.x.H, W = a.x.W, Ci = a.x.C, Co = a.gz.C, R = a.R;
+  const int tci = (Ci + 31) / 32, tco = (Co + 31) / 32;
+  const int nw = tci * tco * a.nsplit;
+  if ((int)blockIdx.x >= nw) {
+    const int k = blockIdx.x - nw;
+    channel_sums(a.gz, k % kPartBlocks, k / kPartBlocks, a.cpart, reinterpret_cast<float*>(gzs));
+    return;
+  }
+  const int tile = blockIdx.x % (tci * tco), split = blockIdx.x / (tci * tco);
+  const int ci0 = (tile % tci) * 32, co0 = (tile / tci) * 32;
+  const int cpr = W / CW, rpi = H / R;
+  const int nchunks = a.x.N * rpi * cpr;
+  const int ng = R * CW * 4, nx = (R + 2) * XW * 4;
+  u32x4 pg[NG], px[NX];
+  auto fetch = [&](int ch) {
+    const int n = ch / (rpi * cpr);
+    const int rem = ch - n * rpi * cpr;
+    const int y0 = (rem / cpr) * R, x0 = (rem - (rem / cpr) * cpr) * CW;
+    const bf16_t* __restrict__ gb = a.gz.p + tv_at(a.gz, n, y0, x0) + co0;
+    const bf16_t* __restrict__ xb = a.x.p + tv_at(a.x, n, 0, 0) + ci0;
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+      const int e = threadIdx.x + q * 256, v = e & 3, p = e >> 2;
+      const int py = p / CW, pxx = p - py * CW;
+      pg[q] = u32x4{0u, 0u, 0u, 0u};
+      if (e < ng && co0 + 8 * v < Co) pg[q] = load_u32x4(gb + (long)(py * W + pxx) * a.gz.cs + 8 * v);
+    }
+#pragma unroll
+    for (int q = 0; q < NX; ++q) {
+      const int e = threadIdx.x + q * 256, v = e & 3, k = e >> 2;
+      const int rr = k / XW, p = k - rr * XW;
+      const int yy = y0 + rr - 1, xx = x0 + p - 1;
+      px[q] = u32x4{0u, 0u, 0u, 0u};
+      if (e < nx && (unsigned)yy < (unsigned)H && (unsigned)xx < (unsigned)W && ci0 + 8 * v < Ci)
+        px[q] = load_u32x4(xb + (long)(yy * W + xx) * a.x.cs + 8 * v);
+    }
+  };
+  f32x16 acc[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[d][v] = 0.0f;
+  // the lane's place in a transposing read: pixels 8 (lane / 32) + (lane % 16) / 4,
+  // channels 16 (lane / 16 % 2) + 4 (lane % 4)
+  const int tr = (8 * (lane >> 5) + ((lane & 15) >> 2)) * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+  fetch(split);  // nsplit <= nchunks
+  for (int ch = split; ch < nchunks; ch += a.nsplit) {
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+      const int e = threadIdx.x + q * 256;
+      if (e < ng) *reinterpret_cast<u32x4*>(gzs + e * 8) = pg[q];
+    }
+#pragma unroll
+    for (int q = 0; q < NX; ++q) {
+      const int e = threadIdx.x + q * 256;
+      if (e < nx) *reinterpret_cast<u32x4*>(xs + e * 8) = px[q];
+    }
+    __syncthreads();
+    if (ch + a.nsplit < nchunks) fetch(ch + a.nsplit);
+    if (dy < 3)
+      for (int rr = 0; rr < R; ++rr) {
+        const bf16_t* ap = gzs + rr * CW * 32 + tr;
+        const bf16_t* bp = xs + (rr + dy) * XW * 32 + tr;
+#pragma unroll
+        for (int kk = 0; kk < CW; kk += 16) {
+          const bf16x8 A = load_tr(ap + kk * 32);
+#pragma unroll
+          for (int d = 0; d < 3; ++d)
+            acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, load_tr(bp + (kk + d) * 32), acc[d], 0, 0, 0);
+        }
+      }
+  }
+  if (dy < 3) {
+    const int r = lane & 31, half = lane >> 5;
+    const int ci = ci0 + r;
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int co = co0 + (v >> 2) * 8 + half * 4 + (v & 3);
+        if (co < Co && ci < Ci) a.part[(((long)split * Co + co) * 9 + dy * 3 + d) * Ci + ci] = acc[d][v];
+      }
+  }
+}
+
+// out[k] = sum over s of part[s][k], for two sets of partials in one launch (a
+// layer's weight gradient, blocks 0 .. wb - 1, and its bias gradient). A block
+// takes 32 outputs; its 8 groups of 32 lanes each sum a contiguous eighth of the
+// splits in order, and the eight sums are added in group order (fixed order:
+// deterministic). Sixteen loads are in flight per lane.
+struct ReduceSet {
+  const float* part;
+  float* out;
+  long n;
+  int nsplit;
+};
+
+__global__ void __launch_bounds__(256) reduce_splits(ReduceSet w, ReduceSet b, int wb) {
   __shared__ float red[256];
+  const bool second = (int)blockIdx.x >= wb;
+  const float* __restrict__ part = second ? b.part : w.part;
+  float* __restrict__ out = second ? b.out : w.out;
+  const long n = second ? b.n : w.n;
+  const int nsplit = second ? b.nsplit : w.nsplit;
   const int kl = threadIdx.x & 31, g = threadIdx.x >> 5;
-  const long k = blockIdx.x * 32L + kl;
+  const long k = (long)((int)blockIdx.x - (second ? wb : 0)) * 32 + kl;
   const int per = (nsplit + 7) / 8;
   const int s0 = min(nsplit, g * per), s1 = min(nsplit, s0 + per);
   float s = 0.0f;
-  if (k < n)
-    for (int i = s0; i < s1; ++i) s += part[(long)i * n + k];
+  if (k < n) {
+    constexpr int U = 16;
+    int i = s0;
+    for (; i + U <= s1; i += U) {
+      float v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = part[(long)(i + u) * n + k];
+#pragma unroll
+      for (int u = 0; u < U; ++u) s += v[u];
+    }
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = i + u < s1 ? part[(long)(i + u) * n + k] : 0.0f;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i + u < s1) s += v[u];
+  }
   red[threadIdx.x] = s;
   __syncthreads();
   if (g == 0 && k < n) {
@@ -581,164 +693,97 @@ __device__ __forceinline__ void unpack8(const u32x4 v, float (&x)[8]) {
   }
 }
 
-// Per-block channel sums of an NHWC view (bf16 g, or fp32 gf with channel
-// stride gf_cs) into fp32 partials [nblk][C]. Block y takes channels
-// [256 y, 256 y + Cc), Cc = min(C - 256 y, 256). For g (Cc % 8 == 0) thread t
-// sums the 8-channel group t % G (G = Cc / 8) over the pixels b0 + t / G, step
-// 256 / G, of the block's pixel range; for gf, channel t % Cc over the pixels
-// b0 + t / Cc, step 256 / Cc. The lane sums of each channel are then added in
-// lane order (deterministic).
-__global__ void __launch_bounds__(256) channel_sums(TV g, const float* __restrict__ gf, int gf_cs, long npix, int C,
-                                                    float* __restrict__ part) {
-  __shared__ float red[256 * 8];
-  const int t = threadIdx.x;
-  const int c0 = 256 * blockIdx.y;
-  const int Cc = min(C - c0, 256);
-  const long per = (npix + gridDim.x - 1) / gridDim.x;
-  const long b0 = blockIdx.x * per, b1 = std::min(npix, b0 + per);
-  if (gf) {
-    const int L = 256 / Cc;
-    const int c = t % Cc, l = t / Cc;
-    float s = 0.0f;
-    if (l < L)
-      for (long p = b0 + l; p < b1; p += L) s += gf[p * gf_cs + c0 + c];
-    red[t] = s;
-    __syncthreads();
-    if (t < Cc) {
-      float a = 0.0f;
-      for (int k = 0; k < L; ++k) a += red[k * Cc + t];
-      part[(long)blockIdx.x * C + c0 + t] = a;
-    }
-    return;
-  }
-  const int G = Cc / 8, L = 256 / G;
-  const int e = t % G, l = t / G;
-  float s[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-  if (l < L)
-    for (long p = b0 + l; p < b1; p += L) {
-      float v[8];
-      unpack8(load_u32x4(g.p + p * g.cs + g.coff + c0 + 8 * e), v);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) s[j] += v[j];
-    }
-#pragma unroll
-  for (int j = 0; j < 8; ++j) red[t * 8 + j] = s[j];
-  __syncthreads();
-  if (t < Cc) {
-    float a = 0.0f;
-    for (int k = 0; k < L; ++k) a += red[(k * G + t / 8) * 8 + t % 8];
-    part[(long)blockIdx.x * C + c0 + t] = a;
-  }
-}
-
-// Pooling, upsampling and SiLU' on NHWC views, one 16-byte vector of 8
-// channels per work item (C, cs and coff multiples of 8); item k is channel
-// group k % (C / 8) of pixel k / (C / 8).
+// Pooling, upsampling and their backward passes (with SiLU' of the layer below)
+// on NHWC views, one 16-byte vector of 8 channels per thread (C, cs and coff
+// multiples of 8): block (bx, y, b) covers 256 vectors of row y of image b, so a
+// thread's place costs one 32-bit division. All are bound by memory: on 256^2 x 32
+// channels, batch 8, avgpool2_bwd 25 us (135 MB; with SiLU' in a pass of its own 43).
 __device__ __forceinline__ u32x4 pack8(const float (&x)[8]) {
   u32x4 r;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) r[j] = (unsigned)f2bf(x[2 * j]) | ((unsigned)f2bf(x[2 * j + 1]) << 16);
+  for (int j = 0; j < 4; ++j) r[j] = pack2(x[2 * j], x[2 * j + 1]);
   return r;
 }
 
 __device__ __forceinline__ void store_u32x4(bf16_t* p, const u32x4 v) { *reinterpret_cast<u32x4*>(p) = v; }
 
-// pixel (b, y, x) and first channel c of work item k of a view with C8 groups per pixel
-__device__ __forceinline__ void item_of(long k, const TV& t, int C8, int& b, int& y, int& x, int& c) {
-  c = 8 * (int)(k % C8);
-  long p = k / C8;
-  x = (int)(p % t.W);
-  p /= t.W;
-  y = (int)(p % t.H);
-  b = (int)(p / t.H);
+// body(b, y, x, c) for every vector of view t: image, pixel and first channel
+template <class F>
+__device__ __forceinline__ void for_vectors(const TV& t, F&& body) {
+  const int C8 = t.C / 8, k = blockIdx.x * 256 + threadIdx.x;
+  if (k >= t.W * C8) return;
+  const int x = k / C8, c = 8 * (k - x * C8);
+  for (int b = blockIdx.z; b < t.N; b += gridDim.z)
+    for (int y = blockIdx.y; y < t.H; y += gridDim.y) body(b, y, x, c);
 }
 
-__global__ void avgpool2_fwd(TV in, TV out) {
-  const int C8 = out.C / 8;
-  const long n = (long)out.N * out.H * out.W * C8;
-  for (long k = blockIdx.x * (long)blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x) {
-    int b, y, x, c;
-    item_of(k, out, C8, b, y, x, c);
-    float s[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    for (int j = 0; j < 2; ++j)
-      for (int i = 0; i < 2; ++i) {
-        float v[8];
-        unpack8(load_u32x4(in.p + tv_at(in, b, 2 * y + j, 2 * x + i) + c), v);
+// sum of the 2x2 block (y, x) of a view, rows first
+__device__ __forceinline__ void sum2x2(const TV& t, int b, int y, int x, int c, float (&s)[8]) {
+  u32x4 raw[4];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) s[e] += v[e];
-      }
+  for (int j = 0; j < 4; ++j) raw[j] = load_u32x4(t.p + tv_at(t, b, 2 * y + (j >> 1), 2 * x + (j & 1)) + c);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) s[e] = 0.0f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    float v[8];
+    unpack8(raw[j], v);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s[e] += v[e];
+  }
+}
+
+// g rounded to BF16 (as a gradient tensor holds it), times SiLU'(z)
+__device__ __forceinline__ u32x4 times_silu_grad(const float (&g)[8], const u32x4 z) {
+  float v[8], zz[8];
+  unpack8(pack8(g), v);
+  unpack8(z, zz);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] *= silu_grad_f(zz[e]);
+  return pack8(v);
+}
+
+__global__ void __launch_bounds__(256) avgpool2_fwd(TV in, TV out) {
+  for_vectors(out, [&](int b, int y, int x, int c) {
+    float s[8];
+    sum2x2(in, b, y, x, c, s);
 #pragma unroll
     for (int e = 0; e < 8; ++e) s[e] *= 0.25f;
     store_u32x4(out.p + tv_at(out, b, y, x) + c, pack8(s));
-  }
+  });
 }
 
-// gin (+)= gout / 4 spread over each 2x2 block
-__global__ void avgpool2_bwd(TV gout, TV gin, int accumulate) {
-  const int C8 = gin.C / 8;
-  const long n = (long)gin.N * gin.H * gin.W * C8;
-  for (long k = blockIdx.x * (long)blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x) {
-    int b, y, x, c;
-    item_of(k, gin, C8, b, y, x, c);
-    float v[8];
-    unpack8(load_u32x4(gout.p + tv_at(gout, b, y >> 1, x >> 1) + c), v);
+// g = (g + gout / 4 spread over each 2x2 block) SiLU'(z)
+__global__ void __launch_bounds__(256) avgpool2_bwd(TV gout, TV g, TV z) {
+  for_vectors(g, [&](int b, int y, int x, int c) {
+    bf16_t* o = g.p + tv_at(g, b, y, x) + c;
+    const u32x4 go = load_u32x4(gout.p + tv_at(gout, b, y >> 1, x >> 1) + c), old = load_u32x4(o);
+    const u32x4 zz = load_u32x4(z.p + tv_at(z, b, y, x) + c);
+    float v[8], w[8];
+    unpack8(go, v);
+    unpack8(old, w);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] *= 0.25f;
-    bf16_t* o = gin.p + tv_at(gin, b, y, x) + c;
-    if (accumulate) {
-      float w[8];
-      unpack8(load_u32x4(o), w);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] += w[e];
-    }
-    store_u32x4(o, pack8(v));
-  }
+    for (int e = 0; e < 8; ++e) v[e] = v[e] * 0.25f + w[e];
+    store_u32x4(o, times_silu_grad(v, zz));
+  });
 }
 
-__global__ void upsample2_fwd(TV in, TV out) {
-  const int C8 = out.C / 8;
-  const long n = (long)out.N * out.H * out.W * C8;
-  for (long k = blockIdx.x * (long)blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x) {
-    int b, y, x, c;
-    item_of(k, out, C8, b, y, x, c);
-    store_u32x4(out.p + tv_at(out, b, y, x) + c, load_u32x4(in.p + tv_at(in, b, y >> 1, x >> 1) + c));
-  }
+__global__ void __launch_bounds__(256) upsample2_fwd(TV in, TV out) {
+  for_vectors(in, [&](int b, int y, int x, int c) {
+    const u32x4 v = load_u32x4(in.p + tv_at(in, b, y, x) + c);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) store_u32x4(out.p + tv_at(out, b, 2 * y + (j >> 1), 2 * x + (j & 1)) + c, v);
+  });
 }
 
-// gin = sum of gout over each 2x2 block
-__global__ void upsample2_bwd(TV gout, TV gin) {
-  const int C8 = gin.C / 8;
-  const long n = (long)gin.N * gin.H * gin.W * C8;
-  for (long k = blockIdx.x * (long)blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x) {
-    int b, y, x, c;
-    item_of(k, gin, C8, b, y, x, c);
-    float s[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    for (int j = 0; j < 2; ++j)
-      for (int i = 0; i < 2; ++i) {
-        float v[8];
-        unpack8(load_u32x4(gout.p + tv_at(gout, b, 2 * y + j, 2 * x + i) + c), v);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s[e] += v[e];
-      }
-    store_u32x4(gin.p + tv_at(gin, b, y, x) + c, pack8(s));
-  }
-}
-
-// g *= SiLU'(z) in place
-__global__ void silu_bwd_inplace(TV g, TV z) {
-  const int C8 = g.C / 8;
-  const long n = (long)g.N * g.H * g.W * C8;
-  for (long k = blockIdx.x * (long)blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x) {
-    const int c = 8 * (int)(k % C8);
-    const long p = k / C8;
-    bf16_t* o = g.p + p * g.cs + g.coff + c;
-    float v[8], zz[8];
-    unpack8(load_u32x4(o), v);
-    unpack8(load_u32x4(z.p + p * z.cs + z.coff + c), zz);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] *= silu_grad_f(zz[e]);
-    store_u32x4(o, pack8(v));
-  }
+// g = (sum of gout over each 2x2 block) SiLU'(z)
+__global__ void __launch_bounds__(256) upsample2_bwd(TV gout, TV g, TV z) {
+  for_vectors(g, [&](int b, int y, int x, int c) {
+    const u32x4 zz = load_u32x4(z.p + tv_at(z, b, y, x) + c);
+    float s[8];
+    sum2x2(gout, b, y, x, c, s);
+    store_u32x4(g.p + tv_at(g, b, y, x) + c, times_silu_grad(s, zz));
+  });
 }
 
 // The 1x1 head (cout <= 8 outputs, C % 8 == 0 input channels): one pixel per
@@ -766,62 +811,80 @@ __global__ void __launch_bounds__(256) head_fwd(TV a, const float* __restrict__ 
   for (int o = 0; o < cout; ++o) out[p * cout + o] = s[o];
 }
 
-// head backward to its input, times SiLU'(z): ga[pix][ci] = SiLU'(z) sum_o gout[pix][o] w[o][ci]
-__global__ void __launch_bounds__(256) head_bwd_data(const float* __restrict__ gout, const float* __restrict__ w,
-                                                     int cout, TV z, TV ga, long npix) {
-  const long p = blockIdx.x * (long)blockDim.x + threadIdx.x;
-  if (p >= npix) return;
-  float g[8];
+// The loss is the mean squared error: the gradient at output k is
+// 2 (out[k] - tgt[k]) / n, formed where it is used.
+
+// head backward to its input, times SiLU'(z): ga[pix][ci] = SiLU'(z) sum_o gout[pix][o] w[o][ci];
+// one 8-channel vector per thread
+template <int COUT>
+__global__ void __launch_bounds__(256) head_bwd_data(const float* __restrict__ out, const float* __restrict__ tgt,
+                                                     float inv, const float* __restrict__ w, TV z, TV ga, long npix) {
+  const int C = ga.C, C8 = C / 8;
+  const int per = 256 / C8;  // pixels per block
+  const int l = threadIdx.x / C8, c0 = 8 * (threadIdx.x - l * C8);
+  const long p = (long)blockIdx.x * per + l;
+  if (l >= per || p >= npix) return;
+  float g[COUT];
 #pragma unroll
-  for (int o = 0; o < 8; ++o) g[o] = o < cout ? gout[p * cout + o] : 0.0f;
-  const bf16_t* zp = z.p + p * z.cs + z.coff;
-  bf16_t* gp = ga.p + p * ga.cs + ga.coff;
-  const int C = ga.C;
-  for (int c0 = 0; c0 < C; c0 += 8) {
-    float zz[8];
-    unpack8(load_u32x4(zp + c0), zz);
-    u32x4 res;
+  for (int o = 0; o < COUT; ++o) g[o] = inv * (out[p * COUT + o] - tgt[p * COUT + o]);
+  float zz[8], r[8];
+  unpack8(load_u32x4(z.p + p * z.cs + z.coff + c0), zz);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      float lo = 0.0f, hi = 0.0f;
+  for (int j = 0; j < 8; ++j) {
+    float s = 0.0f;
 #pragma unroll
-      for (int o = 0; o < 8; ++o)
-        if (o < cout) {
-          lo += g[o] * w[o * C + c0 + 2 * j];
-          hi += g[o] * w[o * C + c0 + 2 * j + 1];
-        }
-      lo *= silu_grad_f(zz[2 * j]);
-      hi *= silu_grad_f(zz[2 * j + 1]);
-      res[j] = (unsigned)f2bf(lo) | ((unsigned)f2bf(hi) << 16);
-    }
-    *reinterpret_cast<u32x4*>(gp + c0) = res;
+    for (int o = 0; o < COUT; ++o) s += g[o] * w[o * C + c0 + j];
+    r[j] = s * silu_grad_f(zz[j]);
   }
+  store_u32x4(ga.p + p * ga.cs + ga.coff + c0, pack8(r));
 }
 
-// Per-block partials of gw[o][ci] = sum_pix gout[pix][o] a[pix][ci] ([nblk][cout * C],
-// cout * C <= 256). Thread t takes the entries (o, 8 channels) e = t % E, E = cout * C / 8,
-// over the pixels b0 + t / E, step L = 256 / E, of the block's range; the L lane sums of
-// each entry are then added in lane order (deterministic).
-__global__ void __launch_bounds__(256) head_wgrad(const float* __restrict__ gout, TV a, int cout, long npix,
-                                                  float* __restrict__ part) {
+// Per-block partials over a range of pixels of the head's weight gradient
+// gw[o][ci] = sum_pix gout[pix][o] a[pix][ci] (wpart, [nblk][cout C], cout C <= 256), its
+// bias gradient (bpart, [nblk][cout]) and the squared error (lpart). Thread t takes the
+// entries (o, 8 channels) e = t % E, E = cout C / 8, over the pixels b0 + t / E, step
+// L = 256 / E, and the bias of output t % cout over the pixels b0 + t / cout, step
+// 256 / cout; lane sums are then added in lane order (deterministic). Eight pixels of a
+// thread are in flight. One launch reads the outputs for all three; the bias and loss
+// loops run over L1 and L2 copies.
+__global__ void __launch_bounds__(256) head_sums(const float* __restrict__ out, const float* __restrict__ tgt,
+                                                 float inv, TV a, int cout, long npix, float* __restrict__ wpart,
+                                                 float* __restrict__ bpart, double* __restrict__ lpart) {
   __shared__ float red[256 * 8];
+  __shared__ double dred[256];
   const int t = threadIdx.x;
   const int C = a.C, C8 = C / 8, E = cout * C8, L = 256 / E, K = cout * C;
   const int e = t % E, l = t / E;
   const int o = e / C8, c0 = (e - o * C8) * 8;
   const long per = (npix + gridDim.x - 1) / gridDim.x;
   const long b0 = blockIdx.x * per, b1 = std::min(npix, b0 + per);
+  constexpr int U = 8;
   float s[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) s[j] = 0.0f;
-  if (l < L)
-    for (long p = b0 + l; p < b1; p += L) {
-      const float g = gout[p * cout + o];
-      float x[8];
-      unpack8(load_u32x4(a.p + p * a.cs + a.coff + c0), x);
+  if (l < L) {
+    const bf16_t* ap = a.p + a.coff + c0;
+    for (long p0 = b0 + l; p0 < b1; p0 += U * L) {
+      u32x4 raw[U];
+      float ov[U], tv[U];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) s[j] += g * x[j];
+      for (int u = 0; u < U; ++u) {
+        const long p = p0 + u * L < b1 ? p0 + u * L : p0;
+        raw[u] = load_u32x4(ap + p * a.cs);
+        ov[u] = out[p * cout + o];
+        tv[u] = tgt[p * cout + o];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (p0 + u * L < b1) {
+          const float g = inv * (ov[u] - tv[u]);
+          float x[8];
+          unpack8(raw[u], x);
+#pragma unroll
+          for (int j = 0; j < 8; ++j) s[j] += g * x[j];
+        }
     }
+  }
 #pragma unroll
   for (int j = 0; j < 8; ++j) red[t * 8 + j] = s[j];
   __syncthreads();
@@ -830,28 +893,42 @@ __global__ void __launch_bounds__(256) head_wgrad(const float* __restrict__ gout
     const int ee = oo * C8 + c / 8, jj = c % 8;
     float acc = 0.0f;
     for (int q = 0; q < L; ++q) acc += red[(q * E + ee) * 8 + jj];
-    part[(long)blockIdx.x * K + t] = acc;
+    wpart[(long)blockIdx.x * K + t] = acc;
   }
-}
-
-// mse: per-block partial sums of (out - t)^2 and gout = 2 (out - t) / count
-__global__ void __launch_bounds__(256) mse_fwd_bwd(const float* __restrict__ out, const float* __restrict__ tgt, long n,
-                                                   float* __restrict__ gout, double* __restrict__ part) {
-  __shared__ double red[256];
-  double s = 0.0;
-  const float inv = 2.0f / (float)n;
-  for (long k = blockIdx.x * 256L + threadIdx.x; k < n; k += (long)gridDim.x * 256L) {
-    const float d = out[k] - tgt[k];
-    s += (double)d * d;
-    gout[k] = inv * d;
-  }
-  red[threadIdx.x] = s;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+  // bias and loss over the same range
+  const int Lb = 256 / cout, ob = t % cout, lb = t / cout;
+  float sb = 0.0f;
+  double sl = 0.0;
+  if (lb < Lb)
+    for (long p0 = b0 + lb; p0 < b1; p0 += U * Lb) {
+      float d[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const long p = p0 + u * Lb;
+        d[u] = p < b1 ? out[p * cout + ob] - tgt[p * cout + ob] : 0.0f;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (p0 + u * Lb < b1) {
+#pragma clang fp contract(off)
+          sb += inv * d[u];
+          sl += (double)d[u] * d[u];
+        }
+    }
+  red[t] = sb;
+  dred[t] = sl;
+  __syncthreads();
+  if (t < cout) {
+    float acc = 0.0f;
+    for (int k = 0; k < Lb; ++k) acc += red[k * cout + t];
+    bpart[(long)blockIdx.x * cout + t] = acc;
+  }
+  for (int k = 128; k > 0; k >>= 1) {
+    if (t < k) dred[t] += dred[t + k];
     __syncthreads();
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+  if (t == 0) lpart[blockIdx.x] = dred[0];
 }
 
 // gradient clipping by global L2 norm: per-block partial sums of g^2 (FP64,
@@ -887,34 +964,55 @@ __global__ void __launch_bounds__(256) grad_clip_scale(const double* __restrict_
   }
 }
 
-// Adam (Kingma and Ba 2015) with bias correction on the gradient times *gscale
-// (gscale nullable: 1); grads g, moments m, v, master p (fp32)
-__global__ void adam_update(float* __restrict__ p, float* __restrict__ m, float* __restrict__ v,
-                            const float* __restrict__ g, const float* __restrict__ gscale, long n, float lr, float b1,
-                            float b2, float eps, float c1, float c2) {
-  const float sc = gscale ? *gscale : 1.0f;
-  for (long k = blockIdx.x * (long)blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x) {
-    const float gk = g[k] * sc;
-    const float mk = b1 * m[k] + (1.0f - b1) * gk;
-    const float vk = b2 * v[k] + (1.0f - b2) * gk * gk;
-    m[k] = mk;
-    v[k] = vk;
-    p[k] -= lr * (mk / c1) / (sqrtf(vk / c2) + eps);
-  }
-}
+// One 3x3 layer's parameters as the update and packing kernel walks them (blockIdx.y
+// = layer; the segment after the last layer holds the head's weights and biases).
+constexpr int kMaxConv = 22;  // 4 * 6 - 2 levels' layers
+struct ParamLayer {
+  long off, n;  // first parameter and parameter count (weights, then Co biases)
+  int Co, Ci;   // 0 for the head
+  bf16_t* wf;
+  bf16_t* wb;
+};
+struct ParamLayers {
+  ParamLayer l[kMaxConv + 1];
+};
 
-// bf16 weight fragments (frag_index) of a 3x3 layer: wf of w[co][t][ci], and wb
-// of the backward-data weights w[co][8 - t][ci] with ci as the output channel
-__global__ void pack_conv_weights(const float* __restrict__ w, int Co, int Ci, bf16_t* __restrict__ wf,
-                                  bf16_t* __restrict__ wb) {
-  const long n = (long)Co * 9 * Ci;
-  for (long k = blockIdx.x * (long)blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x) {
-    const int ci = (int)(k % Ci);
-    const long q = k / Ci;
-    const int t = (int)(q % 9), co = (int)(q / 9);
-    const bf16_t b = f2bf(w[k]);
-    wf[frag_index(co, t, ci, Ci / 16)] = b;
-    wb[frag_index(ci, 8 - t, co, Co / 16)] = b;
+struct AdamArgs {
+  float *m, *v;
+  const float* g;
+  const float* gscale;  // nullable: 1
+  float lr, b1, b2, eps, c1, c2;
+};
+
+// ADAM: one step of Adam (Kingma and Ba 2015) with bias correction on the gradient
+// times *gscale. Then the BF16 weight fragments (frag_index) of the layer: wf of
+// w[co][t][ci], and wb of the backward-data weights w[co][8 - t][ci] with ci as the
+// output channel. One launch for all layers (14 packing launches took 64 us of a
+// step).
+template <bool ADAM>
+__global__ void __launch_bounds__(256) update_params(ParamLayers ls, float* __restrict__ p, AdamArgs a) {
+  const ParamLayer L = ls.l[blockIdx.y];
+  const float sc = ADAM && a.gscale ? *a.gscale : 1.0f;
+  const int nw = L.Co * 9 * L.Ci;
+  for (int q = blockIdx.x * 256 + threadIdx.x; q < (int)L.n; q += gridDim.x * 256) {
+    const long k = L.off + q;
+    float pk = p[k];
+    if (ADAM) {
+      const float gk = a.g[k] * sc;
+      const float mk = a.b1 * a.m[k] + (1.0f - a.b1) * gk;
+      const float vk = a.b2 * a.v[k] + (1.0f - a.b2) * gk * gk;
+      a.m[k] = mk;
+      a.v[k] = vk;
+      pk -= a.lr * (mk / a.c1) / (sqrtf(vk / a.c2) + a.eps);
+      p[k] = pk;
+    }
+    if (q < nw) {
+      const int ci = q % L.Ci, w = q / L.Ci;
+      const int t = w % 9, co = w / 9;
+      const bf16_t b = f2bf(pk);
+      L.wf[frag_index(co, t, ci, L.Ci / 16)] = b;
+      L.wb[frag_index(ci, 8 - t, co, L.Co / 16)] = b;
+    }
   }
 }
 
@@ -965,7 +1063,6 @@ struct ConvL {
   bf16_t* wb;         // backward-data fragments, rup(Ci, 32) * 9 * Co elements
 };
 
-constexpr int kPartBlocks = 256;
 constexpr long kWgradPartFloats = 1024L * 9 * 1024;
 
 }  // namespace
@@ -993,7 +1090,7 @@ struct ssn_net {
   // gradients
   std::vector<HT> gCAT, gT1, gT2, gT3, gP;  // gT3[l]: gradient at the pre-activation of dec_a(l)
   HT gM1, gM2;
-  float *OUT, *GOUT, *part, *cpart;
+  float *OUT, *part, *cpart;
   double* lpart;
   double* npart;   // per-block partial sums of the squared gradient
   float* gscale;   // gradient scale of the clipped Adam step (device)
@@ -1051,7 +1148,6 @@ size_t net_carve(ssn_net* n, char* base) {
   tensor(n->ZMa, HL, WL, cL); tensor(n->AMa, HL, WL, cL); tensor(n->ZMb, HL, WL, cL); tensor(n->AMb, HL, WL, cL);
   tensor(n->gM1, HL, WL, cL); tensor(n->gM2, HL, WL, cL);
   n->OUT = (float*)take((size_t)N * n->H * n->W * n->cout * 4);
-  n->GOUT = (float*)take((size_t)N * n->H * n->W * n->cout * 4);
   n->part = (float*)take(kWgradPartFloats * 4);
   n->cpart = (float*)take((size_t)kPartBlocks * 1024 * 4);
   n->lpart = (double*)take(256 * 8);
@@ -1218,15 +1314,15 @@ void launch_conv_bwd_data(const ssn_net* n, const ConvL& c, TV gz, TV out, const
   launch_conv(n, ca, (long)gz.N * gz.H * gz.W, c.Ci);
 }
 
-// out[k] = sum over s < nsplit of part[s][k], k < nout
-void launch_reduce_splits(const ssn_net* n, const float* part, int nsplit, long nout, float* out) {
-  hipLaunchKernelGGL(reduce_splits, dim3((unsigned)((nout + 31) / 32)), dim3(256), 0, n->stream, part, nsplit, nout,
-                     out);
+// Sums of a layer's weight and bias partials (launch of reduce_splits).
+void launch_reduce_splits(const ssn_net* n, const ReduceSet& w, const ReduceSet& b) {
+  const int wb = (int)((w.n + 31) / 32), bb = (int)((b.n + 31) / 32);
+  hipLaunchKernelGGL(reduce_splits, dim3((unsigned)(wb + bb)), dim3(256), 0, n->stream, w, b, wb);
 }
 
 // Chunk geometry of the weight gradient for a W x H level: cw is the widest
 // multiple of 16 up to 64 that divides W; R the largest power of two with
-// R * cw <= kChunk, H % R == 0 and the x rows within kXLds.
+// R * cw <= kChunk and H % R == 0 (the x pixels then fit kXPix).
 void wgrad_chunk(int W, int H, int& cw, int& R) {
   cw = 16;
   for (int c = 64; c >= 16; c -= 16)
@@ -1235,7 +1331,7 @@ void wgrad_chunk(int W, int H, int& cw, int& R) {
       break;
     }
   R = 1;
-  while (2 * R * cw <= kChunk && H % (2 * R) == 0 && (2 * R + 2) * 32 * (cw + 8) <= kXLds) R *= 2;
+  while (2 * R * cw <= kChunk && H % (2 * R) == 0) R *= 2;
 }
 
 void launch_wgrad(ssn_net* n, const ConvL& c, TV gz, TV x) {
@@ -1251,41 +1347,63 @@ void launch_wgrad(ssn_net* n, const ConvL& c, TV gz, TV x) {
   wa.x = x;
   wa.part = n->part;
   wa.nsplit = nsplit;
-  wa.cw = cw;
   wa.R = R;
-  hipLaunchKernelGGL(conv3x3_wgrad, dim3(tci, tco, nsplit), dim3(576), 0, n->stream, wa);
-  const long nw = (long)c.Co * 9 * c.Ci;
-  launch_reduce_splits(n, n->part, nsplit, nw, n->G + c.w_off);
-  // bias gradient: per-channel sums of gz
-  hipLaunchKernelGGL(channel_sums, dim3(kPartBlocks, (c.Co + 255) / 256), dim3(256), 0, n->stream, gz,
-                     (const float*)nullptr, 0, (long)gz.N * gz.H * gz.W, c.Co, n->cpart);
-  launch_reduce_splits(n, n->cpart, kPartBlocks, (long)c.Co, n->G + c.b_off);
+  wa.cpart = n->cpart;
+  const dim3 grid((unsigned)(tci * tco * nsplit + kPartBlocks * ((c.Co + 255) / 256)));
+  if (cw == 64) hipLaunchKernelGGL((conv3x3_wgrad<64>), grid, dim3(256), 0, n->stream, wa);
+  else if (cw == 48) hipLaunchKernelGGL((conv3x3_wgrad<48>), grid, dim3(256), 0, n->stream, wa);
+  else if (cw == 32) hipLaunchKernelGGL((conv3x3_wgrad<32>), grid, dim3(256), 0, n->stream, wa);
+  else hipLaunchKernelGGL((conv3x3_wgrad<16>), grid, dim3(256), 0, n->stream, wa);
+  launch_reduce_splits(n, {n->part, n->G + c.w_off, (long)c.Co * 9 * c.Ci, nsplit},
+                       {n->cpart, n->G + c.b_off, (long)c.Co, kPartBlocks});
 }
 
-void pack_all(ssn_net* n) {
-  for (const ConvL& c : n->conv) {
-    const long nw = (long)c.Co * 9 * c.Ci;
-    hipLaunchKernelGGL(pack_conv_weights, dim3(grid1(nw)), dim3(256), 0, n->stream, n->P + c.w_off, c.Co, c.Ci, c.wf,
-                       c.wb);
+// The weight fragments of every layer, after an Adam step if there is one.
+void launch_params(ssn_net* n, const AdamArgs* adam) {
+  ParamLayers ls;
+  std::memset(&ls, 0, sizeof(ls));
+  const int nl = (int)n->conv.size();
+  for (int k = 0; k < nl; ++k) {
+    const ConvL& c = n->conv[k];
+    ls.l[k] = {c.w_off, (long)c.Co * 9 * c.Ci + c.Co, c.Co, c.Ci, c.wf, c.wb};
   }
+  ls.l[nl] = {n->hw_off, n->np - n->hw_off, 0, 0, nullptr, nullptr};
+  const dim3 grid(256, (unsigned)(nl + 1));
+  if (adam) hipLaunchKernelGGL((update_params<true>), grid, dim3(256), 0, n->stream, ls, n->P, *adam);
+  else hipLaunchKernelGGL((update_params<false>), grid, dim3(256), 0, n->stream, ls, n->P, AdamArgs());
 }
 
 __global__ void copy_f32(const float* __restrict__ src, float* __restrict__ dst, long n) {
   for (long k = blockIdx.x * (long)blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x) dst[k] = src[k];
 }
 
-__global__ void input_to_bf16(const float* __restrict__ x, int cin, long npix, TV X) {
-  for (long k = blockIdx.x * (long)blockDim.x + threadIdx.x; k < npix * X.C; k += (long)gridDim.x * blockDim.x) {
-    const long p = k / X.C;
-    const int c = (int)(k - p * X.C);
-    X.p[p * X.cs + X.coff + c] = f2bf(c < cin ? x[p * cin + c] : 0.0f);
-  }
+// fp32 images to BF16, the channels padded with zeros to 16: one pixel per thread
+__global__ void __launch_bounds__(256) input_to_bf16(const float* __restrict__ x, int cin, long npix, TV X) {
+  const long p = blockIdx.x * 256L + threadIdx.x;
+  if (p >= npix) return;
+  float v[2][8];
+#pragma unroll
+  for (int c = 0; c < 16; ++c) v[c >> 3][c & 7] = c < cin ? x[p * cin + c] : 0.0f;
+  store_u32x4(X.p + p * X.cs + X.coff, pack8(v[0]));
+  store_u32x4(X.p + p * X.cs + X.coff + 8, pack8(v[1]));
+}
+
+// grid of a for_vectors kernel over view t
+dim3 vector_grid(const TV& t) {
+  return dim3((unsigned)((t.W * (t.C / 8) + 255) / 256), (unsigned)std::min(t.H, 65535), (unsigned)std::min(t.N, 65535));
+}
+
+template <int COUT>
+void launch_head_bwd_data(const ssn_net* n, const float* target, float inv, TV z, TV g, long npix) {
+  const int per = 256 / (g.C / 8);
+  hipLaunchKernelGGL((head_bwd_data<COUT>), dim3((unsigned)((npix + per - 1) / per)), dim3(256), 0, n->stream, n->OUT,
+                     target, inv, n->P + n->hw_off, z, g, npix);
 }
 
 int net_forward(ssn_net* n, const float* x, int nb) {
   const int L = n->L;
   const long npix = (long)nb * n->H * n->W;
-  hipLaunchKernelGGL(input_to_bf16, dim3(grid1(npix * n->cin_pad)), dim3(256), 0, n->stream, x, n->cin, npix,
+  hipLaunchKernelGGL(input_to_bf16, dim3((unsigned)((npix + 255) / 256)), dim3(256), 0, n->stream, x, n->cin, npix,
                      n->X0.all(nb));
   for (int l = 0; l < L; ++l) {
     const int c = n->ch[l], cn = n->ch[l + 1];
@@ -1294,8 +1412,7 @@ int net_forward(ssn_net* n, const float* x, int nb) {
     TV skip = n->CAT[l].view(nb, cn, c);
     launch_conv_fwd(n, n->conv[enc_b(l)], n->AA[l].all(nb), n->ZB[l].all(nb), skip);
     TV pooled = n->Pin[l + 1].all(nb);
-    hipLaunchKernelGGL(avgpool2_fwd, dim3(grid1((long)nb * pooled.H * pooled.W * c / 8)), dim3(256), 0, n->stream, skip,
-                       pooled);
+    hipLaunchKernelGGL(avgpool2_fwd, vector_grid(pooled), dim3(256), 0, n->stream, skip, pooled);
   }
   launch_conv_fwd(n, n->conv[mid_a(n)], n->Pin[L].all(nb), n->ZMa.all(nb), n->AMa.all(nb));
   launch_conv_fwd(n, n->conv[mid_b(n)], n->AMa.all(nb), n->ZMb.all(nb), n->AMb.all(nb));
@@ -1303,7 +1420,7 @@ int net_forward(ssn_net* n, const float* x, int nb) {
     const int cn = n->ch[l + 1];
     TV prev = l == L - 1 ? n->AMb.all(nb) : n->ADb[l + 1].all(nb);
     TV up = n->CAT[l].view(nb, 0, cn);
-    hipLaunchKernelGGL(upsample2_fwd, dim3(grid1((long)nb * up.H * up.W * cn / 8)), dim3(256), 0, n->stream, prev, up);
+    hipLaunchKernelGGL(upsample2_fwd, vector_grid(prev), dim3(256), 0, n->stream, prev, up);
     launch_conv_fwd(n, n->conv[dec_a(n, l)], n->CAT[l].all(nb), n->ZDa[l].all(nb), n->ADa[l].all(nb));
     launch_conv_fwd(n, n->conv[dec_b(n, l)], n->ADa[l].all(nb), n->ZDb[l].all(nb), n->ADb[l].all(nb));
   }
@@ -1317,18 +1434,25 @@ int net_backward(ssn_net* n, const float* target, int nb, double* loss) {
   const int L = n->L;
   const long npix = (long)nb * n->H * n->W;
   const long nout = npix * n->cout;
-  hipLaunchKernelGGL(mse_fwd_bwd, dim3(256), dim3(256), 0, n->stream, n->OUT, target, nout, n->GOUT, n->lpart);
+  const float inv = 2.0f / (float)nout;
   // head
-  hipLaunchKernelGGL(head_wgrad, dim3(kPartBlocks), dim3(256), 0, n->stream, n->GOUT, n->ADb[0].all(nb), n->cout, npix,
-                     n->cpart);
-  launch_reduce_splits(n, n->cpart, kPartBlocks, (long)n->cout * n->ch[0], n->G + n->hw_off);
-  TV none;
-  none.p = nullptr;
-  hipLaunchKernelGGL(channel_sums, dim3(kPartBlocks), dim3(256), 0, n->stream, none, n->GOUT, n->cout, npix, n->cout,
-                     n->cpart);
-  launch_reduce_splits(n, n->cpart, kPartBlocks, (long)n->cout, n->G + n->hb_off);
-  hipLaunchKernelGGL(head_bwd_data, dim3((unsigned)((npix + 255) / 256)), dim3(256), 0, n->stream, n->GOUT,
-                     n->P + n->hw_off, n->cout, n->ZDb[0].all(nb), n->gT1[0].all(nb), npix);
+  hipLaunchKernelGGL(head_sums, dim3(kPartBlocks), dim3(256), 0, n->stream, n->OUT, target, inv, n->ADb[0].all(nb),
+                     n->cout, npix, n->part, n->cpart, n->lpart);
+  launch_reduce_splits(n, {n->part, n->G + n->hw_off, (long)n->cout * n->ch[0], kPartBlocks},
+                       {n->cpart, n->G + n->hb_off, (long)n->cout, kPartBlocks});
+  {
+    TV z = n->ZDb[0].all(nb), g = n->gT1[0].all(nb);
+    switch (n->cout) {
+      case 1: launch_head_bwd_data<1>(n, target, inv, z, g, npix); break;
+      case 2: launch_head_bwd_data<2>(n, target, inv, z, g, npix); break;
+      case 3: launch_head_bwd_data<3>(n, target, inv, z, g, npix); break;
+      case 4: launch_head_bwd_data<4>(n, target, inv, z, g, npix); break;
+      case 5: launch_head_bwd_data<5>(n, target, inv, z, g, npix); break;
+      case 6: launch_head_bwd_data<6>(n, target, inv, z, g, npix); break;
+      case 7: launch_head_bwd_data<7>(n, target, inv, z, g, npix); break;
+      default: launch_head_bwd_data<8>(n, target, inv, z, g, npix); break;
+    }
+  }
   // decoder, top level first
   for (int l = 0; l < L; ++l) {
     const int cn = n->ch[l + 1];
@@ -1343,9 +1467,7 @@ int net_backward(ssn_net* n, const float* target, int nb, double* loss) {
     TV gup = n->gCAT[l].view(nb, 0, cn);
     TV dst = l == L - 1 ? n->gM2.all(nb) : n->gT1[l + 1].all(nb);
     TV zsrc = l == L - 1 ? n->ZMb.all(nb) : n->ZDb[l + 1].all(nb);
-    hipLaunchKernelGGL(upsample2_bwd, dim3(grid1((long)nb * dst.H * dst.W * cn / 8)), dim3(256), 0, n->stream, gup, dst);
-    hipLaunchKernelGGL(silu_bwd_inplace, dim3(grid1((long)nb * dst.H * dst.W * cn / 8)), dim3(256), 0, n->stream, dst,
-                       zsrc);
+    hipLaunchKernelGGL(upsample2_bwd, vector_grid(dst), dim3(256), 0, n->stream, gup, dst, zsrc);
   }
   // bottleneck
   {
@@ -1361,10 +1483,7 @@ int net_backward(ssn_net* n, const float* target, int nb, double* loss) {
   for (int l = L - 1; l >= 0; --l) {
     const int c = n->ch[l], cn = n->ch[l + 1];
     TV gS = n->gCAT[l].view(nb, cn, c);
-    hipLaunchKernelGGL(avgpool2_bwd, dim3(grid1((long)nb * gS.H * gS.W * c / 8)), dim3(256), 0, n->stream,
-                       n->gP[l + 1].all(nb), gS, 1);
-    hipLaunchKernelGGL(silu_bwd_inplace, dim3(grid1((long)nb * gS.H * gS.W * c / 8)), dim3(256), 0, n->stream, gS,
-                       n->ZB[l].all(nb));
+    hipLaunchKernelGGL(avgpool2_bwd, vector_grid(gS), dim3(256), 0, n->stream, n->gP[l + 1].all(nb), gS, n->ZB[l].all(nb));
     const ConvL& cb = n->conv[enc_b(l)];
     const ConvL& ca = n->conv[enc_a(l)];
     launch_wgrad(n, cb, gS, n->AA[l].all(nb));
@@ -1492,7 +1611,7 @@ int ssn_set_weights(ssn_net* n, const float* host, long count) {
   SN_HIP(hipMemsetAsync(n->M, 0, n->np * 4, n->stream));
   SN_HIP(hipMemsetAsync(n->V, 0, n->np * 4, n->stream));
   n->adam_t = 0;
-  pack_all(n);
+  launch_params(n, nullptr);
   SN_HIP(hipGetLastError());
   SN_HIP(hipStreamSynchronize(n->stream));
   return SS_OK;
@@ -1662,9 +1781,8 @@ int ssn_adam_step(ssn_net* n, float lr) {
     hipLaunchKernelGGL(grad_clip_scale, dim3(1), dim3(256), 0, n->stream, n->npart, kPartBlocks, n->clip, n->gscale);
     gs = n->gscale;
   }
-  hipLaunchKernelGGL(adam_update, dim3(grid1(n->np)), dim3(256), 0, n->stream, n->P, n->M, n->V, n->G, gs, n->np, lr,
-                     b1, b2, 1e-8f, c1, c2);
-  pack_all(n);
+  const AdamArgs adam = {n->M, n->V, n->G, gs, lr, b1, b2, 1e-8f, c1, c2};
+  launch_params(n, &adam);
   SN_HIP(hipGetLastError());
   return SS_OK;
 }
