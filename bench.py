@@ -335,7 +335,7 @@ def ss_tile(i):
     return ss.ss_tile_shape(i)
 
 
-STAGE_SOURCES = ["ss_internal.hpp", "ss_theory.hpp", "ss_kernels.hpp", "ss_api.hip"]
+STAGE_SOURCES = ["ss_internal.hpp", "ss_theory.hpp", "ss_kernels.hpp", "ss_launch.hpp", "ss_pass.hpp", "ss_api.hip"]
 
 
 def _code_only(text: str) -> str:

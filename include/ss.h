@@ -204,10 +204,9 @@ int ss_components(const char* theory);
 int ss_workspace_bytes(const char* theory, int Nx, int Ny, int dtype, size_t* bytes);
 
 /* Workspace bytes ss_create needs for these parameters: ss_workspace_bytes
- * plus, with demagnetisation, the solver's stage point (C planes of the
- * dtype) and its FP64 planes (seven on the lattice, three per coarser level;
- * about 75 bytes per site in all for FP32). Validates params as ss_create
- * does. */
+ * plus, with demagnetisation, the solver's FP64 planes (eight on the lattice,
+ * three per coarser level; about 72 bytes per site in all). Validates params as
+ * ss_create does. */
 int ss_workspace_bytes_for(const char* theory, int Nx, int Ny, const ss_params* params, int dtype, size_t* bytes);
 
 /* Create a context. Parameters are validated and resolved before any device
@@ -259,12 +258,11 @@ int ss_init_ansatz(ss_ctx* ctx, int kind, int n, const double* xy, const double*
 
 /* Mean device time per launch of each of the passes, measured with HIP events
  * on the context's stream over n_steps flow steps (the steps are real flow
- * steps). RK4: ms[0..3] = stage passes P1..P4 (P1 including the one-workgroup
- * launch that finalises its reduction), ms[4] = whole step; under a fused plan
- * ms[1] is the pass of stages 2-4 and ms[2] = ms[3] = 0. One-pass integrators:
- * ms[0] = the step's pass with its finalise, ms[1] = velocity Verlet's restart
- * pass (the force of an arrested field; a launch that returns at once on the
- * other steps), ms[2] = ms[3] = 0. Synchronises. */
+ * steps; a pass's reduction is summed at the start of the launch after it). RK4:
+ * ms[0..3] = stage passes P1..P4, ms[4] = whole step; under a fused plan ms[1] is
+ * the pass of stages 2-4 and ms[2] = ms[3] = 0. One-pass integrators: ms[0] = the
+ * step's pass, ms[1] = velocity Verlet's restart pass (the force of an arrested
+ * field; a launch that returns at once on the other steps), ms[2] = ms[3] = 0. Synchronises. */
 int ss_time_passes(ss_ctx* ctx, int n_steps, double* ms);
 
 /* Copy the current field and (if velocity != NULL) the fictitious velocity

@@ -16,8 +16,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libss.so")
-SOURCES = ["ss_api.hip", "ssn_unet.hip"]
-HEADERS = ["ss_internal.hpp", "ss_theory.hpp", "ss_kernels.hpp"]
+SOURCES = ["ss_api.hip", "ssn_unet.hip"] + [f"ss_pass_{t}_{th}.hip" for t in ("f32", "f64") for th in ("ah", "cm", "bs")]
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "-fPIC",
@@ -25,7 +24,7 @@ HIPCC_FLAGS = [
     # keep the compiler from forming packed FP32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-ffp-contract=fast",
-    "-Wno-unused-result",
+    "-Wno-unused-result", "-Wno-unused-function",
 ]
 
 

@@ -22,7 +22,7 @@
 #include <mutex>
 
 #include "../../include/ss.h"
-#include "ss_kernels.hpp"
+#include "ss_launch.hpp"
 #include "ss_demag.hpp"
 #include "ss_bec.hpp"
 
@@ -44,13 +44,6 @@ int fail(int code, const std::string& msg) {
       return fail(SS_EHIP, std::string(#call) + ": " + hipGetErrorString(e_));                \
   } while (0)
 
-// Tile shapes compiled into the library: a workgroup covers TX x TY sites,
-// each thread RY rows of one column. ss_autotune times them on the caller's
-// lattice; SS_TILE (environment) or ss_set_tile force one.
-struct TileCfg {
-  int TX, TY, RY;
-};
-constexpr TileCfg kTiles[] = {{64, 16, 2}, {64, 8, 2}, {64, 16, 4}, {64, 32, 4}};
 constexpr int kNumTiles = 4;
 constexpr int kDefaultTile = 0;
 constexpr int kDefaultPlanF32 = SS_PLAN_FUSED;
@@ -58,7 +51,6 @@ static_assert(kTiles[0].TX == kExTX && kTiles[0].TY == kExTY, "the exact-gradien
 static_assert(kTiles[0].TX == 64 && kTiles[0].TY == 16 && kTiles[1].TX == 64 && kTiles[1].TY == 8,
               "the fused passes use the layouts of tiles 0 (64 x 16) and 1 (64 x 8)");
 constexpr int kDefaultGraphSteps = 16;
-constexpr long kMaxGroups = 2048;  // persistent launch: at most 8 workgroups per CU
 
 int lower_eq(const char* a, const char* b) {
   for (; *a && *b; ++a, ++b) {
@@ -80,7 +72,7 @@ struct Layout {
   long pitch, plane;        // elements
   long col0;                // element offset of padded column 0 from the set base
   size_t set_bytes;         // bytes of one C-plane field set (256-B aligned)
-  size_t status_off, partial_off, init_off, total;
+  size_t status_off, partial_off, init_off, alt_off, total;
   int ntx, nty, nlaunch;    // for the selected tile shape
   int seg;                  // tiles per work unit of the stage launches
 };
@@ -115,7 +107,9 @@ Layout make_layout(int C, int Nx, int Ny, int esize) {
   const long nparts = std::max<long>(4L * kMaxGroups, 5L * nobs);
   L.init_off = L.partial_off + (size_t)round_up(nparts * 8, 256);
   // staging of ansatz centres and windings for ss_init_ansatz
-  L.total = L.init_off + (size_t)round_up(3L * kMaxVortices * 8, 256);
+  L.alt_off = L.init_off + (size_t)round_up(3L * kMaxVortices * 8, 256);
+  // the other status copy and the other partials of the single-lattice passes (Link)
+  L.total = L.alt_off + (size_t)round_up(sizeof(DevStatus), 256) + (size_t)round_up(4L * kMaxGroups * 8, 256);
   return L;
 }
 
@@ -151,6 +145,8 @@ struct ss_ctx {
   void* q;
   DevStatus* st;
   double* partials;
+  DevStatus* alt;     // the other status copy (Link)
+  double* partials2;  // the other partials
   hipGraphExec_t graph;
   int graph_steps;
   int tile;
@@ -162,7 +158,6 @@ struct ss_ctx {
   struct Demag {
     int on;
     int iters_flow, iters_eval;  // conjugate-gradient iterations per solve
-    void* S;                     // stage point (C planes, flow layout)
     DmVecs v;
     int nlev;
     DmLevel lv[kDmMaxLevels];
@@ -212,7 +207,7 @@ PassArgs<T> pass_args(const ss_ctx* c) {
   PassArgs<T> a;
   a.B = bufs_of<T>(c);
   a.cf = coeffs_of(c);
-  a.st = c->st;
+  a.link = Link{c->st, c->st, c->st, nullptr, 0, -1};
   a.partials = c->partials;
   a.src = nullptr;
   a.out = nullptr;
@@ -223,119 +218,113 @@ PassArgs<T> pass_args(const ss_ctx* c) {
   return a;
 }
 
-constexpr long kNumCUs = 256;
+// Where a sequence of passes stands while it is queued: which status copy holds
+// the head, the test that is pending (Link) and the partials it left. A sequence
+// starts and ends settled: the head in c->st, nothing pending.
+struct Run {
+  int alt = 0;     // the head is in c->alt
+  int kind = -1;   // finalise_kind of the pending test, or -1
+  int groups = 0;  // its partials
+  int second = 0;  // they are in c->partials2
+};
 
-// Workgroups of one stage-pass instantiation resident on the whole GPU at
-// once: the runtime's occupancy for one CU, rounded down to a power of two (so
-// units still split evenly over the eight XCD bands), times the CUs. Queried
-// once per instantiation on the first device that launches it.
-template <class T, int TH, int PASS, int TX, int TY, int RY>
-long resident_groups() {
-  static const long n = [] {
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per_cu, reinterpret_cast<const void*>(&stage_pass<T, TH, PASS, TX, TY, RY>), TX * (TY / RY), 0) !=
-            hipSuccess ||
-        per_cu < 1) {
-      (void)hipGetLastError();  // a failed query must not surface as a launch error
-      return kMaxGroups;
-    }
-    int p2 = 1;
-    while (2 * p2 <= per_cu) p2 *= 2;
-    return std::min(kMaxGroups, kNumCUs * p2);
-  }();
-  return n;
+double* run_partials(const ss_ctx* c, int second) { return second ? c->partials2 : c->partials; }
+
+// The link of the next launch, which takes the pending test.
+Link take_link(const ss_ctx* c, Run& r) {
+  Link L;
+  L.st = c->st;
+  L.in = r.alt ? c->alt : c->st;
+  L.kind = r.kind;
+  L.part = run_partials(c, r.second);
+  L.n = r.groups;
+  if (r.kind >= 0) r.alt ^= 1;
+  r.kind = -1;
+  L.out = r.alt ? c->alt : c->st;
+  return L;
 }
 
-// Launches a pass and returns its workgroup count. P1 runs with at most its
-// resident workgroups, each walking longer column segments (on 4096^2 with
-// 64 x 16 tiles: 512 groups, 0.184 -> 0.177 ms against 2048).
-template <class T, int TH, int PASS, int CFG>
-int launch_cfg(const PassArgs<T>& a, int nlaunch, hipStream_t s) {
-  constexpr TileCfg tc = kTiles[CFG];
-  PassArgs<T> b = a;
-  if constexpr (PASS == kP1 || PASS == kPrime || advances_first(PASS) || fixed_tile(PASS) || PASS == kGD) {
-    const long r = resident_groups<T, TH, PASS, tc.TX, tc.TY, tc.RY>();
-    if (nlaunch > r) {
-      nlaunch = (int)r;
-      b.seg = (int)std::min<long>(std::max<long>(1, ((long)a.ntx * a.nty) / nlaunch), a.nty);
-    }
-  }
-  hipLaunchKernelGGL((stage_pass<T, TH, PASS, tc.TX, tc.TY, tc.RY>), dim3(nlaunch), dim3(tc.TX, tc.TY / tc.RY), 0,
-                     s, b);
-  return nlaunch;
-}
-
-template <class T, int TH, int PASS>
-int launch_pass_t(int tile, const PassArgs<T>& a, int nlaunch, hipStream_t s) {
-  switch (tile) {
-    case 0: return launch_cfg<T, TH, PASS, 0>(a, nlaunch, s);
-    case 1: return launch_cfg<T, TH, PASS, 1>(a, nlaunch, s);
-    case 2: return launch_cfg<T, TH, PASS, 2>(a, nlaunch, s);
-    default: return launch_cfg<T, TH, PASS, 3>(a, nlaunch, s);
-  }
+// The status in c->st.
+void settle(const ss_ctx* c, Run& r, hipStream_t s) {
+  if (r.kind < 0 && !r.alt) return;
+  Link L = take_link(c, r);
+  L.out = c->st;
+  r.alt = 0;
+  hipLaunchKernelGGL(settle_status, dim3(1), dim3(256), 0, s, L, c->h);
 }
 
 int dm_groups(long n) { return (int)std::max<long>(1, std::min<long>((n + 255) / 256, 4096)); }
 
-// One V-cycle from level l (the level's psi and rhs are set): smoothing, the
-// residual restricted to the next level, its correction, smoothing; on the
-// coarsest level an even number of sweeps from zero.
+int dm_tile_groups(const DmLevel& L) { return std::min(dm_tiles(L), kDmMaxGroups); }
+
+bool dm_is_small(const ss_ctx::Demag& d, int l) { return dm_small_bytes(d.lv, d.nlev, l) <= kDmSmallLds; }
+
+// One V-cycle from level l > 0, whose rhs is set: psi.
 void dm_vcycle(const ss_ctx::Demag& d, int l, const DevStatus* skip, hipStream_t s) {
   const DmLevel& L = d.lv[l];
-  const long small = dm_small_bytes(d.lv, d.nlev, l);
-  if (small <= kDmSmallLds) {
+  if (dm_is_small(d, l)) {
     // this level and the coarser ones in one workgroup, in LDS
     DmHierarchy H;
     for (int k = 0; k < d.nlev; ++k) H.lv[k] = d.lv[k];
     H.nlev = d.nlev;
     H.cinv = d.cinv;
     H.cn = d.cn;
-    hipLaunchKernelGGL(dm_vcycle_small, dim3(1), dim3(256), (unsigned)small, s, H, l, skip);
+    hipLaunchKernelGGL(dm_vcycle_small, dim3(1), dim3(kDmSmallThreads), (unsigned)dm_small_bytes(d.lv, d.nlev, l), s,
+                       H, l, d.v.part, skip);
     return;
   }
   if (l == d.nlev - 1) {
     hipLaunchKernelGGL(dm_coarse_solve, dim3(1), dim3(256), 0, s, L, skip);
     return;
   }
-  // two sweeps psi -> tmp, the residual of tmp restricted, the coarse
-  // correction, then tmp + P c smoothed by two sweeps into psi
   static_assert(kDmSmooth == 2, "one launch smooths twice");
-  const DmLevel& Cl = d.lv[l + 1];
-  const int gt = std::min(dm_tiles(L), 2048);
-  hipLaunchKernelGGL(dm_jacobi2, dim3(gt), dim3(256), 0, s, L, (const double*)L.psi, L.tmp, Cl, 0, skip);
-  hipLaunchKernelGGL(dm_restrict_res, dim3(std::min(dm_rtiles(Cl), 2048)), dim3(256), 0, s, L,
-                     (const double*)L.tmp, Cl, skip);
+  const int g = dm_tile_groups(L);
+  const DmVecs none = {};
+  hipLaunchKernelGGL((dm_down<false>), dim3(g), dim3(256), 0, s, L, d.lv[l + 1], none, 0, 0, 0, skip);
   dm_vcycle(d, l + 1, skip, s);
-  hipLaunchKernelGGL(dm_jacobi2, dim3(gt), dim3(256), 0, s, L, (const double*)L.tmp, L.psi, Cl, 1, skip);
+  hipLaunchKernelGGL((dm_up<false>), dim3(g), dim3(256), 0, s, L, d.lv[l + 1], (const double*)L.rhs,
+                     (double*)nullptr, skip);
 }
 
 // Demagnetising potential of the stage point of pass PASS (Sec. 4.2, eq. (6)),
-// queued before the pass: the stage point, then `iters` iterations of
-// multigrid-preconditioned conjugate gradients from the last potential. A flow's
-// solves stop with the flow (its status block); an evaluation's always run.
+// queued before the pass: `iters` iterations of multigrid-preconditioned conjugate
+// gradients from the last potential. A flow's solves take its pending test and stop
+// with it; an evaluation's always run.
 template <class T, int PASS>
-void demag_solve(const ss_ctx* c, const PassArgs<T>& a, hipStream_t s) {
+void demag_solve(const ss_ctx* c, const PassArgs<T>& a, Run& run, hipStream_t s) {
   const ss_ctx::Demag& d = c->dm;
-  const DevStatus* skip = PASS == kEval ? nullptr : c->st;
   const int iters = PASS == kEval ? d.iters_eval : d.iters_flow;
-  const DmLevel& L0 = d.lv[0];
-  Bufs<T> B = a.B;
-  T* S = (T*)d.S;
-  hipLaunchKernelGGL((dm_stage_point<T, PASS>), dim3(dm_groups((long)(c->Nx + 4) * (c->Ny + 4))), dim3(256), 0, s, B,
-                     a.cf, (const DevStatus*)c->st, a.src, S);
-  const int g = dm_groups((long)c->Nx * c->Ny);
-  hipLaunchKernelGGL((dm_begin<T>), dim3(g), dim3(256), 0, s, B, (const T*)S, L0, d.v, skip);
+  DmLevel L0 = d.lv[0];
+  const Link link = PASS == kEval ? a.link : take_link(c, run);
+  const DevStatus* skip = PASS == kEval ? nullptr : link.out;
+  const int g = dm_tile_groups(L0);
+  hipLaunchKernelGGL((dm_begin<T, PASS>), dim3(g), dim3(256), 0, s, a.B, a.cf, link, a.src, L0, d.v);
+  // a lattice whose whole hierarchy is small, or that is its own coarsest level,
+  // has its V-cycle in one workgroup
+  const bool small = dm_is_small(d, 0), deep = !small && d.nlev > 1;
+  const int gs = std::min(dm_groups((long)c->Nx * c->Ny), kDmMaxGroups);
+  int nrz = 1;
   for (int it = 0; it < iters; ++it) {
-    const int first = it == 0 ? 1 : 0;
-    dm_vcycle(d, 0, skip, s);
-    // r.z partials; beta and the direction; Ad with the d.Ad partials; alpha and the update
-    hipLaunchKernelGGL(dm_dot, dim3(kDmRedGroups), dim3(256), 0, s, L0, (const double*)d.v.r, (const double*)L0.psi,
-                       d.v.part, skip);
-    hipLaunchKernelGGL(dm_dir, dim3(g), dim3(256), 0, s, L0, d.v, first, skip);
-    hipLaunchKernelGGL(dm_matvec, dim3(kDmRedGroups), dim3(256), 0, s, L0, d.v, skip);
-    hipLaunchKernelGGL(dm_update, dim3(g), dim3(256), 0, s, L0, d.v, skip);
+    // rhs, d: the planes of parity `cur` hold -r and receive d in this iteration
+    const int cur = it & 1;
+    L0.rhs = d.v.rhs[cur];
+    if (deep) {
+      if (it == 0)
+        hipLaunchKernelGGL((dm_down<false>), dim3(g), dim3(256), 0, s, L0, d.lv[1], d.v, 0, 0, 0, skip);
+      else
+        hipLaunchKernelGGL((dm_down<true>), dim3(g), dim3(256), 0, s, L0, d.lv[1], d.v, cur ^ 1, nrz, g, skip);
+      dm_vcycle(d, 1, skip, s);
+      nrz = g;
+      hipLaunchKernelGGL((dm_up<true>), dim3(g), dim3(256), 0, s, L0, d.lv[1], (const double*)L0.rhs, d.v.part, skip);
+    } else {
+      if (it > 0) hipLaunchKernelGGL(dm_update, dim3(gs), dim3(256), 0, s, L0, d.v, cur ^ 1, 1, nrz, g, skip);
+      ss_ctx::Demag d0 = d;
+      d0.lv[0] = L0;
+      dm_vcycle(d0, 0, skip, s);
+    }
+    hipLaunchKernelGGL(dm_direction, dim3(g), dim3(256), 0, s, L0, d.v, cur, it == 0 ? 1 : 0, nrz, skip);
   }
+  hipLaunchKernelGGL(dm_update, dim3(gs), dim3(256), 0, s, L0, d.v, (iters - 1) & 1, 0, nrz, g, skip);
 }
 
 // A BEC pass (RK4 stages, the one-pass steps, the check, the prime pass and the
@@ -370,13 +359,13 @@ void bec_pass(const ss_ctx* c, const PassArgs<T>& a, hipStream_t s) {
 }
 
 template <class T, int PASS>
-void launch_lattice_pass(const ss_ctx* c, const PassArgs<T>& a, hipStream_t s);
+void launch_lattice_pass(const ss_ctx* c, PassArgs<T> a, Run& r, hipStream_t s);
 
-// A pass; a reducing pass (P1, evaluation, check) is followed by its finalise
-// launch, which sums the workgroup partials and updates the status. With
-// demagnetisation the pass is preceded by the solve for its stage point.
+// A pass. A reducing pass leaves its test pending in r (the next launch takes it;
+// an evaluation's result is summed by a launch of its own). With demagnetisation
+// the pass is preceded by the solve for its stage point.
 template <class T, int PASS>
-void launch_pass(const ss_ctx* c, const PassArgs<T>& a, hipStream_t s) {
+void launch_pass(const ss_ctx* c, const PassArgs<T>& a, Run& r, hipStream_t s) {
   if constexpr (PASS == kGF) {
     // only the BEC keeps the force between gradient-flow steps (the lattice
     // theories run kGD)
@@ -389,48 +378,52 @@ void launch_pass(const ss_ctx* c, const PassArgs<T>& a, hipStream_t s) {
         return;
       }
     }
-    launch_lattice_pass<T, PASS>(c, a, s);
+    launch_lattice_pass<T, PASS>(c, a, r, s);
   }
 }
 
 // A pass of the lattice theories (everything but the BEC).
 template <class T, int PASS>
-void launch_lattice_pass(const ss_ctx* c, const PassArgs<T>& a, hipStream_t s) {
+void launch_lattice_pass(const ss_ctx* c, PassArgs<T> a, Run& r, hipStream_t s) {
   // velocity Verlet's restart and end of run evaluate the current field, whose
   // potential the step that made it has solved for
-  if (c->dm.on && PASS != kVVRestart && PASS != kVVEnd) demag_solve<T, PASS>(c, a, s);
+  if (c->dm.on && PASS != kVVRestart && PASS != kVVEnd) {
+    demag_solve<T, PASS>(c, a, r, s);
+  }
+  if (PASS != kEval) a.link = take_link(c, r);
+  if (PASS != kEval && reduces(PASS)) {
+    r.second ^= 1;
+    a.partials = run_partials(c, r.second);
+  }
   int groups = c->L.nlaunch;  // workgroups launched = partials written
   if (c->grad_mode == SS_GRAD_EXACT) {
     // exact-gradient passes: one tile shape (64 x 16), the layout of tile 0
-    if (c->theory == SS_THEORY_AH)
-      hipLaunchKernelGGL((stage_pass_exact<T, kAH, PASS>), dim3(groups), dim3(kExTX, kExTY / kExRY), 0, s, a);
-    else if (c->theory == SS_THEORY_CM)
-      hipLaunchKernelGGL((stage_pass_exact<T, kCM, PASS>), dim3(groups), dim3(kExTX, kExTY / kExRY), 0, s, a);
-    else
-      hipLaunchKernelGGL((stage_pass_exact<T, kBS, PASS>), dim3(groups), dim3(kExTX, kExTY / kExRY), 0, s, a);
-  } else if constexpr (fixed_tile(PASS)) {
-    // once per run, or after an arrest: one tile shape (64 x 16) whatever the
-    // context's tile
-    constexpr int kFixedTile = 0;
-    PassArgs<T> b = a;
-    Layout L = c->L;
-    set_tiles(L, c->Nx, c->Ny, kFixedTile);
-    b.ntx = L.ntx;
-    b.nty = L.nty;
-    b.seg = L.seg;
-    if (c->theory == SS_THEORY_AH) groups = launch_cfg<T, kAH, PASS, kFixedTile>(b, L.nlaunch, s);
-    else if (c->theory == SS_THEORY_CM) groups = launch_cfg<T, kCM, PASS, kFixedTile>(b, L.nlaunch, s);
-    else groups = launch_cfg<T, kBS, PASS, kFixedTile>(b, L.nlaunch, s);
-  } else if (c->theory == SS_THEORY_AH) {
-    groups = launch_pass_t<T, kAH, PASS>(c->tile, a, groups, s);
-  } else if (c->theory == SS_THEORY_CM) {
-    groups = launch_pass_t<T, kCM, PASS>(c->tile, a, groups, s);
+    if (c->theory == SS_THEORY_AH) launch_exact<T, kAH, PASS>(a, groups, s);
+    else if (c->theory == SS_THEORY_CM) launch_exact<T, kCM, PASS>(a, groups, s);
+    else launch_exact<T, kBS, PASS>(a, groups, s);
   } else {
-    groups = launch_pass_t<T, kBS, PASS>(c->tile, a, groups, s);
+    int tile = c->tile;
+    if constexpr (fixed_tile(PASS)) {
+      // once per run, or after an arrest: one tile shape (64 x 16) whatever the
+      // context's tile
+      tile = 0;
+      Layout L = c->L;
+      set_tiles(L, c->Nx, c->Ny, tile);
+      a.ntx = L.ntx;
+      a.nty = L.nty;
+      a.seg = L.seg;
+      groups = L.nlaunch;
+    }
+    if (c->theory == SS_THEORY_AH) groups = launch_tiled<T, kAH, PASS>(tile, a, groups, s);
+    else if (c->theory == SS_THEORY_CM) groups = launch_tiled<T, kCM, PASS>(tile, a, groups, s);
+    else groups = launch_tiled<T, kBS, PASS>(tile, a, groups, s);
   }
-  if constexpr (reduces(PASS))
-    hipLaunchKernelGGL((pass_finalise<PASS>), dim3(1), dim3(256), 0, s, a.st, (const double*)a.partials, groups,
-                       a.cf.h);
+  if constexpr (PASS == kEval) {
+    hipLaunchKernelGGL(eval_finalise, dim3(1), dim3(256), 0, s, a.link.st, (const double*)a.partials, groups, a.cf.h);
+  } else if constexpr (reduces(PASS)) {
+    r.kind = finalise_kind(PASS);
+    r.groups = groups;
+  }
 }
 
 // Fused stages 2-4 run on 64 x 16 tiles (tile 0) or 64 x 8 tiles (tile 1), two
@@ -441,17 +434,6 @@ template <class T>
 int fused_layout_tile(int tile) {
   if (sizeof(T) == 8) return 1;
   return tile == 1 ? 1 : 0;
-}
-
-template <class T, int TH>
-void launch_fused_t(int layout_tile, const PassArgs<T>& a, int nlaunch, hipStream_t s) {
-  if constexpr (sizeof(T) == 4) {
-    if (layout_tile == 0) {
-      hipLaunchKernelGGL((stage_pass_fused<T, TH, 64, 16, 2>), dim3(nlaunch), dim3(64, 8), 0, s, a);
-      return;
-    }
-  }
-  hipLaunchKernelGGL((stage_pass_fused<T, TH, 64, 8, 2>), dim3(nlaunch), dim3(64, 4), 0, s, a);
 }
 
 // Workgroups of a fused launch: as many as are resident at once (one per CU
@@ -468,8 +450,9 @@ long fused_groups(int layout_tile) {
 }
 
 template <class T>
-void launch_fused(const ss_ctx* c, hipStream_t s) {
+void launch_fused(const ss_ctx* c, Run& r, hipStream_t s) {
   PassArgs<T> a = pass_args<T>(c);
+  a.link = take_link(c, r);
   Layout L = c->L;
   const int lt = fused_layout_tile<T>(c->tile);
   set_tiles(L, c->Nx, c->Ny, lt);
@@ -502,98 +485,91 @@ bool vv_kdk(const ss_ctx* c) { return c->integ == SS_INTEG_VV && vv_kdk_form(c);
 bool gd_form(const ss_ctx* c) { return c->integ == SS_INTEG_GF && c->theory != SS_THEORY_BEC; }
 
 template <class T>
-void enqueue_steps(const ss_ctx* c, int n, hipStream_t s) {
+void enqueue_steps(const ss_ctx* c, int n, Run& r, hipStream_t s) {
   PassArgs<T> a = pass_args<T>(c);
   if (c->integ != SS_INTEG_RK4) {
-    // one pass (and its finalise) per step; velocity Verlet's restart pass
-    // before it returns at once unless the last step was arrested
+    // one pass per step; velocity Verlet's restart pass before it returns at
+    // once unless the last step was arrested
     for (int k = 0; k < n; ++k) {
       if (gd_form(c)) {
-        launch_pass<T, kGD>(c, a, s);
+        launch_pass<T, kGD>(c, a, r, s);
       } else if (c->integ == SS_INTEG_GF) {
-        launch_pass<T, kGF>(c, a, s);
+        launch_pass<T, kGF>(c, a, r, s);
       } else if (vv_kdk(c)) {
-        launch_pass<T, kVVRestart>(c, a, s);
-        launch_pass<T, kVV>(c, a, s);
+        launch_pass<T, kVVRestart>(c, a, r, s);
+        launch_pass<T, kVV>(c, a, r, s);
       } else {
-        launch_pass<T, kVVA>(c, a, s);
+        launch_pass<T, kVVA>(c, a, r, s);
       }
     }
     return;
   }
   for (int k = 0; k < n; ++k) {
-    launch_pass<T, kP1>(c, a, s);
+    launch_pass<T, kP1>(c, a, r, s);
     if (c->plan != SS_PLAN_STAGES) {
-      launch_fused<T>(c, s);
+      launch_fused<T>(c, r, s);
       continue;
     }
-    launch_pass<T, kP2>(c, a, s);
-    launch_pass<T, kP3>(c, a, s);
-    launch_pass<T, kP4>(c, a, s);
+    launch_pass<T, kP2>(c, a, r, s);
+    launch_pass<T, kP3>(c, a, r, s);
+    launch_pass<T, kP4>(c, a, r, s);
   }
 }
 
-void enqueue_steps_any(const ss_ctx* c, int n, hipStream_t s) {
-  if (c->dtype == SS_F32) enqueue_steps<float>(c, n, s);
-  else enqueue_steps<double>(c, n, s);
+void enqueue_steps_any(const ss_ctx* c, int n, Run& r, hipStream_t s) {
+  if (c->dtype == SS_F32) enqueue_steps<float>(c, n, r, s);
+  else enqueue_steps<double>(c, n, r, s);
 }
 
-template <class T>
-void enqueue_check(const ss_ctx* c, hipStream_t s) {
-  PassArgs<T> a = pass_args<T>(c);
-  launch_pass<T, kCheck>(c, a, s);
-  hipLaunchKernelGGL((apply_arrest<T>), dim3(1024), dim3(256), 0, s, a.B, c->st, c->C);
-}
-
-void enqueue_check_any(const ss_ctx* c, hipStream_t s) {
-  if (c->dtype == SS_F32) enqueue_check<float>(c, s);
-  else enqueue_check<double>(c, s);
+// One pass on the context's fields.
+template <int PASS>
+void enqueue_pass_any(const ss_ctx* c, Run& r, hipStream_t s) {
+  if (c->dtype == SS_F32) launch_pass<float, PASS>(c, pass_args<float>(c), r, s);
+  else launch_pass<double, PASS>(c, pass_args<double>(c), r, s);
 }
 
 // Start of a run of a one-pass integrator: the arrest test of the current field
 // (as a check pass) and its force stored in the buffer of the step's parity, or
 // for velocity Verlet in kick-drift-kick form u = v + dt/2 a in place of v.
-void enqueue_prime_any(const ss_ctx* c, hipStream_t s) {
-  if (gd_form(c)) return;  // its first step tests the current field
-  if (vv_kdk(c)) {
-    if (c->dtype == SS_F32) launch_pass<float, kVVStart>(c, pass_args<float>(c), s);
-    else launch_pass<double, kVVStart>(c, pass_args<double>(c), s);
-    return;
-  }
-  if (c->dtype == SS_F32) launch_pass<float, kPrime>(c, pass_args<float>(c), s);
-  else launch_pass<double, kPrime>(c, pass_args<double>(c), s);
+void enqueue_prime_any(const ss_ctx* c, Run& r, hipStream_t s) {
+  if (c->integ == SS_INTEG_RK4 || gd_form(c)) return;  // the first step tests the current field
+  if (vv_kdk(c)) enqueue_pass_any<kVVStart>(c, r, s);
+  else enqueue_pass_any<kPrime>(c, r, s);
 }
 
-template <class T>
-void enqueue_apply_arrest(const ss_ctx* c, hipStream_t s) {
-  hipLaunchKernelGGL((apply_arrest<T>), dim3(1024), dim3(256), 0, s, bufs_of<T>(c), c->st, c->C);
+void enqueue_apply_arrest(const ss_ctx* c, Run& r, hipStream_t s) {
+  settle(c, r, s);
+  if (c->dtype == SS_F32)
+    hipLaunchKernelGGL((apply_arrest<float>), dim3(1024), dim3(256), 0, s, bufs_of<float>(c), c->st, c->C);
+  else
+    hipLaunchKernelGGL((apply_arrest<double>), dim3(1024), dim3(256), 0, s, bufs_of<double>(c), c->st, c->C);
 }
 
-// End of a run of a one-pass integrator: the velocity of the current field,
-// zero if the last test arrested the flow (kick-drift-kick velocity Verlet
-// turns u back into v).
-void enqueue_settle_any(const ss_ctx* c, hipStream_t s) {
+// End of a run whose last field has been tested: the velocity of the current
+// field, zero if the last test arrested the flow (kick-drift-kick velocity Verlet
+// turns u back into v). Settled.
+void enqueue_settle_any(const ss_ctx* c, Run& r, hipStream_t s) {
   if (vv_kdk(c)) {
-    if (c->dtype == SS_F32) launch_pass<float, kVVEnd>(c, pass_args<float>(c), s);
-    else launch_pass<double, kVVEnd>(c, pass_args<double>(c), s);
-  } else if (c->dtype == SS_F32) {
-    enqueue_apply_arrest<float>(c, s);
+    enqueue_pass_any<kVVEnd>(c, r, s);
+    settle(c, r, s);
   } else {
-    enqueue_apply_arrest<double>(c, s);
+    enqueue_apply_arrest(c, r, s);
   }
 }
 
 // End of a run of steps: the arrest test of the final field where the
 // integrator has not taken it already, then the velocity zeroed if it fired.
-void enqueue_end_of_run_any(const ss_ctx* c, hipStream_t s) {
+// Settled.
+void enqueue_end_of_run_any(const ss_ctx* c, Run& r, hipStream_t s) {
   if (c->integ == SS_INTEG_RK4) {
-    enqueue_check_any(c, s);
+    enqueue_pass_any<kCheck>(c, r, s);
+    enqueue_apply_arrest(c, r, s);
   } else if (gd_form(c)) {
     // the last field is untested: its energy and gradient
-    if (c->dtype == SS_F32) launch_pass<float, kGDCheck>(c, pass_args<float>(c), s);
-    else launch_pass<double, kGDCheck>(c, pass_args<double>(c), s);
+    enqueue_pass_any<kGDCheck>(c, r, s);
+    settle(c, r, s);
   } else {
-    enqueue_settle_any(c, s);
+    enqueue_settle_any(c, r, s);
   }
 }
 
@@ -759,19 +735,17 @@ int resolve_problem(const char* theory, int Nx, int Ny, double h, const ss_param
   return SS_OK;
 }
 
-// Demagnetisation region of a workspace (after the flow's own buffers): the
-// stage point, level 0 of the solver (x, r, d, Ad and the V-cycle's psi, tmp,
-// rhs), three planes per coarser level, the reduction partials and scalars.
+// Demagnetisation region of a workspace (after the flow's own buffers): level 0
+// of the solver (x, two planes each of -r and d, Ad and the V-cycle's psi and
+// tmp), three planes per coarser level, the reduction partials and scalars.
 // With base == nullptr only the size is computed.
-size_t demag_region(int Nx, int Ny, double h, const Layout& L, int esize, char* base, ss_ctx::Demag* d) {
+size_t demag_region(int Nx, int Ny, double h, char* base, ss_ctx::Demag* d) {
   size_t off = 0;
   auto take = [&](size_t bytes) {
     char* p = base ? base + off : nullptr;
     off += (size_t)round_up((long)bytes, 256);
     return p;
   };
-  char* S = take(L.set_bytes);
-  if (d) d->S = S ? S + L.col0 * esize : nullptr;
   int nx = Nx, ny = Ny, nlev = 0;
   double hl = h;
   for (;;) {
@@ -782,20 +756,22 @@ size_t demag_region(int Nx, int Ny, double h, const Layout& L, int esize, char* 
     lv.pitch = nx + 4;
     lv.h = hl;
     if (nlev == 0) {
-      double* x = (double*)take(pb);
-      double* r = (double*)take(pb);
-      double* dd = (double*)take(pb);
-      double* ad = (double*)take(pb);
+      double* v[6];
+      for (double*& p : v) p = (double*)take(pb);
+      lv.rhs = v[1];
       if (d) {
-        d->v.x = x;
-        d->v.r = r;
-        d->v.d = dd;
-        d->v.Ad = ad;
+        d->v.x = v[0];
+        d->v.rhs[0] = v[1];
+        d->v.rhs[1] = v[2];
+        d->v.d[0] = v[3];
+        d->v.d[1] = v[4];
+        d->v.Ad = v[5];
       }
+    } else {
+      lv.rhs = (double*)take(pb);
     }
     lv.psi = (double*)take(pb);
     lv.tmp = (double*)take(pb);
-    lv.rhs = (double*)take(pb);
     if (d) d->lv[nlev] = lv;
     ++nlev;
     if (std::min(nx, ny) < 8 || nlev == kDmMaxLevels) break;
@@ -803,8 +779,8 @@ size_t demag_region(int Nx, int Ny, double h, const Layout& L, int esize, char* 
     ny = (ny + 1) / 2;
     hl *= 2.0;
   }
-  double* part = (double*)take(kDmRedGroups * sizeof(double));
-  double* pmv = (double*)take(kDmRedGroups * sizeof(double));
+  double* part = (double*)take(kDmMaxGroups * sizeof(double));
+  double* pmv = (double*)take(kDmMaxGroups * sizeof(double));
   double* sc = (double*)take(8 * sizeof(double));
   const int cn = (long)nx * ny <= kDmExactMax ? nx * ny : 0;
   double* cinv = cn ? (double*)take((size_t)cn * cn * sizeof(double)) : nullptr;
@@ -875,7 +851,7 @@ int ss_workspace_bytes_for(const char* theory, int Nx, int Ny, const ss_params* 
   if (rc) return rc;
   if (!bytes) return fail(SS_EINVAL, "bytes is NULL");
   const Layout L = make_layout(pb.C, Nx, Ny, (int)esize_of(dtype));
-  *bytes = L.total + (pb.demag ? demag_region(Nx, Ny, 1.0, L, (int)esize_of(dtype), nullptr, nullptr) : 0) +
+  *bytes = L.total + (pb.demag ? demag_region(Nx, Ny, 1.0, nullptr, nullptr) : 0) +
            (pb.theory == SS_THEORY_BEC ? bec_region(L, nullptr, nullptr) : 0);
   return SS_OK;
 }
@@ -912,6 +888,8 @@ int ss_create(const char* theory, int Nx, int Ny, double h, const ss_params* par
   for (int k = 0; k < 7; ++k) *sets[k] = c->ws + k * c->L.set_bytes + c->L.col0 * esize_of(dtype);
   c->st = (DevStatus*)(c->ws + c->L.status_off);
   c->partials = (double*)(c->ws + c->L.partial_off);
+  c->alt = (DevStatus*)(c->ws + c->L.alt_off);
+  c->partials2 = (double*)(c->ws + c->L.alt_off + (size_t)round_up(sizeof(DevStatus), 256));
   c->graph = nullptr;
   c->graph_steps = 0;
   c->tile = kDefaultTile;
@@ -943,7 +921,7 @@ int ss_create(const char* theory, int Nx, int Ny, double h, const ss_params* par
     c->dm.on = 1;
     c->dm.iters_flow = 2;
     c->dm.iters_eval = 40;
-    demag_region(Nx, Ny, h, c->L, (int)esize_of(dtype), c->ws + c->L.total, &c->dm);
+    demag_region(Nx, Ny, h, c->ws + c->L.total, &c->dm);
   }
   hipError_t e = hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking);
   if (e != hipSuccess) {
@@ -1037,56 +1015,36 @@ int ss_time_passes(ss_ctx* c, int n_steps, double* ms) {
   for (int k = 0; k < 5; ++k) SS_HIP(hipEventCreate(&ev[k]));
   double acc[5] = {0, 0, 0, 0, 0};
   hipLaunchKernelGGL(arm_status, dim3(1), dim3(64), 0, c->stream, c->st, 0, 0.0, 0.0, 0, 0LL);
-  if (c->integ != SS_INTEG_RK4) enqueue_prime_any(c, c->stream);
+  Run r;
+  enqueue_prime_any(c, r, c->stream);
   for (int s = 0; s < n_steps; ++s) {
     SS_HIP(hipEventRecord(ev[0], c->stream));
     if (c->integ != SS_INTEG_RK4) {
-      // one pass per step: its time (with its finalise) in ms[0]; velocity
-      // Verlet's restart pass (timed as launched, also where it returns at
-      // once) in ms[1]
-      if (vv_kdk(c)) {
-        if (c->dtype == SS_F32) launch_pass<float, kVVRestart>(c, pass_args<float>(c), c->stream);
-        else launch_pass<double, kVVRestart>(c, pass_args<double>(c), c->stream);
-      }
+      // one pass per step: its time in ms[0]; velocity Verlet's restart pass
+      // (timed as launched, also where it returns at once) in ms[1]
+      if (vv_kdk(c)) enqueue_pass_any<kVVRestart>(c, r, c->stream);
       SS_HIP(hipEventRecord(ev[1], c->stream));
-      if (c->dtype == SS_F32) {
-        if (gd_form(c)) launch_pass<float, kGD>(c, pass_args<float>(c), c->stream);
-        else if (c->integ == SS_INTEG_GF) launch_pass<float, kGF>(c, pass_args<float>(c), c->stream);
-        else if (vv_kdk(c)) launch_pass<float, kVV>(c, pass_args<float>(c), c->stream);
-        else launch_pass<float, kVVA>(c, pass_args<float>(c), c->stream);
-      } else {
-        if (gd_form(c)) launch_pass<double, kGD>(c, pass_args<double>(c), c->stream);
-        else if (c->integ == SS_INTEG_GF) launch_pass<double, kGF>(c, pass_args<double>(c), c->stream);
-        else if (vv_kdk(c)) launch_pass<double, kVV>(c, pass_args<double>(c), c->stream);
-        else launch_pass<double, kVVA>(c, pass_args<double>(c), c->stream);
-      }
+      if (gd_form(c)) enqueue_pass_any<kGD>(c, r, c->stream);
+      else if (c->integ == SS_INTEG_GF) enqueue_pass_any<kGF>(c, r, c->stream);
+      else if (vv_kdk(c)) enqueue_pass_any<kVV>(c, r, c->stream);
+      else enqueue_pass_any<kVVA>(c, r, c->stream);
       for (int k = 2; k < 5; ++k) SS_HIP(hipEventRecord(ev[k], c->stream));
-    } else if (c->plan != SS_PLAN_STAGES) {
-      // stages 2-4 in one pass: its time in ms[1], zero in ms[2] and ms[3]
-      if (c->dtype == SS_F32) {
-        PassArgs<float> a = pass_args<float>(c);
-        launch_pass<float, kP1>(c, a, c->stream); SS_HIP(hipEventRecord(ev[1], c->stream));
-        launch_fused<float>(c, c->stream);
-      } else {
-        PassArgs<double> a = pass_args<double>(c);
-        launch_pass<double, kP1>(c, a, c->stream); SS_HIP(hipEventRecord(ev[1], c->stream));
-        launch_fused<double>(c, c->stream);
-      }
-      SS_HIP(hipEventRecord(ev[2], c->stream));
-      SS_HIP(hipEventRecord(ev[3], c->stream));
-      SS_HIP(hipEventRecord(ev[4], c->stream));
-    } else if (c->dtype == SS_F32) {
-      PassArgs<float> a = pass_args<float>(c);
-      launch_pass<float, kP1>(c, a, c->stream); SS_HIP(hipEventRecord(ev[1], c->stream));
-      launch_pass<float, kP2>(c, a, c->stream); SS_HIP(hipEventRecord(ev[2], c->stream));
-      launch_pass<float, kP3>(c, a, c->stream); SS_HIP(hipEventRecord(ev[3], c->stream));
-      launch_pass<float, kP4>(c, a, c->stream); SS_HIP(hipEventRecord(ev[4], c->stream));
     } else {
-      PassArgs<double> a = pass_args<double>(c);
-      launch_pass<double, kP1>(c, a, c->stream); SS_HIP(hipEventRecord(ev[1], c->stream));
-      launch_pass<double, kP2>(c, a, c->stream); SS_HIP(hipEventRecord(ev[2], c->stream));
-      launch_pass<double, kP3>(c, a, c->stream); SS_HIP(hipEventRecord(ev[3], c->stream));
-      launch_pass<double, kP4>(c, a, c->stream); SS_HIP(hipEventRecord(ev[4], c->stream));
+      enqueue_pass_any<kP1>(c, r, c->stream);
+      SS_HIP(hipEventRecord(ev[1], c->stream));
+      if (c->plan != SS_PLAN_STAGES) {
+        // stages 2-4 in one pass: its time in ms[1], zero in ms[2] and ms[3]
+        if (c->dtype == SS_F32) launch_fused<float>(c, r, c->stream);
+        else launch_fused<double>(c, r, c->stream);
+        for (int k = 2; k < 5; ++k) SS_HIP(hipEventRecord(ev[k], c->stream));
+      } else {
+        enqueue_pass_any<kP2>(c, r, c->stream);
+        SS_HIP(hipEventRecord(ev[2], c->stream));
+        enqueue_pass_any<kP3>(c, r, c->stream);
+        SS_HIP(hipEventRecord(ev[3], c->stream));
+        enqueue_pass_any<kP4>(c, r, c->stream);
+        SS_HIP(hipEventRecord(ev[4], c->stream));
+      }
     }
     SS_HIP(hipEventSynchronize(ev[4]));
     for (int k = 0; k < 4; ++k) {
@@ -1100,7 +1058,7 @@ int ss_time_passes(ss_ctx* c, int n_steps, double* ms) {
     SS_HIP(hipEventElapsedTime(&t, ev[0], ev[4]));
     acc[4] += t;
   }
-  enqueue_end_of_run_any(c, c->stream);
+  enqueue_end_of_run_any(c, r, c->stream);
   SS_HIP(hipStreamSynchronize(c->stream));
   for (int k = 0; k < 5; ++k) {
     ms[k] = acc[k] / n_steps;
@@ -1207,14 +1165,16 @@ int ss_energy_grad(ss_ctx* c, const void* field, void* grad, double* energy, dou
     a.out = (float*)grad;
     a.out_pitch = c->Nx + 4;
     a.out_plane = (long)(c->Nx + 4) * (c->Ny + 4);
-    launch_pass<float, kEval>(c, a, c->stream);
+    Run r;
+    launch_pass<float, kEval>(c, a, r, c->stream);
   } else {
     PassArgs<double> a = pass_args<double>(c);
     a.src = field ? (const double*)c->q : nullptr;
     a.out = (double*)grad;
     a.out_pitch = c->Nx + 4;
     a.out_plane = (long)(c->Nx + 4) * (c->Ny + 4);
-    launch_pass<double, kEval>(c, a, c->stream);
+    Run r;
+    launch_pass<double, kEval>(c, a, r, c->stream);
   }
   SS_HIP(hipGetLastError());
   DevStatus d;
@@ -1283,7 +1243,7 @@ void enqueue_noalloc_eval(const ss_ctx* c, const void* field, void* grad, hipStr
   a.B.Nx = c->Nx;
   a.B.Ny = c->Ny;
   a.cf = coeffs_of(c);
-  a.st = c->st;
+  a.link = Link{c->st, c->st, c->st, nullptr, 0, -1};
   a.partials = c->partials;
   a.src = (const T*)field;
   a.out = (T*)grad;
@@ -1292,7 +1252,8 @@ void enqueue_noalloc_eval(const ss_ctx* c, const void* field, void* grad, hipStr
   a.ntx = c->L.ntx;
   a.nty = c->L.nty;
   a.seg = c->L.seg;
-  launch_pass<T, kEval>(c, a, s);
+  Run r;
+  launch_pass<T, kEval>(c, a, r, s);
 }
 
 }  // namespace
@@ -1348,9 +1309,10 @@ int ss_flow_step(ss_ctx* c, int n_steps, ss_step_info* info) {
   if (!c) return fail(SS_EINVAL, "ctx is NULL");
   if (n_steps < 0) return fail(SS_EINVAL, "n_steps < 0");
   hipLaunchKernelGGL(arm_status, dim3(1), dim3(64), 0, c->stream, c->st, 0, 0.0, 0.0, 0, 0LL);
-  if (c->integ != SS_INTEG_RK4) enqueue_prime_any(c, c->stream);
-  enqueue_steps_any(c, n_steps, c->stream);
-  enqueue_end_of_run_any(c, c->stream);
+  Run r;
+  enqueue_prime_any(c, r, c->stream);
+  enqueue_steps_any(c, n_steps, r, c->stream);
+  enqueue_end_of_run_any(c, r, c->stream);
   SS_HIP(hipGetLastError());
   if (info) {
     DevStatus d;
@@ -1375,7 +1337,9 @@ int ss_minimise(ss_ctx* c, const ss_stop* stop, ss_min_info* info) {
   if (!c->graph) {
     hipGraph_t g;
     SS_HIP(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeRelaxed));
-    enqueue_steps_any(c, K, c->cap_stream);
+    Run r;
+    enqueue_steps_any(c, K, r, c->cap_stream);
+    settle(c, r, c->cap_stream);
     hipError_t e = hipStreamEndCapture(c->cap_stream, &g);
     if (e != hipSuccess) return fail(SS_EHIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
     e = hipGraphInstantiate(&c->graph, g, nullptr, nullptr, 0);
@@ -1389,7 +1353,9 @@ int ss_minimise(ss_ctx* c, const ss_stop* stop, ss_min_info* info) {
   hipLaunchKernelGGL(arm_status, dim3(1), dim3(64), 0, c->stream, c->st, 1, stop->grad_tol, stop->rel_e_tol,
                      stop->window, (long long)stop->max_steps);
   // a one-pass run starts by testing the current field and storing its force
-  if (c->integ != SS_INTEG_RK4) enqueue_prime_any(c, c->stream);
+  Run run;
+  enqueue_prime_any(c, run, c->stream);
+  settle(c, run, c->stream);
   SS_HIP(hipGetLastError());
   DevStatus d;
   for (;;) {
@@ -1399,12 +1365,8 @@ int ss_minimise(ss_ctx* c, const ss_stop* stop, ss_min_info* info) {
     if (rc) return rc;
     if (d.done) break;
   }
-  if (c->integ == SS_INTEG_RK4) {
-    if (c->dtype == SS_F32) enqueue_apply_arrest<float>(c, c->stream);
-    else enqueue_apply_arrest<double>(c, c->stream);
-  } else {
-    enqueue_settle_any(c, c->stream);
-  }
+  if (c->integ == SS_INTEG_RK4) enqueue_apply_arrest(c, run, c->stream);
+  else enqueue_settle_any(c, run, c->stream);
   int rc = read_status(c, &d);
   if (rc) return rc;
   if (info) {
@@ -1437,7 +1399,10 @@ void obs_enqueue_t(ss_ctx* c, int nobs) {
   }
   if (c->theory == SS_THEORY_CM) {
     // the potential of the current field, for the demagnetising energy
-    if (c->dm.on) demag_solve<T, kEval>(c, pass_args<T>(c), c->stream);
+    if (c->dm.on) {
+      Run r;
+      demag_solve<T, kEval>(c, pass_args<T>(c), r, c->stream);
+    }
     hipLaunchKernelGGL((obs_sites<T, kCM>), dim3(nobs), dim3(256), 0, c->stream, B, coeffs_of(c), c->st, c->partials,
                        nobs);
   }
@@ -1964,23 +1929,6 @@ int batch_compact(ss_batch* b, const std::vector<int>& done) {
   return SS_OK;
 }
 
-template <class T, int TH, int PASS, int CFG>
-void batch_launch_cfg(const BatchArgs<T>& a, int nlaunch, hipStream_t s) {
-  constexpr TileCfg tc = kTiles[CFG];
-  hipLaunchKernelGGL((batch_pass<T, TH, PASS, tc.TX, tc.TY, tc.RY>), dim3(nlaunch), dim3(tc.TX, tc.TY / tc.RY), 0,
-                     s, a);
-}
-
-template <class T, int TH, int PASS>
-void batch_launch_t(int tile, const BatchArgs<T>& a, int nlaunch, hipStream_t s) {
-  switch (tile) {
-    case 0: batch_launch_cfg<T, TH, PASS, 0>(a, nlaunch, s); break;
-    case 1: batch_launch_cfg<T, TH, PASS, 1>(a, nlaunch, s); break;
-    case 2: batch_launch_cfg<T, TH, PASS, 2>(a, nlaunch, s); break;
-    default: batch_launch_cfg<T, TH, PASS, 3>(a, nlaunch, s); break;
-  }
-}
-
 template <class T, int PASS>
 void batch_launch(const ss_batch* b, hipStream_t s) {
   BatchArgs<T> a;
@@ -1990,8 +1938,8 @@ void batch_launch(const ss_batch* b, hipStream_t s) {
   a.nwork = b->nwork;
   a.partials = b->partials;
   const int nlaunch = batch_nlaunch(b);
-  if (b->theory == SS_THEORY_AH) batch_launch_t<T, 0, PASS>(b->tile, a, nlaunch, s);
-  else batch_launch_t<T, 1, PASS>(b->tile, a, nlaunch, s);
+  if (b->theory == SS_THEORY_AH) batch_launch_t<T, kAH, PASS>(b->tile, a, nlaunch, s);
+  else batch_launch_t<T, kCM, PASS>(b->tile, a, nlaunch, s);
   if constexpr (reduces(PASS))
     hipLaunchKernelGGL((batch_finalise<T, PASS>), dim3(b->n), dim3(256), 0, s, a.inst, (const double*)b->partials);
 }
@@ -2011,19 +1959,8 @@ void batch_launch_fused(const ss_batch* b, hipStream_t s) {
   a.partials = b->partials;
   const int nlaunch = batch_nlaunch(b);
   // the batch's tile is 64 x 16 (tile 0, FP32 only) or 64 x 8 (tile 1); see batch_fused
-  if constexpr (sizeof(T) == 4) {
-    if (b->tile == 0) {
-      if (b->theory == SS_THEORY_AH)
-        hipLaunchKernelGGL((batch_pass_fused<T, 0, 64, 16, 2>), dim3(nlaunch), dim3(64, 8), 0, s, a);
-      else
-        hipLaunchKernelGGL((batch_pass_fused<T, 1, 64, 16, 2>), dim3(nlaunch), dim3(64, 8), 0, s, a);
-      return;
-    }
-  }
-  if (b->theory == SS_THEORY_AH)
-    hipLaunchKernelGGL((batch_pass_fused<T, 0, 64, 8, 2>), dim3(nlaunch), dim3(64, 4), 0, s, a);
-  else
-    hipLaunchKernelGGL((batch_pass_fused<T, 1, 64, 8, 2>), dim3(nlaunch), dim3(64, 4), 0, s, a);
+  if (b->theory == SS_THEORY_AH) batch_launch_fused_t<T, kAH>(b->tile, a, nlaunch, s);
+  else batch_launch_fused_t<T, kCM>(b->tile, a, nlaunch, s);
 }
 
 template <class T>

@@ -20,6 +20,13 @@
 // iterations, warm-started from the last potential (stage points change little
 // from one pass to the next), so that it can be captured in a graph. Dot
 // products are summed per workgroup and then in workgroup order (deterministic).
+//
+// Every launch of a solve is bound by its latency (4-6 us for a fraction of a
+// microsecond of memory traffic), so the solve is cut into as few as its global
+// dependencies allow: two per large level and V-cycle, one for the small levels,
+// two per iteration for conjugate gradients, whose update also starts the next
+// V-cycle. Two iterations on 512^2: 23 launches (35 with smoothing, restriction,
+// dot product, direction and operator apart).
 #pragma once
 
 #include "ss_internal.hpp"
@@ -27,7 +34,7 @@
 namespace ss {
 
 constexpr int kDmMaxLevels = 20;
-constexpr int kDmRedGroups = 256;  // workgroups of the dot-product launches (one partial per thread of the sum)
+constexpr int kDmMaxGroups = 2048;  // workgroups of a launch (and partials of a dot product)
 constexpr double kDmOmega = 0.8;   // Jacobi weight (stable below 15/16 for this operator)
 constexpr int kDmSmooth = 2;       // sweeps before and after the coarse correction
 constexpr int kDmCoarse = 40;      // sweeps on the coarsest level (even) where it has no inverse
@@ -36,23 +43,24 @@ constexpr int kDmExactMax = 256;   // coarsest levels up to this many sites are 
 // One level of the hierarchy: padded planes of (Ny + 4) rows of pitch = Nx + 4 doubles.
 struct DmLevel {
   double* psi;  // solution (the preconditioned residual z on level 0)
-  double* tmp;  // Jacobi partner of psi; holds the residual before a restriction
-  double* rhs;
+  double* tmp;  // the pre-smoothed psi
+  double* rhs;  // (level 0: -r, one of the two planes of DmVecs)
   int Nx, Ny;
   long pitch;
   double h;
 };
 
-// Level-0 vectors of conjugate gradients, the reduction partials and the scalars
-// {r.z, beta, alpha, d.Ad}.
+// Level-0 vectors of conjugate gradients, the reduction partials and the scalar
+// r.z of the last iteration. The direction and -r are each read with a halo by the
+// launch that renews them, hence two planes.
 struct DmVecs {
-  double* x;  // the potential psi
-  double* r;
-  double* d;
+  double* x;       // the potential psi
+  double* rhs[2];  // -r
+  double* d[2];
   double* Ad;
-  double* part;  // kDmRedGroups partials of r.z
-  double* pmv;   // kDmRedGroups partials of d.Ad
-  double* sc;    // {r.z of the last iteration, beta, alpha, d.Ad}
+  double* part;    // partials of r.z, one per workgroup
+  double* pmv;     // partials of d.Ad
+  double* sc;      // {r.z of the last iteration}
 };
 
 __device__ __forceinline__ bool dm_skip(const DevStatus* st) { return st != nullptr && st->done != 0; }
@@ -71,14 +79,15 @@ __device__ __forceinline__ double dm_lap(const double* __restrict__ x, long p, i
   for (long k_ = blockIdx.x * 256L + threadIdx.x; k_ < (long)(L).Nx * (L).Ny;              \
        k_ += (long)gridDim.x * 256L)
 
-// The coarsest level: kDmCoarse Jacobi sweeps (psi -> tmp -> psi ...) from the
-// zero start the restriction left, in one workgroup, with a barrier between sweeps
-// (one launch instead of kDmCoarse). Global memory is coherent within a workgroup
-// across the barrier.
-__global__ void __launch_bounds__(256) dm_coarse_solve(DmLevel L, const DevStatus* st) {
+// The coarsest level where it is too large for LDS: kDmCoarse Jacobi sweeps (psi ->
+// tmp -> psi ...) from zero, in one workgroup, with a barrier between sweeps. Global
+// memory is coherent within a workgroup across the barrier.
+static __global__ void __launch_bounds__(256) dm_coarse_solve(DmLevel L, const DevStatus* st) {
   if (dm_skip(st)) return;
   const double s = kDmOmega * L.h * L.h / 5.0;
   const long n = (long)L.Nx * L.Ny;
+  for (long k = threadIdx.x; k < n; k += 256) L.psi[dm_at(L, (int)(k / L.Nx), (int)(k % L.Nx))] = 0.0;
+  __syncthreads();
   for (int sweep = 0; sweep < kDmCoarse; ++sweep) {
     const double* __restrict__ src = (sweep & 1) ? L.tmp : L.psi;
     double* __restrict__ dst = (sweep & 1) ? L.psi : L.tmp;
@@ -110,13 +119,15 @@ __device__ __forceinline__ double dm_prolong_at(const DmLevel& C, const double* 
 }
 
 // ---- the small levels of a V-cycle in one workgroup, in LDS
-// The coarse levels of a V-cycle cost a few microseconds per launch and almost
-// nothing to compute. From the first level whose planes and those of every
-// coarser level fit in kDmSmallLds bytes, the V-cycle down to the coarsest level
-// and back up runs in one workgroup on LDS copies of those planes, phase by phase
-// with a barrier between phases: the same updates in the same order of phases as
-// the per-level launches, so the result is the same bit for bit. The level's rhs
-// and psi are read from global memory at the start and psi written back at the end.
+// From the first level whose planes and those of every coarser level fit in
+// kDmSmallLds bytes, the V-cycle down to the coarsest level and back up runs in one
+// workgroup of kDmSmallThreads on LDS copies of those planes, phase by phase with a
+// barrier between phases, in the arithmetic of the per-level launches. A wave walks
+// the rows of a level, its lanes the columns, so no phase divides. The level's rhs is
+// read from global memory at the start and psi written back at the end (with the r.z
+// partial where it is level 0). From 32^2 down 7 us (256 threads, a division per
+// site, the smoothing sweeps from zero computed as sweeps: 17-24 us).
+constexpr int kDmSmallThreads = 1024;
 constexpr int kDmSmallLds = 64 * 1024;
 
 struct DmHierarchy {
@@ -135,438 +146,492 @@ __host__ __device__ inline long dm_small_bytes(const DmLevel* lv, int nlev, int 
   return 8 * n;
 }
 
-__device__ __forceinline__ void dm_wg_jacobi(const DmLevel& L, const double* __restrict__ src,
-                                             double* __restrict__ dst) {
-  const double s = kDmOmega * L.h * L.h / 5.0;
-  const long n = (long)L.Nx * L.Ny;
-  for (long k = threadIdx.x; k < n; k += 256) {
-    const int j = (int)(k / L.Nx), i = (int)(k - (long)j * L.Nx);
-    const long o = dm_at(L, j, i);
-    dst[o] = src[o] - s * (L.rhs[o] - dm_lap(src, L.pitch, j, i, L.h));
-  }
+// Sum of the workgroup's values in a fixed order (wave sums in wave order); valid
+// in every thread. red: blockDim / 64 doubles.
+__device__ __forceinline__ double dm_block_sum(double v, double* red) {
+  v = wave_sum(v);
   __syncthreads();
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double s = 0.0;
+  for (int k = 0; k < (int)(blockDim.x >> 6); ++k) s += red[k];
+  return s;
 }
 
-__global__ void __launch_bounds__(256) dm_vcycle_small(DmHierarchy H, int l0, const DevStatus* st) {
+// Sum of n partials by a workgroup of 256, in a fixed order.
+__device__ __forceinline__ double dm_partials(const double* __restrict__ part, int n, double* red) {
+  double acc = 0.0;
+  for (int k = threadIdx.x; k < n; k += 256) acc += part[k];
+  return dm_block_sum(acc, red);
+}
+
+static __global__ void __launch_bounds__(kDmSmallThreads) dm_vcycle_small(DmHierarchy H, int l0,
+                                                                          double* __restrict__ part,
+                                                                          const DevStatus* st) {
   if (dm_skip(st)) return;
   extern __shared__ double smem[];
+  __shared__ double red[kDmSmallThreads / 64];
   const int last = H.nlev - 1;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int NWV = kDmSmallThreads / 64;
   // the LDS copy of level l (its planes follow those of levels l0 .. l - 1); a
   // value built per use, so that no array of levels is indexed at run time
   auto lds_level = [&](int l) {
-    long off = 0;
-    for (int k = l0; k < l; ++k) off += 3L * (H.lv[k].Nx + 4) * (H.lv[k].Ny + 4);
+    int off = 0;
+    for (int k = l0; k < l; ++k) off += 3 * (H.lv[k].Nx + 4) * (H.lv[k].Ny + 4);
     DmLevel L = H.lv[l];
-    const long pl = (long)(L.Nx + 4) * (L.Ny + 4);
+    const int pl = (L.Nx + 4) * (L.Ny + 4);
     L.psi = smem + off;
     L.tmp = smem + off + pl;
     L.rhs = smem + off + 2 * pl;
     return L;
   };
+  // body(j, i, o) for every interior site of a level, o its offset in a plane
+  auto sites = [&](const DmLevel& L, auto&& body) {
+    for (int j = wave; j < L.Ny; j += NWV)
+      for (int i = lane; i < L.Nx; i += 64) body(j, i, (j + 2) * (int)L.pitch + i + 2);
+  };
+  auto jacobi = [&](const DmLevel& L, const double* src, double* dst) {
+    const double s = kDmOmega * L.h * L.h / 5.0;
+    sites(L, [&](int j, int i, int o) { dst[o] = src[o] - s * (L.rhs[o] - dm_lap(src, L.pitch, j, i, L.h)); });
+    __syncthreads();
+  };
   // every plane zero (halos included) before the interior of level l0 is read in
-  const long total = dm_small_bytes(H.lv, H.nlev, l0) / 8;
-  for (long k = threadIdx.x; k < total; k += 256) smem[k] = 0.0;
+  const int total = (int)(dm_small_bytes(H.lv, H.nlev, l0) / 8);
+  for (int k = threadIdx.x; k < total; k += kDmSmallThreads) smem[k] = 0.0;
   __syncthreads();
-  const DmLevel L0 = lds_level(l0);
   {
-    const DmLevel& G = H.lv[l0];
-    const long n = (long)G.Nx * G.Ny;
-    for (long k = threadIdx.x; k < n; k += 256) {
-      const int j = (int)(k / G.Nx), i = (int)(k - (long)j * G.Nx);
-      const long o = dm_at(G, j, i);
-      L0.rhs[o] = G.rhs[o];
-      L0.psi[o] = G.psi[o];
-    }
+    const DmLevel G = H.lv[l0], L0 = lds_level(l0);
+    sites(G, [&](int, int, int o) { L0.rhs[o] = G.rhs[o]; });
     __syncthreads();
   }
   for (int l = l0; l < last; ++l) {
     const DmLevel F = lds_level(l);
     const DmLevel C = lds_level(l + 1);
-    for (int k = 0; k < kDmSmooth; k += 2) {
-      dm_wg_jacobi(F, F.psi, F.tmp);
-      dm_wg_jacobi(F, F.tmp, F.psi);
-    }
-    const long nf = (long)F.Nx * F.Ny;
-    for (long k = threadIdx.x; k < nf; k += 256) {
-      const int j = (int)(k / F.Nx), i = (int)(k - (long)j * F.Nx);
-      const long o = dm_at(F, j, i);
-      F.tmp[o] = F.rhs[o] - dm_lap(F.psi, F.pitch, j, i, F.h);
-    }
+    // two sweeps from zero: the first is -s rhs
+    const double s = kDmOmega * F.h * F.h / 5.0;
+    sites(F, [&](int, int, int o) { F.tmp[o] = -(s * F.rhs[o]); });
     __syncthreads();
-    const long nc = (long)C.Nx * C.Ny;
-    for (long k = threadIdx.x; k < nc; k += 256) {
-      const int J = (int)(k / C.Nx), I = (int)(k - (long)J * C.Nx);
+    jacobi(F, F.tmp, F.psi);
+    sites(F, [&](int j, int i, int o) { F.tmp[o] = F.rhs[o] - dm_lap(F.psi, F.pitch, j, i, F.h); });
+    __syncthreads();
+    sites(C, [&](int J, int I, int o) {
+      // rows and columns outside the level carry the zeros of the halo
       double acc = 0.0;
-      for (int j = max(2 * J - 1, 0); j <= min(2 * J + 2, F.Ny - 1); ++j) {
-        double row = 0.0;
-        for (int i = max(2 * I - 1, 0); i <= min(2 * I + 2, F.Nx - 1); ++i) row += dm_w(i, I) * F.tmp[dm_at(F, j, i)];
-        acc += dm_w(j, J) * row;
+#pragma unroll
+      for (int a = -1; a <= 2; ++a) {
+        const double* p = F.tmp + (2 * J + a + 2) * (int)F.pitch + 2 * I + 2;
+        acc += dm_w(a, 0) * (((0.25 * p[-1] + 0.75 * p[0]) + 0.75 * p[1]) + 0.25 * p[2]);
       }
-      const long o = dm_at(C, J, I);
       C.rhs[o] = 0.25 * acc;
-      C.psi[o] = 0.0;
-    }
+    });
     __syncthreads();
   }
   const DmLevel B = lds_level(last);
   if (H.cn > 0) {
     // the coarsest level solved exactly: psi = (Laplace_h)^-1 rhs, each row summed in site order
-    for (int k = threadIdx.x; k < H.cn; k += 256) {
+    for (int k = threadIdx.x; k < H.cn; k += kDmSmallThreads) {
       double acc = 0.0;
-      for (int m = 0; m < H.cn; ++m) {
-        const int jm = m / B.Nx, im = m - jm * B.Nx;
-        acc += H.cinv[(long)k * H.cn + m] * B.rhs[dm_at(B, jm, im)];
-      }
+      int m = 0;
+      for (int jm = 0; jm < B.Ny; ++jm)
+        for (int im = 0; im < B.Nx; ++im, ++m) acc += H.cinv[(long)k * H.cn + m] * B.rhs[dm_at(B, jm, im)];
       const int jk = k / B.Nx, ik = k - jk * B.Nx;
       B.psi[dm_at(B, jk, ik)] = acc;
     }
     __syncthreads();
   } else {
     for (int k = 0; k < kDmCoarse; k += 2) {
-      dm_wg_jacobi(B, B.psi, B.tmp);
-      dm_wg_jacobi(B, B.tmp, B.psi);
+      jacobi(B, B.psi, B.tmp);
+      jacobi(B, B.tmp, B.psi);
     }
   }
   for (int l = last - 1; l >= l0; --l) {
     const DmLevel F = lds_level(l);
     const DmLevel C = lds_level(l + 1);
-    const long nf = (long)F.Nx * F.Ny;
-    for (long k = threadIdx.x; k < nf; k += 256) {
-      const int j = (int)(k / F.Nx), i = (int)(k - (long)j * F.Nx);
-      F.psi[dm_at(F, j, i)] += dm_prolong_at(C, C.psi, j, i);
-    }
+    sites(F, [&](int j, int i, int o) { F.psi[o] += dm_prolong_at(C, C.psi, j, i); });
     __syncthreads();
-    for (int k = 0; k < kDmSmooth; k += 2) {
-      dm_wg_jacobi(F, F.psi, F.tmp);
-      dm_wg_jacobi(F, F.tmp, F.psi);
-    }
+    jacobi(F, F.psi, F.tmp);
+    jacobi(F, F.tmp, F.psi);
   }
-  {
-    const DmLevel& G = H.lv[l0];
-    const long n = (long)G.Nx * G.Ny;
-    for (long k = threadIdx.x; k < n; k += 256) {
-      const int j = (int)(k / G.Nx), i = (int)(k - (long)j * G.Nx);
-      const long o = dm_at(G, j, i);
-      G.psi[o] = L0.psi[o];
-    }
+  const DmLevel G = H.lv[l0], L0 = lds_level(l0);
+  double rz = 0.0;
+  sites(G, [&](int, int, int o) {
+    const double z = L0.psi[o];
+    G.psi[o] = z;
+    rz -= L0.rhs[o] * z;
+  });
+  if (l0 == 0) {
+    rz = dm_block_sum(rz, red);
+    if (threadIdx.x == 0) part[0] = rz;
   }
 }
 
-// ---- the large levels: three launches per level and V-cycle
-// Pre-smoothing (two sweeps, psi -> tmp), the residual restricted to the next
-// level, and prolongation with post-smoothing (tmp + P c -> psi, two sweeps).
-// Weighted Jacobi: x' = x - omega h^2/5 (rhs - Laplace_h x) (the operator's
-// diagonal is -5/h^2), on interior sites only; halos stay zero. These are the
-// same updates, in the same arithmetic, as the one-workgroup small levels and
-// the coarsest-level solve use.
-constexpr int kDmTile = 16;                // interior sites per side of a smoothing tile
-constexpr int kDmTA = kDmTile + 8;         // the input on the tile and a halo of 4
-constexpr int kDmTB = kDmTile + 4;         // after one sweep, and rhs: tile and halo 2
-constexpr int kDmCT = 8;                   // coarse sites per side of a restriction tile
-constexpr int kDmRF = 2 * kDmCT + 2;       // fine residuals it needs per side
-constexpr int kDmRP = kDmRF + 4;           // fine psi per side (residuals and a halo of 2)
+// ---- the large levels: two launches per level and V-cycle
+// Down: pre-smoothing (two sweeps from zero) and the restricted residual. Up: the
+// prolonged correction and post-smoothing (two sweeps). Weighted Jacobi:
+// x' = x - omega h^2/5 (rhs - Laplace_h x) (the operator's diagonal is -5/h^2), on
+// interior sites only; halos stay zero. Both work on 16 x 16 fine sites per
+// workgroup through LDS, with the halo that the sweeps need computed again.
+constexpr int kDmTile = 16;                // fine sites per side of a tile
+constexpr int kDmCT = kDmTile / 2;         // coarse sites per side
+constexpr int kDmRF = kDmTile + 2;         // down: fine residuals per side
+constexpr int kDmSF = kDmRF + 4;           //       smoothed psi
+constexpr int kDmBF = kDmSF + 4;           //       rhs (and the first sweep)
+constexpr int kDmTA = kDmTile + 8;         // up: the input
+constexpr int kDmTB = kDmTile + 4;         //     after one sweep, and rhs
+constexpr int kDmTC = kDmTA / 2 + 2;       //     coarse correction
 
+// tiles of a level: each covers kDmTile sites (an odd last site starts a tile of its own)
 __host__ __device__ inline int dm_tiles(const DmLevel& L) {
   return ((L.Nx + kDmTile - 1) / kDmTile) * ((L.Ny + kDmTile - 1) / kDmTile);
 }
 
-__host__ __device__ inline int dm_rtiles(const DmLevel& C) {
-  return ((C.Nx + kDmCT - 1) / kDmCT) * ((C.Ny + kDmCT - 1) / kDmCT);
-}
-
-// Two weighted Jacobi sweeps of level L from src into dst, through LDS: the
-// first on the tile and a ring of two (zero outside the interior, as the halo of
-// a plane is), the second on the tile. With prolong != 0 the input is
-// src + P (C.psi), the fine correction of the coarse solve. The loads of a phase
-// are unrolled so that a thread has them in flight together.
-__global__ void __launch_bounds__(256) dm_jacobi2(DmLevel L, const double* __restrict__ src, double* __restrict__ dst,
-                                                  DmLevel C, int prolong, const DevStatus* st) {
+// Coarse rhs = P^T (rhs - Laplace_h x) / 4 with x the two sweeps from zero, which is
+// kept in F.tmp. A tile is kDmTile fine sites (2 Y0, 2 X0) .., i.e. kDmCT coarse sites.
+// UPDATE (level 0): rhs is first renewed as the end of a conjugate-gradient iteration,
+// x += alpha d and rhs' = rhs + alpha Ad (-r' of r' = r - alpha Ad) into the other
+// plane, alpha = r.z / d.Ad summed from the partials by every workgroup (0 once d.Ad is
+// 0: the residual has vanished); workgroup 0 keeps r.z for the next iteration's beta.
+template <bool UPDATE>
+__global__ void __launch_bounds__(256) dm_down(DmLevel F, DmLevel C, DmVecs D, int cur, int nrz, int nmv,
+                                               const DevStatus* st) {
   if (dm_skip(st)) return;
-  constexpr int NA = kDmTA * kDmTA, NB = kDmTB * kDmTB, NT = kDmTile * kDmTile;
-  __shared__ double a[NA];
+  constexpr int NB = kDmBF * kDmBF, NS = kDmSF * kDmSF, NR = kDmRF * kDmRF, NC = kDmCT * kDmCT;
   __shared__ double b[NB];
-  __shared__ double r[NB];
-  const double s = kDmOmega * L.h * L.h / 5.0;
-  const int ntx = (L.Nx + kDmTile - 1) / kDmTile;
-  const int nt = dm_tiles(L);
-  auto inside = [&](int j, int i) { return j >= 0 && j < L.Ny && i >= 0 && i < L.Nx; };
+  __shared__ double x1[NB];
+  __shared__ double x2[NS];
+  __shared__ double res[NR];
+  __shared__ double red[4];
+  const double s = kDmOmega * F.h * F.h / 5.0;
+  const int ntx = (F.Nx + kDmTile - 1) / kDmTile;
+  const int nt = dm_tiles(F);
+  auto inside = [&](int j, int i) { return j >= 0 && j < F.Ny && i >= 0 && i < F.Nx; };
+  double alpha = 0.0;
+  bool first = true;
   for (int t = blockIdx.x; t < nt; t += gridDim.x) {
     const int y0 = (t / ntx) * kDmTile, x0 = (t % ntx) * kDmTile;
-    double va[(NA + 255) / 256], vr[(NB + 255) / 256];
+    const double* __restrict__ rhs = UPDATE ? D.rhs[cur] : F.rhs;
+    constexpr int QB = (NB + 255) / 256;
+    double vb[QB], va[QB];
 #pragma unroll
-    for (int q = 0; q < (NA + 255) / 256; ++q) {
+    for (int q = 0; q < QB; ++q) {
       const int k = threadIdx.x + 256 * q;
-      const int ly = k / kDmTA, lx = k - ly * kDmTA;
-      const int j = y0 - 4 + ly, i = x0 - 4 + lx;
-      va[q] = (k < NA && inside(j, i)) ? src[dm_at(L, j, i)] : 0.0;
-      if (prolong && k < NA && inside(j, i)) va[q] += dm_prolong_at(C, C.psi, j, i);
+      const int ly = k / kDmBF, lx = k - ly * kDmBF;
+      const int j = y0 - 5 + ly, i = x0 - 5 + lx;
+      const bool in = k < NB && inside(j, i);
+      vb[q] = in ? rhs[dm_at(F, j, i)] : 0.0;
+      va[q] = (UPDATE && in) ? D.Ad[dm_at(F, j, i)] : 0.0;
+    }
+    double vx = 0.0, vd = 0.0;  // the thread's own site of the tile
+    const int oy = threadIdx.x / kDmTile, ox = threadIdx.x - oy * kDmTile;
+    const bool own = inside(y0 + oy, x0 + ox);
+    const long oo = dm_at(F, y0 + oy, x0 + ox);
+    if (UPDATE && own) {
+      vx = D.x[oo];
+      vd = D.d[cur][oo];
+    }
+    if (UPDATE && first) {
+      const double rz = dm_partials(D.part, nrz, red);
+      const double dad = dm_partials(D.pmv, nmv, red);
+      alpha = dad > 0.0 ? rz / dad : 0.0;
+      if (blockIdx.x == 0 && threadIdx.x == 0) D.sc[0] = rz;
+      first = false;
     }
 #pragma unroll
-    for (int q = 0; q < (NB + 255) / 256; ++q) {
-      const int k = threadIdx.x + 256 * q;
-      const int ly = k / kDmTB, lx = k - ly * kDmTB;
-      const int j = y0 - 2 + ly, i = x0 - 2 + lx;
-      vr[q] = (k < NB && inside(j, i)) ? L.rhs[dm_at(L, j, i)] : 0.0;
-    }
-#pragma unroll
-    for (int q = 0; q < (NA + 255) / 256; ++q) {
-      const int k = threadIdx.x + 256 * q;
-      if (k < NA) a[k] = va[q];
-    }
-#pragma unroll
-    for (int q = 0; q < (NB + 255) / 256; ++q) {
-      const int k = threadIdx.x + 256 * q;
-      if (k < NB) r[k] = vr[q];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < (NB + 255) / 256; ++q) {
+    for (int q = 0; q < QB; ++q) {
       const int k = threadIdx.x + 256 * q;
       if (k < NB) {
-        const int ly = k / kDmTB, lx = k - ly * kDmTB;
-        const int j = y0 - 2 + ly, i = x0 - 2 + lx;
-        double v = 0.0;
-        if (inside(j, i)) v = a[(ly + 2) * kDmTA + (lx + 2)] - s * (r[k] - dm_lap(a, kDmTA, ly, lx, L.h));
+        const double v = UPDATE ? vb[q] + alpha * va[q] : vb[q];
         b[k] = v;
+        x1[k] = -(s * v);
       }
     }
     __syncthreads();
+    if (UPDATE && own) {
+      D.x[oo] = vx + alpha * vd;
+      D.rhs[cur ^ 1][oo] = b[(oy + 5) * kDmBF + ox + 5];
+    }
 #pragma unroll
-    for (int q = 0; q < (NT + 255) / 256; ++q) {
+    for (int q = 0; q < (NS + 255) / 256; ++q) {
       const int k = threadIdx.x + 256 * q;
-      const int ly = k / kDmTile, lx = k - ly * kDmTile;
-      const int j = y0 + ly, i = x0 + lx;
-      if (k < NT && inside(j, i)) {
-        const int o = (ly + 2) * kDmTB + (lx + 2);
-        dst[dm_at(L, j, i)] = b[o] - s * (r[o] - dm_lap(b, kDmTB, ly, lx, L.h));
+      if (k < NS) {
+        const int ly = k / kDmSF, lx = k - ly * kDmSF;
+        const int o = (ly + 2) * kDmBF + lx + 2;
+        x2[k] = inside(y0 - 3 + ly, x0 - 3 + lx) ? x1[o] - s * (b[o] - dm_lap(x1, kDmBF, ly, lx, F.h)) : 0.0;
       }
     }
     __syncthreads();
-  }
-}
-
-// Coarse rhs = P^T (rhs - Laplace_h psi) / 4 on a tile of coarse sites, with the
-// fine residuals it needs formed once in LDS (zero outside the fine interior,
-// where the restriction gives them no weight); coarse psi = 0.
-__global__ void __launch_bounds__(256) dm_restrict_res(DmLevel F, const double* __restrict__ psi, DmLevel C,
-                                                       const DevStatus* st) {
-  if (dm_skip(st)) return;
-  constexpr int NP = kDmRP * kDmRP, NR = kDmRF * kDmRF, NC = kDmCT * kDmCT;
-  __shared__ double x[NP];
-  __shared__ double res[NR];
-  const int ntx = (C.Nx + kDmCT - 1) / kDmCT;
-  const int nt = dm_rtiles(C);
-  auto inside = [&](int j, int i) { return j >= 0 && j < F.Ny && i >= 0 && i < F.Nx; };
-  for (int t = blockIdx.x; t < nt; t += gridDim.x) {
-    const int Y0 = (t / ntx) * kDmCT, X0 = (t % ntx) * kDmCT;
-    // fine residual rows and columns 2*Y0 - 1 .. 2*Y0 + 2*kDmCT
-    const int fy0 = 2 * Y0 - 1, fx0 = 2 * X0 - 1;
-    double vx[(NP + 255) / 256], vb[(NR + 255) / 256];
-#pragma unroll
-    for (int q = 0; q < (NP + 255) / 256; ++q) {
-      const int k = threadIdx.x + 256 * q;
-      const int ly = k / kDmRP, lx = k - ly * kDmRP;
-      const int j = fy0 - 2 + ly, i = fx0 - 2 + lx;
-      vx[q] = (k < NP && inside(j, i)) ? psi[dm_at(F, j, i)] : 0.0;
-    }
-#pragma unroll
-    for (int q = 0; q < (NR + 255) / 256; ++q) {
-      const int k = threadIdx.x + 256 * q;
-      const int ly = k / kDmRF, lx = k - ly * kDmRF;
-      const int j = fy0 + ly, i = fx0 + lx;
-      vb[q] = (k < NR && inside(j, i)) ? F.rhs[dm_at(F, j, i)] : 0.0;
-    }
-#pragma unroll
-    for (int q = 0; q < (NP + 255) / 256; ++q) {
-      const int k = threadIdx.x + 256 * q;
-      if (k < NP) x[k] = vx[q];
-    }
-    __syncthreads();
+    if (own) F.tmp[oo] = x2[(oy + 3) * kDmSF + ox + 3];
 #pragma unroll
     for (int q = 0; q < (NR + 255) / 256; ++q) {
       const int k = threadIdx.x + 256 * q;
       if (k < NR) {
         const int ly = k / kDmRF, lx = k - ly * kDmRF;
-        res[k] = inside(fy0 + ly, fx0 + lx) ? vb[q] - dm_lap(x, kDmRP, ly, lx, F.h) : 0.0;
+        res[k] = inside(y0 - 1 + ly, x0 - 1 + lx)
+                     ? b[(ly + 4) * kDmBF + lx + 4] - dm_lap(x2, kDmSF, ly, lx, F.h) : 0.0;
       }
     }
     __syncthreads();
     if (threadIdx.x < NC) {
       const int cy = threadIdx.x / kDmCT, cx = threadIdx.x - cy * kDmCT;
-      const int J = Y0 + cy, I = X0 + cx;
+      const int J = y0 / 2 + cy, I = x0 / 2 + cx;
       if (J < C.Ny && I < C.Nx) {
         double acc = 0.0;
-        for (int j = max(2 * J - 1, 0); j <= min(2 * J + 2, F.Ny - 1); ++j) {
-          double row = 0.0;
-          for (int i = max(2 * I - 1, 0); i <= min(2 * I + 2, F.Nx - 1); ++i)
-            row += dm_w(i, I) * res[(j - fy0) * kDmRF + (i - fx0)];
-          acc += dm_w(j, J) * row;
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          const double* p = res + (2 * cy + a) * kDmRF + 2 * cx;
+          acc += dm_w(a - 1, 0) * (((0.25 * p[0] + 0.75 * p[1]) + 0.75 * p[2]) + 0.25 * p[3]);
         }
-        const long o = dm_at(C, J, I);
-        C.rhs[o] = 0.25 * acc;
-        C.psi[o] = 0.0;
+        C.rhs[dm_at(C, J, I)] = 0.25 * acc;
       }
     }
     __syncthreads();
   }
 }
 
-// Start of a solve for the stage point S (C planes in the flow's layout):
-// r = b - A x with b = -(d_x S_1 + d_y S_2) and A = -Laplace_h, then the
-// V-cycle's input on level 0: rhs = -r, psi = 0 (it solves Laplace_h z = -r).
-template <class T>
-__global__ void __launch_bounds__(256) dm_begin(Bufs<T> B, const T* __restrict__ S, DmLevel L0, DmVecs D,
-                                                const DevStatus* st) {
+// psi = two sweeps of F.tmp + P (C.psi) against rhs. DOT (level 0): also the
+// workgroup's partial of r.z (r = -rhs, z = psi).
+template <bool DOT>
+__global__ void __launch_bounds__(256) dm_up(DmLevel F, DmLevel C, const double* __restrict__ rhs,
+                                             double* __restrict__ part, const DevStatus* st) {
   if (dm_skip(st)) return;
-  const double c1 = 1.0 / (12.0 * L0.h);
-  const long p = B.pitch;
-  DM_SITES(L0) {
-    const int j = (int)(k_ / L0.Nx), i = (int)(k_ - (long)j * L0.Nx);
-    const T* s1 = S + (long)(j + 2) * p + (i + 2);
-    const T* s2 = s1 + B.plane;
-    const double dx = c1 * (((double)s1[-2] - (double)s1[2]) + 8.0 * ((double)s1[1] - (double)s1[-1]));
-    const double dy = c1 * (((double)s2[-2 * p] - (double)s2[2 * p]) + 8.0 * ((double)s2[p] - (double)s2[-p]));
-    const long o = dm_at(L0, j, i);
-    const double r = -(dx + dy) + dm_lap(D.x, L0.pitch, j, i, L0.h);
-    D.r[o] = r;
-    L0.rhs[o] = -r;
-    L0.psi[o] = 0.0;
+  constexpr int NA = kDmTA * kDmTA, NB = kDmTB * kDmTB, NCC = kDmTC * kDmTC;
+  __shared__ double a[NA];
+  __shared__ double b[NB];
+  __shared__ double r[NB];
+  __shared__ double cc[NCC];
+  __shared__ double red[4];
+  const double s = kDmOmega * F.h * F.h / 5.0;
+  const int ntx = (F.Nx + kDmTile - 1) / kDmTile;
+  const int nt = dm_tiles(F);
+  auto inside = [&](int j, int i) { return j >= 0 && j < F.Ny && i >= 0 && i < F.Nx; };
+  double rz = 0.0;
+  for (int t = blockIdx.x; t < nt; t += gridDim.x) {
+    const int y0 = (t / ntx) * kDmTile, x0 = (t % ntx) * kDmTile;
+    const int cy0 = y0 / 2 - 3, cx0 = x0 / 2 - 3;  // first coarse row and column of cc
+    constexpr int QA = (NA + 255) / 256, QB = (NB + 255) / 256;
+    double va[QA], vr[QB], vc = 0.0;
+#pragma unroll
+    for (int q = 0; q < QA; ++q) {
+      const int k = threadIdx.x + 256 * q;
+      const int ly = k / kDmTA, lx = k - ly * kDmTA;
+      const int j = y0 - 4 + ly, i = x0 - 4 + lx;
+      va[q] = (k < NA && inside(j, i)) ? F.tmp[dm_at(F, j, i)] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < QB; ++q) {
+      const int k = threadIdx.x + 256 * q;
+      const int ly = k / kDmTB, lx = k - ly * kDmTB;
+      const int j = y0 - 2 + ly, i = x0 - 2 + lx;
+      vr[q] = (k < NB && inside(j, i)) ? rhs[dm_at(F, j, i)] : 0.0;
+    }
+    static_assert(NCC <= 256, "one coarse value per thread");
+    if (threadIdx.x < NCC) {
+      const int ly = threadIdx.x / kDmTC, lx = threadIdx.x - ly * kDmTC;
+      const int J = cy0 + ly, I = cx0 + lx;
+      if (J >= 0 && J < C.Ny && I >= 0 && I < C.Nx) vc = C.psi[dm_at(C, J, I)];
+      cc[threadIdx.x] = vc;
+    }
+#pragma unroll
+    for (int q = 0; q < QB; ++q) {
+      const int k = threadIdx.x + 256 * q;
+      if (k < NB) r[k] = vr[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < QA; ++q) {
+      const int k = threadIdx.x + 256 * q;
+      if (k < NA) {
+        const int ly = k / kDmTA, lx = k - ly * kDmTA;
+        const int j = y0 - 4 + ly, i = x0 - 4 + lx;
+        // (P c)(j, i), as dm_prolong_at
+        const double* c0 = cc + ((j >> 1) - cy0) * kDmTC + ((i >> 1) - cx0);
+        const int dj = (j & 1) ? kDmTC : -kDmTC, di = (i & 1) ? 1 : -1;
+        a[k] = inside(j, i)
+                   ? va[q] + (0.5625 * c0[0] + 0.1875 * (c0[di] + c0[dj]) + 0.0625 * c0[dj + di]) : 0.0;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < QB; ++q) {
+      const int k = threadIdx.x + 256 * q;
+      if (k < NB) {
+        const int ly = k / kDmTB, lx = k - ly * kDmTB;
+        b[k] = inside(y0 - 2 + ly, x0 - 2 + lx)
+                   ? a[(ly + 2) * kDmTA + (lx + 2)] - s * (r[k] - dm_lap(a, kDmTA, ly, lx, F.h)) : 0.0;
+      }
+    }
+    __syncthreads();
+    const int ly = threadIdx.x / kDmTile, lx = threadIdx.x - ly * kDmTile;
+    if (inside(y0 + ly, x0 + lx)) {
+      const int o = (ly + 2) * kDmTB + (lx + 2);
+      const double z = b[o] - s * (r[o] - dm_lap(b, kDmTB, ly, lx, F.h));
+      F.psi[dm_at(F, y0 + ly, x0 + lx)] = z;
+      if (DOT) rz -= r[o] * z;
+    }
+    __syncthreads();
+  }
+  if (DOT) {
+    rz = dm_block_sum(rz, red);
+    if (threadIdx.x == 0) part[blockIdx.x] = rz;
   }
 }
 
-// Sum of 256 threads' values in a fixed order; valid in thread 0.
-__device__ __forceinline__ double dm_block_sum(double v, double* red) {
-  v = wave_sum(v);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return red[0] + red[1] + red[2] + red[3];
+// Direction and operator in one launch: d' = z + beta d on the tile and a halo of two
+// (into the other plane), Ad = -Laplace_h d' and the workgroup's partial of d'.Ad.
+// beta = r.z / (r.z of the last iteration) (0 on the first iteration or once that is
+// 0), r.z summed from the partials by every workgroup.
+static __global__ void __launch_bounds__(256) dm_direction(DmLevel L0, DmVecs D, int cur, int first, int nrz,
+                                                           const DevStatus* st) {
+  if (dm_skip(st)) return;
+  constexpr int NB = kDmTB * kDmTB, QB = (NB + 255) / 256;
+  __shared__ double b[NB];
+  __shared__ double red[4];
+  const int ntx = (L0.Nx + kDmTile - 1) / kDmTile;
+  const int nt = dm_tiles(L0);
+  auto inside = [&](int j, int i) { return j >= 0 && j < L0.Ny && i >= 0 && i < L0.Nx; };
+  double beta = 0.0, acc = 0.0;
+  bool head = first == 0;
+  for (int t = blockIdx.x; t < nt; t += gridDim.x) {
+    const int y0 = (t / ntx) * kDmTile, x0 = (t % ntx) * kDmTile;
+    double vz[QB], vd[QB];
+#pragma unroll
+    for (int q = 0; q < QB; ++q) {
+      const int k = threadIdx.x + 256 * q;
+      const int ly = k / kDmTB, lx = k - ly * kDmTB;
+      const int j = y0 - 2 + ly, i = x0 - 2 + lx;
+      const bool in = k < NB && inside(j, i);
+      vz[q] = in ? L0.psi[dm_at(L0, j, i)] : 0.0;
+      vd[q] = (!first && in) ? D.d[cur ^ 1][dm_at(L0, j, i)] : 0.0;
+    }
+    if (head) {
+      const double rz = dm_partials(D.part, nrz, red), last = D.sc[0];
+      beta = last == 0.0 ? 0.0 : rz / last;
+      head = false;
+    }
+#pragma unroll
+    for (int q = 0; q < QB; ++q) {
+      const int k = threadIdx.x + 256 * q;
+      if (k < NB) b[k] = first ? vz[q] : vz[q] + beta * vd[q];
+    }
+    __syncthreads();
+    const int ly = threadIdx.x / kDmTile, lx = threadIdx.x - ly * kDmTile;
+    if (inside(y0 + ly, x0 + lx)) {
+      const double d = b[(ly + 2) * kDmTB + lx + 2];
+      const double ad = -dm_lap(b, kDmTB, ly, lx, L0.h);
+      const long o = dm_at(L0, y0 + ly, x0 + lx);
+      D.d[cur][o] = d;
+      D.Ad[o] = ad;
+      acc += d * ad;
+    }
+    __syncthreads();
+  }
+  acc = dm_block_sum(acc, red);
+  if (threadIdx.x == 0) D.pmv[blockIdx.x] = acc;
 }
 
-// part[block] = sum over the block's sites of a . b (level-0 planes)
-__global__ void __launch_bounds__(256) dm_dot(DmLevel L0, const double* __restrict__ a, const double* __restrict__ b,
-                                              double* __restrict__ part, const DevStatus* st) {
+// The end of an iteration where no dm_down<true> follows: x += alpha d, and (more != 0)
+// rhs += alpha Ad into the other plane. alpha as there.
+static __global__ void __launch_bounds__(256) dm_update(DmLevel L0, DmVecs D, int cur, int more, int nrz, int nmv,
+                                                        const DevStatus* st) {
   if (dm_skip(st)) return;
   __shared__ double red[4];
-  double acc = 0.0;
-  DM_SITES(L0) {
-    const int j = (int)(k_ / L0.Nx), i = (int)(k_ - (long)j * L0.Nx);
-    const long o = dm_at(L0, j, i);
-    acc += a[o] * b[o];
-  }
-  const double s = dm_block_sum(acc, red);
-  if (threadIdx.x == 0) part[blockIdx.x] = s;
-}
-
-// d = z (first iteration) or z + beta d, with beta = r.z / (r.z of the last
-// iteration) (0 on the first iteration or once that is 0). Every workgroup sums
-// the r.z partials itself, in the same fixed order, so no launch of its own is
-// needed for the scalar.
-__global__ void __launch_bounds__(256) dm_dir(DmLevel L0, DmVecs D, int first, const DevStatus* st) {
-  if (dm_skip(st)) return;
-  __shared__ double red[4];
-  const double rz = dm_block_sum(D.part[threadIdx.x], red);  // kDmRedGroups == 256 partials
-  const double beta = (first || D.sc[0] == 0.0) ? 0.0 : rz / D.sc[0];
-  if (blockIdx.x == 0 && threadIdx.x == 0) D.sc[1] = beta;
-  DM_SITES(L0) {
-    const int j = (int)(k_ / L0.Nx), i = (int)(k_ - (long)j * L0.Nx);
-    const long o = dm_at(L0, j, i);
-    D.d[o] = first ? L0.psi[o] : L0.psi[o] + beta * D.d[o];
-  }
-}
-
-// Ad = -Laplace_h d and pmv[block] = sum of d . Ad over the block's sites
-__global__ void __launch_bounds__(256) dm_matvec(DmLevel L0, DmVecs D, const DevStatus* st) {
-  if (dm_skip(st)) return;
-  __shared__ double red[4];
-  double acc = 0.0;
-  DM_SITES(L0) {
-    const int j = (int)(k_ / L0.Nx), i = (int)(k_ - (long)j * L0.Nx);
-    const long o = dm_at(L0, j, i);
-    const double ad = -dm_lap(D.d, L0.pitch, j, i, L0.h);
-    D.Ad[o] = ad;
-    acc += D.d[o] * ad;
-  }
-  const double s = dm_block_sum(acc, red);
-  if (threadIdx.x == 0) D.pmv[blockIdx.x] = s;
-}
-
-// alpha = r.z / d.Ad (0 once d.Ad is 0: the residual has vanished), summed by
-// every workgroup from the partials in fixed order; then x += alpha d,
-// r -= alpha Ad, and the next V-cycle's input (rhs = -r, psi = 0). Workgroup 0
-// keeps r.z for the next iteration's beta.
-__global__ void __launch_bounds__(256) dm_update(DmLevel L0, DmVecs D, const DevStatus* st) {
-  if (dm_skip(st)) return;
-  __shared__ double red[4], red2[4];
-  const double rz = dm_block_sum(D.part[threadIdx.x], red);
-  const double dad = dm_block_sum(D.pmv[threadIdx.x], red2);
+  const double rz = dm_partials(D.part, nrz, red);
+  const double dad = dm_partials(D.pmv, nmv, red);
   const double alpha = dad > 0.0 ? rz / dad : 0.0;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    D.sc[0] = rz;
-    D.sc[2] = alpha;
-    D.sc[3] = dad;
-  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) D.sc[0] = rz;
   DM_SITES(L0) {
     const int j = (int)(k_ / L0.Nx), i = (int)(k_ - (long)j * L0.Nx);
     const long o = dm_at(L0, j, i);
-    D.x[o] += alpha * D.d[o];
-    const double r = D.r[o] - alpha * D.Ad[o];
-    D.r[o] = r;
-    L0.rhs[o] = -r;
-    L0.psi[o] = 0.0;
+    D.x[o] += alpha * D.d[cur][o];
+    if (more) D.rhs[cur ^ 1][o] = D.rhs[cur][o] + alpha * D.Ad[o];
   }
 }
 
-// The stage point a pass evaluates, formed as the pass forms it (phi + cv v + ca a,
-// put on the unit sphere at interior sites when the pass moves the field), over
-// the whole padded lattice, into `out` (the flow's layout). For an evaluation the
-// field is `src` or, when that is null, the current field. Skipped once a flow
-// has stopped, as the pass itself is.
+// Start of a solve for the stage point a pass evaluates: rhs = -r of r = b - A x with
+// b = -(d_x S_1 + d_y S_2) and A = -Laplace_h (the V-cycle solves Laplace_h z = -r),
+// x the last potential. The stage point is formed as the pass forms it
+// (phi + cv v + ca a, put on the unit sphere at interior sites when the pass moves the
+// field) on the tile and its halo of two, in LDS. For an evaluation the field is `src`
+// or, when that is null, the current field. The launch takes the flow's pending test
+// (Link) and is skipped once a flow has stopped, as the pass itself is.
 template <class T, int PASS>
-__global__ void __launch_bounds__(256) dm_stage_point(Bufs<T> B, Coeffs cf, const DevStatus* st,
-                                                      const T* __restrict__ src, T* __restrict__ out) {
-  if (PASS != kEval && st->done) return;
+__global__ void __launch_bounds__(256) dm_begin(Bufs<T> B, Coeffs cf, Link link, const T* __restrict__ src,
+                                                DmLevel L0, DmVecs D) {
+  __shared__ double red[12];
+
+  constexpr int NB = kDmTB * kDmTB, QB = (NB + 255) / 256;
+  __shared__ T s1[NB];
+  __shared__ T s2[NB];
+  __shared__ double xs[NB];
+  Head hd = {};
+  if (PASS == kEval) hd.step = link.st->step;
+  else hd = resolve(link, cf.h * cf.h, threadIdx.x, red);
+  if (PASS != kEval && hd.done) return;
   constexpr bool ONEPASS = advances_first(PASS);
   constexpr bool STAGED = staged(PASS);
   constexpr bool WITH_V = stage_reads_v(PASS);
   constexpr bool WITH_A = stage_reads_a(PASS);
   constexpr bool AFTER_P1 = (PASS == kP2 || PASS == kP3 || PASS == kP4);
-  const long long step = st->step;
-  const int cur = AFTER_P1 ? int((step - 1) & 1) : int(step & 1);
-  const bool arrest = uses_arrest(PASS) ? (st->arrest != 0) : false;
+  const int cur = AFTER_P1 ? int((hd.step - 1) & 1) : int(hd.step & 1);
+  const bool arrest = uses_arrest(PASS) ? (hd.arrest != 0) : false;
   const T dt = (T)cf.dt;
   T cv, ca;
   stage_coeffs<T, PASS>(dt, arrest, cv, ca);
   const T* __restrict__ ph = (PASS == kEval && src != nullptr) ? src : (cur ? B.phi[1] : B.phi[0]);
   const T* __restrict__ vv = cur ? B.vel[1] : B.vel[0];
   const T* __restrict__ aa = ONEPASS ? (cur ? B.a2 : B.a1) : (PASS == kP3) ? B.a1 : B.a2;
-  const long W = B.Nx + 4, H = B.Ny + 4;
-  for (long k = blockIdx.x * 256L + threadIdx.x; k < W * H; k += (long)gridDim.x * 256L) {
-    const int jj = (int)(k / W), ii = (int)(k - (long)jj * W);
-    const long o = (long)jj * B.pitch + ii;
-    T S[3];
+  const double c1 = 1.0 / (12.0 * L0.h);
+  const int ntx = (L0.Nx + kDmTile - 1) / kDmTile;
+  const int nt = dm_tiles(L0);
+  for (int t = blockIdx.x; t < nt; t += gridDim.x) {
+    const int y0 = (t / ntx) * kDmTile, x0 = (t % ntx) * kDmTile;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      T x = ph[c * B.plane + o];
-      if (STAGED) {
-        if (WITH_V) x += cv * vv[c * B.plane + o];
-        if (WITH_A) x += ca * aa[c * B.plane + o];
+    for (int q = 0; q < QB; ++q) {
+      const int k = threadIdx.x + 256 * q;
+      if (k >= NB) break;
+      const int ly = k / kDmTB, lx = k - ly * kDmTB;
+      const int j = y0 - 2 + ly, i = x0 - 2 + lx;  // the padded lattice ends at N + 1
+      T S[3] = {T(0), T(0), T(0)};
+      double xv = 0.0;
+      if (j <= L0.Ny + 1 && i <= L0.Nx + 1) {
+        const long o = (long)(j + 2) * B.pitch + (i + 2);
+        const bool in = j >= 0 && j < L0.Ny && i >= 0 && i < L0.Nx;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          if (!STAGED && c == 2) continue;
+          T x = ph[c * B.plane + o];
+          if (STAGED) {
+            if (WITH_V) x += cv * vv[c * B.plane + o];
+            if (WITH_A) x += ca * aa[c * B.plane + o];
+          }
+          S[c] = x;
+        }
+        if (STAGED && in) {
+          const T inv = T(1) / sqrt(S[0] * S[0] + S[1] * S[1] + S[2] * S[2]);
+          S[0] *= inv;
+          S[1] *= inv;
+        }
+        if (in) xv = D.x[dm_at(L0, j, i)];
       }
-      S[c] = x;
+      s1[k] = S[0];
+      s2[k] = S[1];
+      xs[k] = xv;
     }
-    if (STAGED && ii >= 2 && ii < B.Nx + 2 && jj >= 2 && jj < B.Ny + 2) {
-      const T inv = T(1) / sqrt(S[0] * S[0] + S[1] * S[1] + S[2] * S[2]);
-#pragma unroll
-      for (int c = 0; c < 3; ++c) S[c] *= inv;
+    __syncthreads();
+    const int ly = threadIdx.x / kDmTile, lx = threadIdx.x - ly * kDmTile;
+    const int j = y0 + ly, i = x0 + lx;
+    if (j < L0.Ny && i < L0.Nx) {
+      const T* p1 = s1 + (ly + 2) * kDmTB + lx + 2;
+      const T* p2 = s2 + (ly + 2) * kDmTB + lx + 2;
+      const double dx = c1 * (((double)p1[-2] - (double)p1[2]) + 8.0 * ((double)p1[1] - (double)p1[-1]));
+      const double dy = c1 * (((double)p2[-2 * kDmTB] - (double)p2[2 * kDmTB]) +
+                              8.0 * ((double)p2[kDmTB] - (double)p2[-kDmTB]));
+      const double r = -(dx + dy) + dm_lap(xs, kDmTB, ly, lx, L0.h);
+      D.rhs[0][dm_at(L0, j, i)] = -r;
     }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) out[c * B.plane + o] = S[c];
+    __syncthreads();
   }
-}
-
-// Zero-fill of n doubles (the hierarchy's planes at set-up, and the potential
-// when a new field is set).
-__global__ void __launch_bounds__(256) dm_fill_zero(double* p, long n) {
-  for (long k = blockIdx.x * 256L + threadIdx.x; k < n; k += (long)gridDim.x * 256L) p[k] = 0.0;
 }
 
 #undef DM_SITES

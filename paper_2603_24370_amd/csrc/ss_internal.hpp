@@ -41,6 +41,46 @@ struct DevStatus {
   double obs[16];        // observable sums (see ss_api)
 };
 
+// The part of the status that a reduction changes, as a kernel holds it.
+struct Head {
+  double E, E_prev, gmax;
+  long long step, n_arrests;
+  int arrest, done, nonfinite, fresh;
+};
+
+__device__ __forceinline__ Head load_head(const DevStatus* s) {
+  return Head{s->E, s->E_prev, s->gmax, s->step, s->n_arrests, s->arrest, s->done, s->nonfinite, s->fresh};
+}
+
+__device__ __forceinline__ void store_head(DevStatus* s, const Head& h) {
+  s->E = h.E;
+  s->E_prev = h.E_prev;
+  s->gmax = h.gmax;
+  s->step = h.step;
+  s->n_arrests = h.n_arrests;
+  s->arrest = h.arrest;
+  s->done = h.done;
+  s->nonfinite = h.nonfinite;
+  s->fresh = h.fresh;
+}
+
+// How a pass of the single lattice learns the status. A reducing pass ends with
+// one partial per workgroup; the next launch that needs the status sums them
+// itself, every workgroup in the same fixed order, and takes the decisions of
+// that test (Head, as decide() gives it), so a test costs no launch of its own
+// (a one-workgroup launch between two passes of a small lattice takes as long as
+// a third of the pass: 3.6 of 13.8 us per velocity Verlet step on 128^2). Its first
+// workgroup stores the result in the other of two status copies, since the rest
+// still read the first. Rules and the energy history are in st alone.
+struct Link {
+  DevStatus* st;
+  const DevStatus* in;  // head before the pending test
+  DevStatus* out;       // head after it (in where none is pending)
+  const double* part;   // the pending test's partials, 4 doubles per workgroup
+  int n;                // their number
+  int kind;             // the tested pass's finalise_kind, or -1: nothing is pending
+};
+
 // Field buffers of one context, in the device layout: component planes of
 // (Ny + 4) rows of `pitch` elements; element (c, j, i) at c*plane + (j+2)*pitch + (i+2).
 template <class T>
@@ -121,6 +161,13 @@ constexpr bool uses_arrest(int pass) {
 // The pass writes the velocity buffer of the current field in place (each site
 // by the thread that reads it): the velocity Verlet passes around the steps.
 constexpr bool vv_in_place(int pass) { return pass == kVVStart || pass == kVVRestart || pass == kVVEnd; }
+// What the status update after a reducing pass does (bits): the step advances
+// before the test, the test takes no arrest decision, the step advances after it.
+constexpr int kAdvanceFirst = 1, kNoArrest = 2, kAdvanceAfter = 4;
+constexpr int finalise_kind(int pass) {
+  return (advances_first(pass) ? kAdvanceFirst : 0) | (no_arrest(pass) ? kNoArrest : 0) |
+         ((pass == kP1 || pass == kGD) ? kAdvanceAfter : 0);
+}
 // Passes launched once per run (or after an arrest) on one tile shape, whatever
 // the context's tile.
 constexpr bool fixed_tile(int pass) { return vv_in_place(pass) || pass == kGDCheck; }
@@ -193,6 +240,130 @@ __device__ __forceinline__ void block_reduce3(double& s, double& m, int& n, doub
     m = mm;
     n = (int)nn;
   }
+}
+
+
+// The stop rules, and the energy of `window` steps back for the stall rule.
+struct Rules {
+  double grad_tol, rel_e_tol, e_target, e_window;
+  long long max_steps;
+  int window, minimise;
+};
+
+// The rules for the test of a head (kind: finalise_kind of the tested pass).
+__device__ __forceinline__ Rules load_rules(const DevStatus* st, const Head& h, int kind) {
+  Rules q{st->grad_tol, st->rel_e_tol, st->e_target, 0.0, st->max_steps, st->window, st->minimise};
+  const long long s0 = h.step + (kind & kAdvanceFirst ? 1 : 0);
+  if (q.window > 0 && s0 >= q.window) q.e_window = st->hist[(s0 - q.window) % kHistLen];
+  return q;
+}
+
+// Status update after a reduction of one field: arrest test E > E_prev (strict,
+// eq. (4)), the stop rules when minimising, and the step counter. E is already
+// multiplied by h^2. The tested step is returned (its place in the history).
+__device__ __forceinline__ long long decide(Head& h, const Rules& q, int kind, double E, double gmax, int nfin) {
+  // a one-pass step has written the new field: it becomes the current one, and
+  // the tests below are those of the new field
+  if (kind & kAdvanceFirst) ++h.step;
+  const long long s0 = h.step;
+  // The first test of a run is of the field the last run ended on, whose arrest
+  // that run decided (and applied), or of a fresh field (E_prev infinite): it
+  // takes no new arrest decision and keeps the energy the next test compares
+  // with, so a run split in two decides its arrests as one run does. (Its own
+  // sum of the same field may differ in the last bits: another launch shape.)
+  const bool retest = h.fresh != 0;
+  h.fresh = 0;
+  // gradient flow has no velocity, hence no arrest
+  const int arr = (!(kind & kNoArrest) && !retest && E > h.E_prev) ? 1 : 0;
+  if (!retest) h.arrest = arr;
+  if (arr) h.n_arrests += 1;
+  if (!retest || !isfinite(h.E_prev)) h.E_prev = E;
+  h.E = E;
+  h.gmax = gmax;
+  h.nonfinite = nfin;
+  int done = 0;
+  if (nfin > 0) {
+    done = 4;
+  } else if (q.minimise) {
+    if (gmax < q.grad_tol) done = 1;
+    else if (q.window > 0 && s0 >= q.window && fabs(E - q.e_window) <= q.rel_e_tol * fabs(E)) done = 2;
+    else if (E <= q.e_target) done = 5;
+    else if (s0 >= q.max_steps) done = 3;
+  }
+  if (done) h.done = done;
+  else if (kind & kAdvanceAfter) h.step = s0 + 1;
+  return s0;
+}
+
+// The first 256 threads' sum of n partials of (energy, max |G|, non-finite count)
+// in workgroup order (strided by 256, then in wave order), for every thread. The
+// loads of up to four strides are in flight together. red: 12 doubles of LDS. All
+// threads of the workgroup call it.
+__device__ __forceinline__ void sum_partials(const double* __restrict__ part, int n, int tid, double* red, double& se,
+                                             double& sg, int& sn) {
+  se = 0.0;
+  sg = 0.0;
+  sn = 0;
+  if (tid < 256) {
+    constexpr int U = 4;
+    for (int k0 = 0; k0 < n; k0 += 256 * U) {
+      double p[U][3];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = k0 + 256 * u + tid;
+        const double* q = part + 4 * (long)(k < n ? k : 0);
+        p[u][0] = q[0];
+        p[u][1] = q[1];
+        p[u][2] = q[2];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (k0 + 256 * u + tid < n) {
+          se += p[u][0];
+          sg = fmax(sg, p[u][1]);
+          sn += (int)p[u][2];
+        }
+    }
+    se = wave_sum(se);
+    sg = wave_max(sg);
+    sn = wave_isum(sn);
+    if ((tid & 63) == 0) {
+      const int w = tid >> 6;
+      red[w] = se;
+      red[4 + w] = sg;
+      red[8 + w] = (double)sn;
+    }
+  }
+  __syncthreads();
+  double ss = 0.0, mm = 0.0, nn = 0.0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    ss += red[k];
+    mm = fmax(mm, red[4 + k]);
+    nn += red[8 + k];
+  }
+  se = ss;
+  sg = mm;
+  sn = (int)nn;
+}
+
+// The status as of this launch (Link), for every thread of a workgroup of at
+// least 256. h2 = h^2 of the lattice. red: 12 doubles of LDS, free again after
+// the workgroup's next barrier. Its loads are independent of each other, so the
+// launch waits for memory once.
+__device__ __forceinline__ Head resolve(const Link& L, double h2, int tid, double* red) {
+  Head h = load_head(L.in);
+  if (L.kind < 0) return h;
+  const Rules q = load_rules(L.st, h, L.kind);
+  double se, sg;
+  int sn;
+  sum_partials(L.part, L.n, tid, red, se, sg, sn);
+  if (!h.done) {
+    const long long s0 = decide(h, q, L.kind, h2 * se, sg, sn);
+    if (blockIdx.x == 0 && tid == 0) L.st->hist[s0 % kHistLen] = h.E;
+  }
+  if (blockIdx.x == 0 && tid == 0) store_head(L.out, h);
+  return h;
 }
 
 }  // namespace ss

@@ -15,9 +15,9 @@
 // chiral magnet every stage point is put back on the unit sphere and G is
 // projected on its tangent plane; phi' is renormalised and v' projected.
 // P1 also reduces E_h (FP64 from the stored values), max |G| and a non-finite
-// count to one partial per workgroup; pass_finalise, launched after it, sums
-// the partials in a fixed order, applies the arrest test E > E_prev (strict)
-// and the stop rules, and advances the step counter, all on the device.
+// count to one partial per workgroup; the launch after it sums the partials in a
+// fixed order, applies the arrest test E > E_prev (strict) and the stop rules,
+// and advances the step counter, all on the device.
 #pragma once
 
 #include "ss_internal.hpp"
@@ -76,8 +76,8 @@ template <class T>
 struct PassArgs {
   Bufs<T> B;
   Coeffs cf;
-  DevStatus* st;
-  double* partials;
+  Link link;         // the status (kEval: link.st receives the result)
+  double* partials;  // of a reducing pass
   const T* src;  // kEval: field to evaluate in the internal layout (nullptr = current field)
   T* out;        // kEval: gradient output in the caller's layout (nullptr = none)
   long out_pitch, out_plane;
@@ -1015,9 +1015,8 @@ __device__ __forceinline__ void tile_body_exact(const InstView<T>& V, int cur, b
   __syncthreads();
 }
 
-// Status update after a reduction of one field (thread 0 of the finalising
-// workgroup): arrest test E > E_prev (strict, eq. (4)), the stop rules when
-// minimising, and the step counter (P1 only). E is already multiplied by h^2.
+// Status update of an evaluation, a batch member or the BEC after a reduction
+// (thread 0 of the finalising workgroup). E is already multiplied by h^2.
 template <int PASS>
 __device__ __forceinline__ void finalise_status(DevStatus* st, double E, double gmax, int nfin) {
   st->counter = 0u;
@@ -1027,43 +1026,17 @@ __device__ __forceinline__ void finalise_status(DevStatus* st, double E, double 
     st->nonfinite = nfin;
     return;
   }
-  // a one-pass step has written the new field: it becomes the current one, and
-  // the tests below are those of the new field
-  long long s0 = st->step;
-  if (advances_first(PASS)) st->step = ++s0;
-  // The first test of a run is of the field the last run ended on, whose arrest
-  // that run decided (and applied), or of a fresh field (E_prev infinite): it
-  // takes no new arrest decision and keeps the energy the next test compares
-  // with, so a run split in two decides its arrests as one run does. (Its own
-  // sum of the same field may differ in the last bits: another launch shape.)
-  const bool retest = st->fresh != 0;
-  st->fresh = 0;
-  // gradient flow has no velocity, hence no arrest
-  const int arr = (!no_arrest(PASS) && !retest && E > st->E_prev) ? 1 : 0;
-  if (!retest) st->arrest = arr;
-  if (arr) st->n_arrests += 1;
-  if (!retest || !isfinite(st->E_prev)) st->E_prev = E;
-  st->E = E;
-  st->gmax = gmax;
-  st->nonfinite = nfin;
+  constexpr int kind = finalise_kind(PASS);
+  Head h = load_head(st);
+  const Rules q = load_rules(st, h, kind);
+  const long long s0 = decide(h, q, kind, E, gmax, nfin);
   st->hist[s0 % kHistLen] = E;
-  int done = 0;
-  if (nfin > 0) {
-    done = 4;
-  } else if (st->minimise) {
-    const int W = st->window;
-    if (gmax < st->grad_tol) done = 1;
-    else if (W > 0 && s0 >= W && fabs(E - st->hist[(s0 - W) % kHistLen]) <= st->rel_e_tol * fabs(E)) done = 2;
-    else if (E <= st->e_target) done = 5;
-    else if (s0 >= st->max_steps) done = 3;
-  }
-  if (done) st->done = done;
-  else if (PASS == kP1 || PASS == kGD) st->step = s0 + 1;
+  store_head(st, h);
 }
 
 // Launch: gridDim.x is a multiple of 8; tiles are assigned by for_each_tile.
-// Each workgroup accumulates its tiles' reductions into one partial;
-// pass_finalise sums the partials in a fixed order and updates the status.
+// Each workgroup accumulates its tiles' reductions into one partial; the next
+// launch that needs the status sums them in a fixed order (Link).
 // Waves per SIMD a stage pass is compiled for. The Abelian-Higgs one-pass
 // integrators in FP32 on two-row tiles are held to 128 VGPRs (four waves; 160
 // uncapped), so that two 512-thread workgroups share a CU, without spills; the
@@ -1073,6 +1046,18 @@ template <class T, int TH, int PASS, int RY>
 struct StageWaves {
   static constexpr int value = (sizeof(T) == 4 && TH == 0 && RY == 2 && (advances_first(PASS) || PASS == kGD)) ? 4 : 1;
 };
+
+// The status a pass starts from. An evaluation reads the current field's parity
+// only (it runs between runs, with nothing pending).
+template <int PASS, class T>
+__device__ __forceinline__ Head pass_head(const PassArgs<T>& a, int tid, double* red) {
+  if (PASS == kEval) {
+    Head h = {};
+    h.step = a.link.st->step;
+    return h;
+  }
+  return resolve(a.link, a.cf.h * a.cf.h, tid, red);
+}
 
 template <class T, int TH, int PASS, int TX, int TY, int RY>
 __global__ void __launch_bounds__(TX*(TY / RY))
@@ -1087,15 +1072,15 @@ __attribute__((amdgpu_waves_per_eu(StageWaves<T, TH, PASS, RY>::value))) stage_p
   __shared__ __align__(16) T lds[TileLds<T, TH, PASS, TX, TY>::size];
   __shared__ double red[3 * (NT / 64)];
 
-  DevStatus* __restrict__ st = a.st;
   // a finished flow skips its remaining passes; velocity Verlet's end of run
   // converts the velocity whatever the status, and its restart runs only after
   // an arrest
-  if (PASS != kEval && PASS != kVVEnd && st->done) return;
-  if (PASS == kVVRestart && !st->arrest) return;
-  const long long step = st->step;
+  const Head hd = pass_head<PASS>(a, threadIdx.y * TX + threadIdx.x, red);
+  if (PASS != kEval && PASS != kVVEnd && hd.done) return;
+  if (PASS == kVVRestart && !hd.arrest) return;
+  const long long step = hd.step;
   const int cur = AFTER_P1 ? int((step - 1) & 1) : int(step & 1);
-  const bool arrest = uses_arrest(PASS) ? (st->arrest != 0) : false;
+  const bool arrest = uses_arrest(PASS) ? (hd.arrest != 0) : false;
   const InstView<T> V = view_of<T>(a.B, a.cf);
 
   double e_acc = 0.0, g_acc = 0.0;
@@ -1107,7 +1092,7 @@ __attribute__((amdgpu_waves_per_eu(StageWaves<T, TH, PASS, RY>::value))) stage_p
   if (!REDUCE) return;
 
   // ---- first level of the FP64 reduction: one partial per workgroup (the
-  // second level is pass_finalise, launched after the pass)
+  // second level is the next launch's, resolve())
   block_reduce3<NT>(e_acc, g_acc, nf, red);
   if (threadIdx.y * TX + threadIdx.x == 0) {
     double* p = a.partials + 4 * (long)blockIdx.x;
@@ -1117,24 +1102,22 @@ __attribute__((amdgpu_waves_per_eu(StageWaves<T, TH, PASS, RY>::value))) stage_p
   }
 }
 
-// Second level of a reducing pass (one workgroup of 256 threads): the nparts
-// workgroup partials summed in workgroup order, then the status update. Being a
-// launch of its own, it needs no fence or atomic inside the pass.
-template <int PASS>
-__global__ void __launch_bounds__(256) pass_finalise(DevStatus* st, const double* __restrict__ partials, int nparts,
+// Second level of an evaluation, one workgroup of 256 threads.
+static __global__ void __launch_bounds__(256) eval_finalise(DevStatus* st, const double* __restrict__ partials, int nparts,
                                                      double h) {
-  if (PASS != kEval && st->done) return;
-  double se = 0.0, sg = 0.0;
-  int sn = 0;
-  for (int k = threadIdx.x; k < nparts; k += 256) {
-    const double* p = partials + 4 * (long)k;
-    se += p[0];
-    sg = fmax(sg, p[1]);
-    sn += (int)p[2];
-  }
-  __shared__ double red[3 * 4];
-  block_reduce3<256>(se, sg, sn, red);
-  if (threadIdx.x == 0) finalise_status<PASS>(st, h * h * se, sg, sn);
+  __shared__ double red[12];
+  double se, sg;
+  int sn;
+  sum_partials(partials, nparts, threadIdx.x, red, se, sg, sn);
+  if (threadIdx.x == 0) finalise_status<kEval>(st, h * h * se, sg, sn);
+}
+
+// End of a sequence of passes: the pending test taken and the status copied back
+// to st (one workgroup of 256 threads; link.out = link.st).
+static __global__ void __launch_bounds__(256) settle_status(Link link, double h) {
+  __shared__ double red[12];
+  const Head hd = resolve(link, h * h, threadIdx.x, red);
+  if (link.kind < 0 && threadIdx.x == 0) store_head(link.out, hd);
 }
 
 // ------------------------------------------------- fused stages 2-4 (EL gradient)
@@ -1445,10 +1428,11 @@ template <class T, int TH, int TX, int TY, int RY>
 __global__ void __launch_bounds__(TX*(TY / RY)) __attribute__((amdgpu_waves_per_eu(FusedWaves<T>::value)))
 stage_pass_fused(PassArgs<T> a) {
   __shared__ __align__(16) T lds[FusedLds<T, TH, TX, TY>::value];
-  DevStatus* __restrict__ st = a.st;
-  if (st->done) return;
-  const int cur = int((st->step - 1) & 1);
-  const bool arrest = st->arrest != 0;
+  __shared__ double red[12];
+  const Head hd = resolve(a.link, a.cf.h * a.cf.h, threadIdx.y * TX + threadIdx.x, red);
+  if (hd.done) return;
+  const int cur = int((hd.step - 1) & 1);
+  const bool arrest = hd.arrest != 0;
   const InstView<T> V = view_of<T>(a.B, a.cf);
   for_each_tile(a.ntx, a.nty, a.seg, [&](int tx, int ty, int, bool) {
     tile_body_fused<T, TH, TX, TY, RY>(V, cur, arrest, tx * TX, ty * TY, lds);
@@ -1468,12 +1452,15 @@ __global__ void __launch_bounds__(256) stage_pass_exact(PassArgs<T> a) {
   __shared__ __align__(16) T lds[NLDS];
   __shared__ double red[3 * (NT / 64)];
 
-  DevStatus* __restrict__ st = a.st;
-  if (PASS != kEval && PASS != kVVEnd && st->done) return;
-  if (PASS == kVVRestart && !st->arrest) return;
-  const long long step = st->step;
+  // a finished flow skips its remaining passes; velocity Verlet's end of run
+  // converts the velocity whatever the status, and its restart runs only after
+  // an arrest
+  const Head hd = pass_head<PASS>(a, threadIdx.y * kExTX + threadIdx.x, red);
+  if (PASS != kEval && PASS != kVVEnd && hd.done) return;
+  if (PASS == kVVRestart && !hd.arrest) return;
+  const long long step = hd.step;
   const int cur = AFTER_P1 ? int((step - 1) & 1) : int(step & 1);
-  const bool arrest = uses_arrest(PASS) ? (st->arrest != 0) : false;
+  const bool arrest = uses_arrest(PASS) ? (hd.arrest != 0) : false;
   const InstView<T> V = view_of<T>(a.B, a.cf);
   double e_acc = 0.0, g_acc = 0.0;
   int nf = 0;
@@ -1623,7 +1610,7 @@ __global__ void __launch_bounds__(256) batch_apply_arrest(const BatchInst<T>* in
 }
 
 // Arm every batch member for a run (same rule for all).
-__global__ void batch_arm(DevStatus* const* st, int n, int minimise, double grad_tol, double rel_e_tol, int window,
+static __global__ void batch_arm(DevStatus* const* st, int n, int minimise, double grad_tol, double rel_e_tol, int window,
                           long long max_steps) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) {
@@ -1639,7 +1626,7 @@ __global__ void batch_arm(DevStatus* const* st, int n, int minimise, double grad
 }
 
 // Collect the stop flags of all batch members (host reads n ints, not n status blocks).
-__global__ void batch_done_flags(DevStatus* const* st, int n, int* flags) {
+static __global__ void batch_done_flags(DevStatus* const* st, int n, int* flags) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) flags[i] = st[i]->done;
 }
@@ -1655,7 +1642,7 @@ __global__ void apply_arrest(Bufs<T> B, const DevStatus* __restrict__ st, int C)
 }
 
 // Reset the stop flag and load the stop rules before a run of steps.
-__global__ void arm_status(DevStatus* st, int minimise, double grad_tol, double rel_e_tol, int window,
+static __global__ void arm_status(DevStatus* st, int minimise, double grad_tol, double rel_e_tol, int window,
                            long long max_steps) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     st->done = 0;
@@ -1946,7 +1933,7 @@ __global__ void __launch_bounds__(256) init_ansatz(Bufs<T> B, Coeffs cf, InitArg
 // Network input on the interior grid (Ny x Nx x 2, fp32, row-major):
 // channel 0 = sum_k exp(-r_k^2 / 2) (unit Gaussians at the vortex centres),
 // channel 1 = kappa.
-__global__ void __launch_bounds__(256) learned_input(int Nx, int Ny, double h, const double* xy, int n, double kappa,
+static __global__ void __launch_bounds__(256) learned_input(int Nx, int Ny, double h, const double* xy, int n, double kappa,
                                                      float* out) {
   const long k = blockIdx.x * 256L + threadIdx.x;
   if (k >= (long)Nx * Ny) return;

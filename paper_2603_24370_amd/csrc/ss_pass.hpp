@@ -1,0 +1,131 @@
+// Definitions and instances of ss_launch.hpp for one element type and theory.
+#pragma once
+
+#include <algorithm>
+
+#include "ss_launch.hpp"
+
+namespace ss {
+
+// Workgroups of one stage-pass instantiation resident on the whole GPU at
+// once: the runtime's occupancy for one CU, rounded down to a power of two (so
+// units still split evenly over the eight XCD bands), times the CUs. Queried
+// once per instantiation on the first device that launches it.
+template <class T, int TH, int PASS, int TX, int TY, int RY>
+long resident_groups() {
+  static const long n = [] {
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &per_cu, reinterpret_cast<const void*>(&stage_pass<T, TH, PASS, TX, TY, RY>), TX * (TY / RY), 0) !=
+            hipSuccess ||
+        per_cu < 1) {
+      (void)hipGetLastError();  // a failed query must not surface as a launch error
+      return kMaxGroups;
+    }
+    int p2 = 1;
+    while (2 * p2 <= per_cu) p2 *= 2;
+    return std::min(kMaxGroups, kNumCUs * p2);
+  }();
+  return n;
+}
+
+// Launches a pass and returns its workgroup count. P1 runs with at most its
+// resident workgroups, each walking longer column segments (on 4096^2 with
+// 64 x 16 tiles: 512 groups, 0.184 -> 0.177 ms against 2048).
+template <class T, int TH, int PASS, int CFG>
+int launch_cfg(const PassArgs<T>& a, int nlaunch, hipStream_t s) {
+  constexpr TileCfg tc = kTiles[CFG];
+  PassArgs<T> b = a;
+  if constexpr (PASS == kP1 || PASS == kPrime || advances_first(PASS) || fixed_tile(PASS) || PASS == kGD) {
+    const long r = resident_groups<T, TH, PASS, tc.TX, tc.TY, tc.RY>();
+    if (nlaunch > r) {
+      nlaunch = (int)r;
+      b.seg = (int)std::min<long>(std::max<long>(1, ((long)a.ntx * a.nty) / nlaunch), a.nty);
+    }
+  }
+  hipLaunchKernelGGL((stage_pass<T, TH, PASS, tc.TX, tc.TY, tc.RY>), dim3(nlaunch), dim3(tc.TX, tc.TY / tc.RY), 0,
+                     s, b);
+  return nlaunch;
+}
+
+template <class T, int TH, int PASS>
+int launch_tiled(int tile, const PassArgs<T>& a, int nlaunch, hipStream_t s) {
+  if constexpr (!fixed_tile(PASS)) {
+    if (tile == 1) return launch_cfg<T, TH, PASS, 1>(a, nlaunch, s);
+    if (tile == 2) return launch_cfg<T, TH, PASS, 2>(a, nlaunch, s);
+    if (tile == 3) return launch_cfg<T, TH, PASS, 3>(a, nlaunch, s);
+  }
+  return launch_cfg<T, TH, PASS, 0>(a, nlaunch, s);
+}
+
+template <class T, int TH, int PASS>
+void launch_exact(const PassArgs<T>& a, int groups, hipStream_t s) {
+  hipLaunchKernelGGL((stage_pass_exact<T, TH, PASS>), dim3(groups), dim3(kExTX, kExTY / kExRY), 0, s, a);
+}
+
+template <class T, int TH>
+void launch_fused_t(int layout_tile, const PassArgs<T>& a, int nlaunch, hipStream_t s) {
+  if constexpr (sizeof(T) == 4) {
+    if (layout_tile == 0) {
+      hipLaunchKernelGGL((stage_pass_fused<T, TH, 64, 16, 2>), dim3(nlaunch), dim3(64, 8), 0, s, a);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((stage_pass_fused<T, TH, 64, 8, 2>), dim3(nlaunch), dim3(64, 4), 0, s, a);
+}
+
+template <class T, int TH, int PASS, int CFG>
+void batch_launch_cfg(const BatchArgs<T>& a, int nlaunch, hipStream_t s) {
+  constexpr TileCfg tc = kTiles[CFG];
+  hipLaunchKernelGGL((batch_pass<T, TH, PASS, tc.TX, tc.TY, tc.RY>), dim3(nlaunch), dim3(tc.TX, tc.TY / tc.RY), 0,
+                     s, a);
+}
+
+template <class T, int TH, int PASS>
+void batch_launch_t(int tile, const BatchArgs<T>& a, int nlaunch, hipStream_t s) {
+  switch (tile) {
+    case 0: batch_launch_cfg<T, TH, PASS, 0>(a, nlaunch, s); break;
+    case 1: batch_launch_cfg<T, TH, PASS, 1>(a, nlaunch, s); break;
+    case 2: batch_launch_cfg<T, TH, PASS, 2>(a, nlaunch, s); break;
+    default: batch_launch_cfg<T, TH, PASS, 3>(a, nlaunch, s); break;
+  }
+}
+
+template <class T, int TH>
+void batch_launch_fused_t(int tile, const BatchArgs<T>& a, int nlaunch, hipStream_t s) {
+  if constexpr (sizeof(T) == 4) {
+    if (tile == 0) {
+      hipLaunchKernelGGL((batch_pass_fused<T, TH, 64, 16, 2>), dim3(nlaunch), dim3(64, 8), 0, s, a);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((batch_pass_fused<T, TH, 64, 8, 2>), dim3(nlaunch), dim3(64, 4), 0, s, a);
+}
+
+#define SS_LATTICE_PASS(T, TH, P)                                                       \
+  template int launch_tiled<T, TH, P>(int, const PassArgs<T>&, int, hipStream_t);       \
+  template void launch_exact<T, TH, P>(const PassArgs<T>&, int, hipStream_t);
+
+// every pass of the lattice theories
+#define SS_LATTICE_PASSES(T, TH)                                                        \
+  SS_LATTICE_PASS(T, TH, kP1) SS_LATTICE_PASS(T, TH, kP2) SS_LATTICE_PASS(T, TH, kP3)   \
+  SS_LATTICE_PASS(T, TH, kP4) SS_LATTICE_PASS(T, TH, kEval)                             \
+  SS_LATTICE_PASS(T, TH, kCheck) SS_LATTICE_PASS(T, TH, kPrime)                         \
+  SS_LATTICE_PASS(T, TH, kVVA) SS_LATTICE_PASS(T, TH, kVV)                              \
+  SS_LATTICE_PASS(T, TH, kVVStart) SS_LATTICE_PASS(T, TH, kVVRestart)                   \
+  SS_LATTICE_PASS(T, TH, kVVEnd) SS_LATTICE_PASS(T, TH, kGD)                            \
+  SS_LATTICE_PASS(T, TH, kGDCheck)                                                      \
+  template void launch_fused_t<T, TH>(int, const PassArgs<T>&, int, hipStream_t);
+
+#define SS_BATCH_PASS(T, TH, P) \
+  template void batch_launch_t<T, TH, P>(int, const BatchArgs<T>&, int, hipStream_t);
+
+// every pass of a batch
+#define SS_BATCH_PASSES(T, TH)                                                          \
+  SS_BATCH_PASS(T, TH, kP1) SS_BATCH_PASS(T, TH, kP2) SS_BATCH_PASS(T, TH, kP3)         \
+  SS_BATCH_PASS(T, TH, kP4) SS_BATCH_PASS(T, TH, kCheck) SS_BATCH_PASS(T, TH, kVV)      \
+  SS_BATCH_PASS(T, TH, kVVStart) SS_BATCH_PASS(T, TH, kVVRestart)                       \
+  SS_BATCH_PASS(T, TH, kVVEnd) SS_BATCH_PASS(T, TH, kGD) SS_BATCH_PASS(T, TH, kGDCheck) \
+  template void batch_launch_fused_t<T, TH>(int, const BatchArgs<T>&, int, hipStream_t);
+
+}  // namespace ss
