@@ -102,9 +102,9 @@ Layout make_layout(int C, int Nx, int Ny, int esize) {
   set_tiles(L, Nx, Ny, kDefaultTile);
   L.status_off = 7 * L.set_bytes;
   L.partial_off = L.status_off + (size_t)round_up(sizeof(DevStatus), 256);
-  // partials: 4 doubles per stage-pass workgroup, 5 per observable workgroup
+  // partials: 4 doubles per stage-pass workgroup, 6 per observable workgroup
   const long nobs = 1024;
-  const long nparts = std::max<long>(4L * kMaxGroups, 5L * nobs);
+  const long nparts = std::max<long>(4L * kMaxGroups, 6L * nobs);
   L.init_off = L.partial_off + (size_t)round_up(nparts * 8, 256);
   // staging of ansatz centres and windings for ss_init_ansatz
   L.alt_off = L.init_off + (size_t)round_up(3L * kMaxVortices * 8, 256);
@@ -579,7 +579,8 @@ int read_status(ss_ctx* c, DevStatus* out) {
   return SS_OK;
 }
 
-void fill_info(const DevStatus& d, ss_step_info* info) {
+template <class S>  // DevStatus or Head
+void fill_info(const S& d, ss_step_info* info) {
   info->energy = d.E;
   info->energy_prev = d.E_prev;
   info->gnorm_inf = d.gmax;
@@ -591,18 +592,45 @@ void fill_info(const DevStatus& d, ss_step_info* info) {
 
 size_t esize_of(int dtype) { return dtype == SS_F32 ? 4 : 8; }
 
+// Launch shape of the field copies: 256 pairs of columns per workgroup.
+dim3 copy_grid(const ss_ctx* c) {
+  return dim3((unsigned)((c->Nx + 4 + 511) / 512), (unsigned)std::min(c->C * (c->Ny + 4), 65535));
+}
+
+// Whether a caller's tight rows all start on two-element boundaries.
+bool paired(const ss_ctx* c, const void* a, const void* b) {
+  const uintptr_t m = 2 * esize_of(c->dtype) - 1;
+  return (c->Nx & 1) == 0 && ((uintptr_t)a & m) == 0 && ((uintptr_t)b & m) == 0;
+}
+
+template <class T>
+void enqueue_export(const ss_ctx* c, void* field, void* velocity) {
+  if (paired(c, field, velocity))
+    hipLaunchKernelGGL((export_field<T, true>), copy_grid(c), dim3(256), 0, c->stream, bufs_of<T>(c),
+                       (const DevStatus*)c->st, c->C, (T*)field, (T*)velocity);
+  else
+    hipLaunchKernelGGL((export_field<T, false>), copy_grid(c), dim3(256), 0, c->stream, bufs_of<T>(c),
+                       (const DevStatus*)c->st, c->C, (T*)field, (T*)velocity);
+}
+
+template <class T>
+void enqueue_import(const ss_ctx* c, const void* field, const void* velocity) {
+  if (paired(c, field, velocity))
+    hipLaunchKernelGGL((import_field<T, true>), copy_grid(c), dim3(256), 0, c->stream, bufs_of<T>(c), c->C,
+                       (const T*)field, (const T*)velocity);
+  else
+    hipLaunchKernelGGL((import_field<T, false>), copy_grid(c), dim3(256), 0, c->stream, bufs_of<T>(c), c->C,
+                       (const T*)field, (const T*)velocity);
+}
+
 // Start from rest (Sec. 3.2): zero velocity and stage arrays, reset counters.
 int reset_state(ss_ctx* c) {
-  SS_HIP(hipMemsetAsync(c->ws + 2 * c->L.set_bytes, 0, 5 * c->L.set_bytes, c->stream));
-  // the demagnetising potential (warm start of the solves) restarts from zero
-  if (c->dm.on)
-    SS_HIP(hipMemsetAsync(c->dm.v.x, 0, (size_t)(c->Nx + 4) * (c->Ny + 4) * sizeof(double), c->stream));
-  DevStatus s;
-  std::memset(&s, 0, sizeof(s));
-  s.E = s.E_prev = std::numeric_limits<double>::infinity();
-  s.gmax = std::numeric_limits<double>::infinity();
-  s.e_target = -std::numeric_limits<double>::infinity();
-  SS_HIP(hipMemcpyAsync(c->st, &s, sizeof(s), hipMemcpyHostToDevice, c->stream));
+  // the velocity and stage sets, and the demagnetising potential (warm start of the solves)
+  const long n16 = (long)(5 * c->L.set_bytes / 16), m = c->dm.on ? (long)(c->Nx + 4) * (c->Ny + 4) : 0;
+  const int nb = (int)std::min<long>(8 * kNumCUs, (n16 + 255) / 256);
+  hipLaunchKernelGGL(reset_flow, dim3(nb), dim3(256), 0, c->stream, (uint4*)(c->ws + 2 * c->L.set_bytes), n16,
+                     c->dm.on ? c->dm.v.x : nullptr, m, c->st);
+  SS_HIP(hipGetLastError());
   SS_HIP(hipStreamSynchronize(c->stream));
   return SS_OK;
 }
@@ -957,14 +985,8 @@ void ss_destroy(ss_ctx* c) {
 
 int ss_set_field(ss_ctx* c, const void* field) {
   if (!c || !field) return fail(SS_EINVAL, "ctx or field is NULL");
-  const size_t es = esize_of(c->dtype);
-  const size_t upitch = (size_t)(c->Nx + 4) * es;
-  const size_t uplane = upitch * (c->Ny + 4);
-  for (int b = 0; b < 2; ++b)
-    for (int comp = 0; comp < c->C; ++comp)
-      SS_HIP(hipMemcpy2DAsync((char*)c->phi[b] + comp * c->L.plane * es, c->L.pitch * es,
-                              (const char*)field + comp * uplane, upitch, upitch, c->Ny + 4,
-                              hipMemcpyDeviceToDevice, c->stream));
+  if (c->dtype == SS_F32) enqueue_import<float>(c, field, nullptr);
+  else enqueue_import<double>(c, field, nullptr);
   return reset_state(c);
 }
 
@@ -1069,20 +1091,9 @@ int ss_time_passes(ss_ctx* c, int n_steps, double* ms) {
 
 int ss_get_field(ss_ctx* c, void* field, void* velocity) {
   if (!c || !field) return fail(SS_EINVAL, "ctx or field is NULL");
-  DevStatus d;
-  int rc = read_status(c, &d);
-  if (rc) return rc;
-  const int cur = int(d.step & 1);
-  const size_t es = esize_of(c->dtype);
-  const size_t upitch = (size_t)(c->Nx + 4) * es;
-  const size_t uplane = upitch * (c->Ny + 4);
-  for (int comp = 0; comp < c->C; ++comp) {
-    SS_HIP(hipMemcpy2DAsync((char*)field + comp * uplane, upitch, (char*)c->phi[cur] + comp * c->L.plane * es,
-                            c->L.pitch * es, upitch, c->Ny + 4, hipMemcpyDeviceToDevice, c->stream));
-    if (velocity)
-      SS_HIP(hipMemcpy2DAsync((char*)velocity + comp * uplane, upitch, (char*)c->vel[cur] + comp * c->L.plane * es,
-                              c->L.pitch * es, upitch, c->Ny + 4, hipMemcpyDeviceToDevice, c->stream));
-  }
+  if (c->dtype == SS_F32) enqueue_export<float>(c, field, velocity);
+  else enqueue_export<double>(c, field, velocity);
+  SS_HIP(hipGetLastError());
   SS_HIP(hipStreamSynchronize(c->stream));
   return SS_OK;
 }
@@ -1128,54 +1139,48 @@ int ss_set_state(ss_ctx* c, const void* field, const void* velocity, const void*
   if (b.st.counter != 0u || b.st.counter_obs != 0u) return fail(SS_EINVAL, "state blob is inconsistent");
   // both ping-pong buffers get the field and the velocity (the halo of the
   // buffer the next step writes must hold the boundary values too)
-  const size_t es = esize_of(c->dtype);
-  const size_t upitch = (size_t)(c->Nx + 4) * es;
-  const size_t uplane = upitch * (c->Ny + 4);
-  for (int buf = 0; buf < 2; ++buf)
-    for (int comp = 0; comp < c->C; ++comp) {
-      SS_HIP(hipMemcpy2DAsync((char*)c->phi[buf] + comp * c->L.plane * es, c->L.pitch * es,
-                              (const char*)field + comp * uplane, upitch, upitch, c->Ny + 4,
-                              hipMemcpyDeviceToDevice, c->stream));
-      SS_HIP(hipMemcpy2DAsync((char*)c->vel[buf] + comp * c->L.plane * es, c->L.pitch * es,
-                              (const char*)velocity + comp * uplane, upitch, upitch, c->Ny + 4,
-                              hipMemcpyDeviceToDevice, c->stream));
-    }
+  if (c->dtype == SS_F32) enqueue_import<float>(c, field, velocity);
+  else enqueue_import<double>(c, field, velocity);
+  SS_HIP(hipGetLastError());
   SS_HIP(hipMemcpyAsync(c->st, &b.st, sizeof(DevStatus), hipMemcpyHostToDevice, c->stream));
   SS_HIP(hipStreamSynchronize(c->stream));
   return SS_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// An evaluation of `field` (the caller's tight layout, read where it lies) or, when
+// that is null, of the current field of a; the gradient's halo is zeroed.
+template <class T>
+void enqueue_eval(const ss_ctx* c, PassArgs<T> a, const void* field, void* grad, hipStream_t s) {
+  const long pitch = c->Nx + 4, plane = pitch * (c->Ny + 4);
+  if (grad) {
+    const long n = (long)c->C * 4 * (c->Nx + 4 + c->Ny);
+    hipLaunchKernelGGL((zero_frame<T>), dim3((unsigned)std::min<long>(256, (n + 255) / 256)), dim3(256), 0, s, (T*)grad,
+                       c->Nx, c->Ny, c->C);
+  }
+  if (field) {
+    a.B.pitch = pitch;
+    a.B.plane = plane;
+    a.src = (const T*)field;
+  }
+  a.out = (T*)grad;
+  a.out_pitch = pitch;
+  a.out_plane = plane;
+  Run r;
+  launch_pass<T, kEval>(c, a, r, s);
+}
+
+}  // namespace
+
+extern "C" {
+
 int ss_energy_grad(ss_ctx* c, const void* field, void* grad, double* energy, double* gnorm_inf) {
   if (!c) return fail(SS_EINVAL, "ctx is NULL");
-  const size_t es = esize_of(c->dtype);
-  const size_t upitch = (size_t)(c->Nx + 4) * es;
-  const size_t uplane = upitch * (c->Ny + 4);
-  if (grad) SS_HIP(hipMemsetAsync(grad, 0, (size_t)c->C * uplane, c->stream));
-  // a caller's field is first copied into the q stage array (internal layout);
-  // q is rewritten by every third stage pass before it is read, so the flow
-  // state is not disturbed
-  if (field)
-    for (int comp = 0; comp < c->C; ++comp)
-      SS_HIP(hipMemcpy2DAsync((char*)c->q + comp * c->L.plane * es, c->L.pitch * es,
-                              (const char*)field + comp * uplane, upitch, upitch, c->Ny + 4,
-                              hipMemcpyDeviceToDevice, c->stream));
-  if (c->dtype == SS_F32) {
-    PassArgs<float> a = pass_args<float>(c);
-    a.src = field ? (const float*)c->q : nullptr;
-    a.out = (float*)grad;
-    a.out_pitch = c->Nx + 4;
-    a.out_plane = (long)(c->Nx + 4) * (c->Ny + 4);
-    Run r;
-    launch_pass<float, kEval>(c, a, r, c->stream);
-  } else {
-    PassArgs<double> a = pass_args<double>(c);
-    a.src = field ? (const double*)c->q : nullptr;
-    a.out = (double*)grad;
-    a.out_pitch = c->Nx + 4;
-    a.out_plane = (long)(c->Nx + 4) * (c->Ny + 4);
-    Run r;
-    launch_pass<double, kEval>(c, a, r, c->stream);
-  }
+  if (c->dtype == SS_F32) enqueue_eval<float>(c, pass_args<float>(c), field, grad, c->stream);
+  else enqueue_eval<double>(c, pass_args<double>(c), field, grad, c->stream);
   SS_HIP(hipGetLastError());
   DevStatus d;
   int rc = read_status(c, &d);
@@ -1222,38 +1227,20 @@ int scratch_of_current_device(void** out) {
 }
 
 template <class T>
-__global__ void __launch_bounds__(256) fill_zero(T* __restrict__ p, long n) {
-  for (long k = blockIdx.x * 256L + threadIdx.x; k < n; k += (long)gridDim.x * 256L) p[k] = T(0);
-}
-
-template <class T>
 void enqueue_noalloc_eval(const ss_ctx* c, const void* field, void* grad, hipStream_t s) {
-  const long pitch = c->Nx + 4, plane = pitch * (c->Ny + 4);
-  if (grad) {
-    const long n = (long)c->C * plane;
-    const int nb = (int)std::min<long>(1024, (n + 255) / 256);
-    hipLaunchKernelGGL((fill_zero<T>), dim3(nb), dim3(256), 0, s, (T*)grad, n);
-  }
   PassArgs<T> a;
   std::memset(&a, 0, sizeof(a));
-  // the evaluation pass reads only the source field, here in the caller's layout
+  // the evaluation pass reads only the source field
   a.B.phi[0] = a.B.phi[1] = (T*)field;
-  a.B.pitch = pitch;
-  a.B.plane = plane;
   a.B.Nx = c->Nx;
   a.B.Ny = c->Ny;
   a.cf = coeffs_of(c);
   a.link = Link{c->st, c->st, c->st, nullptr, 0, -1};
   a.partials = c->partials;
-  a.src = (const T*)field;
-  a.out = (T*)grad;
-  a.out_pitch = pitch;
-  a.out_plane = plane;
   a.ntx = c->L.ntx;
   a.nty = c->L.nty;
   a.seg = c->L.seg;
-  Run r;
-  launch_pass<T, kEval>(c, a, r, s);
+  enqueue_eval<T>(c, a, field, grad, s);
 }
 
 }  // namespace
@@ -1386,30 +1373,32 @@ namespace {
 // Observable passes of one context, enqueued on its stream; obs_collect reads them back.
 template <class T>
 void obs_enqueue_t(ss_ctx* c, int nobs) {
-  Bufs<T> B = bufs_of<T>(c);
+  const Bufs<T> B = bufs_of<T>(c);
+  const Coeffs cf = coeffs_of(c);
+  const DevStatus* st = c->st;
+  double* p2 = c->partials + 5L * nobs;
+  int n1 = 5, n2 = 0;
   if (c->theory == SS_THEORY_AH) {
-    hipLaunchKernelGGL((obs_sites<T, kAH>), dim3(nobs), dim3(256), 0, c->stream, B, coeffs_of(c), c->st, c->partials,
-                       nobs);
-    hipLaunchKernelGGL((obs_winding<T>), dim3(1), dim3(256), 0, c->stream, B, c->st);
-    return;
-  }
-  if (c->theory == SS_THEORY_BEC) {
-    hipLaunchKernelGGL((bec_obs<T>), dim3(nobs), dim3(256), 0, c->stream, B, coeffs_of(c), c->st, c->partials, nobs);
-    return;
-  }
-  if (c->theory == SS_THEORY_CM) {
-    // the potential of the current field, for the demagnetising energy
-    if (c->dm.on) {
-      Run r;
-      demag_solve<T, kEval>(c, pass_args<T>(c), r, c->stream);
+    hipLaunchKernelGGL((obs_sites<T, kAH>), dim3(nobs), dim3(256), 0, c->stream, B, cf, st, c->partials);
+  } else if (c->theory == SS_THEORY_BEC) {
+    n1 = 3;
+    hipLaunchKernelGGL((bec_obs<T>), dim3(nobs), dim3(256), 0, c->stream, B, cf, st, c->partials);
+  } else {
+    n2 = 1;
+    if (c->theory == SS_THEORY_CM) {
+      // the potential of the current field, for the demagnetising energy
+      if (c->dm.on) {
+        Run r;
+        demag_solve<T, kEval>(c, pass_args<T>(c), r, c->stream);
+      }
+      hipLaunchKernelGGL((obs_sites<T, kCM>), dim3(nobs), dim3(256), 0, c->stream, B, cf, st, c->partials);
+    } else {
+      hipLaunchKernelGGL((obs_sites<T, kBS>), dim3(nobs), dim3(256), 0, c->stream, B, cf, st, c->partials);
     }
-    hipLaunchKernelGGL((obs_sites<T, kCM>), dim3(nobs), dim3(256), 0, c->stream, B, coeffs_of(c), c->st, c->partials,
-                       nobs);
+    hipLaunchKernelGGL((obs_berg_luscher<T>), dim3(nobs), dim3(256), 0, c->stream, B, st, p2);
   }
-  else
-    hipLaunchKernelGGL((obs_sites<T, kBS>), dim3(nobs), dim3(256), 0, c->stream, B, coeffs_of(c), c->st, c->partials,
-                       nobs);
-  hipLaunchKernelGGL((obs_berg_luscher<T>), dim3(nobs), dim3(256), 0, c->stream, B, c->st, c->partials, nobs);
+  hipLaunchKernelGGL((obs_finalise<T>), dim3(c->theory == SS_THEORY_AH ? 2 : 1), dim3(256), 0, c->stream, B, c->st,
+                     (const double*)c->partials, n1, (const double*)p2, n2, nobs);
 }
 
 int obs_enqueue(ss_ctx* c) {
@@ -1796,6 +1785,7 @@ struct ss_batch {
   int* work;           // [max tiles]
   int* nwork;          // [1]
   int* done_flags;     // [n]
+  Head* heads;         // [n]
   double* partials;    // [4 * max tiles]
   int max_tiles;
   hipGraphExec_t graph;
@@ -1812,6 +1802,7 @@ size_t batch_table_bytes(int n, int max_tiles) {
   b += (size_t)round_up((long)max_tiles * 4, 256);
   b += 256;
   b += (size_t)round_up((long)n * 4, 256);
+  b += (size_t)round_up((long)n * (long)sizeof(Head), 256);
   b += (size_t)round_up((long)max_tiles * 32, 256);
   return b;
 }
@@ -2053,6 +2044,16 @@ void batch_enqueue_apply_arrest(const ss_batch* b, hipStream_t s) {
                        b->C);
 }
 
+// The status heads of all members (synchronises).
+int batch_read_heads(ss_batch* b, std::vector<Head>& heads) {
+  hipLaunchKernelGGL(batch_heads, dim3((b->n + 255) / 256), dim3(256), 0, b->stream, b->st_ptrs, b->n, b->heads);
+  SS_HIP(hipGetLastError());
+  heads.resize(b->n);
+  SS_HIP(hipMemcpyAsync(heads.data(), b->heads, b->n * sizeof(Head), hipMemcpyDeviceToHost, b->stream));
+  SS_HIP(hipStreamSynchronize(b->stream));
+  return SS_OK;
+}
+
 int batch_read_done(ss_batch* b, std::vector<int>& done) {
   hipLaunchKernelGGL(batch_done_flags, dim3((b->n + 255) / 256), dim3(256), 0, b->stream, b->st_ptrs, b->n,
                      b->done_flags);
@@ -2140,6 +2141,7 @@ int ss_batch_create(const char* theory, int n, const ss_instance* inst, int dtyp
   b->work = (int*)t; t += round_up((long)b->max_tiles * 4, 256);
   b->nwork = (int*)t; t += 256;
   b->done_flags = (int*)t; t += round_up((long)n * 4, 256);
+  b->heads = (Head*)t; t += round_up((long)n * (long)sizeof(Head), 256);
   b->partials = (double*)t;
   hipError_t e = hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking);
   if (e != hipSuccess) {
@@ -2243,10 +2245,10 @@ int ss_batch_flow_step(ss_batch* b, int n_steps, ss_step_info* infos) {
   batch_enqueue_check(b, b->stream);
   SS_HIP(hipGetLastError());
   if (infos) {
-    for (int i = 0; i < b->n; ++i) {
-      rc = ss_get_info(b->members[i], &infos[i]);
-      if (rc) return rc;
-    }
+    std::vector<Head> heads;
+    rc = batch_read_heads(b, heads);
+    if (rc) return rc;
+    for (int i = 0; i < b->n; ++i) fill_info(heads[i], &infos[i]);
   }
   return SS_OK;
 }
@@ -2300,10 +2302,11 @@ int ss_batch_minimise(ss_batch* b, const ss_stop* stop, ss_min_info* infos) {
   if (b->integ == SS_INTEG_RK4) batch_enqueue_apply_arrest(b, b->stream);
   else batch_enqueue_settle(b, b->stream);
   int worst = SS_OK;
+  std::vector<Head> heads;
+  rc = batch_read_heads(b, heads);
+  if (rc) return rc;
   for (int i = 0; i < b->n; ++i) {
-    DevStatus d;
-    rc = read_status(b->members[i], &d);
-    if (rc) return rc;
+    const Head& d = heads[i];
     if (infos) {
       fill_info(d, &infos[i].last);
       infos[i].reason = d.done;

@@ -19,7 +19,7 @@
 // every workgroup of the launch that needs the total.
 #pragma once
 
-#include "ss_internal.hpp"
+#include "ss_kernels.hpp"
 
 namespace ss {
 
@@ -400,7 +400,7 @@ __global__ void __launch_bounds__(256) bec_vproj(Bufs<T> B, const DevStatus* __r
 
 // Observables of the current field: {E density, |psi|^2, Re(psi* L_z psi)} summed.
 template <class T>
-__global__ void __launch_bounds__(256) bec_obs(Bufs<T> B, Coeffs cf, DevStatus* st, double* partials, int nlaunch) {
+__global__ void __launch_bounds__(256) bec_obs(Bufs<T> B, Coeffs cf, const DevStatus* st, double* partials) {
   const int cur = int(st->step & 1);
   const T* __restrict__ ph = cur ? B.phi[1] : B.phi[0];
   const double h = cf.h, d1 = 1.0 / (12.0 * h);
@@ -425,7 +425,7 @@ __global__ void __launch_bounds__(256) bec_obs(Bufs<T> B, Coeffs cf, DevStatus* 
     v[1] += rho;
     v[2] += lz;
   }
-  reduce_n_to<3, 256>(v, partials, &st->counter_obs, nlaunch, st->obs);
+  obs_partials(v, partials);
 }
 
 #undef BEC_SITES

@@ -1625,6 +1625,12 @@ static __global__ void batch_arm(DevStatus* const* st, int n, int minimise, doub
   }
 }
 
+// The heads of all batch members in one array.
+static __global__ void batch_heads(DevStatus* const* st, int n, Head* heads) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) heads[i] = load_head(st[i]);
+}
+
 // Collect the stop flags of all batch members (host reads n ints, not n status blocks).
 static __global__ void batch_done_flags(DevStatus* const* st, int n, int* flags) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1657,61 +1663,31 @@ static __global__ void arm_status(DevStatus* st, int minimise, double grad_tol, 
 
 // ---------------------------------------------------------------- observables
 // Sums over interior sites (FP64 from the stored values, first derivatives by
-// eq. (1)), two-level reduction into st->obs[0..4]:
+// eq. (1)), reduced to one set of partials per workgroup; obs_finalise adds them
+// into st->obs (as a launch of its own: with the last workgroup to finish doing it,
+// behind a device-scope fence per workgroup, obs_sites took 30 us on 128^2, now 5):
 //   AH: E density, B, rho = [B W + 2 (P1 Q2 - Q1 P2)]/(2 pi), |r1|^2, r2^2
 //   CM: E density, n.(d_x n x d_y n)
-template <int N, int NT>
-__device__ __forceinline__ void reduce_n_to(double (&v)[N], double* partials, unsigned* counter,
-                                            int nlaunch, double* dst) {
-  constexpr int NW = NT / 64;
-  __shared__ double red[N * NW];
-  __shared__ int last;
-  const int tid = threadIdx.y * blockDim.x + threadIdx.x;
-  const int lane = tid & 63, w = tid >> 6;
+template <int N>
+__device__ __forceinline__ void obs_partials(const double (&v)[N], double* __restrict__ partials) {
+  __shared__ double red[N * 4];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
 #pragma unroll
   for (int k = 0; k < N; ++k) {
     const double x = wave_sum(v[k]);
-    if (lane == 0) red[k * NW + w] = x;
+    if (lane == 0) red[k * 4 + w] = x;
   }
   __syncthreads();
-  if (tid == 0) {
+  if (threadIdx.x == 0)
     for (int k = 0; k < N; ++k) {
       double s = 0.0;
-      for (int j = 0; j < NW; ++j) s += red[k * NW + j];
+      for (int j = 0; j < 4; ++j) s += red[k * 4 + j];
       partials[(long)blockIdx.x * N + k] = s;
     }
-    __threadfence();
-    last = (atomicAdd(counter, 1u) == (unsigned)(nlaunch - 1));
-  }
-  __syncthreads();
-  if (!last) return;
-  __threadfence();
-  double acc[N];
-#pragma unroll
-  for (int k = 0; k < N; ++k) acc[k] = 0.0;
-  for (int b = tid; b < nlaunch; b += NT)
-#pragma unroll
-    for (int k = 0; k < N; ++k) acc[k] += __builtin_nontemporal_load(partials + (long)b * N + k);
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < N; ++k) {
-    const double x = wave_sum(acc[k]);
-    if (lane == 0) red[k * NW + w] = x;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    for (int k = 0; k < N; ++k) {
-      double s = 0.0;
-      for (int j = 0; j < NW; ++j) s += red[k * NW + j];
-      dst[k] = s;
-    }
-    *counter = 0u;
-  }
 }
 
 template <class T, int TH>
-__global__ void __launch_bounds__(256) obs_sites(Bufs<T> B, Coeffs cf, DevStatus* st, double* partials,
-                                                 int nlaunch) {
+__global__ void __launch_bounds__(256) obs_sites(Bufs<T> B, Coeffs cf, const DevStatus* st, double* partials) {
   const int cur = int(st->step & 1);
   const T* __restrict__ ph = B.phi[cur];
   const long nsite = (long)B.Nx * B.Ny;
@@ -1759,14 +1735,14 @@ __global__ void __launch_bounds__(256) obs_sites(Bufs<T> B, Coeffs cf, DevStatus
       v[1] += f[0] * tx + f[1] * ty + f[2] * tz;
     }
   }
-  reduce_n_to<5, 256>(v, partials, &st->counter_obs, nlaunch, st->obs);
+  obs_partials(v, partials);
 }
 
 // Berg-Luescher charge: every plaquette (i, j) .. (i+1, j+1) of the padded
 // lattice, split into triangles (a, b, c) and (a, c, d), each contributing its
-// signed solid angle 2 atan2(a.(b x c), 1 + a.b + b.c + c.a). Sum into st->obs[5].
+// signed solid angle 2 atan2(a.(b x c), 1 + a.b + b.c + c.a).
 template <class T>
-__global__ void __launch_bounds__(256) obs_berg_luscher(Bufs<T> B, DevStatus* st, double* partials, int nlaunch) {
+__global__ void __launch_bounds__(256) obs_berg_luscher(Bufs<T> B, const DevStatus* st, double* partials) {
   const int cur = int(st->step & 1);
   const T* __restrict__ ph = B.phi[cur];
   const int PW = B.Nx + 3, PH = B.Ny + 3;  // plaquettes per row / column
@@ -1790,13 +1766,13 @@ __global__ void __launch_bounds__(256) obs_berg_luscher(Bufs<T> B, DevStatus* st
       v[0] += 2.0 * atan2(num, den);
     }
   }
-  reduce_n_to<1, 256>(v, partials, &st->counter_obs, nlaunch, st->obs + 5);
+  obs_partials(v, partials);
 }
 
 // Phase winding of psi along the ring of outermost interior sites (one
 // workgroup, fixed order), into st->obs[6] (in units of 2 pi).
 template <class T>
-__global__ void __launch_bounds__(256) obs_winding(Bufs<T> B, DevStatus* st) {
+__device__ __forceinline__ void obs_winding(const Bufs<T>& B, DevStatus* st) {
   const int cur = int(st->step & 1);
   const T* __restrict__ ph = B.phi[cur];
   const int Nx = B.Nx, Ny = B.Ny;
@@ -1827,6 +1803,140 @@ __global__ void __launch_bounds__(256) obs_winding(Bufs<T> B, DevStatus* st) {
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
   __syncthreads();
   if (threadIdx.x == 0) st->obs[6] = (red[0] + red[1] + red[2] + red[3]) / (2.0 * pi);
+}
+
+// The observable sums: n1 quantities into st->obs[0 ..] and n2 into st->obs[5 ..]
+// from nlaunch workgroups' partials, in workgroup order (block 0); the winding of an
+// Abelian Higgs field (block 1).
+template <class T>
+__global__ void __launch_bounds__(256) obs_finalise(Bufs<T> B, DevStatus* st, const double* __restrict__ p1, int n1,
+                                                    const double* __restrict__ p2, int n2, int nlaunch) {
+  if (blockIdx.x == 1) {
+    obs_winding(B, st);
+    return;
+  }
+  __shared__ double red[4];
+  for (int k = 0; k < n1 + n2; ++k) {
+    const double* __restrict__ p = k < n1 ? p1 + k : p2 + (k - n1);
+    const int N = k < n1 ? n1 : n2;
+    double acc = 0.0;
+    for (int b = threadIdx.x; b < nlaunch; b += 256) acc += p[(long)b * N];
+    const double x = wave_sum(acc);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
+    __syncthreads();
+    if (threadIdx.x == 0) st->obs[k < n1 ? k : 5 + (k - n1)] = ((red[0] + red[1]) + red[2]) + red[3];
+  }
+}
+
+// ------------------------------------------------------ fields in and out
+// A caller's array is tight (rows of Nx + 4), the flow's rows are padded: two
+// neighbouring elements per thread, a row and column block per workgroup
+// (blockIdx.y strides over the rows of all components). PAIR: the caller's rows
+// start on two-element boundaries, else its elements go one by one.
+template <class T>
+struct Pair {
+  T a, b;
+};
+
+template <class T, class F>
+__device__ __forceinline__ void for_padded_pairs(const Bufs<T>& B, int C, F&& body) {
+  const int W = B.Nx + 4, H = B.Ny + 4;
+  const int i = 2 * (blockIdx.x * 256 + threadIdx.x);
+  if (i >= W) return;
+  for (int r = blockIdx.y; r < C * H; r += gridDim.y) {
+    const int c = r / H, j = r - c * H;
+    body((long)r * W + i, c * B.plane + (long)j * B.pitch + i, i + 1 < W);
+  }
+}
+
+// The current field and (velocity != nullptr) velocity.
+template <class T, bool PAIR>
+__global__ void __launch_bounds__(256) export_field(Bufs<T> B, const DevStatus* st, int C, T* __restrict__ field,
+                                                    T* __restrict__ velocity) {
+  typedef T T2 __attribute__((ext_vector_type(2)));
+  const int cur = int(st->step & 1);
+  const T* __restrict__ ph = cur ? B.phi[1] : B.phi[0];
+  const T* __restrict__ vv = cur ? B.vel[1] : B.vel[0];
+  auto put = [&](T* __restrict__ dst, const T* __restrict__ src, long u, long o, bool two) {
+    const T2 v = *reinterpret_cast<const T2*>(src + o);  // within the row's padding
+    if (PAIR) {
+      *reinterpret_cast<T2*>(dst + u) = v;
+    } else {
+      dst[u] = v.x;
+      if (two) dst[u + 1] = v.y;
+    }
+  };
+  for_padded_pairs(B, C, [&](long u, long o, bool two) {
+    put(field, ph, u, o, two);
+    if (velocity != nullptr) put(velocity, vv, u, o, two);
+  });
+}
+
+// Both field buffers, and (velocity != nullptr) both velocity buffers.
+template <class T, bool PAIR>
+__global__ void __launch_bounds__(256) import_field(Bufs<T> B, int C, const T* __restrict__ field,
+                                                    const T* __restrict__ velocity) {
+  typedef T T2 __attribute__((ext_vector_type(2)));
+  auto put = [&](T* d0, T* d1, const T* __restrict__ src, long u, long o, bool two) {
+    T2 v;
+    if (PAIR) {
+      v = *reinterpret_cast<const T2*>(src + u);
+    } else {
+      v.x = src[u];
+      v.y = two ? src[u + 1] : T(0);
+    }
+    if (PAIR || two) {
+      *reinterpret_cast<T2*>(d0 + o) = v;
+      *reinterpret_cast<T2*>(d1 + o) = v;
+    } else {
+      d0[o] = v.x;
+      d1[o] = v.x;
+    }
+  };
+  for_padded_pairs(B, C, [&](long u, long o, bool two) {
+    put(B.phi[0], B.phi[1], field, u, o, two);
+    if (velocity != nullptr) put(B.vel[0], B.vel[1], velocity, u, o, two);
+  });
+}
+
+// Start from rest: n16 16-byte words (the velocity and stage sets) and m doubles (the
+// demagnetising potential) zeroed, the status reset.
+static __global__ void __launch_bounds__(256) reset_flow(uint4* __restrict__ sets, long n16, double* __restrict__ x,
+                                                         long m, DevStatus* st) {
+  const long t = blockIdx.x * 256L + threadIdx.x, nt = (long)gridDim.x * 256L;
+  for (long k = t; k < n16; k += nt) sets[k] = make_uint4(0u, 0u, 0u, 0u);
+  for (long k = t; k < m; k += nt) x[k] = 0.0;
+  if (blockIdx.x != 0) return;
+  static_assert(sizeof(DevStatus) % 4 == 0, "zeroed word by word");
+  for (int k = threadIdx.x; k < (int)(sizeof(DevStatus) / 4); k += 256) reinterpret_cast<unsigned*>(st)[k] = 0u;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const double inf = __builtin_huge_val();
+    st->E = st->E_prev = st->gmax = inf;
+    st->e_target = -inf;
+  }
+}
+
+// The halo of a caller's gradient array (the evaluation writes its interior).
+template <class T>
+__global__ void __launch_bounds__(256) zero_frame(T* __restrict__ g, int Nx, int Ny, int C) {
+  const int W = Nx + 4, H = Ny + 4, per = 4 * W + 4 * Ny;
+  const long n = (long)C * per;
+  for (long k = blockIdx.x * 256L + threadIdx.x; k < n; k += (long)gridDim.x * 256L) {
+    const int c = (int)(k / per), e = (int)(k - (long)c * per);
+    int j, i;
+    if (e < 4 * W) {
+      const int r = e / W;
+      j = r < 2 ? r : H - 4 + r;
+      i = e - r * W;
+    } else {
+      const int q = e - 4 * W;
+      j = 2 + (q >> 2);
+      i = (q & 3) < 2 ? (q & 3) : W - 4 + (q & 3);
+    }
+    g[((long)c * H + j) * W + i] = T(0);
+  }
 }
 
 // --------------------------------------------------------------- state init
