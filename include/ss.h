@@ -448,7 +448,9 @@ int ss_set_demag_iters(ss_ctx* ctx, int iters_flow, int iters_eval);
 
 /* Tile shapes of the stage kernels. The library carries ss_tile_count()
  * compiled shapes (a workgroup covers TX x TY sites, each thread RY rows of
- * one column); under a fused plan the shape applies to P1. ss_set_tile selects
+ * one column); under a fused plan the shape applies to P1. Tile 0, the default,
+ * stands for 64 x 4 (FP64) or 64 x 8 sites on lattices of at most 128 of its tiles,
+ * and for 64 x 8 on large ones in FP64 and of the one-pass integrators. ss_set_tile selects
  * one for a context. ss_autotune times every plan with every shape over
  * n_steps flow steps of a uniform vacuum on the context's lattice, keeps the
  * fastest pair, writes the mean step times in ms_out (may be NULL, else

@@ -44,7 +44,6 @@ int fail(int code, const std::string& msg) {
       return fail(SS_EHIP, std::string(#call) + ": " + hipGetErrorString(e_));                \
   } while (0)
 
-constexpr int kNumTiles = 4;
 constexpr int kDefaultTile = 0;
 constexpr int kDefaultPlanF32 = SS_PLAN_FUSED;
 static_assert(kTiles[0].TX == kExTX && kTiles[0].TY == kExTY, "the exact-gradient passes use the layout of tile 0");
@@ -82,9 +81,36 @@ void set_tiles(Layout& L, int Nx, int Ny, int tile) {
   L.ntx = (Nx + tc.TX - 1) / tc.TX;
   L.nty = (Ny + tc.TY - 1) / tc.TY;
   L.nlaunch = (int)std::min<long>(round_up((long)L.ntx * L.nty, 8), kMaxGroups);
-  // one unit per workgroup where there are enough tiles, else single tiles
-  L.seg = (int)std::max<long>(1, ((long)L.ntx * L.nty) / L.nlaunch);
-  L.seg = std::min(L.seg, L.nty);
+  L.seg = choose_seg(L.ntx, L.nty, L.nlaunch);
+}
+
+// The compiled shape behind tile 0 of the Euler-Lagrange passes (us per step on
+// 64 x 4 / 64 x 8 / 64 x 16 sites):
+//  - in FP64 64 x 4 with one row per thread, in FP32 64 x 8, where 64 x 16 would give
+//    at most kSmallTiles workgroups, that is where a pass takes as long as one of its
+//    workgroups: velocity Verlet on 128^2 FP64 8.4 / 9.9 / 11.4, on 256^2 FP32 (chiral
+//    magnet, 64 tiles of 64 x 16) - / 10.3 / 10.8; on 512^2 FP32 (256 tiles) - / 12.1 /
+//    11.3. One row per thread is FP64 only: the compiler contracts a single row's
+//    products in another order, which a flow's steps in FP32 carry to 1e-4 of its
+//    velocities; two rows in 128 threads took 11.6 on that 256^2;
+//  - 64 x 8 in FP64 from kWideSitesF64 sites: Abelian Higgs 1024^2 RK4 - / 144 / 150,
+//    2048^2 gradient flow - / 81 / 91, chiral magnet velocity Verlet - / 144 / 170; at
+//    700^2 the two are within 3% of each other, at 512^2 64 x 16 is ahead (chiral
+//    magnet RK4 - / 40.0 / 39.1);
+//  - 64 x 8 for velocity Verlet in FP32, and gradient flow of the chiral magnet,
+//    from kWideSites sites, where shorter units spread better: Abelian Higgs 4096^2
+//    - / 322 / 350, chiral magnet 1000^2 - / 30.7 / 34.5 and 2048^2 - / 100 / 122 (700^2
+//    - / 20.7 / 19.8). Baby Skyrme's, RK4's and the other gradient-flow passes are as
+//    fast or faster on 64 x 16.
+constexpr long kSmallTiles = 128, kWideSites = 800000, kWideSitesF64 = 400000;
+bool small_lattice(int Nx, int Ny) { return (long)((Nx + 63) / 64) * ((Ny + 15) / 16) <= kSmallTiles; }
+
+int default_shape(int theory, int dtype, int integ, int Nx, int Ny) {
+  if (small_lattice(Nx, Ny)) return dtype == SS_F64 ? kSmallShape : 1;
+  if (dtype == SS_F64) return (long)Nx * Ny >= kWideSitesF64 ? 1 : 0;
+  const bool vv = integ == SS_INTEG_VV && (theory == SS_THEORY_AH || theory == SS_THEORY_CM);
+  const bool gf = integ == SS_INTEG_GF && theory == SS_THEORY_CM;
+  return (vv || gf) && (long)Nx * Ny >= kWideSites ? 1 : 0;
 }
 
 Layout make_layout(int C, int Nx, int Ny, int esize) {
@@ -149,7 +175,8 @@ struct ss_ctx {
   double* partials2;  // the other partials
   hipGraphExec_t graph;
   int graph_steps;
-  int tile;
+  int tile;   // as selected
+  int shape;  // the compiled shape it stands for (L is cut for it)
   int plan;   // SS_PLAN_*: how stages 2-4 of a step are launched
   int integ;  // SS_INTEG_*: the flow's integrator
   int vv_form;  // SS_VV_*: how velocity Verlet keeps its state between steps
@@ -174,6 +201,14 @@ struct ss_ctx {
 };
 
 namespace {
+
+// Tile `tile` of a context: the shape it stands for, and the lattice cut for it.
+void apply_tile(ss_ctx* c, int tile) {
+  c->tile = tile;
+  c->shape = tile == 0 && c->grad_mode != SS_GRAD_EXACT
+                 ? default_shape(c->theory, c->dtype, c->integ, c->Nx, c->Ny) : tile;
+  set_tiles(c->L, c->Nx, c->Ny, c->shape);
+}
 
 template <class T>
 Bufs<T> bufs_of(const ss_ctx* c) {
@@ -402,11 +437,10 @@ void launch_lattice_pass(const ss_ctx* c, PassArgs<T> a, Run& r, hipStream_t s) 
     else if (c->theory == SS_THEORY_CM) launch_exact<T, kCM, PASS>(a, groups, s);
     else launch_exact<T, kBS, PASS>(a, groups, s);
   } else {
-    int tile = c->tile;
+    int tile = c->shape;
     if constexpr (fixed_tile(PASS)) {
-      // once per run, or after an arrest: one tile shape (64 x 16) whatever the
-      // context's tile
-      tile = 0;
+      // once per run, or after an arrest: tile 0 whatever the context's tile
+      tile = sizeof(T) == 8 && small_lattice(c->Nx, c->Ny) ? kSmallShape : 0;
       Layout L = c->L;
       set_tiles(L, c->Nx, c->Ny, tile);
       a.ntx = L.ntx;
@@ -459,7 +493,7 @@ void launch_fused(const ss_ctx* c, Run& r, hipStream_t s) {
   const long groups = fused_groups<T>(lt);
   if (L.nlaunch > groups) {
     L.nlaunch = (int)groups;
-    L.seg = (int)std::min<long>(std::max<long>(1, ((long)L.ntx * L.nty) / groups), L.nty);
+    L.seg = choose_seg(L.ntx, L.nty, L.nlaunch);
   }
   a.ntx = L.ntx;
   a.nty = L.nty;
@@ -926,10 +960,10 @@ int ss_create(const char* theory, int Nx, int Ny, double h, const ss_params* par
     if (t >= 0 && t < kNumTiles) c->tile = t;
   }
   if (grad_mode == SS_GRAD_EXACT) c->tile = 0;
-  set_tiles(c->L, Nx, Ny, c->tile);
   c->plan = (grad_mode == SS_GRAD_EL && dtype == SS_F32 && !pb.demag && th != SS_THEORY_BEC) ? kDefaultPlanF32
                                                                                           : SS_PLAN_STAGES;
   c->integ = SS_INTEG_RK4;
+  apply_tile(c, c->tile);
   c->vv_form = SS_VV_AUTO;
   c->ws_total = need;
   std::memset(&c->dm, 0, sizeof(c->dm));
@@ -1271,8 +1305,7 @@ int ss_energy_grad_noalloc(const char* theory, int Nx, int Ny, double h, const s
   c.courant = pb.courant;
   for (int k = 0; k < kNumParams; ++k) c.p[k] = pb.p[k];
   c.stream = (hipStream_t)stream;
-  c.tile = kDefaultTile;
-  set_tiles(c.L, Nx, Ny, c.tile);
+  apply_tile(&c, kDefaultTile);
   if (c.L.nlaunch > kMaxGroups) return fail(SS_ESHAPE, "more workgroup partials than the scratch array holds");
   c.st = (DevStatus*)sp;
   c.partials = (double*)((char*)sp + kScratchStatus);
@@ -1448,8 +1481,7 @@ int ss_set_tile(ss_ctx* c, int tile) {
   if (tile < 0 || tile >= kNumTiles) return fail(SS_EINVAL, "tile index out of range");
   if (c->grad_mode == SS_GRAD_EXACT && tile != 0) return fail(SS_EINVAL, "the exact-gradient passes use tile 0 only");
   SS_HIP(hipStreamSynchronize(c->stream));
-  c->tile = tile;
-  set_tiles(c->L, c->Nx, c->Ny, tile);
+  apply_tile(c, tile);
   if (c->graph) {
     (void)hipGraphExecDestroy(c->graph);
     c->graph = nullptr;
@@ -1483,6 +1515,7 @@ int ss_set_integrator(ss_ctx* c, int integ) {
     return fail(SS_EINVAL, "unknown integrator");
   SS_HIP(hipStreamSynchronize(c->stream));
   c->integ = integ;
+  apply_tile(c, c->tile);
   if (c->graph) {
     (void)hipGraphExecDestroy(c->graph);
     c->graph = nullptr;
@@ -1856,7 +1889,7 @@ int batch_build_tables(ss_batch* b) {
   long tot = 0;
   for (int i = 0; i < b->n; ++i) {
     ss_ctx* c = b->members[i];
-    c->tile = b->tile;
+    c->tile = c->shape = b->tile;  // the batch's launches run on the shape itself
     set_tiles(c->L, c->Nx, c->Ny, b->tile);
     b->ntiles_of[i] = c->L.ntx * c->L.nty;
     tot += b->ntiles_of[i];

@@ -8,9 +8,8 @@
 namespace ss {
 
 // Workgroups of one stage-pass instantiation resident on the whole GPU at
-// once: the runtime's occupancy for one CU, rounded down to a power of two (so
-// units still split evenly over the eight XCD bands), times the CUs. Queried
-// once per instantiation on the first device that launches it.
+// once: the runtime's occupancy for one CU times the CUs. Queried once per
+// instantiation on the first device that launches it.
 template <class T, int TH, int PASS, int TX, int TY, int RY>
 long resident_groups() {
   static const long n = [] {
@@ -22,9 +21,7 @@ long resident_groups() {
       (void)hipGetLastError();  // a failed query must not surface as a launch error
       return kMaxGroups;
     }
-    int p2 = 1;
-    while (2 * p2 <= per_cu) p2 *= 2;
-    return std::min(kMaxGroups, kNumCUs * p2);
+    return std::min(kMaxGroups, kNumCUs * per_cu);
   }();
   return n;
 }
@@ -40,7 +37,7 @@ int launch_cfg(const PassArgs<T>& a, int nlaunch, hipStream_t s) {
     const long r = resident_groups<T, TH, PASS, tc.TX, tc.TY, tc.RY>();
     if (nlaunch > r) {
       nlaunch = (int)r;
-      b.seg = (int)std::min<long>(std::max<long>(1, ((long)a.ntx * a.nty) / nlaunch), a.nty);
+      b.seg = choose_seg(a.ntx, a.nty, nlaunch);
     }
   }
   hipLaunchKernelGGL((stage_pass<T, TH, PASS, tc.TX, tc.TY, tc.RY>), dim3(nlaunch), dim3(tc.TX, tc.TY / tc.RY), 0,
@@ -55,6 +52,8 @@ int launch_tiled(int tile, const PassArgs<T>& a, int nlaunch, hipStream_t s) {
     if (tile == 2) return launch_cfg<T, TH, PASS, 2>(a, nlaunch, s);
     if (tile == 3) return launch_cfg<T, TH, PASS, 3>(a, nlaunch, s);
   }
+  if constexpr (sizeof(T) == 8)
+    if (tile == kSmallShape) return launch_cfg<T, TH, PASS, kSmallShape>(a, nlaunch, s);
   return launch_cfg<T, TH, PASS, 0>(a, nlaunch, s);
 }
 

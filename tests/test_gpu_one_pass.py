@@ -289,3 +289,34 @@ def test_split_runs_keep_the_oracle_arrests(ss, orc, integ):
     assert total > 0
     assert np.abs(_np(s.get_field()) - phi_r).max() <= 1e-10 * np.abs(phi_r).max()
     s.close()
+
+
+# lattices on either side of each rule of the default tile's shape: 128 tiles of
+# 64 x 16 sites (511 x 253), 135 (555 x 230), and 400000 sites (FP64) and 800000
+# (FP32); odd sizes, so that the last tiles and the last units are partial
+DEFAULT_TILE_SHAPES = [("f64", 511, 253), ("f32", 511, 253), ("f64", 555, 230), ("f32", 555, 230),
+                       ("f64", 1291, 307), ("f64", 1291, 311), ("f32", 1291, 617), ("f32", 1291, 623)]
+
+
+@pytest.mark.parametrize("theory,integ", [(AH, "vv"), (AH, "gf"), (AH, "rk4"), (CM, "vv"), (CM, "gf"), (CM, "rk4")])
+@pytest.mark.parametrize("dtype,Nx,Ny", DEFAULT_TILE_SHAPES)
+def test_default_tile_over_lattice_sizes(ss, orc, dtype, Nx, Ny, theory, integ):
+    """The default tile's flow over the sizes where its compiled shape changes,
+    every site against the oracle."""
+    h, n = 0.2, 3
+    print(f"[case] default tile {theory} {integ} {dtype} {Nx}x{Ny}", flush=True)
+    f = _field(theory, Nx, Ny, h, seed=Nx + Ny)
+    if dtype == "f32":
+        f = f.astype(np.float32).astype(np.float64)
+    s = ss.Solver(theory, Nx, Ny, h, _params(theory), dtype=dtype)
+    s.set_integrator(integ)
+    s.set_field(f)
+    info = s.flow_step(n)
+    phi, vel = (_np(x) for x in s.get_field(velocity=True))
+    phi_r, v_r, _, na_r = orc.flow(theory, f, np.zeros_like(f), h, _params(theory), n, scheme=integ)
+    rel = 1e-11 if dtype == "f64" else 1e-5
+    assert np.abs(phi - phi_r).max() <= rel * np.abs(phi_r).max()
+    assert np.abs(vel - v_r).max() <= rel * max(np.abs(phi_r).max(), 1.0)
+    assert info["step"] == n and info["n_arrests"] == na_r
+    assert info["energy"] == pytest.approx(orc.energy(theory, phi, h, _params(theory)), rel=1e-12, abs=1e-12)
+    s.close()
