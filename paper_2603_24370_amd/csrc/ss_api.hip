@@ -300,7 +300,12 @@ void dm_vcycle(const ss_ctx::Demag& d, int l, const DevStatus* skip, hipStream_t
   if (dm_is_small(d, l)) {
     // this level and the coarser ones in one workgroup, in LDS
     DmHierarchy H;
-    for (int k = 0; k < d.nlev; ++k) H.lv[k] = d.lv[k];
+    int off = 0;
+    for (int k = 0; k < d.nlev; ++k) {
+      H.lv[k] = d.lv[k];
+      H.off[k] = off;
+      if (k >= l) off += 3 * (d.lv[k].Nx + 4) * (d.lv[k].Ny + 4);
+    }
     H.nlev = d.nlev;
     H.cinv = d.cinv;
     H.cn = d.cn;
@@ -817,6 +822,7 @@ size_t demag_region(int Nx, int Ny, double h, char* base, ss_ctx::Demag* d) {
     lv.Ny = ny;
     lv.pitch = nx + 4;
     lv.h = hl;
+    lv.lap = 1.0 / (12.0 * hl * hl);
     if (nlev == 0) {
       double* v[6];
       for (double*& p : v) p = (double*)take(pb);

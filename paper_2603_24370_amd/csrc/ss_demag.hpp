@@ -25,7 +25,7 @@
 // microsecond of memory traffic), so the solve is cut into as few as its global
 // dependencies allow: two per large level and V-cycle, one for the small levels,
 // two per iteration for conjugate gradients, whose update also starts the next
-// V-cycle. Two iterations on 512^2: 23 launches (35 with smoothing, restriction,
+// V-cycle. Two iterations on 512^2: 22 launches (36 with smoothing, restriction,
 // dot product, direction and operator apart).
 #pragma once
 
@@ -48,6 +48,7 @@ struct DmLevel {
   int Nx, Ny;
   long pitch;
   double h;
+  double lap;  // 1 / (12 h^2), the factor of eq. (2)
 };
 
 // Level-0 vectors of conjugate gradients, the reduction partials and the scalar
@@ -68,11 +69,11 @@ __device__ __forceinline__ bool dm_skip(const DevStatus* st) { return st != null
 __device__ __forceinline__ long dm_at(const DmLevel& L, int j, int i) { return (long)(j + 2) * L.pitch + (i + 2); }
 
 // Laplace_h of a padded plane at interior site (j, i): eq. (2) along both axes.
-__device__ __forceinline__ double dm_lap(const double* __restrict__ x, long p, int j, int i, double h) {
+__device__ __forceinline__ double dm_lap(const double* __restrict__ x, long p, int j, int i, double lap) {
   const double* c = x + (long)(j + 2) * p + (i + 2);
   const double sx = -(c[-2] + c[2]) + 16.0 * (c[-1] + c[1]);
   const double sy = -(c[-2 * p] + c[2 * p]) + 16.0 * (c[-p] + c[p]);
-  return (sx + sy - 60.0 * c[0]) / (12.0 * h * h);
+  return (sx + sy - 60.0 * c[0]) * lap;
 }
 
 #define DM_SITES(L)                                                                        \
@@ -94,7 +95,7 @@ static __global__ void __launch_bounds__(256) dm_coarse_solve(DmLevel L, const D
     for (long k = threadIdx.x; k < n; k += 256) {
       const int j = (int)(k / L.Nx), i = (int)(k - (long)j * L.Nx);
       const long o = dm_at(L, j, i);
-      dst[o] = src[o] - s * (L.rhs[o] - dm_lap(src, L.pitch, j, i, L.h));
+      dst[o] = src[o] - s * (L.rhs[o] - dm_lap(src, L.pitch, j, i, L.lap));
     }
     __syncthreads();
   }
@@ -122,11 +123,15 @@ __device__ __forceinline__ double dm_prolong_at(const DmLevel& C, const double* 
 // From the first level whose planes and those of every coarser level fit in
 // kDmSmallLds bytes, the V-cycle down to the coarsest level and back up runs in one
 // workgroup of kDmSmallThreads on LDS copies of those planes, phase by phase with a
-// barrier between phases, in the arithmetic of the per-level launches. A wave walks
-// the rows of a level, its lanes the columns, so no phase divides. The level's rhs is
-// read from global memory at the start and psi written back at the end (with the r.z
-// partial where it is level 0). From 32^2 down 7 us (256 threads, a division per
-// site, the smoothing sweeps from zero computed as sweeps: 17-24 us).
+// barrier between phases, in the arithmetic of the per-level launches. It is a chain of
+// some ten phases per level, each as long as its longest thread, so a thread's sites
+// come without a division (rows of lanes as wide as the level, a power of two, so that
+// a narrow level fills the lanes too) and the operator's factor is a product. The
+// level's rhs is read from global memory at the start and psi written back at the end
+// (with the r.z partial where it is level 0). From 32^2 down 12.5 us; with whole waves
+// to a row, a division in the operator and the sweep from zero as a phase of its own
+// 20.7, and on narrow levels (14 x 156) several times that. From 64^2 down, which
+// 160 KB would hold, 24.4 us: more than the 9 of the two launches that it saves.
 constexpr int kDmSmallThreads = 1024;
 constexpr int kDmSmallLds = 64 * 1024;
 
@@ -137,6 +142,7 @@ struct DmHierarchy {
   // numbered row-major over the interior), or cn = 0 for Jacobi sweeps there
   const double* cinv;
   int cn;
+  int off[kDmMaxLevels];  // a level's three planes in LDS, from the first small level's
 };
 
 // LDS bytes of levels l .. nlev - 1 (three padded planes each)
@@ -158,11 +164,47 @@ __device__ __forceinline__ double dm_block_sum(double v, double* red) {
   return s;
 }
 
-// Sum of n partials by a workgroup of 256, in a fixed order.
-__device__ __forceinline__ double dm_partials(const double* __restrict__ part, int n, double* red) {
-  double acc = 0.0;
-  for (int k = threadIdx.x; k < n; k += 256) acc += part[k];
-  return dm_block_sum(acc, red);
+// Sums of n[m] partials part[m] by a workgroup of 256, each in a fixed order, for every
+// thread. The loads of four strides of every sum are in flight together: one after the
+// other, the 1024 partials of a dot product on 512^2 cost their launch 2-3 us. red: 4 N
+// doubles that nothing else uses.
+template <int N>
+__device__ __forceinline__ void dm_partials(const double* const (&part)[N], const int (&n)[N], double (&v)[N],
+                                            double* red) {
+  constexpr int U = 4;
+  int top = 0;
+#pragma unroll
+  for (int m = 0; m < N; ++m) {
+    v[m] = 0.0;
+    top = n[m] > top ? n[m] : top;
+  }
+  for (int k0 = 0; k0 < top; k0 += 256 * U) {
+    double p[N][U];
+#pragma unroll
+    for (int m = 0; m < N; ++m)
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = k0 + 256 * u + threadIdx.x;
+        p[m][u] = part[m][k < n[m] ? k : 0];
+      }
+#pragma unroll
+    for (int m = 0; m < N; ++m)
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (k0 + 256 * u + (int)threadIdx.x < n[m]) v[m] += p[m][u];
+  }
+#pragma unroll
+  for (int m = 0; m < N; ++m) {
+    v[m] = wave_sum(v[m]);
+    if ((threadIdx.x & 63) == 0) red[4 * m + (threadIdx.x >> 6)] = v[m];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < N; ++m) {
+    v[m] = 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[m] += red[4 * m + k];
+  }
 }
 
 static __global__ void __launch_bounds__(kDmSmallThreads) dm_vcycle_small(DmHierarchy H, int l0,
@@ -172,48 +214,70 @@ static __global__ void __launch_bounds__(kDmSmallThreads) dm_vcycle_small(DmHier
   extern __shared__ double smem[];
   __shared__ double red[kDmSmallThreads / 64];
   const int last = H.nlev - 1;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  constexpr int NWV = kDmSmallThreads / 64;
-  // the LDS copy of level l (its planes follow those of levels l0 .. l - 1); a
-  // value built per use, so that no array of levels is indexed at run time
+  // the LDS copy of level l, a value built per use, so that no array of levels is
+  // indexed at run time
   auto lds_level = [&](int l) {
-    int off = 0;
-    for (int k = l0; k < l; ++k) off += 3 * (H.lv[k].Nx + 4) * (H.lv[k].Ny + 4);
     DmLevel L = H.lv[l];
     const int pl = (L.Nx + 4) * (L.Ny + 4);
-    L.psi = smem + off;
-    L.tmp = smem + off + pl;
-    L.rhs = smem + off + 2 * pl;
+    L.psi = smem + H.off[l];
+    L.tmp = L.psi + pl;
+    L.rhs = L.tmp + pl;
     return L;
   };
-  // body(j, i, o) for every interior site of a level, o its offset in a plane
+  // body(j, i, o) for every interior site of a level, o its offset in a plane: 2^w
+  // lanes, up to a wave, along a row
   auto sites = [&](const DmLevel& L, auto&& body) {
-    for (int j = wave; j < L.Ny; j += NWV)
-      for (int i = lane; i < L.Nx; i += 64) body(j, i, (j + 2) * (int)L.pitch + i + 2);
+    const int w = L.Nx > 32 ? 6 : L.Nx > 16 ? 5 : L.Nx > 8 ? 4 : 3;
+    for (int j = threadIdx.x >> w; j < L.Ny; j += kDmSmallThreads >> w)
+      for (int i = threadIdx.x & ((1 << w) - 1); i < L.Nx; i += 64) body(j, i, (j + 2) * (int)L.pitch + i + 2);
   };
   auto jacobi = [&](const DmLevel& L, const double* src, double* dst) {
     const double s = kDmOmega * L.h * L.h / 5.0;
-    sites(L, [&](int j, int i, int o) { dst[o] = src[o] - s * (L.rhs[o] - dm_lap(src, L.pitch, j, i, L.h)); });
+    sites(L, [&](int j, int i, int o) { dst[o] = src[o] - s * (L.rhs[o] - dm_lap(src, L.pitch, j, i, L.lap)); });
     __syncthreads();
   };
-  // every plane zero (halos included) before the interior of level l0 is read in
-  const int total = (int)(dm_small_bytes(H.lv, H.nlev, l0) / 8);
-  for (int k = threadIdx.x; k < total; k += kDmSmallThreads) smem[k] = 0.0;
-  __syncthreads();
   {
+    // every plane zero, halos included, but the first level's rhs, whose loads are
+    // issued before that
     const DmLevel G = H.lv[l0], L0 = lds_level(l0);
-    sites(G, [&](int, int, int o) { L0.rhs[o] = G.rhs[o]; });
+    const int pl = (G.Nx + 4) * (G.Ny + 4), total = (int)(dm_small_bytes(H.lv, H.nlev, l0) / 8);
+    const int row = (int)G.pitch;
+    auto interior = [&](int k) {
+      const int j = k / row - 2, i = k - (j + 2) * row - 2;
+      return i >= 0 && i < G.Nx && j >= 0 && j < G.Ny ? G.rhs[k] : 0.0;
+    };
+    constexpr int Q = 2;
+    double v[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int k = threadIdx.x + q * kDmSmallThreads;
+      v[q] = k < pl ? interior(k) : 0.0;
+    }
+    for (int k = threadIdx.x; k < 2 * pl; k += kDmSmallThreads) smem[k] = 0.0;
+    for (int k = 3 * pl + threadIdx.x; k < total; k += kDmSmallThreads) smem[k] = 0.0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int k = threadIdx.x + q * kDmSmallThreads;
+      if (k < pl) L0.rhs[k] = v[q];
+    }
+    for (int k = threadIdx.x + Q * kDmSmallThreads; k < pl; k += kDmSmallThreads) L0.rhs[k] = interior(k);
     __syncthreads();
   }
   for (int l = l0; l < last; ++l) {
     const DmLevel F = lds_level(l);
     const DmLevel C = lds_level(l + 1);
-    // two sweeps from zero: the first is -s rhs
+    // two sweeps from zero, the first of which is x = -s rhs; rhs is read as it is
+    // needed for it (its halo is zero)
     const double s = kDmOmega * F.h * F.h / 5.0;
-    sites(F, [&](int, int, int o) { F.tmp[o] = -(s * F.rhs[o]); });
+    sites(F, [&](int, int, int o) {
+      const int p = (int)F.pitch;
+      auto x = [&](int k) { return -(s * F.rhs[o + k]); };
+      const double sx = -(x(-2) + x(2)) + 16.0 * (x(-1) + x(1));
+      const double sy = -(x(-2 * p) + x(2 * p)) + 16.0 * (x(-p) + x(p));
+      F.psi[o] = x(0) - s * (F.rhs[o] - (sx + sy - 60.0 * x(0)) * F.lap);
+    });
     __syncthreads();
-    jacobi(F, F.tmp, F.psi);
-    sites(F, [&](int j, int i, int o) { F.tmp[o] = F.rhs[o] - dm_lap(F.psi, F.pitch, j, i, F.h); });
+    sites(F, [&](int j, int i, int o) { F.tmp[o] = F.rhs[o] - dm_lap(F.psi, F.pitch, j, i, F.lap); });
     __syncthreads();
     sites(C, [&](int J, int I, int o) {
       // rows and columns outside the level carry the zeros of the halo
@@ -301,7 +365,7 @@ __global__ void __launch_bounds__(256) dm_down(DmLevel F, DmLevel C, DmVecs D, i
   __shared__ double x1[NB];
   __shared__ double x2[NS];
   __shared__ double res[NR];
-  __shared__ double red[4];
+  __shared__ double red[8];
   const double s = kDmOmega * F.h * F.h / 5.0;
   const int ntx = (F.Nx + kDmTile - 1) / kDmTile;
   const int nt = dm_tiles(F);
@@ -331,10 +395,10 @@ __global__ void __launch_bounds__(256) dm_down(DmLevel F, DmLevel C, DmVecs D, i
       vd = D.d[cur][oo];
     }
     if (UPDATE && first) {
-      const double rz = dm_partials(D.part, nrz, red);
-      const double dad = dm_partials(D.pmv, nmv, red);
-      alpha = dad > 0.0 ? rz / dad : 0.0;
-      if (blockIdx.x == 0 && threadIdx.x == 0) D.sc[0] = rz;
+      double v[2];  // r.z, d.Ad
+      dm_partials({D.part, D.pmv}, {nrz, nmv}, v, red);
+      alpha = v[1] > 0.0 ? v[0] / v[1] : 0.0;
+      if (blockIdx.x == 0 && threadIdx.x == 0) D.sc[0] = v[0];
       first = false;
     }
 #pragma unroll
@@ -357,7 +421,7 @@ __global__ void __launch_bounds__(256) dm_down(DmLevel F, DmLevel C, DmVecs D, i
       if (k < NS) {
         const int ly = k / kDmSF, lx = k - ly * kDmSF;
         const int o = (ly + 2) * kDmBF + lx + 2;
-        x2[k] = inside(y0 - 3 + ly, x0 - 3 + lx) ? x1[o] - s * (b[o] - dm_lap(x1, kDmBF, ly, lx, F.h)) : 0.0;
+        x2[k] = inside(y0 - 3 + ly, x0 - 3 + lx) ? x1[o] - s * (b[o] - dm_lap(x1, kDmBF, ly, lx, F.lap)) : 0.0;
       }
     }
     __syncthreads();
@@ -368,7 +432,7 @@ __global__ void __launch_bounds__(256) dm_down(DmLevel F, DmLevel C, DmVecs D, i
       if (k < NR) {
         const int ly = k / kDmRF, lx = k - ly * kDmRF;
         res[k] = inside(y0 - 1 + ly, x0 - 1 + lx)
-                     ? b[(ly + 4) * kDmBF + lx + 4] - dm_lap(x2, kDmSF, ly, lx, F.h) : 0.0;
+                     ? b[(ly + 4) * kDmBF + lx + 4] - dm_lap(x2, kDmSF, ly, lx, F.lap) : 0.0;
       }
     }
     __syncthreads();
@@ -458,14 +522,14 @@ __global__ void __launch_bounds__(256) dm_up(DmLevel F, DmLevel C, const double*
       if (k < NB) {
         const int ly = k / kDmTB, lx = k - ly * kDmTB;
         b[k] = inside(y0 - 2 + ly, x0 - 2 + lx)
-                   ? a[(ly + 2) * kDmTA + (lx + 2)] - s * (r[k] - dm_lap(a, kDmTA, ly, lx, F.h)) : 0.0;
+                   ? a[(ly + 2) * kDmTA + (lx + 2)] - s * (r[k] - dm_lap(a, kDmTA, ly, lx, F.lap)) : 0.0;
       }
     }
     __syncthreads();
     const int ly = threadIdx.x / kDmTile, lx = threadIdx.x - ly * kDmTile;
     if (inside(y0 + ly, x0 + lx)) {
       const int o = (ly + 2) * kDmTB + (lx + 2);
-      const double z = b[o] - s * (r[o] - dm_lap(b, kDmTB, ly, lx, F.h));
+      const double z = b[o] - s * (r[o] - dm_lap(b, kDmTB, ly, lx, F.lap));
       F.psi[dm_at(F, y0 + ly, x0 + lx)] = z;
       if (DOT) rz -= r[o] * z;
     }
@@ -486,7 +550,7 @@ static __global__ void __launch_bounds__(256) dm_direction(DmLevel L0, DmVecs D,
   if (dm_skip(st)) return;
   constexpr int NB = kDmTB * kDmTB, QB = (NB + 255) / 256;
   __shared__ double b[NB];
-  __shared__ double red[4];
+  __shared__ double red[4], redp[4];
   const int ntx = (L0.Nx + kDmTile - 1) / kDmTile;
   const int nt = dm_tiles(L0);
   auto inside = [&](int j, int i) { return j >= 0 && j < L0.Ny && i >= 0 && i < L0.Nx; };
@@ -505,8 +569,10 @@ static __global__ void __launch_bounds__(256) dm_direction(DmLevel L0, DmVecs D,
       vd[q] = (!first && in) ? D.d[cur ^ 1][dm_at(L0, j, i)] : 0.0;
     }
     if (head) {
-      const double rz = dm_partials(D.part, nrz, red), last = D.sc[0];
-      beta = last == 0.0 ? 0.0 : rz / last;
+      double v[1];
+      const double last = D.sc[0];
+      dm_partials({D.part}, {nrz}, v, redp);
+      beta = last == 0.0 ? 0.0 : v[0] / last;
       head = false;
     }
 #pragma unroll
@@ -518,7 +584,7 @@ static __global__ void __launch_bounds__(256) dm_direction(DmLevel L0, DmVecs D,
     const int ly = threadIdx.x / kDmTile, lx = threadIdx.x - ly * kDmTile;
     if (inside(y0 + ly, x0 + lx)) {
       const double d = b[(ly + 2) * kDmTB + lx + 2];
-      const double ad = -dm_lap(b, kDmTB, ly, lx, L0.h);
+      const double ad = -dm_lap(b, kDmTB, ly, lx, L0.lap);
       const long o = dm_at(L0, y0 + ly, x0 + lx);
       D.d[cur][o] = d;
       D.Ad[o] = ad;
@@ -535,11 +601,11 @@ static __global__ void __launch_bounds__(256) dm_direction(DmLevel L0, DmVecs D,
 static __global__ void __launch_bounds__(256) dm_update(DmLevel L0, DmVecs D, int cur, int more, int nrz, int nmv,
                                                         const DevStatus* st) {
   if (dm_skip(st)) return;
-  __shared__ double red[4];
-  const double rz = dm_partials(D.part, nrz, red);
-  const double dad = dm_partials(D.pmv, nmv, red);
-  const double alpha = dad > 0.0 ? rz / dad : 0.0;
-  if (blockIdx.x == 0 && threadIdx.x == 0) D.sc[0] = rz;
+  __shared__ double red[8];
+  double v[2];  // r.z, d.Ad
+  dm_partials({D.part, D.pmv}, {nrz, nmv}, v, red);
+  const double alpha = v[1] > 0.0 ? v[0] / v[1] : 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) D.sc[0] = v[0];
   DM_SITES(L0) {
     const int j = (int)(k_ / L0.Nx), i = (int)(k_ - (long)j * L0.Nx);
     const long o = dm_at(L0, j, i);
@@ -559,11 +625,24 @@ template <class T, int PASS>
 __global__ void __launch_bounds__(256) dm_begin(Bufs<T> B, Coeffs cf, Link link, const T* __restrict__ src,
                                                 DmLevel L0, DmVecs D) {
   __shared__ double red[12];
-
   constexpr int NB = kDmTB * kDmTB, QB = (NB + 255) / 256;
   __shared__ T s1[NB];
   __shared__ T s2[NB];
   __shared__ double xs[NB];
+  const int ntx = (L0.Nx + kDmTile - 1) / kDmTile;
+  const int nt = dm_tiles(L0);
+  // a tile's potential; the first tile's while the test is taken
+  double xv[QB];
+  auto load_x = [&](int t) {
+#pragma unroll
+    for (int q = 0; q < QB; ++q) {
+      const int k = threadIdx.x + 256 * q;
+      const int ly = k / kDmTB, lx = k - ly * kDmTB;
+      const int j = (t / ntx) * kDmTile - 2 + ly, i = (t % ntx) * kDmTile - 2 + lx;
+      xv[q] = k < NB && j >= 0 && j < L0.Ny && i >= 0 && i < L0.Nx ? D.x[dm_at(L0, j, i)] : 0.0;
+    }
+  };
+  load_x(blockIdx.x);
   Head hd = {};
   if (PASS == kEval) hd.step = link.st->step;
   else hd = resolve(link, cf.h * cf.h, threadIdx.x, red);
@@ -582,9 +661,8 @@ __global__ void __launch_bounds__(256) dm_begin(Bufs<T> B, Coeffs cf, Link link,
   const T* __restrict__ vv = cur ? B.vel[1] : B.vel[0];
   const T* __restrict__ aa = ONEPASS ? (cur ? B.a2 : B.a1) : (PASS == kP3) ? B.a1 : B.a2;
   const double c1 = 1.0 / (12.0 * L0.h);
-  const int ntx = (L0.Nx + kDmTile - 1) / kDmTile;
-  const int nt = dm_tiles(L0);
   for (int t = blockIdx.x; t < nt; t += gridDim.x) {
+    if (t != (int)blockIdx.x) load_x(t);
     const int y0 = (t / ntx) * kDmTile, x0 = (t % ntx) * kDmTile;
 #pragma unroll
     for (int q = 0; q < QB; ++q) {
@@ -593,7 +671,6 @@ __global__ void __launch_bounds__(256) dm_begin(Bufs<T> B, Coeffs cf, Link link,
       const int ly = k / kDmTB, lx = k - ly * kDmTB;
       const int j = y0 - 2 + ly, i = x0 - 2 + lx;  // the padded lattice ends at N + 1
       T S[3] = {T(0), T(0), T(0)};
-      double xv = 0.0;
       if (j <= L0.Ny + 1 && i <= L0.Nx + 1) {
         const long o = (long)(j + 2) * B.pitch + (i + 2);
         const bool in = j >= 0 && j < L0.Ny && i >= 0 && i < L0.Nx;
@@ -612,11 +689,10 @@ __global__ void __launch_bounds__(256) dm_begin(Bufs<T> B, Coeffs cf, Link link,
           S[0] *= inv;
           S[1] *= inv;
         }
-        if (in) xv = D.x[dm_at(L0, j, i)];
       }
       s1[k] = S[0];
       s2[k] = S[1];
-      xs[k] = xv;
+      xs[k] = xv[q];
     }
     __syncthreads();
     const int ly = threadIdx.x / kDmTile, lx = threadIdx.x - ly * kDmTile;
@@ -627,7 +703,7 @@ __global__ void __launch_bounds__(256) dm_begin(Bufs<T> B, Coeffs cf, Link link,
       const double dx = c1 * (((double)p1[-2] - (double)p1[2]) + 8.0 * ((double)p1[1] - (double)p1[-1]));
       const double dy = c1 * (((double)p2[-2 * kDmTB] - (double)p2[2 * kDmTB]) +
                               8.0 * ((double)p2[kDmTB] - (double)p2[-kDmTB]));
-      const double r = -(dx + dy) + dm_lap(xs, kDmTB, ly, lx, L0.h);
+      const double r = -(dx + dy) + dm_lap(xs, kDmTB, ly, lx, L0.lap);
       D.rhs[0][dm_at(L0, j, i)] = -r;
     }
     __syncthreads();

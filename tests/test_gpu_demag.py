@@ -111,6 +111,13 @@ def test_demag_energy_and_gradient(ss, orc, dtype, dmi, shape):
     s.close()
 
 
+# the small levels' rows are 2^w lanes wide, w by the level's width: widths around the
+# powers of two, lattices far longer than wide, and a coarsest level that is swept
+@pytest.mark.parametrize("shape", [(9, 40), (17, 130), (33, 260), (65, 30), (27, 312), (312, 27), (45, 525)])
+def test_demag_on_narrow_lattices(ss, orc, shape):
+    test_demag_energy_and_gradient(ss, orc, "f64", "bulk", shape)
+
+
 def test_demag_solver_converges_geometrically(ss, orc):
     """The energy of a fresh context's first evaluation with k iterations (from a
     zero potential) approaches the oracle's: the error falls by at least 10^3 from
