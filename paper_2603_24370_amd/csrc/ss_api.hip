@@ -261,6 +261,7 @@ struct Run {
   int kind = -1;   // finalise_kind of the pending test, or -1
   int groups = 0;  // its partials
   int second = 0;  // they are in c->partials2
+  int bec_end = kBecNone;  // what the last BEC step leaves to be done
 };
 
 double* run_partials(const ss_ctx* c, int second) { return second ? c->partials2 : c->partials; }
@@ -279,8 +280,25 @@ Link take_link(const ss_ctx* c, Run& r) {
   return L;
 }
 
-// The status in c->st.
+template <class T>
+BecBufs<T> bec_bufs(const ss_ctx* c) {
+  return BecBufs<T>{(T*)c->bec_S, (T*)c->bec_G, c->bec_part, c->bec_sc, c->bec_ps, c->bec_pg};
+}
+
+template <class T>
+void launch_bec_end(const ss_ctx* c, const DevStatus* st, int end, hipStream_t s) {
+  hipLaunchKernelGGL((bec_end<T>), dim3(kBecGroups), dim3(256), 0, s, bufs_of<T>(c), coeffs_of(c), st, bec_bufs<T>(c),
+                     end);
+}
+
+// The status in c->st, and a BEC's last step ended.
 void settle(const ss_ctx* c, Run& r, hipStream_t s) {
+  if (r.bec_end != kBecNone) {
+    const DevStatus* st = r.alt ? c->alt : c->st;
+    if (c->dtype == SS_F32) launch_bec_end<float>(c, st, r.bec_end, s);
+    else launch_bec_end<double>(c, st, r.bec_end, s);
+    r.bec_end = kBecNone;
+  }
   if (r.kind < 0 && !r.alt) return;
   Link L = take_link(c, r);
   L.out = c->st;
@@ -368,34 +386,34 @@ void demag_solve(const ss_ctx* c, const PassArgs<T>& a, Run& run, hipStream_t s)
 }
 
 // A BEC pass (RK4 stages, the one-pass steps, the check, the prime pass and the
-// evaluation) in three launches: the stage point and its norm partials; its scale
-// to the atom number, G and the partials for mu; mu, the force and the pass's
-// update. P4 ends with the step's constraint, velocity Verlet with the projection
-// of v', a reducing pass with the status update.
+// evaluation): the stage point, unless the stage before has formed it; its scale to
+// the atom number and G; the force and the pass's update.
 template <class T, int PASS>
-void bec_pass(const ss_ctx* c, const PassArgs<T>& a, hipStream_t s) {
-  BecBufs<T> W;
-  W.S = (T*)c->bec_S;
-  W.G = (T*)c->bec_G;
-  W.part = c->bec_part;
-  W.sc = c->bec_sc;
-  W.ps = c->bec_ps;
-  W.pg = c->bec_pg;
-  const dim3 g(kBecGroups), b(256), b1(256);
-  hipLaunchKernelGGL((bec_stage<T, PASS>), g, b, 0, s, a.B, a.cf, (const DevStatus*)c->st, a.src, W);
-  hipLaunchKernelGGL((bec_grad<T, PASS>), g, b, 0, s, a.B, a.cf, (const DevStatus*)c->st, W);
-  hipLaunchKernelGGL((bec_apply<T, PASS>), g, b, 0, s, a.B, a.cf, (const DevStatus*)c->st, W, (const double*)W.sc,
-                     a.out, a.out_pitch, a.out_plane);
-  if constexpr (PASS == kP4 || PASS == kVVA) {
-    hipLaunchKernelGGL(bec_fix_scalars, dim3(1), b1, 0, s, (const double*)W.part, W.sc, a.cf,
-                       (const DevStatus*)c->st);
-    if constexpr (PASS == kP4)
-      hipLaunchKernelGGL((bec_fix<T>), g, b, 0, s, a.B, (const DevStatus*)c->st, (const double*)W.sc);
-    else
-      hipLaunchKernelGGL((bec_vproj<T>), g, b, 0, s, a.B, (const DevStatus*)c->st, (const double*)W.sc);
+void bec_pass(const ss_ctx* c, const PassArgs<T>& a, Run& r, hipStream_t s) {
+  const BecBufs<T> W = bec_bufs<T>(c);
+  const dim3 g(kBecGroups), b(256);
+  auto link = [&] { return PASS == kEval ? a.link : take_link(c, r); };
+  if constexpr (PASS != kP2 && PASS != kP3 && PASS != kP4) {
+    constexpr int STAGE = PASS == kEval || advances_first(PASS) ? PASS : kP1;  // kP1: the current field
+    hipLaunchKernelGGL((bec_stage<T, STAGE>), g, b, 0, s, a.B, a.cf, link(), a.src, W, r.bec_end);
+    if (PASS != kEval) r.bec_end = kBecNone;
   }
-  if constexpr (reduces(PASS))
-    hipLaunchKernelGGL((bec_finalise<PASS>), dim3(1), b1, 0, s, c->st, (const double*)W.part, (const double*)W.sc);
+  hipLaunchKernelGGL((bec_grad<T, PASS>), g, b, 0, s, a.B, a.cf, link(), W);
+  double* partials = a.partials;
+  if constexpr (PASS != kEval && reduces(PASS)) {
+    r.second ^= 1;
+    partials = run_partials(c, r.second);
+  }
+  hipLaunchKernelGGL((bec_apply<T, PASS>), g, b, 0, s, a.B, a.cf, link(), W, partials, a.out, a.out_pitch,
+                     a.out_plane);
+  if constexpr (PASS == kEval) {
+    hipLaunchKernelGGL(eval_finalise, dim3(1), b, 0, s, a.link.st, (const double*)partials, kBecGroups, a.cf.h);
+  } else if constexpr (reduces(PASS)) {
+    r.kind = finalise_kind(PASS);
+    r.groups = kBecGroups;
+  }
+  if constexpr (PASS == kP4) r.bec_end = kBecScale;
+  if constexpr (PASS == kVVA) r.bec_end = kBecProject;
 }
 
 template <class T, int PASS>
@@ -409,12 +427,12 @@ void launch_pass(const ss_ctx* c, const PassArgs<T>& a, Run& r, hipStream_t s) {
   if constexpr (PASS == kGF) {
     // only the BEC keeps the force between gradient-flow steps (the lattice
     // theories run kGD)
-    bec_pass<T, PASS>(c, a, s);
+    bec_pass<T, PASS>(c, a, r, s);
     return;
   } else {
     if constexpr (!fixed_tile(PASS) && PASS != kGD) {
       if (c->theory == SS_THEORY_BEC) {
-        bec_pass<T, PASS>(c, a, s);
+        bec_pass<T, PASS>(c, a, r, s);
         return;
       }
     }

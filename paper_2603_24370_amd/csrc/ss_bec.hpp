@@ -12,11 +12,19 @@
 // scaled to N before its force is taken, the force is -(G - mu psi) with
 // mu = <psi, G> / <psi, psi> (its projection on the tangent space of that
 // sphere), and after each step the field is scaled to N and the velocity
-// projected on the tangent space. Both need sums over the whole lattice, so a
-// stage is three launches: the stage point and the partials of its norm; the
-// scale and G with the partials of psi.G and psi.psi; mu and the pass's own
-// update. All sums are FP64 per-workgroup partials added in workgroup order, by
-// every workgroup of the launch that needs the total.
+// projected on the tangent space. Each of these needs sums over the whole lattice,
+// and a sum costs a launch boundary; whatever else follows a sum is of the same site,
+// and is done in the launch that ends at the next sum:
+//   bec_stage   the last step's constraint, the next stage point; its norm
+//   bec_grad    the scale, G; the sums of psi.G and psi.psi
+//   bec_apply   mu, the force and the stage's update; in RK4's stages 1-3 the next
+//               stage point and its norm, else the sums of the step's constraint
+// that is 9 launches per RK4 step and 3 per step of the one-pass integrators (15 and
+// 6 with a launch for each of these; 256^2 sites FP32, RK4: 89 us per step then, 60
+// now). A small lattice's launch takes the latency of its chain (partials, their
+// sum, sites, a block sum), so the loads of a thread's first site are issued before
+// the sums that they wait for. All sums are FP64 per-workgroup partials added in
+// workgroup order, by every workgroup of the launch that needs the total.
 #pragma once
 
 #include "ss_kernels.hpp"
@@ -28,149 +36,235 @@ constexpr int kBecGroups = 512;  // workgroups of every BEC launch (grid-stride 
 // Work buffers: the stage point S and the gradient G (two planes each, the flow's
 // layout), three sets of FP64 workgroup partials (the stage point's norm,
 // kBecGroups; the gradient's sums and the update's, kBecGroups * 4 each), and the
-// scalars of a stage {c (scale to N), mu, E h^2, non-finite count, c' (end of
-// step), m (velocity projection)}. The scale c and mu are summed from their
-// partials by every workgroup of the launch that uses them (in the same fixed
-// order), workgroup 0 keeping them in sc for the launches after.
+// scale c of the stage point to N. Sums of partials are taken by every workgroup of
+// the launch that uses them (in the same fixed order), workgroup 0 of bec_grad
+// keeping the scale for bec_apply.
 template <class T>
 struct BecBufs {
   T* S;
   T* G;
-  double* part;  // partials of the update (bec_apply)
-  double* sc;
-  double* ps;    // partials of the stage point's norm (bec_stage)
-  double* pg;    // partials of the gradient's sums (bec_grad)
+  double* part;  // {phi'.phi', phi'.v'} of the update (bec_apply)
+  double* sc;    // c
+  double* ps;    // the stage point's norm (bec_stage, bec_apply)
+  double* pg;    // the gradient's sums (bec_grad): psi.G, psi.psi, energy, non-finite count
 };
+
+// What a step leaves to be done before the next stage point: nothing; phi' scaled to N
+// and v' projected (RK4); v' projected (velocity Verlet).
+enum BecEnd : int { kBecNone = 0, kBecScale = 1, kBecProject = 2 };
 
 #define BEC_SITES(n) for (long k_ = blockIdx.x * 256L + threadIdx.x; k_ < (n); k_ += (long)gridDim.x * 256L)
 
-// Sum of 256 threads' value in a fixed order (valid in thread 0).
-__device__ __forceinline__ double bec_block_sum(double v, double* red) {
-  v = wave_sum(v);
+// Sums of N values over 256 threads in a fixed order, for every thread. red: 4 N
+// doubles of LDS that nothing else uses.
+template <int N>
+__device__ __forceinline__ void bec_block_sums(double (&v)[N], double* red) {
+#pragma unroll
+  for (int m = 0; m < N; ++m) v[m] = wave_sum(v[m]);
+  if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+    for (int m = 0; m < N; ++m) red[4 * m + (threadIdx.x >> 6)] = v[m];
+  }
   __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return red[0] + red[1] + red[2] + red[3];
+#pragma unroll
+  for (int m = 0; m < N; ++m) v[m] = red[4 * m] + red[4 * m + 1] + red[4 * m + 2] + red[4 * m + 3];
 }
 
-// Sum over the kBecGroups partials part[k * stride + off] by one workgroup of 256
-// threads in a fixed order (strided per thread, then in wave order); valid in
-// thread 0.
-__device__ __forceinline__ double bec_partials_sum(const double* __restrict__ part, int stride, int off,
-                                                   double* red) {
-  double acc = 0.0;
-  for (int k = threadIdx.x; k < kBecGroups; k += 256) acc += part[(long)k * stride + off];
-  return bec_block_sum(acc, red);
+// Sums over the kBecGroups partials part[k * STRIDE + m], m < N, by a workgroup of 256
+// threads in a fixed order (strided per thread, then in wave order), for every thread.
+template <int N, int STRIDE>
+__device__ __forceinline__ void bec_partials_sums(const double* __restrict__ part, double (&v)[N], double* red) {
+  double p[kBecGroups / 256][N];
+#pragma unroll
+  for (int k = 0; k < kBecGroups / 256; ++k)
+#pragma unroll
+    for (int m = 0; m < N; ++m) p[k][m] = part[(long)(k * 256 + threadIdx.x) * STRIDE + m];
+#pragma unroll
+  for (int m = 0; m < N; ++m) {
+    v[m] = 0.0;
+#pragma unroll
+    for (int k = 0; k < kBecGroups / 256; ++k) v[m] += p[k][m];
+  }
+  bec_block_sums(v, red);
 }
 
 __device__ __forceinline__ double bec_block_max(double v, double* red) {
   v = wave_max(v);
-  __syncthreads();
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   return fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
 }
 
-// Stage point of a pass over the padded lattice (as the stage passes form it) and
-// the partial sums of its squares over the interior.
+// A site's share of the end-of-step constraint: v' projected on the tangent space at
+// phi' (RK4 with the unscaled phi', the coefficient being scale-free), phi' scaled.
+template <class T>
+struct BecConstraint {
+  T cs, m;
+};
+
+template <class T>
+__device__ __forceinline__ BecConstraint<T> bec_constraint(const double* __restrict__ part, const Coeffs& cf,
+                                                           double* red) {
+  double v[2];
+  bec_partials_sums<2, 4>(part, v, red);
+  return BecConstraint<T>{(T)sqrt(cf.p[2] / (cf.h * cf.h * v[0])), (T)(v[1] / v[0])};
+}
+
+// Stage point of a pass over the padded lattice (as the stage passes form it) and the
+// partial sums of its squares over the interior: the current field (PASS kP1, for all
+// passes that evaluate it, and kEval, which takes src where that is given), or the new
+// field of a one-pass step. The launch takes the pending test (Link), and before that
+// ends the last step (BecEnd), which a flow that this test stops has taken as well.
 template <class T, int PASS>
-__global__ void __launch_bounds__(256) bec_stage(Bufs<T> B, Coeffs cf, const DevStatus* __restrict__ st,
-                                                 const T* __restrict__ src, BecBufs<T> W) {
-  if (PASS != kEval && st->done) return;
-  __shared__ double red[4];
-  constexpr bool AFTER_P1 = (PASS == kP2 || PASS == kP3 || PASS == kP4);
+__global__ void __launch_bounds__(256) bec_stage(Bufs<T> B, Coeffs cf, Link link, const T* __restrict__ src,
+                                                 BecBufs<T> W, int end) {
+  __shared__ double red[12], redc[8], reds[4];
   constexpr bool ONEPASS = advances_first(PASS);
-  constexpr bool STAGED = AFTER_P1 || ONEPASS;
-  const long long step = st->step;
-  const int cur = AFTER_P1 ? int((step - 1) & 1) : int(step & 1);
-  const bool arrest = (AFTER_P1 || PASS == kVVA) ? (st->arrest != 0) : false;
-  const T dt = (T)cf.dt;
-  T cv = T(0), ca = T(0);
-  if (PASS == kP2) cv = T(0.5) * dt;
-  if (PASS == kP3) { cv = T(0.5) * dt; ca = T(0.25) * dt * dt; }
-  if (PASS == kP4 || PASS == kVVA) { cv = dt; ca = T(0.5) * dt * dt; }
-  if (PASS == kGF) ca = T(0.5) * dt * dt;
-  if (arrest) cv = T(0);
-  const T* __restrict__ ph = (PASS == kEval && src != nullptr) ? src : (cur ? B.phi[1] : B.phi[0]);
-  const T* __restrict__ vv = cur ? B.vel[1] : B.vel[0];
+  Head hd = {};
+  bool ended = false;
+  if (PASS == kEval) {
+    hd.step = link.st->step;
+  } else {
+    ended = end != kBecNone && !link.in->done;
+    hd = resolve(link, cf.h * cf.h, threadIdx.x, red);
+    if (hd.done && !ended) return;
+  }
+  BecConstraint<T> k = {T(1), T(0)};
+  if (ended) k = bec_constraint<T>(W.part, cf, redc);
+  const int cur = int(hd.step & 1);
+  T cv, ca;
+  stage_coeffs<T, PASS>((T)cf.dt, PASS == kVVA && hd.arrest != 0, cv, ca);
+  T* __restrict__ phc = cur ? B.phi[1] : B.phi[0];
+  const T* __restrict__ ph = (PASS == kEval && src != nullptr) ? src : phc;
+  T* __restrict__ vv = cur ? B.vel[1] : B.vel[0];
   // one-pass integrators: the current field's force in the buffer of the step's parity
-  const T* __restrict__ aa = ONEPASS ? (cur ? B.a2 : B.a1) : (PASS == kP3) ? B.a1 : B.a2;
+  const T* __restrict__ aa = cur ? B.a2 : B.a1;
   const long Wd = B.Nx + 4, H = B.Ny + 4;
-  double acc = 0.0;
+  double acc[1] = {0.0};
   BEC_SITES(Wd * H) {
     const int jj = (int)(k_ / Wd), ii = (int)(k_ - (long)jj * Wd);
     const long o = (long)jj * B.pitch + ii;
     const bool inner = ii >= 2 && ii < B.Nx + 2 && jj >= 2 && jj < B.Ny + 2;
+    const bool fix = ended && inner;
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-      T x = ph[c * B.plane + o];
-      if (STAGED) {
-        if (PASS != kGF) x += cv * vv[c * B.plane + o];
-        if (PASS != kP2) x += ca * aa[c * B.plane + o];
+      T x = ph[c * B.plane + o], v = T(0);
+      if (PASS == kVVA || fix) v = vv[c * B.plane + o];
+      if (fix) {
+        v = v - k.m * x;
+        vv[c * B.plane + o] = v;
+        if (end == kBecScale) {
+          x = k.cs * x;
+          phc[c * B.plane + o] = x;
+        }
       }
+      if (PASS == kVVA) x += cv * v;
+      if (ONEPASS) x += ca * aa[c * B.plane + o];
       W.S[c * B.plane + o] = x;
-      if (inner) acc += (double)x * (double)x;
+      if (inner) acc[0] += (double)x * (double)x;
     }
   }
-  const double s = bec_block_sum(acc, red);
-  if (threadIdx.x == 0) W.ps[blockIdx.x] = s;
+  bec_block_sums(acc, reds);
+  if (threadIdx.x == 0) W.ps[blockIdx.x] = acc[0];
 }
 
-// c = sqrt(N / (h^2 sum S^2)): the scale of the stage point onto the sphere of
-// atom number N, from the stage partials (every thread of the workgroup).
-__device__ __forceinline__ double bec_scale_of(const double* __restrict__ ps, const Coeffs& cf, double* red) {
-  const double s = bec_partials_sum(ps, 1, 0, red);
-  return sqrt(cf.p[2] / (cf.h * cf.h * s));
-}
-
-// Value of the scaled stage point at padded (jj, ii): c S inside the interior, S on the halo.
+// The end of a run's last step, where no stage follows (no test is taken).
 template <class T>
-__device__ __forceinline__ T bec_at(const T* __restrict__ S, long pitch, int Nx, int Ny, T c, int jj, int ii) {
-  const T v = S[(long)jj * pitch + ii];
-  return (ii >= 2 && ii < Nx + 2 && jj >= 2 && jj < Ny + 2) ? c * v : v;
+__global__ void __launch_bounds__(256) bec_end(Bufs<T> B, Coeffs cf, const DevStatus* __restrict__ st, BecBufs<T> W,
+                                               int end) {
+  __shared__ double red[8];
+  if (st->done) return;
+  const BecConstraint<T> k = bec_constraint<T>(W.part, cf, red);
+  // an RK4 step has advanced the counter; velocity Verlet's pending test does
+  const int nxt = int((st->step + (end == kBecProject ? 1 : 0)) & 1);
+  T* __restrict__ ph = nxt ? B.phi[1] : B.phi[0];
+  T* __restrict__ v = nxt ? B.vel[1] : B.vel[0];
+  const long n = (long)B.Nx * B.Ny;
+  BEC_SITES(n) {
+    const int j = (int)(k_ / B.Nx), i = (int)(k_ - (long)j * B.Nx);
+    const long o = (long)(j + 2) * B.pitch + (i + 2);
+#pragma unroll
+    for (int comp = 0; comp < 2; ++comp) {
+      const long q = comp * B.plane + o;
+      const T p = ph[q];
+      v[q] = v[q] - k.m * p;
+      if (end == kBecScale) ph[q] = k.cs * p;
+    }
+  }
 }
 
 // G at the scaled stage point; partials {psi.G, psi.psi, energy density sum,
-// non-finite count}. The energy is that of the field the pass tests, in FP64: the
-// stage point as stored (unscaled) for an evaluation, a check or the first stage of
-// RK4; the scaled stage point, which becomes the new field, for a one-pass step.
+// non-finite count}. The scale is c = sqrt(N / (h^2 sum S^2)), of the interior. The
+// energy is that of the field the pass tests, in FP64: the stage point as stored
+// (unscaled) for an evaluation, a check or the first stage of RK4; the scaled stage
+// point, which becomes the new field, for a one-pass step. RK4's stage 2 takes the
+// test of stage 1 (Link).
 template <class T, int PASS>
-__global__ void __launch_bounds__(256) bec_grad(Bufs<T> B, Coeffs cf, const DevStatus* __restrict__ st,
-                                                BecBufs<T> W) {
-  if (PASS != kEval && st->done) return;
-  __shared__ double red[4];
+__global__ void __launch_bounds__(256) bec_grad(Bufs<T> B, Coeffs cf, Link link, BecBufs<T> W) {
+  __shared__ double red[12], redc[4], reds[16];
   constexpr bool REDUCE = reduces(PASS);
-  const double cd = bec_scale_of(W.ps, cf, red);
+  const long n = (long)B.Nx * B.Ny;
+  // stage values along x and y at distances -2 .. 2 (the centre in both)
+  T sx[2][5], sy[2][5];
+  int i = 0, j = 0;
+  auto load = [&](long k) {
+    j = (int)(k / B.Nx);
+    i = (int)(k - (long)j * B.Nx);
+#pragma unroll
+    for (int comp = 0; comp < 2; ++comp) {
+      const T* Sc = W.S + comp * B.plane + (long)(j + 2) * B.pitch + (i + 2);
+#pragma unroll
+      for (int d = 0; d < 5; ++d) {
+        sx[comp][d] = Sc[d - 2];
+        if (d != 2) sy[comp][d] = Sc[(long)(d - 2) * B.pitch];
+      }
+      sy[comp][2] = sx[comp][2];
+    }
+  };
+  const long step = (long)gridDim.x * 256L;
+  long k = blockIdx.x * 256L + threadIdx.x;
+  if (k < n) load(k);
+  if (PASS == kP2) {
+    if (resolve(link, cf.h * cf.h, threadIdx.x, red).done) return;
+  } else if (PASS != kEval) {
+    if (link.in->done) return;
+  }
+  double norm[1];
+  bec_partials_sums<1, 1>(W.ps, norm, redc);
+  const double cd = sqrt(cf.p[2] / (cf.h * cf.h * norm[0]));
   if (blockIdx.x == 0 && threadIdx.x == 0) W.sc[0] = cd;
   const T c = (T)cd;
   const T g = (T)cf.p[0], Om = (T)cf.p[1];
   const double h = cf.h;
   const T c1 = T(1.0 / (12.0 * h)), c2 = T(1.0 / (12.0 * h * h));
   const double d1 = 1.0 / (12.0 * h);
-  const long n = (long)B.Nx * B.Ny;
-  double sG = 0.0, ss = 0.0, se = 0.0, nf = 0.0;
-  BEC_SITES(n) {
-    const int j = (int)(k_ / B.Nx), i = (int)(k_ - (long)j * B.Nx);
-    const int jj = j + 2, ii = i + 2;
+  double sums[4] = {0.0, 0.0, 0.0, 0.0};
+  for (; k < n; k += step) {
     T f[2], dx[2], dy[2], lap[2];
     double fd[2], dxd[2], dyd[2];
 #pragma unroll
     for (int comp = 0; comp < 2; ++comp) {
-      const T* Sc = W.S + comp * B.plane;
-      auto at = [&](int dj, int di) { return bec_at(Sc, B.pitch, B.Nx, B.Ny, c, jj + dj, ii + di); };
-      const T xm2 = at(0, -2), xm1 = at(0, -1), x0 = at(0, 0), xp1 = at(0, 1), xp2 = at(0, 2);
-      const T ym2 = at(-2, 0), ym1 = at(-1, 0), yp1 = at(1, 0), yp2 = at(2, 0);
+      // the scaled value: c S inside the interior, S on the halo
+      auto ax = [&](int d) {
+        const T v = sx[comp][d + 2];
+        return (i + d >= 0 && i + d < B.Nx) ? c * v : v;
+      };
+      auto ay = [&](int d) {
+        const T v = sy[comp][d + 2];
+        return (j + d >= 0 && j + d < B.Ny) ? c * v : v;
+      };
+      const T xm2 = ax(-2), xm1 = ax(-1), x0 = ax(0), xp1 = ax(1), xp2 = ax(2);
+      const T ym2 = ay(-2), ym1 = ay(-1), yp1 = ay(1), yp2 = ay(2);
       f[comp] = x0;
       dx[comp] = c1 * ((xm2 - xp2) + T(8) * (xp1 - xm1));
       dy[comp] = c1 * ((ym2 - yp2) + T(8) * (yp1 - ym1));
       lap[comp] = c2 * ((-(xm2 + xp2) + T(16) * (xm1 + xp1)) + (-(ym2 + yp2) + T(16) * (ym1 + yp1)) - T(60) * x0);
       if (REDUCE) {
-        auto raw = [&](int dj, int di) {
-          return advances_first(PASS) ? (double)at(dj, di) : (double)Sc[(long)(jj + dj) * B.pitch + (ii + di)];
-        };
-        fd[comp] = raw(0, 0);
-        dxd[comp] = d1 * ((raw(0, -2) - raw(0, 2)) + 8.0 * (raw(0, 1) - raw(0, -1)));
-        dyd[comp] = d1 * ((raw(-2, 0) - raw(2, 0)) + 8.0 * (raw(1, 0) - raw(-1, 0)));
+        auto rx = [&](int d) { return advances_first(PASS) ? (double)ax(d) : (double)sx[comp][d + 2]; };
+        auto ry = [&](int d) { return advances_first(PASS) ? (double)ay(d) : (double)sy[comp][d + 2]; };
+        fd[comp] = rx(0);
+        dxd[comp] = d1 * ((rx(-2) - rx(2)) + 8.0 * (rx(1) - rx(-1)));
+        dyd[comp] = d1 * ((ry(-2) - ry(2)) + 8.0 * (ry(1) - ry(-1)));
       }
     }
     const double xd = (i - 0.5 * (B.Nx - 1)) * h, yd = (j - 0.5 * (B.Ny - 1)) * h;
@@ -178,68 +272,49 @@ __global__ void __launch_bounds__(256) bec_grad(Bufs<T> B, Coeffs cf, const DevS
     const T u = f[0], w = f[1], rho = u * u + w * w;
     const T G0 = -lap[0] + r2 * u + T(2) * g * rho * u - T(2) * Om * (x * dy[1] - y * dx[1]);
     const T G1 = -lap[1] + r2 * w + T(2) * g * rho * w + T(2) * Om * (x * dy[0] - y * dx[0]);
-    const long o = (long)jj * B.pitch + ii;
+    const long o = (long)(j + 2) * B.pitch + (i + 2);
     W.G[o] = G0;
     W.G[B.plane + o] = G1;
-    sG += (double)u * (double)G0 + (double)w * (double)G1;
-    ss += (double)u * (double)u + (double)w * (double)w;
-    if (!isfinite(G0) || !isfinite(G1)) nf += 1.0;
+    sums[0] += (double)u * (double)G0 + (double)w * (double)G1;
+    sums[1] += (double)u * (double)u + (double)w * (double)w;
+    if (!isfinite(G0) || !isfinite(G1)) sums[3] += 1.0;
     if (REDUCE) {
       const double ud = fd[0], wd = fd[1];
       const double rhod = ud * ud + wd * wd;
       const double lz = ud * (xd * dyd[1] - yd * dxd[1]) - wd * (xd * dyd[0] - yd * dxd[0]);
       const double e = 0.5 * (dxd[0] * dxd[0] + dyd[0] * dyd[0] + dxd[1] * dxd[1] + dyd[1] * dyd[1]) +
                        0.5 * (xd * xd + yd * yd) * rhod + 0.5 * cf.p[0] * rhod * rhod - cf.p[1] * lz;
-      se += e;
-      if (!isfinite(e)) nf += 1.0;
+      sums[2] += e;
+      if (!isfinite(e)) sums[3] += 1.0;
     }
+    if (k + step < n) load(k + step);
   }
-  const double a0 = bec_block_sum(sG, red);
-  const double a1 = bec_block_sum(ss, red);
-  const double a2 = bec_block_sum(se, red);
-  const double a3 = bec_block_sum(nf, red);
+  bec_block_sums(sums, reds);
   if (threadIdx.x == 0) {
     double* p = W.pg + 4 * (long)blockIdx.x;
-    p[0] = a0;
-    p[1] = a1;
-    p[2] = a2;
-    p[3] = a3;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) p[m] = sums[m];
   }
 }
 
-// mu = <psi, G> / <psi, psi> from the gradient partials (every thread of the
-// workgroup); workgroup 0 also keeps mu, E h^2 and the non-finite count of the
-// stage in sc[1..3].
-__device__ __forceinline__ double bec_mu_of(const double* __restrict__ pg, double* sc, const Coeffs& cf,
-                                            double* red) {
-  const double sG = bec_partials_sum(pg, 4, 0, red);
-  const double ss = bec_partials_sum(pg, 4, 1, red);
-  const double se = bec_partials_sum(pg, 4, 2, red);
-  const double nf = bec_partials_sum(pg, 4, 3, red);
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    sc[1] = sG / ss;
-    sc[2] = cf.h * cf.h * se;
-    sc[3] = nf;
-  }
-  return sG / ss;
-}
-
-// The force a = -(G - mu psi) at the scaled stage point and the pass's update; a
-// reducing pass also writes the partial max |G - mu psi|. P4 writes the new field
-// and velocity before the end-of-step constraint (bec_fix) and the partial sums
-// {phi'.phi', phi'.v'}.
+// The force a = -(G - mu psi) at the scaled stage point (mu = <psi, G> / <psi, psi>)
+// and the pass's update. A reducing pass leaves the partials of its test (energy,
+// max |G - mu psi|, non-finite count). RK4's stages 1-3 form the next stage point in
+// place of their own, over the padded lattice, and the partials of its norm; stage 2
+// starts from rest after an arrest, which the energy of stage 1 decides here as the
+// test will. P4 writes the new field and velocity before the step's constraint
+// (BecEnd) and the partial sums {phi'.phi', phi'.v'}.
 template <class T, int PASS>
-__global__ void __launch_bounds__(256) bec_apply(Bufs<T> B, Coeffs cf, const DevStatus* __restrict__ st,
-                                                 BecBufs<T> W, const double* __restrict__ sc, T* __restrict__ out,
-                                                 long out_pitch, long out_plane) {
-  if (PASS != kEval && st->done) return;
-  __shared__ double red[4];
+__global__ void __launch_bounds__(256) bec_apply(Bufs<T> B, Coeffs cf, Link link, BecBufs<T> W,
+                                                 double* __restrict__ partials, T* __restrict__ out, long out_pitch,
+                                                 long out_plane) {
+  __shared__ double red[16], redm[4], reds[8];
   constexpr bool STAGED = (PASS == kP2 || PASS == kP3 || PASS == kP4);
-  const long long step = st->step;
-  const int cur = STAGED ? int((step - 1) & 1) : int(step & 1);
-  const bool arrest = (STAGED || PASS == kVVA) ? (st->arrest != 0) : false;
-  const T mu = (T)bec_mu_of(W.pg, W.sc, cf, red);
-  const T c = (T)sc[0];
+  constexpr bool THEN = (PASS == kP1 || PASS == kP2 || PASS == kP3);  // forms the next stage point
+  constexpr int NEXT = PASS == kP1 ? kP2 : PASS == kP2 ? kP3 : kP4;
+  const Head hd = load_head(PASS == kEval ? link.st : link.in);
+  if (PASS != kEval && hd.done) return;
+  const int cur = STAGED ? int((hd.step - 1) & 1) : int(hd.step & 1);
   // one-pass integrators: current force (read) and new force (written) by parity
   const T* __restrict__ a_cur = cur ? B.a2 : B.a1;
   T* __restrict__ a_new = cur ? B.a1 : B.a2;
@@ -248,152 +323,115 @@ __global__ void __launch_bounds__(256) bec_apply(Bufs<T> B, Coeffs cf, const Dev
   const T* __restrict__ vv = cur ? B.vel[1] : B.vel[0];
   T* __restrict__ phn = cur ? B.phi[0] : B.phi[1];
   T* __restrict__ vn = cur ? B.vel[0] : B.vel[1];
-  const long n = (long)B.Nx * B.Ny;
-  double gm = 0.0, spp = 0.0, spv = 0.0;
-  BEC_SITES(n) {
-    const int j = (int)(k_ / B.Nx), i = (int)(k_ - (long)j * B.Nx);
-    const long o = (long)(j + 2) * B.pitch + (i + 2);
-    T a[2];
+  const int X0 = THEN ? 0 : 2, Wd = THEN ? B.Nx + 4 : B.Nx;
+  const long n = (long)Wd * (THEN ? B.Ny + 4 : B.Ny);
+  constexpr bool READ_A1 = PASS == kP2 || PASS == kP3 || PASS == kP4, READ_V = THEN || PASS == kP4 || PASS == kVVA;
+  T S[2], G[2], p0[2], v0[2], a1[2], a2[2], qq[2];
+  long o = 0, oo = 0;
+  bool inner = false;
+  auto load = [&](long k) {
+    const int jj = (int)(k / Wd) + X0, ii = (int)(k - (long)(jj - X0) * Wd) + X0;
+    o = (long)jj * B.pitch + ii;
+    oo = (long)jj * out_pitch + ii;
+    inner = !THEN || (ii >= 2 && ii < B.Nx + 2 && jj >= 2 && jj < B.Ny + 2);
 #pragma unroll
     for (int comp = 0; comp < 2; ++comp) {
-      const long k = comp * B.plane + o;
-      const T Gp = W.G[k] - mu * (c * W.S[k]);
-      a[comp] = -Gp;
-      gm = fmax(gm, fabs((double)Gp));
+      const long q = comp * B.plane + o;
+      S[comp] = W.S[q];
+      G[comp] = W.G[q];
+      if (THEN || PASS == kP4) p0[comp] = ph[q];
+      if (READ_V) v0[comp] = vv[q];
+      if (READ_A1) a1[comp] = B.a1[q];
+      if (PASS == kP3) a2[comp] = B.a2[q];
+      if (PASS == kP4) qq[comp] = B.q[q];
+      if (PASS == kVVA) a1[comp] = a_cur[q];
     }
-    if (PASS == kEval) {
-      if (out != nullptr) {
-        const long oo = (long)(j + 2) * out_pitch + (i + 2);
-        out[oo] = -a[0];
-        out[out_plane + oo] = -a[1];
-      }
-    } else if (PASS == kP1) {
-      B.a1[o] = a[0];
-      B.a1[B.plane + o] = a[1];
-    } else if (PASS == kPrime) {
-      // the current field's force, in the buffer of the step's parity
-      T* __restrict__ as = cur ? B.a2 : B.a1;
-      as[o] = a[0];
-      as[B.plane + o] = a[1];
-    } else if (PASS == kVVA || PASS == kGF) {
-      // the scaled stage point is the new field; velocity Verlet also forms
-      // v' = v + dt/2 (a + a'), projected by bec_vproj after the sums below
+  };
+  const long step = (long)gridDim.x * 256L;
+  long k = blockIdx.x * 256L + threadIdx.x;
+  if (k < n) load(k);
+  constexpr int NS = PASS == kP1 ? 3 : 2;
+  double sg[NS];  // psi.G, psi.psi, energy
+  bec_partials_sums<NS, 4>(W.pg, sg, red);
+  const T mu = (T)(sg[0] / sg[1]);
+  const T c = (T)W.sc[0];
+  bool arrest = hd.arrest != 0;
+  if constexpr (PASS == kP1) arrest = arrests(hd, finalise_kind(PASS), cf.h * cf.h * sg[2]);
+  T cv, ca;
+  stage_coeffs<T, NEXT>(dt, arrest, cv, ca);
+  double gm = 0.0, acc[1] = {0.0}, sums[2] = {0.0, 0.0};
+  for (; k < n; k += step) {
 #pragma unroll
-      for (int comp = 0; comp < 2; ++comp) {
-        const long k = comp * B.plane + o;
-        const T pn = c * W.S[k];
-        phn[k] = pn;
-        a_new[k] = a[comp];
-        spp += (double)pn * (double)pn;
-        if (PASS == kVVA) {
-          const T vnew = (arrest ? T(0) : vv[k]) + (T(0.5) * dt) * (a_cur[k] + a[comp]);
-          vn[k] = vnew;
-          spv += (double)pn * (double)vnew;
+    for (int comp = 0; comp < 2; ++comp) {
+      const long q = comp * B.plane + o;
+      T a = T(0);
+      if (inner) {
+        const T Gp = G[comp] - mu * (c * S[comp]);
+        a = -Gp;
+        gm = fmax(gm, fabs((double)Gp));
+        if (PASS == kEval) {
+          if (out != nullptr) out[comp * out_plane + oo] = Gp;
+        } else if (PASS == kP1) {
+          B.a1[q] = a;
+        } else if (PASS == kPrime) {
+          // the current field's force, in the buffer of the step's parity
+          T* __restrict__ as = cur ? B.a2 : B.a1;
+          as[q] = a;
+        } else if (PASS == kVVA || PASS == kGF) {
+          // the scaled stage point is the new field; velocity Verlet also forms
+          // v' = v + dt/2 (a + a'), projected after the sums below (BecEnd)
+          const T pn = c * S[comp];
+          phn[q] = pn;
+          a_new[q] = a;
+          sums[0] += (double)pn * (double)pn;
+          if (PASS == kVVA) {
+            const T vnew = (arrest ? T(0) : v0[comp]) + (T(0.5) * dt) * (a1[comp] + a);
+            vn[q] = vnew;
+            sums[1] += (double)pn * (double)vnew;
+          }
+        } else if (PASS == kP2) {
+          B.a2[q] = a;
+        } else if (PASS == kP3) {
+          B.q[q] = a1[comp] + T(2) * a2[comp] + T(2) * a;
+        } else if (PASS == kP4) {
+          const T vs = arrest ? T(0) : v0[comp];
+          const T pn = p0[comp] + dt * vs + (dt * dt / T(12)) * (qq[comp] + a1[comp]);
+          const T vnew = vs + (dt / T(6)) * (qq[comp] + a);
+          phn[q] = pn;
+          vn[q] = vnew;
+          sums[0] += (double)pn * (double)pn;
+          sums[1] += (double)pn * (double)vnew;
         }
       }
-    } else if (PASS == kP2) {
-      B.a2[o] = a[0];
-      B.a2[B.plane + o] = a[1];
-    } else if (PASS == kP3) {
-#pragma unroll
-      for (int comp = 0; comp < 2; ++comp) {
-        const long k = comp * B.plane + o;
-        B.q[k] = B.a1[k] + T(2) * B.a2[k] + T(2) * a[comp];
-      }
-    } else if (PASS == kP4) {
-#pragma unroll
-      for (int comp = 0; comp < 2; ++comp) {
-        const long k = comp * B.plane + o;
-        const T v0 = arrest ? T(0) : vv[k];
-        const T qq = B.q[k];
-        const T pn = ph[k] + dt * v0 + (dt * dt / T(12)) * (qq + B.a1[k]);
-        const T vnew = v0 + (dt / T(6)) * (qq + a[comp]);
-        phn[k] = pn;
-        vn[k] = vnew;
-        spp += (double)pn * (double)pn;
-        spv += (double)pn * (double)vnew;
+      if (THEN) {
+        T x = p0[comp];
+        x += cv * v0[comp];
+        if (PASS == kP2) x += ca * a1[comp];
+        if (PASS == kP3) x += ca * a2[comp];
+        W.S[q] = x;
+        if (inner) acc[0] += (double)x * (double)x;
       }
     }
+    if (k + step < n) load(k + step);
   }
-  // partials, four per workgroup: {max |G - mu psi|, phi'.phi', phi'.v', unused}
-  const double m = reduces(PASS) ? bec_block_max(gm, red) : 0.0;
-  const double a1 = (PASS == kP4 || PASS == kVVA) ? bec_block_sum(spp, red) : 0.0;
-  const double a2 = (PASS == kP4 || PASS == kVVA) ? bec_block_sum(spv, red) : 0.0;
-  if (threadIdx.x == 0) {
-    double* p = W.part + 4 * (long)blockIdx.x;
-    p[0] = m;
-    p[1] = a1;
-    p[2] = a2;
+  if (THEN) {
+    bec_block_sums(acc, reds);
+    if (threadIdx.x == 0) W.ps[blockIdx.x] = acc[0];
   }
-}
-
-// Status update of a reducing BEC pass: the stage's energy and non-finite count
-// (bec_mu) and the max of the constrained force, through the common finalise.
-template <int PASS>
-__global__ void __launch_bounds__(256) bec_finalise(DevStatus* st, const double* __restrict__ part,
-                                                    const double* __restrict__ sc) {
-  if (PASS != kEval && st->done) return;
-  __shared__ double red[4];
-  double gm = 0.0;
-  for (int k = threadIdx.x; k < kBecGroups; k += 256) gm = fmax(gm, part[4 * (long)k]);
-  gm = bec_block_max(gm, red);
-  if (threadIdx.x == 0) finalise_status<PASS>(st, sc[2], gm, (int)sc[3]);
-}
-
-// End of a step: phi' scaled to N, v' projected on the tangent space at phi'
-// (the projection uses the unscaled phi'; the coefficient is scale-free).
-__global__ void __launch_bounds__(256) bec_fix_scalars(const double* __restrict__ part, double* sc, Coeffs cf,
-                                                       const DevStatus* __restrict__ st) {
-  if (st->done) return;
-  __shared__ double red[4];
-  const double pp = bec_partials_sum(part, 4, 1, red);
-  const double pv = bec_partials_sum(part, 4, 2, red);
-  if (threadIdx.x == 0) {
-    sc[4] = sqrt(cf.p[2] / (cf.h * cf.h * pp));
-    sc[5] = pv / pp;
-  }
-}
-
-template <class T>
-__global__ void __launch_bounds__(256) bec_fix(Bufs<T> B, const DevStatus* __restrict__ st, const double* __restrict__ sc) {
-  if (st->done) return;
-  // P4 ran after P1 advanced the step: the new field is in the buffer of parity step & 1
-  const int nxt = int(st->step & 1);
-  T* __restrict__ ph = nxt ? B.phi[1] : B.phi[0];
-  T* __restrict__ v = nxt ? B.vel[1] : B.vel[0];
-  const T cs = (T)sc[4], m = (T)sc[5];
-  const long n = (long)B.Nx * B.Ny;
-  BEC_SITES(n) {
-    const int j = (int)(k_ / B.Nx), i = (int)(k_ - (long)j * B.Nx);
-    const long o = (long)(j + 2) * B.pitch + (i + 2);
-#pragma unroll
-    for (int comp = 0; comp < 2; ++comp) {
-      const long k = comp * B.plane + o;
-      const T p = ph[k];
-      v[k] = v[k] - m * p;
-      ph[k] = cs * p;
+  if (PASS == kP4 || PASS == kVVA) {
+    bec_block_sums(sums, reds);
+    if (threadIdx.x == 0) {
+      W.part[4 * (long)blockIdx.x] = sums[0];
+      W.part[4 * (long)blockIdx.x + 1] = sums[1];
     }
   }
-}
-
-// Velocity Verlet: v' projected on the tangent space at the new field (which the
-// pass wrote into the buffer of the other parity; the step counter advances after).
-template <class T>
-__global__ void __launch_bounds__(256) bec_vproj(Bufs<T> B, const DevStatus* __restrict__ st,
-                                                 const double* __restrict__ sc) {
-  if (st->done) return;
-  const int nxt = 1 - int(st->step & 1);
-  const T* __restrict__ ph = nxt ? B.phi[1] : B.phi[0];
-  T* __restrict__ v = nxt ? B.vel[1] : B.vel[0];
-  const T m = (T)sc[5];
-  const long n = (long)B.Nx * B.Ny;
-  BEC_SITES(n) {
-    const int j = (int)(k_ / B.Nx), i = (int)(k_ - (long)j * B.Nx);
-    const long o = (long)(j + 2) * B.pitch + (i + 2);
-#pragma unroll
-    for (int comp = 0; comp < 2; ++comp) {
-      const long k = comp * B.plane + o;
-      v[k] = v[k] - m * ph[k];
+  if (reduces(PASS)) {
+    const double m = bec_block_max(gm, redm);
+    if (threadIdx.x == 0) {
+      double* p = partials + 4 * (long)blockIdx.x;
+      p[0] = W.pg[4 * (long)blockIdx.x + 2];
+      p[1] = m;
+      p[2] = W.pg[4 * (long)blockIdx.x + 3];
     }
   }
 }

@@ -258,6 +258,12 @@ __device__ __forceinline__ Rules load_rules(const DevStatus* st, const Head& h, 
   return q;
 }
 
+// Whether a test of energy E arrests the flow: not the first one of a run (decide()),
+// nor gradient flow's, which has no velocity.
+__device__ __forceinline__ bool arrests(const Head& h, int kind, double E) {
+  return !(kind & kNoArrest) && h.fresh == 0 && E > h.E_prev;
+}
+
 // Status update after a reduction of one field: arrest test E > E_prev (strict,
 // eq. (4)), the stop rules when minimising, and the step counter. E is already
 // multiplied by h^2. The tested step is returned (its place in the history).
@@ -272,9 +278,8 @@ __device__ __forceinline__ long long decide(Head& h, const Rules& q, int kind, d
   // with, so a run split in two decides its arrests as one run does. (Its own
   // sum of the same field may differ in the last bits: another launch shape.)
   const bool retest = h.fresh != 0;
+  const int arr = arrests(h, kind, E) ? 1 : 0;
   h.fresh = 0;
-  // gradient flow has no velocity, hence no arrest
-  const int arr = (!(kind & kNoArrest) && !retest && E > h.E_prev) ? 1 : 0;
   if (!retest) h.arrest = arr;
   if (arr) h.n_arrests += 1;
   if (!retest || !isfinite(h.E_prev)) h.E_prev = E;

@@ -116,6 +116,30 @@ def test_flow_tracks_the_oracle_and_holds_the_atom_number(ss, orc, dtype, scheme
     s.close()
 
 
+@pytest.mark.parametrize("scheme", ["rk4", "vv", "gf"])
+@pytest.mark.parametrize("shape", [(400, 397), (9, 8)])
+def test_flow_in_two_runs_over_lattice_sizes(ss, orc, scheme, shape):
+    """More sites than a launch has threads (131072), and a lattice smaller than a
+    workgroup; the constraint of a run's last step and of the steps within it."""
+    Nx, Ny = shape
+    h = 9.6 / Nx
+    p = [2.0, 0.7, 3.0]
+    print(f"[case] bec two runs {scheme} {shape}", flush=True)
+    f = _field(Nx, Ny, h, seed=5)
+    s = ss.Solver(BEC, Nx, Ny, h, p, dtype="f64")
+    s.set_integrator(scheme)
+    s.set_field(f)
+    s.flow_step(2)
+    info = s.flow_step(3)
+    phi, vel = (_np(x) for x in s.get_field(velocity=True))
+    phi_r, v_r, E_r, na_r = orc.flow(BEC, f, np.zeros_like(f), h, p, 5, scheme=scheme)
+    assert np.abs(phi - phi_r).max() <= 1e-11 * np.abs(phi_r).max()
+    assert np.abs(vel - v_r).max() <= 1e-11 * max(np.abs(v_r).max(), np.abs(phi_r).max())
+    assert info["step"] == 5 and info["n_arrests"] == na_r
+    assert info["energy"] == pytest.approx(E_r, rel=1e-12)
+    s.close()
+
+
 @pytest.mark.parametrize("scheme", ["rk4", "vv"])
 def test_ground_state_without_interaction(ss, orc, scheme):
     """FP64, g = 0, Omega = 0.5: the minimum is the oscillator ground state, E = N to
