@@ -195,22 +195,71 @@ __device__ __forceinline__ int xcd_tile(int b, int nlaunch) {
   return (b & 7) * per + (b >> 3);
 }
 
+// The two operands that lane i of a wave combines to reduce over lanes i and i ^ O,
+// given that x is the same at lanes whose numbers differ in the bits above O (as the
+// reductions below, from 32 down, leave it). Every exchange stays in the vector units:
+// swaps of halves and rows, rotations within rows of 16, permutations of quads. As
+// shuffles, an LDS access of some 100 cycles per step and word, the reductions of a pass
+// (the pending test's and its own, three values each) took 0.6-0.7 us longer: velocity
+// Verlet on 128^2 FP32 8.8 us per step, now 8.2; gradient flow of baby Skyrme on
+// 1021 x 517 18.0 and 16.5.
+template <int O>
+__device__ __forceinline__ void lane_pair(unsigned x, unsigned& a, unsigned& b) {
+  if constexpr (O == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    a = r[0];
+    b = r[1];
+  } else if constexpr (O == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    a = r[0];
+    b = r[1];
+  } else {
+    constexpr int kRor8 = 0x128, kRor4 = 0x124, kQuad2301 = 0x4E, kQuad1032 = 0xB1;
+    constexpr int ctrl = O == 8 ? kRor8 : O == 4 ? kRor4 : O == 2 ? kQuad2301 : kQuad1032;
+    a = x;
+    b = (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, 0xF, 0xF, true);
+  }
+}
+
+template <int O>
+__device__ __forceinline__ void lane_pair(double x, double& a, double& b) {
+  const unsigned long long u = __double_as_longlong(x);
+  unsigned al, bl, ah, bh;
+  lane_pair<O>((unsigned)u, al, bl);
+  lane_pair<O>((unsigned)(u >> 32), ah, bh);
+  a = __longlong_as_double((long long)(((unsigned long long)ah << 32) | al));
+  b = __longlong_as_double((long long)(((unsigned long long)bh << 32) | bl));
+}
+
+// x reduced over the 64 lanes of a wave in pairs at distance 32, 16, ..., 1, for every
+// lane.
+template <class V, class F>
+__device__ __forceinline__ V wave_reduce(V x, F&& f) {
+  V a, b;
+  lane_pair<32>(x, a, b);
+  x = f(a, b);
+  lane_pair<16>(x, a, b);
+  x = f(a, b);
+  lane_pair<8>(x, a, b);
+  x = f(a, b);
+  lane_pair<4>(x, a, b);
+  x = f(a, b);
+  lane_pair<2>(x, a, b);
+  x = f(a, b);
+  lane_pair<1>(x, a, b);
+  return f(a, b);
+}
+
 __device__ __forceinline__ double wave_sum(double x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
+  return wave_reduce(x, [](double a, double b) { return a + b; });
 }
 
 __device__ __forceinline__ double wave_max(double x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o, 64));
-  return x;
+  return wave_reduce(x, [](double a, double b) { return fmax(a, b); });
 }
 
 __device__ __forceinline__ int wave_isum(int x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
+  return (int)wave_reduce((unsigned)x, [](unsigned a, unsigned b) { return a + b; });
 }
 
 // Workgroup reduction of (sum, max, count) in a fixed order; the result is valid
