@@ -131,7 +131,7 @@ __global__ void __launch_bounds__(256) bec_stage(Bufs<T> B, Coeffs cf, Link link
   }
   BecConstraint<T> k = {T(1), T(0)};
   if (ended) k = bec_constraint<T>(W.part, cf, redc);
-  const int cur = int(hd.step & 1);
+  const int cur = uniform(int(hd.step & 1));
   T cv, ca;
   stage_coeffs<T, PASS>((T)cf.dt, PASS == kVVA && hd.arrest != 0, cv, ca);
   T* __restrict__ phc = cur ? B.phi[1] : B.phi[0];
@@ -314,7 +314,7 @@ __global__ void __launch_bounds__(256) bec_apply(Bufs<T> B, Coeffs cf, Link link
   constexpr int NEXT = PASS == kP1 ? kP2 : PASS == kP2 ? kP3 : kP4;
   const Head hd = load_head(PASS == kEval ? link.st : link.in);
   if (PASS != kEval && hd.done) return;
-  const int cur = STAGED ? int((hd.step - 1) & 1) : int(hd.step & 1);
+  const int cur = uniform(STAGED ? int((hd.step - 1) & 1) : int(hd.step & 1));
   // one-pass integrators: current force (read) and new force (written) by parity
   const T* __restrict__ a_cur = cur ? B.a2 : B.a1;
   T* __restrict__ a_new = cur ? B.a1 : B.a2;

@@ -652,8 +652,8 @@ __global__ void __launch_bounds__(256) dm_begin(Bufs<T> B, Coeffs cf, Link link,
   constexpr bool WITH_V = stage_reads_v(PASS);
   constexpr bool WITH_A = stage_reads_a(PASS);
   constexpr bool AFTER_P1 = (PASS == kP2 || PASS == kP3 || PASS == kP4);
-  const int cur = AFTER_P1 ? int((hd.step - 1) & 1) : int(hd.step & 1);
-  const bool arrest = uses_arrest(PASS) ? (hd.arrest != 0) : false;
+  const int cur = uniform(AFTER_P1 ? int((hd.step - 1) & 1) : int(hd.step & 1));
+  const bool arrest = uses_arrest(PASS) ? (uniform(hd.arrest) != 0) : false;
   const T dt = (T)cf.dt;
   T cv, ca;
   stage_coeffs<T, PASS>(dt, arrest, cv, ca);

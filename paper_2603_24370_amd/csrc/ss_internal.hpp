@@ -292,6 +292,10 @@ __device__ __forceinline__ void block_reduce3(double& s, double& m, int& n, doub
 }
 
 
+// x, the same in every lane, as a scalar: what is selected by it (a ping-pong buffer's
+// base) then stays in scalar registers too. The status is computed in vector registers.
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
 // The stop rules, and the energy of `window` steps back for the stall rule.
 struct Rules {
   double grad_tol, rel_e_tol, e_target, e_window;

@@ -184,6 +184,10 @@ __device__ __forceinline__ T vv_partial(bool arrest, T dt, T v, T a) {
   return (arrest ? T(0) : v) + (T(0.5) * dt) * a;
 }
 
+// Epilogues write a site as (plane base + row)[tx]: the row's offset is the wave's, so
+// that an address is a scalar base and the lane, not 64-bit vector arithmetic per
+// component.
+//
 // Epilogue of a one-pass step at one site: S is the new field, G = G(S), and u
 // the part of the new velocity known before G: the half-step velocity read by
 // the kick-drift-kick step, or w = v0 + dt/2 a of the stored-force step. Both
@@ -193,7 +197,7 @@ __device__ __forceinline__ T vv_partial(bool arrest, T dt, T v, T a) {
 template <class T, int TH, int PASS>
 __device__ __forceinline__ void one_pass_epilogue(T dt, const T (&u)[4], const T (&S)[4], const T (&G)[4],
                                                   T* __restrict__ phn, T* __restrict__ vn, T* __restrict__ an,
-                                                  long plane, long off) {
+                                                  long plane, long row, unsigned tx) {
   constexpr int C = NComp<TH>::value;
   if (PASS == kVV || PASS == kVVA) {
     const T hd = T(0.5) * dt;
@@ -207,19 +211,19 @@ __device__ __forceinline__ void one_pass_epilogue(T dt, const T (&u)[4], const T
     }
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-      __builtin_nontemporal_store(S[c], &phn[c * plane + off]);
+      __builtin_nontemporal_store(S[c], &(phn + c * plane + row)[tx]);
       if (PASS == kVV) {
-        __builtin_nontemporal_store(vnew[c] - hd * G[c], &vn[c * plane + off]);
+        __builtin_nontemporal_store(vnew[c] - hd * G[c], &(vn + c * plane + row)[tx]);
       } else {
-        __builtin_nontemporal_store(vnew[c], &vn[c * plane + off]);
-        __builtin_nontemporal_store(-G[c], &an[c * plane + off]);
+        __builtin_nontemporal_store(vnew[c], &(vn + c * plane + row)[tx]);
+        __builtin_nontemporal_store(-G[c], &(an + c * plane + row)[tx]);
       }
     }
   } else {
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-      __builtin_nontemporal_store(S[c], &phn[c * plane + off]);
-      __builtin_nontemporal_store(-G[c], &an[c * plane + off]);
+      __builtin_nontemporal_store(S[c], &(phn + c * plane + row)[tx]);
+      __builtin_nontemporal_store(-G[c], &(an + c * plane + row)[tx]);
     }
   }
 }
@@ -228,7 +232,7 @@ __device__ __forceinline__ void one_pass_epilogue(T dt, const T (&u)[4], const T
 // tau = dt^2/2, put on the unit sphere for unit fields, into the other buffer.
 template <class T, int TH>
 __device__ __forceinline__ void gd_epilogue(T dt, const T (&phi)[4], const T (&G)[4], T* __restrict__ phn,
-                                            long plane, long off) {
+                                            long plane, long row, unsigned tx) {
   constexpr int C = NComp<TH>::value;
   const T tau = T(0.5) * dt * dt;
   T pn[4];
@@ -240,7 +244,7 @@ __device__ __forceinline__ void gd_epilogue(T dt, const T (&phi)[4], const T (&G
     for (int c = 0; c < 3; ++c) pn[c] *= inv;
   }
 #pragma unroll
-  for (int c = 0; c < C; ++c) __builtin_nontemporal_store(pn[c], &phn[c * plane + off]);
+  for (int c = 0; c < C; ++c) __builtin_nontemporal_store(pn[c], &(phn + c * plane + row)[tx]);
 }
 
 // Epilogue of the velocity Verlet passes around the steps at one site of the
@@ -249,17 +253,17 @@ __device__ __forceinline__ void gd_epilogue(T dt, const T (&phi)[4], const T (&G
 // arrest).
 template <class T, int TH, int PASS>
 __device__ __forceinline__ void vv_in_place_epilogue(T dt, bool arrest, const T (&G)[4], T* __restrict__ vc,
-                                                     long plane, long off) {
+                                                     long plane, long row, unsigned tx) {
   constexpr int C = NComp<TH>::value;
   const T hd = T(0.5) * dt;
 #pragma unroll
   for (int c = 0; c < C; ++c) {
-    const long k = c * plane + off;
+    T* __restrict__ v = vc + c * plane + row;
     T x;
-    if (PASS == kVVStart) x = vc[k] - hd * G[c];
+    if (PASS == kVVStart) x = v[tx] - hd * G[c];
     else if (PASS == kVVRestart) x = -hd * G[c];
-    else x = arrest ? T(0) : vc[k] + hd * G[c];
-    vc[k] = x;
+    else x = arrest ? T(0) : v[tx] + hd * G[c];
+    v[tx] = x;
   }
 }
 
@@ -280,6 +284,44 @@ struct TileLds {
   static constexpr int RAW = (PASS == kVV || PASS == kVVA) ? 2 * 2 * C * TX : 0;
   static constexpr int size = STAGE + ROWS + RAW;
 };
+
+// The four stage rows that a tile shares with the next one, kept from the bottom of its
+// C planes and put at the top of the next one's, 16 bytes per access: a plane's four
+// rows are contiguous. A tile of the one-pass integrators is bound by its vector
+// instructions (some 900 per thread on 64 x 8 FP32 Abelian Higgs), of which these copies
+// took a fifth by the element, with a division each for its plane. us per step, before
+// and now: Abelian Higgs 4096^2 FP32 velocity Verlet 322 / 298, gradient flow 172 / 159,
+// chiral magnet 2048^2 gradient flow 61 / 48, FP64 velocity Verlet 144 / 140. Unrolled, or
+// with a tile's own loads on scalar bases as well, some passes lose a wave per SIMD to
+// the registers (baby Skyrme 2048^2 83 us per step, 114 then).
+template <class T, int C, int LX, int LY, int NT>
+__device__ __forceinline__ void keep_rows(const T* __restrict__ lds, T* __restrict__ cs, int tid) {
+  typedef typename Vec16<T>::type V;
+  constexpr int VN = Vec16<T>::n, N = 4 * LX / VN;  // vectors per plane
+  static_assert(4 * LX % VN == 0 && LX * LY % VN == 0 && (LY - 4) * LX % VN == 0, "rows in whole vectors");
+#pragma unroll 1
+  for (int b = 0; b < (C * N + NT - 1) / NT; ++b) {
+    const int k = tid + b * NT;
+    if (k < C * N) {
+      const int c = k / N;
+      reinterpret_cast<V*>(cs)[k] = reinterpret_cast<const V*>(lds)[c * (LX * LY / VN - N) + (LY - 4) * LX / VN + k];
+    }
+  }
+}
+
+template <class T, int C, int LX, int LY, int NT>
+__device__ __forceinline__ void carry_rows(T* __restrict__ lds, const T* __restrict__ cs, int tid) {
+  typedef typename Vec16<T>::type V;
+  constexpr int VN = Vec16<T>::n, N = 4 * LX / VN;
+#pragma unroll 1
+  for (int b = 0; b < (C * N + NT - 1) / NT; ++b) {
+    const int k = tid + b * NT;
+    if (k < C * N) {
+      const int c = k / N;
+      reinterpret_cast<V*>(lds)[c * (LX * LY / VN - N) + k] = reinterpret_cast<const V*>(cs)[k];
+    }
+  }
+}
 
 // One tile of one pass. Thread (tx, ty) owns column tx and rows ty*RY ..
 // ty*RY + RY - 1 of the tile: it loads those sites' raw inputs into registers
@@ -338,6 +380,7 @@ __device__ __forceinline__ void tile_body(const InstView<T>& V, int cur, bool ar
   const int wy = (TX == 64) ? __builtin_amdgcn_readfirstlane((int)threadIdx.y) : (int)threadIdx.y;
   const int ly0 = wy * RY + 2;
   const int gi = x0 + threadIdx.x;
+  const unsigned tx = threadIdx.x;
 
   // Stage point of padded element (gi, gj) (interior coordinates) and its raw
   // inputs, in two halves, so that a thread can have the loads of all its own
@@ -403,10 +446,7 @@ __device__ __forceinline__ void tile_body(const InstView<T>& V, int cur, bool ar
   const bool carried = CARRY && k > 0;
   const int par = k & 1;
   if (carried) {
-    for (int idx = tid; idx < C * 4 * LX; idx += NT) {
-      const int c = idx / (4 * LX);
-      s[c][idx - c * 4 * LX] = cs[idx];
-    }
+    carry_rows<T, C, LX, LY, NT>(lds, cs, tid);
   }
 
   // ---- own sites: raw inputs kept in registers, stage point to LDS (and, for
@@ -487,10 +527,7 @@ __device__ __forceinline__ void tile_body(const InstView<T>& V, int cur, bool ar
   if (CARRY && more) {
     // stage rows TY .. TY+3 are the next tile's rows 0-3; saved before any
     // in-place change of the stage point below
-    for (int idx = tid; idx < C * 4 * LX; idx += NT) {
-      const int c = idx / (4 * LX);
-      cs[idx] = s[c][(LY - 4) * LX + idx - c * 4 * LX];
-    }
+    keep_rows<T, C, LX, LY, NT>(lds, cs, tid);
   }
 
   // E_h density in FP64 from the stored (unnormalised) values in LDS, own sites
@@ -587,7 +624,7 @@ __device__ __forceinline__ void tile_body(const InstView<T>& V, int cur, bool ar
 #pragma unroll
       for (int c = 0; c < 3; ++c) G[c] -= gn * Js[c].f;
     }
-    const long off = (long)(gj + 2) * pitch + (gi + 2);
+    const long row = (long)(gj + 2) * pitch + (x0 + 2);  // the wave's
     if (REDUCE) {
 #pragma unroll
       for (int c = 0; c < C; ++c) {
@@ -597,37 +634,38 @@ __device__ __forceinline__ void tile_body(const InstView<T>& V, int cur, bool ar
     }
     if (PASS == kP1 || PASS == kPrime) {
 #pragma unroll
-      for (int c = 0; c < C; ++c) __builtin_nontemporal_store(-G[c], &a_store[c * plane + off]);
+      for (int c = 0; c < C; ++c) __builtin_nontemporal_store(-G[c], &(a_store + c * plane + row)[tx]);
     } else if (ONEPASS) {
-      one_pass_epilogue<T, TH, PASS>(dt, rv[r], so[r], G, phn, vn, a_store, plane, off);
+      one_pass_epilogue<T, TH, PASS>(dt, rv[r], so[r], G, phn, vn, a_store, plane, row, tx);
     } else if (vv_in_place(PASS)) {
-      vv_in_place_epilogue<T, TH, PASS>(dt, arrest, G, vcur, plane, off);
+      vv_in_place_epilogue<T, TH, PASS>(dt, arrest, G, vcur, plane, row, tx);
     } else if (PASS == kGD) {
-      gd_epilogue<T, TH>(dt, so[r], G, phn, plane, off);
+      gd_epilogue<T, TH>(dt, so[r], G, phn, plane, row, tx);
     } else if (PASS == kEval) {
       if (out != nullptr) {
-        const long o = (long)(gj + 2) * out_pitch + (gi + 2);
+        const long o = (long)(gj + 2) * out_pitch + (x0 + 2);
 #pragma unroll
-        for (int c = 0; c < C; ++c) out[c * out_plane + o] = G[c];
+        for (int c = 0; c < C; ++c) (out + c * out_plane + o)[tx] = G[c];
       }
     } else if (PASS == kP2) {
 #pragma unroll
-      for (int c = 0; c < C; ++c) __builtin_nontemporal_store(-G[c], &V.a2[c * plane + off]);
+      for (int c = 0; c < C; ++c) __builtin_nontemporal_store(-G[c], &(V.a2 + c * plane + row)[tx]);
     } else if (PASS == kP3) {
       // q = a1 + 2 a2 + 2 a3; a1 (a raw stage input) is in registers
 #pragma unroll
       for (int c = 0; c < C; ++c) {
-        const long k = c * plane + off;
-        __builtin_nontemporal_store(ra[r][c] + T(2) * __builtin_nontemporal_load(&V.a2[k]) - T(2) * G[c], &V.q[k]);
+        const long k = c * plane + row;
+        __builtin_nontemporal_store(ra[r][c] + T(2) * __builtin_nontemporal_load(&(V.a2 + k)[tx]) - T(2) * G[c],
+                                    &(V.q + k)[tx]);
       }
     } else if (PASS == kP4) {
       T pn[4], vnew[4];
 #pragma unroll
       for (int c = 0; c < C; ++c) {
-        const long k = c * plane + off;
+        const long k = c * plane + row;
         const T v0 = arrest ? T(0) : rv[r][c];
-        const T qq = __builtin_nontemporal_load(&V.q[k]);
-        pn[c] = rp[r][c] + dt * v0 + (dt * dt / T(12)) * (qq + __builtin_nontemporal_load(&V.a1[k]));
+        const T qq = __builtin_nontemporal_load(&(V.q + k)[tx]);
+        pn[c] = rp[r][c] + dt * v0 + (dt * dt / T(12)) * (qq + __builtin_nontemporal_load(&(V.a1 + k)[tx]));
         vnew[c] = v0 + (dt / T(6)) * (qq - G[c]);
       }
       if (unit_field(TH)) {
@@ -640,9 +678,9 @@ __device__ __forceinline__ void tile_body(const InstView<T>& V, int cur, bool ar
       }
 #pragma unroll
       for (int c = 0; c < C; ++c) {
-        const long k = c * plane + off;
-        __builtin_nontemporal_store(pn[c], &phn[k]);
-        __builtin_nontemporal_store(vnew[c], &vn[k]);
+        const long k = c * plane + row;
+        __builtin_nontemporal_store(pn[c], &(phn + k)[tx]);
+        __builtin_nontemporal_store(vnew[c], &(vn + k)[tx]);
       }
     }
   }
@@ -748,6 +786,7 @@ __device__ __forceinline__ void tile_body_exact(const InstView<T>& V, int cur, b
   // a 64-wide tile row is one wavefront: its row index is wave-uniform
   const int wy = (TX == 64) ? __builtin_amdgcn_readfirstlane((int)threadIdx.y) : (int)threadIdx.y;
   const int gi = x0 + threadIdx.x;
+  const unsigned tx = threadIdx.x;
 
   auto stage_at = [&](int gi_, int gj_, T (&raw_p)[4], T (&raw_v)[4], T (&raw_a)[4], T (&S)[4]) {
 #pragma unroll
@@ -953,7 +992,7 @@ __device__ __forceinline__ void tile_body_exact(const InstView<T>& V, int cur, b
       for (int c = 0; c < 3; ++c) G[c] -= gn * cen[r][c];
       G[3] = T(0);
     }
-    const long off = (long)(gj + 2) * pitch + (gi + 2);
+    const long row = (long)(gj + 2) * pitch + (x0 + 2);  // the wave's
     if (REDUCE) {
 #pragma unroll
       for (int c = 0; c < C; ++c) {
@@ -963,36 +1002,37 @@ __device__ __forceinline__ void tile_body_exact(const InstView<T>& V, int cur, b
     }
     if (PASS == kP1 || PASS == kPrime) {
 #pragma unroll
-      for (int c = 0; c < C; ++c) __builtin_nontemporal_store(-G[c], &a_store[c * plane + off]);
+      for (int c = 0; c < C; ++c) __builtin_nontemporal_store(-G[c], &(a_store + c * plane + row)[tx]);
     } else if (ONEPASS) {
-      one_pass_epilogue<T, TH, PASS>(dt, rv[r], so[r], G, phn, vn, a_store, plane, off);
+      one_pass_epilogue<T, TH, PASS>(dt, rv[r], so[r], G, phn, vn, a_store, plane, row, tx);
     } else if (vv_in_place(PASS)) {
-      vv_in_place_epilogue<T, TH, PASS>(dt, arrest, G, vcur, plane, off);
+      vv_in_place_epilogue<T, TH, PASS>(dt, arrest, G, vcur, plane, row, tx);
     } else if (PASS == kGD) {
-      gd_epilogue<T, TH>(dt, so[r], G, phn, plane, off);
+      gd_epilogue<T, TH>(dt, so[r], G, phn, plane, row, tx);
     } else if (PASS == kEval) {
       if (out != nullptr) {
-        const long o = (long)(gj + 2) * out_pitch + (gi + 2);
+        const long o = (long)(gj + 2) * out_pitch + (x0 + 2);
 #pragma unroll
-        for (int c = 0; c < C; ++c) out[c * out_plane + o] = G[c];
+        for (int c = 0; c < C; ++c) (out + c * out_plane + o)[tx] = G[c];
       }
     } else if (PASS == kP2) {
 #pragma unroll
-      for (int c = 0; c < C; ++c) __builtin_nontemporal_store(-G[c], &V.a2[c * plane + off]);
+      for (int c = 0; c < C; ++c) __builtin_nontemporal_store(-G[c], &(V.a2 + c * plane + row)[tx]);
     } else if (PASS == kP3) {
 #pragma unroll
       for (int c = 0; c < C; ++c) {
-        const long k = c * plane + off;
-        __builtin_nontemporal_store(ra[r][c] + T(2) * __builtin_nontemporal_load(&V.a2[k]) - T(2) * G[c], &V.q[k]);
+        const long k = c * plane + row;
+        __builtin_nontemporal_store(ra[r][c] + T(2) * __builtin_nontemporal_load(&(V.a2 + k)[tx]) - T(2) * G[c],
+                                    &(V.q + k)[tx]);
       }
     } else if (PASS == kP4) {
       T pn[4], vnew[4];
 #pragma unroll
       for (int c = 0; c < C; ++c) {
-        const long k = c * plane + off;
+        const long k = c * plane + row;
         const T v0 = arrest ? T(0) : rv[r][c];
-        const T qq = __builtin_nontemporal_load(&V.q[k]);
-        pn[c] = rp[r][c] + dt * v0 + (dt * dt / T(12)) * (qq + __builtin_nontemporal_load(&V.a1[k]));
+        const T qq = __builtin_nontemporal_load(&(V.q + k)[tx]);
+        pn[c] = rp[r][c] + dt * v0 + (dt * dt / T(12)) * (qq + __builtin_nontemporal_load(&(V.a1 + k)[tx]));
         vnew[c] = v0 + (dt / T(6)) * (qq - G[c]);
       }
       if (unit_field(TH)) {
@@ -1005,9 +1045,9 @@ __device__ __forceinline__ void tile_body_exact(const InstView<T>& V, int cur, b
       }
 #pragma unroll
       for (int c = 0; c < C; ++c) {
-        const long k = c * plane + off;
-        __builtin_nontemporal_store(pn[c], &phn[k]);
-        __builtin_nontemporal_store(vnew[c], &vn[k]);
+        const long k = c * plane + row;
+        __builtin_nontemporal_store(pn[c], &(phn + k)[tx]);
+        __builtin_nontemporal_store(vnew[c], &(vn + k)[tx]);
       }
     }
   }
@@ -1079,8 +1119,8 @@ __attribute__((amdgpu_waves_per_eu(StageWaves<T, TH, PASS, RY>::value))) stage_p
   if (PASS != kEval && PASS != kVVEnd && hd.done) return;
   if (PASS == kVVRestart && !hd.arrest) return;
   const long long step = hd.step;
-  const int cur = AFTER_P1 ? int((step - 1) & 1) : int(step & 1);
-  const bool arrest = uses_arrest(PASS) ? (hd.arrest != 0) : false;
+  const int cur = uniform(AFTER_P1 ? int((step - 1) & 1) : int(step & 1));
+  const bool arrest = uses_arrest(PASS) ? (uniform(hd.arrest) != 0) : false;
   const InstView<T> V = view_of<T>(a.B, a.cf);
 
   double e_acc = 0.0, g_acc = 0.0;
@@ -1431,8 +1471,8 @@ stage_pass_fused(PassArgs<T> a) {
   __shared__ double red[12];
   const Head hd = resolve(a.link, a.cf.h * a.cf.h, threadIdx.y * TX + threadIdx.x, red);
   if (hd.done) return;
-  const int cur = int((hd.step - 1) & 1);
-  const bool arrest = hd.arrest != 0;
+  const int cur = uniform(int((hd.step - 1) & 1));
+  const bool arrest = uniform(hd.arrest) != 0;
   const InstView<T> V = view_of<T>(a.B, a.cf);
   for_each_tile(a.ntx, a.nty, a.seg, [&](int tx, int ty, int, bool) {
     tile_body_fused<T, TH, TX, TY, RY>(V, cur, arrest, tx * TX, ty * TY, lds);
@@ -1459,8 +1499,8 @@ __global__ void __launch_bounds__(256) stage_pass_exact(PassArgs<T> a) {
   if (PASS != kEval && PASS != kVVEnd && hd.done) return;
   if (PASS == kVVRestart && !hd.arrest) return;
   const long long step = hd.step;
-  const int cur = AFTER_P1 ? int((step - 1) & 1) : int(step & 1);
-  const bool arrest = uses_arrest(PASS) ? (hd.arrest != 0) : false;
+  const int cur = uniform(AFTER_P1 ? int((step - 1) & 1) : int(step & 1));
+  const bool arrest = uses_arrest(PASS) ? (uniform(hd.arrest) != 0) : false;
   const InstView<T> V = view_of<T>(a.B, a.cf);
   double e_acc = 0.0, g_acc = 0.0;
   int nf = 0;
