@@ -493,19 +493,6 @@ int fused_layout_tile(int tile) {
   return tile == 1 ? 1 : 0;
 }
 
-// Workgroups of a fused launch: as many as are resident at once (one per CU
-// for 512-thread groups at two waves per SIMD, two for 256-thread groups; one
-// in FP64), each walking longer column segments, so no workgroup waits for a
-// free CU. On 4096^2 (64 x 16, FP32) this took the pass from 0.622 to 0.610 ms
-// against 2048 groups.
-
-template <class T>
-long fused_groups(int layout_tile) {
-  const int threads = (sizeof(T) == 4 && layout_tile == 0) ? 512 : 256;
-  const int waves_per_cu = 4 * FusedWaves<T>::value;
-  return kNumCUs * std::max(1, waves_per_cu * 64 / threads);
-}
-
 template <class T>
 void launch_fused(const ss_ctx* c, Run& r, hipStream_t s) {
   PassArgs<T> a = pass_args<T>(c);
@@ -513,11 +500,6 @@ void launch_fused(const ss_ctx* c, Run& r, hipStream_t s) {
   Layout L = c->L;
   const int lt = fused_layout_tile<T>(c->tile);
   set_tiles(L, c->Nx, c->Ny, lt);
-  const long groups = fused_groups<T>(lt);
-  if (L.nlaunch > groups) {
-    L.nlaunch = (int)groups;
-    L.seg = choose_seg(L.ntx, L.nty, L.nlaunch);
-  }
   a.ntx = L.ntx;
   a.nty = L.nty;
   a.seg = L.seg;

@@ -1172,6 +1172,13 @@ static __global__ void __launch_bounds__(256) settle_status(Link link, double h)
 // a2 is needed at the halo of S4's stencil, so it is recomputed on a ring of 2
 // around the tile from S2 staged with halo 4. Per site the pass reads 3 field
 // sets and writes 2, against 10 and 4 for P2, P3 and P4 run separately.
+// S3 needs nothing of the pass's own and is staged with S2; S4 lacks only a2, which
+// the thread that forms it adds in place. So the three gradients are two barriers
+// apart from the loads and each other, and the LDS holds three stage points. (With
+// phi, v, a1 and a2 staged, and S3 and S4 formed from them between barriers, 4096^2
+// Abelian Higgs FP32 took 768 us per step, now 673; 1024^2 56.6, now 50.7; chiral magnet
+// 54.6, now 44.6.) What bounds it is its registers: one 512-thread workgroup to a CU, at
+// 229 per lane; capped at 168 or 128 for more, it spills and takes twice as long.
 
 // Jets of one site from an LDS plane with row length LX, arithmetic as column_jets.
 template <class T, int LX, bool MIXED>
@@ -1220,27 +1227,24 @@ template <class T, int TH, int TX, int TY, int RY>
 __device__ __forceinline__ void tile_body_fused(const InstView<T>& V, int cur, bool arrest, int x0, int y0,
                                                 T* __restrict__ lds) {
   constexpr int C = NComp<TH>::value;
-  constexpr int AX = TX + 8, AY = TY + 8;   // A: S2 with halo 4, then S3 / S4 with halo 2
-  constexpr int BX = TX + 4, BY = TY + 4;   // B-shaped planes (tile plus halo 2)
+  constexpr int AX = TX + 8, AY = TY + 8;   // S2, halo 4
+  constexpr int BX = TX + 4, BY = TY + 4;   // S3 and S4, halo 2
   constexpr int NA = AX * AY, NB = BX * BY;
   constexpr int NT = TX * (TY / RY);
   constexpr int NRB = NB - TX * TY;         // ring of B around the tile
   constexpr int KRB = (NRB + NT - 1) / NT;
   constexpr bool MIXED = el_mixed(TH);
-  // LDS: A [C][AY][AX] | a2 [C][BY][BX] | phi [C][BY][BX] | v [C][BY][BX] | a1 [C][BY][BX]
-  T* sa[4];
+  // LDS: S2 [C][AY][AX] | S3 [C][BY][BX] | S4 [C][BY][BX], S4 without its force until
+  // phase 2 adds it
   T* s2[4];
-  T* sp[4];
-  T* sv[4];
-  T* s1[4];
+  T* s3[4];
+  T* s4[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     const int cc = c < C ? c : 0;
-    sa[c] = lds + cc * NA;
-    s2[c] = lds + C * NA + cc * NB;
-    sp[c] = lds + C * NA + C * NB + cc * NB;
-    sv[c] = lds + C * NA + 2 * C * NB + cc * NB;
-    s1[c] = lds + C * NA + 3 * C * NB + cc * NB;
+    s2[c] = lds + cc * NA;
+    s3[c] = lds + C * NA + cc * NB;
+    s4[c] = lds + C * NA + C * NB + cc * NB;
   }
   const int Nx = V.Nx, Ny = V.Ny;
   const long pitch = V.pitch, plane = V.plane;
@@ -1254,6 +1258,7 @@ __device__ __forceinline__ void tile_body_fused(const InstView<T>& V, int cur, b
   const double h = V.h;
   const T c1 = T(1.0 / (12.0 * h)), c2 = T(1.0 / (12.0 * h * h));
   const int tid = threadIdx.y * TX + threadIdx.x;
+  const unsigned tx = threadIdx.x;
   const int gi = x0 + threadIdx.x;
   // a 64-wide tile row is one wavefront: its row index is wave-uniform
   const int wy = (TX == 64) ? __builtin_amdgcn_readfirstlane((int)threadIdx.y) : (int)threadIdx.y;
@@ -1262,57 +1267,79 @@ __device__ __forceinline__ void tile_body_fused(const InstView<T>& V, int cur, b
   auto offs = [&](int x, int y) { return (long)(y + 2) * pitch + (x + 2); };
   auto in_pad = [&](int x, int y) { return x >= -2 && x <= Nx + 1 && y >= -2 && y <= Ny + 1; };
 
-  // ---- phase 1 (all global reads of the tile): phi, v on the tile plus halo 4,
-  // S2 = phi + dt/2 v -> A; raw phi, v and a1 on the tile plus halo 2 -> LDS
-  auto load_entry = [&](int idx) {
-    const int ly = idx / AX, lx = idx - ly * AX;
-    const int x = x0 - 4 + lx, y = y0 - 4 + ly;
-    const bool inb = ly >= 2 && ly < AY - 2 && lx >= 2 && lx < AX - 2;
-    const int ib = (ly - 2) * BX + (lx - 2);
-    T P[4] = {T(0), T(0), T(0), T(0)}, W[4] = {T(0), T(0), T(0), T(0)}, S[4] = {T(0), T(0), T(0), T(0)};
-    T A1[4] = {T(0), T(0), T(0), T(0)};
-    if (in_pad(x, y)) {
-      const long o = offs(x, y);
+  // ---- phase 1: phi, v on the tile plus halo 4 and a1 on the tile plus halo 2 are
+  // read; S2 = phi + dt/2 v, S3 = S2 + dt^2/4 a1 (of S2 before its normalisation) and
+  // phi + dt v of S4. Loads and arithmetic are apart, so that the loads of KB entries
+  // are in flight together: all of a tall tile's, two of a 64 x 8 tile's (measured).
+  constexpr int KA = (NA + NT - 1) / NT, KB = TY >= 16 ? KA : 2;
+  for (int k0 = 0; k0 < KA; k0 += KB) {
+    T P[KB][4], W[KB][4], R[KB][4];
+#pragma unroll
+    for (int k = 0; k < KB; ++k) {
+      const int idx = min(tid + (k0 + k) * NT, NA - 1);
+      const int ly = idx / AX, lx = idx - ly * AX;
+      const bool inb = ly >= 2 && ly < AY - 2 && lx >= 2 && lx < AX - 2;
+      // outside the padded lattice the nearest element is read and dropped below
+      const long o = offs(max(-2, min(x0 - 4 + lx, Nx + 1)), max(-2, min(y0 - 4 + ly, Ny + 1)));
 #pragma unroll
       for (int c = 0; c < C; ++c) {
-        P[c] = ph[c * plane + o];
-        W[c] = vv[c * plane + o];
-        if (inb) A1[c] = a1p[c * plane + o];
-        S[c] = P[c] + cv2 * W[c];
+        P[k][c] = ph[c * plane + o];
+        W[k][c] = vv[c * plane + o];
+        R[k][c] = T(0);
+        if (inb) R[k][c] = a1p[c * plane + o];
       }
-      if (unit_field(TH) && inside(x, y)) unit3(S);
     }
 #pragma unroll
-    for (int c = 0; c < C; ++c) sa[c][idx] = S[c];
-    if (inb) {
+    for (int k = 0; k < KB; ++k) {
+      const int idx = tid + (k0 + k) * NT;
+      if (idx >= NA) continue;
+      const int ly = idx / AX, lx = idx - ly * AX;
+      const int x = x0 - 4 + lx, y = y0 - 4 + ly;
+      const bool inb = ly >= 2 && ly < AY - 2 && lx >= 2 && lx < AX - 2;
+      const int ib = (ly - 2) * BX + (lx - 2);
+      const bool pad = in_pad(x, y), site = unit_field(TH) && inside(x, y);
+      T S[4] = {T(0), T(0), T(0), T(0)}, S3[4] = {T(0), T(0), T(0), T(0)}, S4[4] = {T(0), T(0), T(0), T(0)};
 #pragma unroll
       for (int c = 0; c < C; ++c) {
-        sp[c][ib] = P[c];
-        sv[c][ib] = W[c];
-        s1[c][ib] = A1[c];
+        const T p = pad ? P[k][c] : T(0), w = pad ? W[k][c] : T(0), a = pad ? R[k][c] : T(0);
+        S[c] = p + cv2 * w;
+        S3[c] = S[c] + ca3 * a;
+        S4[c] = p + cv4 * w;
+      }
+      if (site) {
+        unit3(S);
+        if (inb) unit3(S3);
+      }
+#pragma unroll
+      for (int c = 0; c < C; ++c) s2[c][idx] = S[c];
+      if (inb) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          s3[c][ib] = S3[c];
+          s4[c][ib] = S4[c];
+        }
       }
     }
-  };
-  // Tall tiles take one fully unrolled sweep (every load of the tile in flight
-  // at once); 64 x 8 tiles schedule better with two sweeps in flight (measured).
-  if constexpr (TY >= 16) {
-    constexpr int KA = (NA + NT - 1) / NT;
-#pragma unroll
-    for (int k = 0; k < KA; ++k)
-      if (tid + k * NT < NA) load_entry(tid + k * NT);
-  } else {
-#pragma unroll 2
-    for (int idx = tid; idx < NA; idx += NT) load_entry(idx);
   }
   __syncthreads();
 
-  // ---- phase 2: a2 = -G(S2) on the tile (column jets) and its ring (site jets); 0 off the interior
+  // ---- phase 2: a2 = -G(S2) on the tile (column jets, kept for phase 3) and its ring
+  // (site jets), 0 off the interior; S4 = phi + dt v + dt^2/2 a2 where it lies
+  auto add_force = [&](const T (&a)[4], int ib, bool in) {
+    T S[4] = {T(0), T(0), T(0), T(0)};
+#pragma unroll
+    for (int c = 0; c < C; ++c) S[c] = s4[c][ib] + ca4 * a[c];
+    if (unit_field(TH) && in) unit3(S);
+#pragma unroll
+    for (int c = 0; c < C; ++c) s4[c][ib] = S[c];
+  };
+  T a2[RY][4];
   {
     Jet<T> J[C][RY];
     double dx_[C][RY], dy_[C][RY];
 #pragma unroll
     for (int c = 0; c < C; ++c)
-      column_jets<T, AX, RY, MIXED, false>(sa[c], 4 + threadIdx.x, 4 + wy * RY, c1, c2, 0.0, J[c], dx_[c],
+      column_jets<T, AX, RY, MIXED, false>(s2[c], 4 + threadIdx.x, 4 + wy * RY, c1, c2, 0.0, J[c], dx_[c],
                                            dy_[c]);
 #pragma unroll
     for (int r = 0; r < RY; ++r) {
@@ -1322,9 +1349,9 @@ __device__ __forceinline__ void tile_body_fused(const InstView<T>& V, int cur, b
       T G[4] = {T(0), T(0), T(0), T(0)};
       site_gradient<T, TH>(Js, V, G);
       const bool in = inside(gi, y0 + wy * RY + r);
-      const int ib = (2 + wy * RY + r) * BX + 2 + threadIdx.x;
 #pragma unroll
-      for (int c = 0; c < C; ++c) s2[c][ib] = in ? -G[c] : T(0);
+      for (int c = 0; c < 4; ++c) a2[r][c] = in ? -G[c] : T(0);
+      add_force(a2[r], (2 + wy * RY + r) * BX + 2 + threadIdx.x, in);
     }
   }
 #pragma unroll
@@ -1342,48 +1369,43 @@ __device__ __forceinline__ void tile_body_fused(const InstView<T>& V, int cur, b
         const int cc = j & 3;
         bx = cc < 2 ? cc : BX - 4 + cc;
       }
-      T a[4] = {T(0), T(0), T(0), T(0)};
+      // off the interior the force is zero, and the stage point stands as it is
       if (inside(x0 - 2 + bx, y0 - 2 + by)) {
+        T a[4] = {T(0), T(0), T(0), T(0)};
         Jet<T> Js[4];
 #pragma unroll
-        for (int c = 0; c < C; ++c) site_jet<T, AX, MIXED>(sa[c], by + 2, bx + 2, c1, c2, Js[c]);
+        for (int c = 0; c < C; ++c) site_jet<T, AX, MIXED>(s2[c], by + 2, bx + 2, c1, c2, Js[c]);
         T G[4] = {T(0), T(0), T(0), T(0)};
         site_gradient<T, TH>(Js, V, G);
 #pragma unroll
         for (int c = 0; c < C; ++c) a[c] = -G[c];
+        add_force(a, by * BX + bx, true);
       }
+    }
+  }
+  // the own sites' inputs again, for the epilogue (from L2), while the barrier is waited for
+  T p0[RY][4], w0[RY][4], a1[RY][4];
 #pragma unroll
-      for (int c = 0; c < C; ++c) s2[c][by * BX + bx] = a[c];
+  for (int r = 0; r < RY; ++r) {
+    const int gj = y0 + wy * RY + r;
+    const long row = (long)(min(gj, Ny - 1) + 2) * pitch + (x0 + 2);
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      p0[r][c] = (ph + c * plane + row)[tx];
+      w0[r][c] = (vv + c * plane + row)[tx];
+      a1[r][c] = (a1p + c * plane + row)[tx];
     }
   }
   __syncthreads();
 
-  // stage point on the tile plus halo 2 -> A (offset 2): phi + cv v + ca acc
-  auto stage_b = [&](T cv, T ca, T* const (&acc)[4]) {
-#pragma unroll 1
-    for (int ib = tid; ib < NB; ib += NT) {
-      const int by = ib / BX, bx = ib - by * BX;
-      T S[4] = {T(0), T(0), T(0), T(0)};
-#pragma unroll
-      for (int c = 0; c < C; ++c) S[c] = sp[c][ib] + cv * sv[c][ib] + ca * acc[c][ib];
-      if (unit_field(TH) && inside(x0 - 2 + bx, y0 - 2 + by)) unit3(S);
-#pragma unroll
-      for (int c = 0; c < C; ++c) sa[c][(by + 2) * AX + bx + 2] = S[c];
-    }
-  };
-
-  // ---- phase 3: S3 = phi + dt/2 v + dt^2/4 a1
-  stage_b(cv2, ca3, s1);
-  __syncthreads();
-
-  // ---- phase 4: q = a1 + 2 a2 - 2 G(S3) at the own sites
-  T qo[RY][4];
+  // ---- phase 3: q = a1 + 2 a2 - 2 G(S3) and phi' at the own sites
+  T qo[RY][4], pn[RY][4];
   {
     Jet<T> J[C][RY];
     double dx_[C][RY], dy_[C][RY];
 #pragma unroll
     for (int c = 0; c < C; ++c)
-      column_jets<T, AX, RY, MIXED, false>(sa[c], 4 + threadIdx.x, 4 + wy * RY, c1, c2, 0.0, J[c], dx_[c],
+      column_jets<T, BX, RY, MIXED, false>(s3[c], 2 + threadIdx.x, 2 + wy * RY, c1, c2, 0.0, J[c], dx_[c],
                                            dy_[c]);
 #pragma unroll
     for (int r = 0; r < RY; ++r) {
@@ -1392,20 +1414,22 @@ __device__ __forceinline__ void tile_body_fused(const InstView<T>& V, int cur, b
       for (int c = 0; c < C; ++c) Js[c] = J[c][r];
       T G[4] = {T(0), T(0), T(0), T(0)};
       site_gradient<T, TH>(Js, V, G);
-      const int ib = (2 + wy * RY + r) * BX + 2 + threadIdx.x;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) qo[r][c] = T(0);
+      for (int c = 0; c < 4; ++c) qo[r][c] = pn[r][c] = T(0);
 #pragma unroll
-      for (int c = 0; c < C; ++c) qo[r][c] = s1[c][ib] + T(2) * s2[c][ib] - T(2) * G[c];
+      for (int c = 0; c < C; ++c) {
+        qo[r][c] = a1[r][c] + T(2) * a2[r][c] - T(2) * G[c];
+        // q is a value of its own in phi' and v': without this the compiler forms
+        // q + a1 from q's parts, which rounds otherwise
+        asm("" : "+v"(qo[r][c]));
+        w0[r][c] = arrest ? T(0) : w0[r][c];
+        pn[r][c] = p0[r][c] + dt * w0[r][c] + (dt * dt / T(12)) * (qo[r][c] + a1[r][c]);
+      }
+      if (unit_field(TH)) unit3(pn[r]);
     }
   }
-  __syncthreads();
 
-  // ---- phase 5: S4 = phi + dt v + dt^2/2 a2
-  stage_b(cv4, ca4, s2);
-  __syncthreads();
-
-  // ---- phase 6: a4 = -G(S4); phi', v' at the own sites
+  // ---- phase 4: a4 = -G(S4); v' at the own sites
   T* __restrict__ phn = cur ? V.phi[0] : V.phi[1];
   T* __restrict__ vn = cur ? V.vel[0] : V.vel[1];
   {
@@ -1413,7 +1437,7 @@ __device__ __forceinline__ void tile_body_fused(const InstView<T>& V, int cur, b
     double dx_[C][RY], dy_[C][RY];
 #pragma unroll
     for (int c = 0; c < C; ++c)
-      column_jets<T, AX, RY, MIXED, false>(sa[c], 4 + threadIdx.x, 4 + wy * RY, c1, c2, 0.0, J[c], dx_[c],
+      column_jets<T, BX, RY, MIXED, false>(s4[c], 2 + threadIdx.x, 2 + wy * RY, c1, c2, 0.0, J[c], dx_[c],
                                            dy_[c]);
 #pragma unroll
     for (int r = 0; r < RY; ++r) {
@@ -1424,25 +1448,19 @@ __device__ __forceinline__ void tile_body_fused(const InstView<T>& V, int cur, b
       for (int c = 0; c < C; ++c) Js[c] = J[c][r];
       T G[4] = {T(0), T(0), T(0), T(0)};
       site_gradient<T, TH>(Js, V, G);
-      const int ib = (2 + wy * RY + r) * BX + 2 + threadIdx.x;
-      T pn[4], vnew[4];
+      T vnew[4];
 #pragma unroll
-      for (int c = 0; c < C; ++c) {
-        const T v0 = arrest ? T(0) : sv[c][ib];
-        pn[c] = sp[c][ib] + dt * v0 + (dt * dt / T(12)) * (qo[r][c] + s1[c][ib]);
-        vnew[c] = v0 + (dt / T(6)) * (qo[r][c] - G[c]);
-      }
+      for (int c = 0; c < C; ++c) vnew[c] = w0[r][c] + (dt / T(6)) * (qo[r][c] - G[c]);
       if (unit_field(TH)) {
-        unit3(pn);
-        const T vd = vnew[0] * pn[0] + vnew[1] * pn[1] + vnew[2] * pn[2];
+        const T vd = vnew[0] * pn[r][0] + vnew[1] * pn[r][1] + vnew[2] * pn[r][2];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) vnew[c] -= vd * pn[c];
+        for (int c = 0; c < 3; ++c) vnew[c] -= vd * pn[r][c];
       }
-      const long o = offs(gi, gj);
+      const long row = (long)(gj + 2) * pitch + (x0 + 2);
 #pragma unroll
       for (int c = 0; c < C; ++c) {
-        __builtin_nontemporal_store(pn[c], &phn[c * plane + o]);
-        __builtin_nontemporal_store(vnew[c], &vn[c * plane + o]);
+        __builtin_nontemporal_store(pn[r][c], &(phn + c * plane + row)[tx]);
+        __builtin_nontemporal_store(vnew[c], &(vn + c * plane + row)[tx]);
       }
     }
   }
@@ -1461,7 +1479,7 @@ struct FusedWaves {
 template <class T, int TH, int TX, int TY>
 struct FusedLds {
   static constexpr int C = NComp<TH>::value;
-  static constexpr int value = C * ((TX + 8) * (TY + 8) + 4 * (TX + 4) * (TY + 4));
+  static constexpr int value = C * ((TX + 8) * (TY + 8) + 2 * (TX + 4) * (TY + 4));
 };
 
 template <class T, int TH, int TX, int TY, int RY>

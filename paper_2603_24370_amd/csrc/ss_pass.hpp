@@ -7,22 +7,21 @@
 
 namespace ss {
 
-// Workgroups of one stage-pass instantiation resident on the whole GPU at
-// once: the runtime's occupancy for one CU times the CUs. Queried once per
-// instantiation on the first device that launches it.
+// Workgroups of one kernel resident on the whole GPU at once: the runtime's occupancy
+// for one CU times the CUs.
+inline long resident_of(const void* kernel, int threads) {
+  int per_cu = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess || per_cu < 1) {
+    (void)hipGetLastError();  // a failed query must not surface as a launch error
+    return kMaxGroups;
+  }
+  return std::min(kMaxGroups, kNumCUs * per_cu);
+}
+
+// Of one stage-pass instantiation, queried once, on the first device that launches it.
 template <class T, int TH, int PASS, int TX, int TY, int RY>
 long resident_groups() {
-  static const long n = [] {
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per_cu, reinterpret_cast<const void*>(&stage_pass<T, TH, PASS, TX, TY, RY>), TX * (TY / RY), 0) !=
-            hipSuccess ||
-        per_cu < 1) {
-      (void)hipGetLastError();  // a failed query must not surface as a launch error
-      return kMaxGroups;
-    }
-    return std::min(kMaxGroups, kNumCUs * per_cu);
-  }();
+  static const long n = resident_of(reinterpret_cast<const void*>(&stage_pass<T, TH, PASS, TX, TY, RY>), TX * (TY / RY));
   return n;
 }
 
@@ -62,15 +61,25 @@ void launch_exact(const PassArgs<T>& a, int groups, hipStream_t s) {
   hipLaunchKernelGGL((stage_pass_exact<T, TH, PASS>), dim3(groups), dim3(kExTX, kExTY / kExRY), 0, s, a);
 }
 
+// The fused pass with at most its resident workgroups, each walking longer column
+// segments, so that none waits for a free CU.
+template <class T, int TH, int TY>
+void launch_fused_cfg(const PassArgs<T>& a, int nlaunch, hipStream_t s) {
+  static const long resident = resident_of(reinterpret_cast<const void*>(&stage_pass_fused<T, TH, 64, TY, 2>), 32 * TY);
+  PassArgs<T> b = a;
+  if (nlaunch > resident) {
+    nlaunch = (int)resident;
+    b.seg = choose_seg(a.ntx, a.nty, nlaunch);
+  }
+  hipLaunchKernelGGL((stage_pass_fused<T, TH, 64, TY, 2>), dim3(nlaunch), dim3(64, TY / 2), 0, s, b);
+}
+
 template <class T, int TH>
 void launch_fused_t(int layout_tile, const PassArgs<T>& a, int nlaunch, hipStream_t s) {
   if constexpr (sizeof(T) == 4) {
-    if (layout_tile == 0) {
-      hipLaunchKernelGGL((stage_pass_fused<T, TH, 64, 16, 2>), dim3(nlaunch), dim3(64, 8), 0, s, a);
-      return;
-    }
+    if (layout_tile == 0) return launch_fused_cfg<T, TH, 16>(a, nlaunch, s);
   }
-  hipLaunchKernelGGL((stage_pass_fused<T, TH, 64, 8, 2>), dim3(nlaunch), dim3(64, 4), 0, s, a);
+  launch_fused_cfg<T, TH, 8>(a, nlaunch, s);
 }
 
 template <class T, int TH, int PASS, int CFG>
