@@ -372,9 +372,9 @@ int ss_init_learned(ss_ctx* ctx, int n, const double* xy, const double* w, const
  *                       the update on a tile, recomputing stage 2 on a ring
  *                       of 2 around it (7 field sets per site and step).
  * All plans give the same step up to rounding order. The fused plans exist for
- * the Euler-Lagrange gradient only (SS_EINVAL otherwise). New FP32 contexts
- * with the Euler-Lagrange gradient start with SS_PLAN_FUSED, others with
- * SS_PLAN_STAGES. ss_set_plan synchronises the stream. */
+ * the Euler-Lagrange gradient only (SS_EINVAL otherwise). New contexts with
+ * the Euler-Lagrange gradient start with SS_PLAN_FUSED, others (and the BEC, and
+ * demagnetisation) with SS_PLAN_STAGES. ss_set_plan synchronises the stream. */
 #define SS_PLAN_STAGES 0
 #define SS_PLAN_FUSED 1
 #define SS_NUM_PLANS 2

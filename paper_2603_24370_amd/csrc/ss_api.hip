@@ -45,7 +45,10 @@ int fail(int code, const std::string& msg) {
   } while (0)
 
 constexpr int kDefaultTile = 0;
-constexpr int kDefaultPlanF32 = SS_PLAN_FUSED;
+// Where the fused pass exists it is the faster plan: us per RK4 step fused and in
+// stages, Abelian Higgs FP32 1024^2 51 / 87, FP64 128^2 18 / 21 and 1024^2 108 / 150,
+// chiral magnet FP64 2048^2 250 / 402.
+constexpr int kDefaultPlan = SS_PLAN_FUSED;
 static_assert(kTiles[0].TX == kExTX && kTiles[0].TY == kExTY, "the exact-gradient passes use the layout of tile 0");
 static_assert(kTiles[0].TX == 64 && kTiles[0].TY == 16 && kTiles[1].TX == 64 && kTiles[1].TY == 8,
               "the fused passes use the layouts of tiles 0 (64 x 16) and 1 (64 x 8)");
@@ -966,8 +969,7 @@ int ss_create(const char* theory, int Nx, int Ny, double h, const ss_params* par
     if (t >= 0 && t < kNumTiles) c->tile = t;
   }
   if (grad_mode == SS_GRAD_EXACT) c->tile = 0;
-  c->plan = (grad_mode == SS_GRAD_EL && dtype == SS_F32 && !pb.demag && th != SS_THEORY_BEC) ? kDefaultPlanF32
-                                                                                          : SS_PLAN_STAGES;
+  c->plan = (grad_mode == SS_GRAD_EL && !pb.demag && th != SS_THEORY_BEC) ? kDefaultPlan : SS_PLAN_STAGES;
   c->integ = SS_INTEG_RK4;
   apply_tile(c, c->tile);
   c->vv_form = SS_VV_AUTO;
