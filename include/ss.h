@@ -502,8 +502,9 @@ int ss_batch_flow_step(ss_batch* batch, int n_steps, ss_step_info* infos);
 int ss_batch_minimise(ss_batch* batch, const ss_stop* stop, ss_min_info* infos);
 int ss_batch_set_tile(ss_batch* batch, int tile);
 /* Plan of the batch's steps (SS_PLAN_*, default SS_PLAN_FUSED). The fused pass
- * runs on one tile shape, 64 x 16 (FP32) or 64 x 8 (FP64), i.e. tile 0 or 1;
- * with any other shape the batch runs separate stage passes. */
+ * runs on 64 x 16 or 64 x 8 sites in FP32 and on 64 x 8 in FP64, i.e. tile 0 or 1
+ * (tile 0 of a batch stands for 64 x 8 sites in FP64 and for the one-pass
+ * integrators); with any other shape the batch runs separate stage passes. */
 int ss_batch_set_plan(ss_batch* batch, int plan);
 int ss_batch_get_plan(ss_batch* batch);
 /* Integrator of the batch's steps (SS_INTEG_*, default SS_INTEG_RK4; Sec. 3.2),

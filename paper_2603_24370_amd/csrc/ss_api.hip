@@ -1807,7 +1807,9 @@ int ctx_shape(const ss_ctx* c, int* Nx, int* Ny, int* theory) {
 // ======================================================================= batch
 
 struct ss_batch {
-  int theory, dtype, C, n, tile;
+  int theory, dtype, C, n;
+  int tile;   // as selected
+  int shape;  // the compiled shape it stands for
   int plan;   // SS_PLAN_*; the fused pass runs on tiles 0 and 1 only (see batch_fused)
   int integ;  // SS_INTEG_*
   hipStream_t stream;
@@ -1883,6 +1885,15 @@ BatchInst<T> batch_inst_of(const ss_ctx* c, int unit0, int nunits) {
 // Workgroups of a batch launch (persistent, at most 8 per CU).
 int batch_nlaunch(const ss_batch* b) { return (int)std::min<long>(round_up(b->nunits_total, 8), kMaxGroups); }
 
+// The compiled shape behind tile 0 of a batch: 64 x 8 sites in FP64, where RK4's fused
+// pass runs on nothing else (64 members: 474 us per step, in stages on 64 x 16 639;
+// gradient flow 107 / 116), and for the one-pass integrators (256 members FP32: velocity
+// Verlet 336 / 380 us per step, gradient flow 180 / 190; the same bits). RK4 in FP32 keeps
+// 64 x 16 (749 / 768).
+int batch_shape(const ss_batch* b) {
+  return b->tile == 0 && (b->dtype == SS_F64 || b->integ != SS_INTEG_RK4) ? 1 : b->tile;
+}
+
 // (Re)build, for the batch's tile shape, the per-member tile and unit counts,
 // the units, the member descriptors and a full work list. Units are column
 // segments: seg is half the tile count per workgroup of the launch (two or
@@ -1891,14 +1902,16 @@ int batch_nlaunch(const ss_batch* b) { return (int)std::min<long>(round_up(b->nu
 // near-equal length, so that units differ little in work. A member's units are
 // numbered row-major over (segment row, tile column).
 int batch_build_tables(ss_batch* b) {
+  b->shape = batch_shape(b);
   b->ntiles_of.assign(b->n, 0);
   b->unit0_of.assign(b->n, 0);
   b->nunits_of.assign(b->n, 0);
   long tot = 0;
   for (int i = 0; i < b->n; ++i) {
     ss_ctx* c = b->members[i];
-    c->tile = c->shape = b->tile;  // the batch's launches run on the shape itself
-    set_tiles(c->L, c->Nx, c->Ny, b->tile);
+    c->tile = b->tile;
+    c->shape = b->shape;
+    set_tiles(c->L, c->Nx, c->Ny, b->shape);
     b->ntiles_of[i] = c->L.ntx * c->L.nty;
     tot += b->ntiles_of[i];
   }
@@ -1970,15 +1983,15 @@ void batch_launch(const ss_batch* b, hipStream_t s) {
   a.nwork = b->nwork;
   a.partials = b->partials;
   const int nlaunch = batch_nlaunch(b);
-  if (b->theory == SS_THEORY_AH) batch_launch_t<T, kAH, PASS>(b->tile, a, nlaunch, s);
-  else batch_launch_t<T, kCM, PASS>(b->tile, a, nlaunch, s);
+  if (b->theory == SS_THEORY_AH) batch_launch_t<T, kAH, PASS>(b->shape, a, nlaunch, s);
+  else batch_launch_t<T, kCM, PASS>(b->shape, a, nlaunch, s);
   if constexpr (reduces(PASS))
     hipLaunchKernelGGL((batch_finalise<T, PASS>), dim3(b->n), dim3(256), 0, s, a.inst, (const double*)b->partials);
 }
 
 template <class T>
 bool batch_fused(const ss_batch* b) {
-  return b->plan == SS_PLAN_FUSED && b->tile == fused_layout_tile<T>(b->tile);
+  return b->plan == SS_PLAN_FUSED && b->shape == fused_layout_tile<T>(b->shape);
 }
 
 template <class T>
@@ -1991,8 +2004,8 @@ void batch_launch_fused(const ss_batch* b, hipStream_t s) {
   a.partials = b->partials;
   const int nlaunch = batch_nlaunch(b);
   // the batch's tile is 64 x 16 (tile 0, FP32 only) or 64 x 8 (tile 1); see batch_fused
-  if (b->theory == SS_THEORY_AH) batch_launch_fused_t<T, kAH>(b->tile, a, nlaunch, s);
-  else batch_launch_fused_t<T, kCM>(b->tile, a, nlaunch, s);
+  if (b->theory == SS_THEORY_AH) batch_launch_fused_t<T, kAH>(b->shape, a, nlaunch, s);
+  else batch_launch_fused_t<T, kCM>(b->shape, a, nlaunch, s);
 }
 
 template <class T>
@@ -2250,6 +2263,7 @@ int ss_batch_set_integrator(ss_batch* b, int integ) {
     return fail(SS_EINVAL, "unknown integrator");
   SS_HIP(hipStreamSynchronize(b->stream));
   b->integ = integ;
+  if (b->shape != batch_shape(b)) return batch_build_tables(b);
   if (b->graph) {
     (void)hipGraphExecDestroy(b->graph);
     b->graph = nullptr;

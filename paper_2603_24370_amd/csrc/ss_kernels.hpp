@@ -1578,6 +1578,11 @@ __device__ __forceinline__ void for_each_item(int nwork, F&& body) {
   for (int w = xcd * per + q; w < wend; w += m) body(w);
 }
 
+template <bool COPY, class V>
+struct Held { typedef const V type; };
+template <class V>
+struct Held<false, V> { typedef const V& type; };
+
 template <class T, int TH, int PASS, int TX, int TY, int RY>
 __global__ void __launch_bounds__(TX*(TY / RY))
 __attribute__((amdgpu_waves_per_eu(StageWaves<T, TH, PASS, RY>::value))) batch_pass(BatchArgs<T> a) {
@@ -1599,12 +1604,17 @@ __attribute__((amdgpu_waves_per_eu(StageWaves<T, TH, PASS, RY>::value))) batch_p
     if (PASS != kVVEnd && st->done) return;
     if (PASS == kVVRestart && !st->arrest) return;
     const long long step = st->step;
-    const int cur = STAGED ? int((step - 1) & 1) : int(step & 1);
-    const bool arrest = uses_arrest(PASS) ? (st->arrest != 0) : false;
+    const int cur = uniform(STAGED ? int((step - 1) & 1) : int(step & 1));
+    const bool arrest = uses_arrest(PASS) ? (uniform(st->arrest) != 0) : false;
+    // The Abelian Higgs passes hold the descriptor, which the tiles' stores may alias
+    // (256 members FP32, velocity Verlet on 64 x 8: 351 us per step, 336 held); in the
+    // chiral magnet's FP32 passes that costs a wave per SIMD (385, 432).
+    typedef typename Held<TH == kAH, InstView<T>>::type View;
+    View V = I.V;
     double e_acc = 0.0, g_acc = 0.0;
     int nf = 0;
     for (int k = 0; k < U.n; ++k)
-      tile_body<T, TH, PASS, TX, TY, RY>(I.V, cur, arrest, nullptr, nullptr, 0, 0, U.tx * TX, (U.ty0 + k) * TY, k,
+      tile_body<T, TH, PASS, TX, TY, RY>(V, cur, arrest, nullptr, nullptr, 0, 0, U.tx * TX, (U.ty0 + k) * TY, k,
                                          k + 1 < U.n, lds, e_acc, g_acc, nf);
     if (!REDUCE) return;
     block_reduce3<NT>(e_acc, g_acc, nf, red);
@@ -1650,10 +1660,14 @@ batch_pass_fused(BatchArgs<T> a) {
     const BatchInst<T>& I = a.inst[U.inst];
     const DevStatus* __restrict__ st = I.st;
     if (st->done) return;
-    const int cur = int((st->step - 1) & 1);
-    const bool arrest = st->arrest != 0;
+    const int cur = uniform(int((st->step - 1) & 1));
+    const bool arrest = uniform(st->arrest) != 0;
+    // as batch_pass: held (256 members FP32, RK4, Abelian Higgs on 64 x 16 862 us per step,
+    // 768 held) but in the chiral magnet's tall tiles (665, 700)
+    typedef typename Held<TH == kAH || TY == 8, InstView<T>>::type View;
+    View V = I.V;
     for (int k = 0; k < U.n; ++k)
-      tile_body_fused<T, TH, TX, TY, RY>(I.V, cur, arrest, U.tx * TX, (U.ty0 + k) * TY, lds);
+      tile_body_fused<T, TH, TX, TY, RY>(V, cur, arrest, U.tx * TX, (U.ty0 + k) * TY, lds);
   });
 }
 

@@ -223,3 +223,39 @@ def test_one_pass_batch_minimise_stops_each_member_where_the_oracle_does(ss, orc
         steps.add(info_r["steps"])
     assert len(steps) > 1
     B.close()
+
+
+@pytest.mark.parametrize("integ", ["vv", "gf", "rk4"])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("theory", ["abelian_higgs", "chiral_magnet"])
+def test_default_tile_follows_the_integrator(ss, theory, dtype, integ):
+    """Tile 0 of a batch stands for 64 x 16 or 64 x 8 sites by type and integrator:
+    ragged members (a partial tile, a whole one, several), the integrator chosen
+    after the batch is built and changed once, against single contexts (FP64
+    1e-11, FP32 1e-5 of max|phi|: rounding order)."""
+    params = [1.0] if theory == "abelian_higgs" else [1.0, 1.0, 0.1, 0.6]
+    sizes, h, n = [(9, 65), (64, 64), (131, 37)], 0.17, 4
+    print(f"[case] batch default tile {theory} {dtype} {integ}", flush=True)
+    rel = 1e-11 if dtype == "f64" else 1e-5
+
+    def start(s):
+        if theory == "abelian_higgs":
+            s.init_vortices([(0.0, 0.0)], seed=3, noise_amp=1e-3)
+        else:
+            s.init_skyrmion(R=0.4, seed=3, noise_amp=1e-3)
+
+    B = ss.Batch(theory, [(nx, ny, h, params) for nx, ny in sizes], dtype=dtype)
+    B.set_integrator("rk4" if integ != "rk4" else "vv")
+    B.set_integrator(integ)
+    for m in B.members:
+        start(m)
+    B.flow_step(n)
+    for (nx, ny), m in zip(sizes, B.members):
+        s = ss.Solver(theory, nx, ny, h, params, dtype=dtype)
+        s.set_integrator(integ)
+        start(s)
+        s.flow_step(n)
+        a, b = m.get_field().double(), s.get_field().double()
+        assert (a - b).abs().max() <= rel * b.abs().max(), (nx, ny)
+        s.close()
+    B.close()
