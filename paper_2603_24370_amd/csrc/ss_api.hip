@@ -88,32 +88,32 @@ void set_tiles(Layout& L, int Nx, int Ny, int tile) {
 }
 
 // The compiled shape behind tile 0 of the Euler-Lagrange passes (us per step on
-// 64 x 4 / 64 x 8 / 64 x 16 sites):
+// 64 x 4 / 64 x 8 / 64 x 16 sites; 64 x 4 where it is compiled):
 //  - in FP64 64 x 4 with one row per thread, in FP32 64 x 8, where 64 x 16 would give
 //    at most kSmallTiles workgroups, that is where a pass takes as long as one of its
 //    workgroups: velocity Verlet on 128^2 FP64 8.4 / 9.9 / 11.4, on 256^2 FP32 (chiral
 //    magnet, 64 tiles of 64 x 16) - / 10.3 / 10.8; on 512^2 FP32 (256 tiles) - / 12.1 /
-//    11.3. One row per thread is FP64 only: the compiler contracts a single row's
-//    products in another order, which a flow's steps in FP32 carry to 1e-4 of its
-//    velocities; two rows in 128 threads took 11.6 on that 256^2;
-//  - 64 x 8 in FP64 from kWideSitesF64 sites: Abelian Higgs 1024^2 RK4 - / 144 / 150,
-//    2048^2 gradient flow - / 81 / 91, chiral magnet velocity Verlet - / 144 / 170; at
-//    700^2 the two are within 3% of each other, at 512^2 64 x 16 is ahead (chiral
-//    magnet RK4 - / 40.0 / 39.1);
-//  - 64 x 8 for velocity Verlet in FP32, and gradient flow of the chiral magnet,
-//    from kWideSites sites, where shorter units spread better: Abelian Higgs 4096^2
-//    - / 322 / 350, chiral magnet 1000^2 - / 30.7 / 34.5 and 2048^2 - / 100 / 122 (700^2
-//    - / 20.7 / 19.8). Baby Skyrme's, RK4's and the other gradient-flow passes are as
-//    fast or faster on 64 x 16.
-constexpr long kSmallTiles = 128, kWideSites = 800000, kWideSitesF64 = 400000;
+//    11.3 (before the wave reductions left LDS, 0.6 less each since). One row per thread
+//    is FP64 only: the compiler contracts a single row's products in another order,
+//    which a flow's steps in FP32 carry to 1e-4 of its velocities; two rows in 128
+//    threads took 11.6 on that 256^2;
+//  - 64 x 8 in FP64 from kWideSitesF64 sites: Abelian Higgs velocity Verlet 700^2
+//    - / 25.0 / 26.4, gradient flow 2048^2 - / 77 / 89, chiral magnet velocity Verlet
+//    - / 139 / 163; at 512^2 the two are alike;
+//  - 64 x 8 in FP32 for the chiral magnet's one-pass integrators from kWideSites sites
+//    (900^2 velocity Verlet - / 29.3 / 32.2, 2048^2 - / 92 / 115, gradient flow - / 48 / 70;
+//    alike at 700^2) and the Abelian Higgs velocity Verlet from kWideSitesAH (4096^2
+//    - / 299 / 310, alike at 2048^2, 1500^2 - / 52.7 / 50.0), where shorter units spread
+//    better. Baby Skyrme's and the other gradient-flow passes are alike on both.
+constexpr long kSmallTiles = 128, kWideSites = 800000, kWideSitesAH = 1L << 22, kWideSitesF64 = 400000;
 bool small_lattice(int Nx, int Ny) { return (long)((Nx + 63) / 64) * ((Ny + 15) / 16) <= kSmallTiles; }
 
 int default_shape(int theory, int dtype, int integ, int Nx, int Ny) {
   if (small_lattice(Nx, Ny)) return dtype == SS_F64 ? kSmallShape : 1;
   if (dtype == SS_F64) return (long)Nx * Ny >= kWideSitesF64 ? 1 : 0;
-  const bool vv = integ == SS_INTEG_VV && (theory == SS_THEORY_AH || theory == SS_THEORY_CM);
-  const bool gf = integ == SS_INTEG_GF && theory == SS_THEORY_CM;
-  return (vv || gf) && (long)Nx * Ny >= kWideSites ? 1 : 0;
+  const long n = (long)Nx * Ny;
+  if (theory == SS_THEORY_AH && integ == SS_INTEG_VV) return n >= kWideSitesAH ? 1 : 0;
+  return theory == SS_THEORY_CM && integ != SS_INTEG_RK4 && n >= kWideSites ? 1 : 0;
 }
 
 Layout make_layout(int C, int Nx, int Ny, int esize) {

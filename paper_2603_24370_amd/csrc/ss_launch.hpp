@@ -29,9 +29,10 @@ constexpr long kNumCUs = 256;
 // times one more than the workgroups that share a CU in it (two take less than twice
 // the time of one). Cut by the mean number of tiles per group, rounded down, an odd
 // lattice's units did not fit the groups: on 1000^2 (16 x 63 tiles) 336 units of 3 for
-// 256 groups, two rounds, 72.7 us per RK4 step; 256 units of 4 take 55.7. The other way
-// round, 528 tiles for 512 groups are best left single: gradient flow of baby Skyrme on
-// 1021 x 517 takes 22.6 us per step, in 272 units of 2 28.0.
+// 256 groups, two rounds, take 1.3 times as long per RK4 step as 256 units of 4 (72.7 and
+// 55.7 us with the fused pass of then). The other way round, 528 tiles for 512 groups are
+// best left single: gradient flow of baby Skyrme on 1021 x 517 takes 1.24 times as long
+// in 272 units of 2.
 inline int choose_seg(int ntx, int nty, int groups) {
   int best = nty;
   double best_cost = 1e300;
