@@ -311,7 +311,7 @@ void settle(const ss_ctx* c, Run& r, hipStream_t s) {
 
 int dm_groups(long n) { return (int)std::max<long>(1, std::min<long>((n + 255) / 256, 4096)); }
 
-int dm_tile_groups(const DmLevel& L) { return std::min(dm_tiles(L), kDmMaxGroups); }
+int dm_tile_groups(const DmLevel& L) { return std::min(dm_items(dm_tiles(L)), kDmMaxGroups); }
 
 bool dm_is_small(const ss_ctx::Demag& d, int l) { return dm_small_bytes(d.lv, d.nlev, l) <= kDmSmallLds; }
 
