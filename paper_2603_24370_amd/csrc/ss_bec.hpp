@@ -21,7 +21,7 @@
 //               stage point and its norm, else the sums of the step's constraint
 // that is 9 launches per RK4 step and 3 per step of the one-pass integrators (15 and
 // 6 with a launch for each of these; 256^2 sites FP32, RK4: 89 us per step then, 60
-// now). A small lattice's launch takes the latency of its chain (partials, their
+// with these alone). A small lattice's launch takes the latency of its chain (partials, their
 // sum, sites, a block sum), so the loads of a thread's first site are issued before
 // the sums that they wait for. All sums are FP64 per-workgroup partials added in
 // workgroup order, by every workgroup of the launch that needs the total.
@@ -53,7 +53,20 @@ struct BecBufs {
 // and v' projected (RK4); v' projected (velocity Verlet).
 enum BecEnd : int { kBecNone = 0, kBecScale = 1, kBecProject = 2 };
 
-#define BEC_SITES(n) for (long k_ = blockIdx.x * 256L + threadIdx.x; k_ < (n); k_ += (long)gridDim.x * 256L)
+// The block of 256 sites that a workgroup takes first, and whose place its partials
+// have: workgroups of one XCD (numbers that agree mod 8) take a band of the lattice's
+// first kBecGroups blocks, so that rows that neighbours share are in one L2. A
+// permutation of 0 .. kBecGroups - 1, so sums over partials keep their order. us per RK4
+// step in the order of the workgroups and in bands: 256^2 FP32 39 / 37, FP64 46 / 40, 512^2
+// FP32 61 / 49.
+__device__ __forceinline__ int bec_block(long n) {
+  const int nb = (int)min((long)kBecGroups, (n + 255) / 256), per = (nb + 7) / 8;
+  const int b = blockIdx.x, q = b >> 3;
+  return q < per ? (b & 7) * per + q : b;
+}
+
+#define BEC_SITES(n) \
+  for (long k_ = bec_block(n) * 256L + threadIdx.x; k_ < (n); k_ += (long)gridDim.x * 256L)
 
 // Sums of N values over 256 threads in a fixed order, for every thread. red: 4 N
 // doubles of LDS that nothing else uses.
@@ -165,7 +178,7 @@ __global__ void __launch_bounds__(256) bec_stage(Bufs<T> B, Coeffs cf, Link link
     }
   }
   bec_block_sums(acc, reds);
-  if (threadIdx.x == 0) W.ps[blockIdx.x] = acc[0];
+  if (threadIdx.x == 0) W.ps[bec_block(Wd * H)] = acc[0];
 }
 
 // The end of a run's last step, where no stage follows (no test is taken).
@@ -222,7 +235,8 @@ __global__ void __launch_bounds__(256) bec_grad(Bufs<T> B, Coeffs cf, Link link,
     }
   };
   const long step = (long)gridDim.x * 256L;
-  long k = blockIdx.x * 256L + threadIdx.x;
+  const int lb = bec_block(n);
+  long k = lb * 256L + threadIdx.x;
   if (k < n) load(k);
   if (PASS == kP2) {
     if (resolve(link, cf.h * cf.h, threadIdx.x, red).done) return;
@@ -291,7 +305,7 @@ __global__ void __launch_bounds__(256) bec_grad(Bufs<T> B, Coeffs cf, Link link,
   }
   bec_block_sums(sums, reds);
   if (threadIdx.x == 0) {
-    double* p = W.pg + 4 * (long)blockIdx.x;
+    double* p = W.pg + 4 * (long)lb;
 #pragma unroll
     for (int m = 0; m < 4; ++m) p[m] = sums[m];
   }
@@ -348,7 +362,8 @@ __global__ void __launch_bounds__(256) bec_apply(Bufs<T> B, Coeffs cf, Link link
     }
   };
   const long step = (long)gridDim.x * 256L;
-  long k = blockIdx.x * 256L + threadIdx.x;
+  const int lb = bec_block(n);
+  long k = lb * 256L + threadIdx.x;
   if (k < n) load(k);
   constexpr int NS = PASS == kP1 ? 3 : 2;
   double sg[NS];  // psi.G, psi.psi, energy
@@ -416,22 +431,22 @@ __global__ void __launch_bounds__(256) bec_apply(Bufs<T> B, Coeffs cf, Link link
   }
   if (THEN) {
     bec_block_sums(acc, reds);
-    if (threadIdx.x == 0) W.ps[blockIdx.x] = acc[0];
+    if (threadIdx.x == 0) W.ps[lb] = acc[0];
   }
   if (PASS == kP4 || PASS == kVVA) {
     bec_block_sums(sums, reds);
     if (threadIdx.x == 0) {
-      W.part[4 * (long)blockIdx.x] = sums[0];
-      W.part[4 * (long)blockIdx.x + 1] = sums[1];
+      W.part[4 * (long)lb] = sums[0];
+      W.part[4 * (long)lb + 1] = sums[1];
     }
   }
   if (reduces(PASS)) {
     const double m = bec_block_max(gm, redm);
     if (threadIdx.x == 0) {
-      double* p = partials + 4 * (long)blockIdx.x;
-      p[0] = W.pg[4 * (long)blockIdx.x + 2];
+      double* p = partials + 4 * (long)lb;
+      p[0] = W.pg[4 * (long)lb + 2];
       p[1] = m;
-      p[2] = W.pg[4 * (long)blockIdx.x + 3];
+      p[2] = W.pg[4 * (long)lb + 3];
     }
   }
 }
@@ -444,7 +459,7 @@ __global__ void __launch_bounds__(256) bec_obs(Bufs<T> B, Coeffs cf, const DevSt
   const double h = cf.h, d1 = 1.0 / (12.0 * h);
   double v[3] = {0.0, 0.0, 0.0};
   const long n = (long)B.Nx * B.Ny;
-  BEC_SITES(n) {
+  for (long k_ = blockIdx.x * 256L + threadIdx.x; k_ < n; k_ += (long)gridDim.x * 256L) {
     const int j = (int)(k_ / B.Nx), i = (int)(k_ - (long)j * B.Nx);
     const long o = (long)(j + 2) * B.pitch + (i + 2);
     double f[2], dx[2], dy[2];
