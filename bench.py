@@ -493,7 +493,12 @@ def traffic_record(pass_name, wl_name, tile):
         rec = json.load(fh)
     if rec.get("kernel_source") != kernel_source_hash():
         return None
-    return rec.get(wl_name, {}).get(f"tile{tile}", {}).get(pass_name)
+    by_tile = rec.get(wl_name, {})
+    found = by_tile.get(f"tile{tile}", {}).get(pass_name)
+    if found is None and tile == 0:
+        # tile 0 stands for 64 x 8 sites, tile 1's, in some passes; the counters name the shape that ran
+        found = by_tile.get("tile1", {}).get(pass_name)
+    return found
 
 
 def main():
