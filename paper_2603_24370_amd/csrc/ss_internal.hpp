@@ -406,9 +406,10 @@ __device__ __forceinline__ void sum_partials(const double* __restrict__ part, in
 }
 
 // The status as of this launch (Link), for every thread of a workgroup of at
-// least 256. h2 = h^2 of the lattice. red: 12 doubles of LDS, free again after
-// the workgroup's next barrier. Its loads are independent of each other, so the
-// launch waits for memory once.
+// least 256. h2 = h^2 of the lattice. red: 12 doubles of LDS that nothing else uses:
+// they are read after the last barrier here, and a workgroup without work has no
+// other before it sums its own values. Its loads are independent of each other, so
+// the launch waits for memory once.
 __device__ __forceinline__ Head resolve(const Link& L, double h2, int tid, double* red) {
   Head h = load_head(L.in);
   if (L.kind < 0) return h;

@@ -1111,11 +1111,12 @@ __attribute__((amdgpu_waves_per_eu(StageWaves<T, TH, PASS, RY>::value))) stage_p
   constexpr bool AFTER_P1 = (PASS == kP2 || PASS == kP3 || PASS == kP4);
   __shared__ __align__(16) T lds[TileLds<T, TH, PASS, TX, TY>::size];
   __shared__ double red[3 * (NT / 64)];
+  __shared__ double pend[12];  // the pending test's; a workgroup without a tile has no barrier between the two
 
   // a finished flow skips its remaining passes; velocity Verlet's end of run
   // converts the velocity whatever the status, and its restart runs only after
   // an arrest
-  const Head hd = pass_head<PASS>(a, threadIdx.y * TX + threadIdx.x, red);
+  const Head hd = pass_head<PASS>(a, threadIdx.y * TX + threadIdx.x, pend);
   if (PASS != kEval && PASS != kVVEnd && hd.done) return;
   if (PASS == kVVRestart && !hd.arrest) return;
   const long long step = hd.step;
@@ -1509,11 +1510,12 @@ __global__ void __launch_bounds__(256) stage_pass_exact(PassArgs<T> a) {
   constexpr bool AFTER_P1 = (PASS == kP2 || PASS == kP3 || PASS == kP4);
   __shared__ __align__(16) T lds[NLDS];
   __shared__ double red[3 * (NT / 64)];
+  __shared__ double pend[12];  // the pending test's; a workgroup without a tile has no barrier between the two
 
   // a finished flow skips its remaining passes; velocity Verlet's end of run
   // converts the velocity whatever the status, and its restart runs only after
   // an arrest
-  const Head hd = pass_head<PASS>(a, threadIdx.y * kExTX + threadIdx.x, red);
+  const Head hd = pass_head<PASS>(a, threadIdx.y * kExTX + threadIdx.x, pend);
   if (PASS != kEval && PASS != kVVEnd && hd.done) return;
   if (PASS == kVVRestart && !hd.arrest) return;
   const long long step = hd.step;
