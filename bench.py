@@ -271,7 +271,7 @@ def run_batch(args, wl):
            "roofline": {"bound": "hbm", "achieved": round(step_gbps, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                         "frac": round(step_gbps / HBM_PEAK_GBS, 4), "traffic": None, "step_sets": step_sets,
                         "kernel": kname},
-           "tile": {"chosen": list(ss_tile(tune[0])) if tune else None,
+           "tile": {"chosen": list(ss.ss_batch_get_shape(B.batch)) if tune else None,
                     "plan": "one pass" if one_pass else PLAN_NAMES[batch_plan],
                     "step_ms_by_plan_and_tile": {PLAN_NAMES[p]: [round(x, 4) for x in row]
                                                  for p, row in enumerate(tune[2])} if tune else None},
@@ -330,9 +330,11 @@ def run_converge(args):
     print(json.dumps(out), flush=True)
 
 
-def ss_tile(i):
+def shape_index(ctx):
+    """Index of the context's shape among the library's tiles (None: none of them)."""
     import paper_2603_24370_amd as ss
-    return ss.ss_tile_shape(i)
+    shape = ss.ss_get_shape(ctx)
+    return next((t for t in range(ss.ss_tile_count()) if ss.ss_tile_shape(t) == shape), None)
 
 
 STAGE_SOURCES = ["ss_internal.hpp", "ss_theory.hpp", "ss_kernels.hpp", "ss_launch.hpp", "ss_pass.hpp", "ss_api.hip"]
@@ -493,12 +495,7 @@ def traffic_record(pass_name, wl_name, tile):
         rec = json.load(fh)
     if rec.get("kernel_source") != kernel_source_hash():
         return None
-    by_tile = rec.get(wl_name, {})
-    found = by_tile.get(f"tile{tile}", {}).get(pass_name)
-    if found is None and tile == 0:
-        # tile 0 stands for 64 x 8 sites, tile 1's, in some passes; the counters name the shape that ran
-        found = by_tile.get("tile1", {}).get(pass_name)
-    return found
+    return rec.get(wl_name, {}).get(f"tile{tile}", {}).get(pass_name)
 
 
 def main():
@@ -599,7 +596,7 @@ def main():
         step_sets = STEP_SETS if plan == 0 else STEP_SETS_FUSED
     step_gbps = step_sets * C * b * sites / (ms_step * 1e-3) / 1e9
     # the counter record covers the Euler-Lagrange kernels only
-    tr = traffic_record(dom, args.workload, ss.ss_get_tile(s.ctx)) if args.grad == "el" else None
+    tr = traffic_record(dom, args.workload, shape_index(s.ctx)) if args.grad == "el" else None
     tr_gb = tr["total_GB"] if tr else None
     kname = {"P234": "stage_pass_fused (stages 2-4)", "VV": "stage_pass (velocity Verlet step, half-step form)",
              "VVA": "stage_pass (velocity Verlet step, stored force)",
@@ -640,7 +637,7 @@ def main():
                    "grad_form": "euler-lagrange" if args.grad == "el" else "exact",
                    "integrator": INTEGRATOR_NAMES[args.integrator], "parallelism": "single GPU"},
         "roofline": roof,
-        "tile": {"chosen": list(ss_tile(tune[0])) if tune else None,
+        "tile": {"chosen": list(ss.ss_get_shape(s.ctx)) if tune else None,
                  "plan": PLAN_NAMES[plan] if args.integrator == "rk4" else "one pass",
                  "step_ms_by_plan_and_tile": {PLAN_NAMES[p]: [round(x, 4) for x in row]
                                               for p, row in enumerate(tune[2])} if tune else None},

@@ -448,15 +448,19 @@ int ss_set_demag_iters(ss_ctx* ctx, int iters_flow, int iters_eval);
 
 /* Tile shapes of the stage kernels. The library carries ss_tile_count()
  * compiled shapes (a workgroup covers TX x TY sites, each thread RY rows of
- * one column); under a fused plan the shape applies to P1. Tile 0, the default,
- * stands for 64 x 4 (FP64) or 64 x 8 sites on lattices of at most 128 of its tiles,
- * and for 64 x 8 on large ones in FP64 and of the one-pass integrators. ss_set_tile selects
- * one for a context. ss_autotune times every plan with every shape over
+ * one column); under a fused plan the shape applies to P1. ss_set_tile selects
+ * one for a context. While none is selected (ss_get_tile: 0) the shape follows the
+ * lattice: 64 x 16, but 64 x 4 (FP64; none of the ss_tile_count() shapes) or 64 x 8
+ * sites on lattices of at most 128 tiles of 64 x 16, and 64 x 8 on large ones in FP64
+ * and of the one-pass integrators. ss_get_shape tells the shape that runs.
+ * ss_autotune times every plan with every shape over
  * n_steps flow steps of a uniform vacuum on the context's lattice, keeps the
  * fastest pair, writes the mean step times in ms_out (may be NULL, else
  * SS_NUM_PLANS * ss_tile_count() doubles, index plan * ss_tile_count() + tile;
  * -1 where a pair does not apply) and returns the chosen tile index (>= 0; the
- * plan is read with ss_get_plan). It overwrites the field: call ss_set_field
+ * plan is read with ss_get_plan). Where the unselected shape is none of the
+ * ss_tile_count() shapes it is timed too; if it is the fastest, no tile is selected, 0 is
+ * returned and the entry of tile 0 is its time. ss_autotune overwrites the field: call ss_set_field
  * or ss_init_ansatz afterwards. If the environment variable SS_AUTOTUNE_CACHE
  * names a file, ss_autotune first looks the problem (theory, dtype, gradient
  * form, Nx, Ny, compiled shapes, integrator, demagnetisation) up there and, if found, applies the stored
@@ -467,6 +471,7 @@ int ss_tile_count(void);
 int ss_tile_shape(int tile, int* tx, int* ty, int* ry);
 int ss_set_tile(ss_ctx* ctx, int tile);
 int ss_get_tile(ss_ctx* ctx);
+int ss_get_shape(ss_ctx* ctx, int* tx, int* ty, int* ry);
 int ss_autotune(ss_ctx* ctx, int n_steps, double* ms_out);
 
 /* ------------------------------------------------------------ batching
@@ -501,10 +506,12 @@ int ss_batch_flow_step(ss_batch* batch, int n_steps, ss_step_info* infos);
  * SS_OK if all converged, SS_NOT_CONVERGED if any hit max_steps. */
 int ss_batch_minimise(ss_batch* batch, const ss_stop* stop, ss_min_info* infos);
 int ss_batch_set_tile(ss_batch* batch, int tile);
+int ss_batch_get_shape(ss_batch* batch, int* tx, int* ty, int* ry);
 /* Plan of the batch's steps (SS_PLAN_*, default SS_PLAN_FUSED). The fused pass
- * runs on 64 x 16 or 64 x 8 sites in FP32 and on 64 x 8 in FP64, i.e. tile 0 or 1
- * (tile 0 of a batch stands for 64 x 8 sites in FP64 and for the one-pass
- * integrators); with any other shape the batch runs separate stage passes. */
+ * runs on 64 x 16 or 64 x 8 sites in FP32 and on 64 x 8 in FP64, i.e. tile 0 or 1;
+ * with any other shape the batch runs separate stage passes. While no tile is
+ * selected a batch runs on 64 x 8 sites in FP64 and with the one-pass integrators, on
+ * 64 x 16 with RK4 in FP32 (ss_batch_get_shape). */
 int ss_batch_set_plan(ss_batch* batch, int plan);
 int ss_batch_get_plan(ss_batch* batch);
 /* Integrator of the batch's steps (SS_INTEG_*, default SS_INTEG_RK4; Sec. 3.2),

@@ -79,10 +79,10 @@ EXPORTS = ["ss_theory_id", "ss_components", "ss_workspace_bytes", "ss_create", "
            "ss_init_ansatz", "ss_time_passes",
            "ss_get_field", "ss_energy_grad", "ss_flow_step", "ss_minimise", "ss_observables", "ss_get_info",
            "ss_status_string", "ss_last_error", "ss_gl_lambda_from_kappa", "ss_tile_count", "ss_tile_shape",
-           "ss_set_tile", "ss_get_tile", "ss_autotune", "ss_set_plan", "ss_get_plan", "ss_batch_workspace_bytes",
+           "ss_set_tile", "ss_get_tile", "ss_get_shape", "ss_autotune", "ss_set_plan", "ss_get_plan", "ss_batch_workspace_bytes",
            "ss_batch_create",
            "ss_batch_destroy", "ss_batch_member", "ss_batch_size", "ss_batch_flow_step", "ss_batch_minimise",
-           "ss_batch_set_tile", "ss_batch_autotune", "ss_batch_set_plan", "ss_batch_get_plan", "ss_batch_observables", "ss_set_energy_target", "ss_learned_input",
+           "ss_batch_set_tile", "ss_batch_get_shape", "ss_batch_autotune", "ss_batch_set_plan", "ss_batch_get_plan", "ss_batch_observables", "ss_set_energy_target", "ss_learned_input",
            "ss_learned_targets", "ss_init_learned", "ss_state_bytes", "ss_get_state", "ss_set_state",
            "ss_energy_grad_noalloc", "ss_set_integrator", "ss_get_integrator", "ss_workspace_bytes_for",
            "ss_set_demag_iters", "ss_batch_set_integrator", "ss_batch_get_integrator", "ss_set_vv_form",
@@ -141,6 +141,7 @@ def lib():
     L.ss_tile_shape.argtypes = [i, ip, ip, ip]
     L.ss_set_tile.argtypes = [vp, i]
     L.ss_get_tile.argtypes = [vp]
+    L.ss_get_shape.argtypes = [vp, ip, ip, ip]
     L.ss_autotune.argtypes = [vp, i, dp]
     L.ss_set_plan.argtypes = [vp, i]
     L.ss_set_integrator.argtypes = [vp, i]
@@ -159,6 +160,7 @@ def lib():
     L.ss_batch_flow_step.argtypes = [vp, i, ctypes.POINTER(ss_step_info)]
     L.ss_batch_minimise.argtypes = [vp, ctypes.POINTER(ss_stop), ctypes.POINTER(ss_min_info)]
     L.ss_batch_set_tile.argtypes = [vp, i]
+    L.ss_batch_get_shape.argtypes = [vp, ip, ip, ip]
     L.ss_batch_autotune.argtypes = [vp, i, dp]
     L.ss_batch_set_plan.argtypes = [vp, i]
     L.ss_batch_get_plan.argtypes = [vp]
@@ -340,6 +342,13 @@ def ss_get_tile(ctx) -> int:
     return _check_nonneg(lib().ss_get_tile(ctx))
 
 
+def ss_get_shape(ctx):
+    """(TX, TY, rows per thread) of the stage passes that the context runs."""
+    tx, ty, ry = ctypes.c_int(), ctypes.c_int(), ctypes.c_int()
+    _check(lib().ss_get_shape(ctx, ctypes.byref(tx), ctypes.byref(ty), ctypes.byref(ry)))
+    return tx.value, ty.value, ry.value
+
+
 def ss_set_plan(ctx, plan: int):
     _check(lib().ss_set_plan(ctx, plan))
 
@@ -443,6 +452,12 @@ def ss_batch_minimise(batch, n_members, grad_tol=0.0, rel_e_tol=0.0, window=0, m
 
 def ss_batch_set_tile(batch, tile):
     _check(lib().ss_batch_set_tile(batch, tile))
+
+
+def ss_batch_get_shape(batch):
+    tx, ty, ry = ctypes.c_int(), ctypes.c_int(), ctypes.c_int()
+    _check(lib().ss_batch_get_shape(batch, ctypes.byref(tx), ctypes.byref(ty), ctypes.byref(ry)))
+    return tx.value, ty.value, ry.value
 
 
 def ss_batch_set_plan(batch, plan: int):

@@ -87,7 +87,7 @@ void set_tiles(Layout& L, int Nx, int Ny, int tile) {
   L.seg = choose_seg(L.ntx, L.nty, L.nlaunch);
 }
 
-// The compiled shape behind tile 0 of the Euler-Lagrange passes (us per step on
+// The shape of the Euler-Lagrange passes where no tile is selected (us per step on
 // 64 x 4 / 64 x 8 / 64 x 16 sites; 64 x 4 where it is compiled):
 //  - in FP64 64 x 4 with one row per thread, in FP32 64 x 8, where 64 x 16 would give
 //    at most kSmallTiles workgroups, that is where a pass takes as long as one of its
@@ -178,8 +178,9 @@ struct ss_ctx {
   double* partials2;  // the other partials
   hipGraphExec_t graph;
   int graph_steps;
-  int tile;   // as selected
-  int shape;  // the compiled shape it stands for (L is cut for it)
+  int tile;       // as selected, or kDefaultTile
+  bool selected;  // a tile was (ss_set_tile, SS_TILE, the autotuner): it is the shape
+  int shape;      // the compiled shape that runs (L is cut for it)
   int plan;   // SS_PLAN_*: how stages 2-4 of a step are launched
   int integ;  // SS_INTEG_*: the flow's integrator
   int vv_form;  // SS_VV_*: how velocity Verlet keeps its state between steps
@@ -205,11 +206,11 @@ struct ss_ctx {
 
 namespace {
 
-// Tile `tile` of a context: the shape it stands for, and the lattice cut for it.
-void apply_tile(ss_ctx* c, int tile) {
-  c->tile = tile;
-  c->shape = tile == 0 && c->grad_mode != SS_GRAD_EXACT
-                 ? default_shape(c->theory, c->dtype, c->integ, c->Nx, c->Ny) : tile;
+// The shape of a context, its selected tile's or the default rule's, and the lattice cut
+// for it.
+void apply_tile(ss_ctx* c) {
+  c->shape = c->selected || c->grad_mode == SS_GRAD_EXACT
+                 ? c->tile : default_shape(c->theory, c->dtype, c->integ, c->Nx, c->Ny);
   set_tiles(c->L, c->Nx, c->Ny, c->shape);
 }
 
@@ -964,14 +965,18 @@ int ss_create(const char* theory, int Nx, int Ny, double h, const ss_params* par
   c->graph = nullptr;
   c->graph_steps = 0;
   c->tile = kDefaultTile;
+  c->selected = false;
   if (const char* env = std::getenv("SS_TILE")) {
     const int t = std::atoi(env);
-    if (t >= 0 && t < kNumTiles) c->tile = t;
+    if (t >= 0 && t < kNumTiles) {
+      c->tile = t;
+      c->selected = true;
+    }
   }
   if (grad_mode == SS_GRAD_EXACT) c->tile = 0;
   c->plan = (grad_mode == SS_GRAD_EL && !pb.demag && th != SS_THEORY_BEC) ? kDefaultPlan : SS_PLAN_STAGES;
   c->integ = SS_INTEG_RK4;
-  apply_tile(c, c->tile);
+  apply_tile(c);
   c->vv_form = SS_VV_AUTO;
   c->ws_total = need;
   std::memset(&c->dm, 0, sizeof(c->dm));
@@ -1313,7 +1318,8 @@ int ss_energy_grad_noalloc(const char* theory, int Nx, int Ny, double h, const s
   c.courant = pb.courant;
   for (int k = 0; k < kNumParams; ++k) c.p[k] = pb.p[k];
   c.stream = (hipStream_t)stream;
-  apply_tile(&c, kDefaultTile);
+  c.tile = kDefaultTile;
+  apply_tile(&c);
   if (c.L.nlaunch > kMaxGroups) return fail(SS_ESHAPE, "more workgroup partials than the scratch array holds");
   c.st = (DevStatus*)sp;
   c.partials = (double*)((char*)sp + kScratchStatus);
@@ -1484,17 +1490,46 @@ int ss_observables(ss_ctx* c, ss_obs* out) {
   return rc ? rc : obs_collect(c, out);
 }
 
-int ss_set_tile(ss_ctx* c, int tile) {
-  if (!c) return fail(SS_EINVAL, "ctx is NULL");
-  if (tile < 0 || tile >= kNumTiles) return fail(SS_EINVAL, "tile index out of range");
-  if (c->grad_mode == SS_GRAD_EXACT && tile != 0) return fail(SS_EINVAL, "the exact-gradient passes use tile 0 only");
+}  // extern "C"
+
+namespace {
+
+// Selects a tile, or (kNoTile) leaves the shape to the default rule.
+constexpr int kNoTile = -1;
+int select_tile(ss_ctx* c, int tile) {
   SS_HIP(hipStreamSynchronize(c->stream));
-  apply_tile(c, tile);
+  c->selected = tile != kNoTile;
+  c->tile = c->selected ? tile : kDefaultTile;
+  apply_tile(c);
   if (c->graph) {
     (void)hipGraphExecDestroy(c->graph);
     c->graph = nullptr;
   }
   return SS_OK;
+}
+
+int shape_of(int shape, int* tx, int* ty, int* ry) {
+  if (!tx || !ty || !ry) return fail(SS_EINVAL, "NULL argument");
+  *tx = kTiles[shape].TX;
+  *ty = kTiles[shape].TY;
+  *ry = kTiles[shape].RY;
+  return SS_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+int ss_set_tile(ss_ctx* c, int tile) {
+  if (!c) return fail(SS_EINVAL, "ctx is NULL");
+  if (tile < 0 || tile >= kNumTiles) return fail(SS_EINVAL, "tile index out of range");
+  if (c->grad_mode == SS_GRAD_EXACT && tile != 0) return fail(SS_EINVAL, "the exact-gradient passes use tile 0 only");
+  return select_tile(c, tile);
+}
+
+int ss_get_shape(ss_ctx* c, int* tx, int* ty, int* ry) {
+  if (!c) return fail(SS_EINVAL, "ctx is NULL");
+  return shape_of(c->shape, tx, ty, ry);
 }
 
 int ss_set_plan(ss_ctx* c, int plan) {
@@ -1523,7 +1558,7 @@ int ss_set_integrator(ss_ctx* c, int integ) {
     return fail(SS_EINVAL, "unknown integrator");
   SS_HIP(hipStreamSynchronize(c->stream));
   c->integ = integ;
-  apply_tile(c, c->tile);
+  apply_tile(c);
   if (c->graph) {
     (void)hipGraphExecDestroy(c->graph);
     c->graph = nullptr;
@@ -1571,11 +1606,8 @@ int ss_set_demag_iters(ss_ctx* c, int iters_flow, int iters_eval) {
 int ss_tile_count(void) { return kNumTiles; }
 
 int ss_tile_shape(int tile, int* tx, int* ty, int* ry) {
-  if (tile < 0 || tile >= kNumTiles || !tx || !ty || !ry) return fail(SS_EINVAL, "bad tile query");
-  *tx = kTiles[tile].TX;
-  *ty = kTiles[tile].TY;
-  *ry = kTiles[tile].RY;
-  return SS_OK;
+  if (tile < 0 || tile >= kNumTiles) return fail(SS_EINVAL, "bad tile query");
+  return shape_of(tile, tx, ty, ry);
 }
 
 }  // extern "C"
@@ -1585,7 +1617,8 @@ namespace {
 // Autotune cache: a text file (path in SS_AUTOTUNE_CACHE) of lines
 // "theory dtype grad_mode Nx Ny tiles integrator plan tile", one per tuned problem; the
 // last line for a problem wins. "tiles" is the number of compiled tile shapes,
-// so entries from a library with other shapes are not used.
+// so entries from a library with other shapes are not used. Tile -1 (kNoTile): the
+// default rule's shape, where it is none of the caller's.
 std::string tune_key(const ss_ctx* c) {
   char buf[128];
   std::snprintf(buf, sizeof(buf), "%d %d %d %d %d %d %d %d", c->theory, c->dtype, c->grad_mode, c->Nx, c->Ny,
@@ -1607,7 +1640,7 @@ bool tune_lookup(const ss_ctx* c, int* plan, int* tile) {
       continue;
     char k[128];
     std::snprintf(k, sizeof(k), "%d %d %d %d %d %d %d %d", th, dt, gm, nx, ny, nt, ig, dm);
-    if (key == k && p >= 0 && p < SS_NUM_PLANS && t >= 0 && t < kNumTiles) {
+    if (key == k && p >= 0 && p < SS_NUM_PLANS && t >= kNoTile && t < kNumTiles) {
       *plan = p;
       *tile = t;
       found = true;
@@ -1642,9 +1675,9 @@ int ss_autotune(ss_ctx* c, int n_steps, double* ms_out) {
   if (tune_lookup(c, &cached_p, &cached_t)) {
     int rc = ss_set_plan(c, cached_p);
     if (rc) return rc;
-    rc = ss_set_tile(c, cached_t);
+    rc = select_tile(c, cached_t);
     if (rc) return rc;
-    return cached_t;  // nothing timed: ms_out stays -1 throughout
+    return c->tile;  // nothing timed: ms_out stays -1 throughout
   }
   // a uniform vacuum (psi = 1, A = 0; n = e_3) keeps every pass finite
   const double zero[2] = {0.0, 0.0};
@@ -1652,21 +1685,23 @@ int ss_autotune(ss_ctx* c, int n_steps, double* ms_out) {
   int rc = c->theory == SS_THEORY_AH ? ss_init_ansatz(c, SS_ANSATZ_VORTICES, 0, nullptr, nullptr, nullptr, 0, 0.0)
                                      : ss_init_ansatz(c, SS_ANSATZ_SKYRMION, 1, zero, nullptr, shape, 0, 0.0);
   if (rc) return rc;
-  int best_t = c->tile, best_p = c->plan;
+  int best_t = c->selected ? c->tile : kNoTile, best_p = c->plan;
   double best_ms = 1e300;
   const int nplans = c->dm.on ? 1 : SS_NUM_PLANS;
+  // the default rule's shape is a candidate of its own where it is none of the caller's
+  const bool own = default_shape(c->theory, c->dtype, c->integ, c->Nx, c->Ny) >= kNumTiles;
   for (int p = 0; p < nplans; ++p) {
     rc = ss_set_plan(c, p);
     if (rc) return rc;
-    for (int t = 0; t < kNumTiles; ++t) {
-      rc = ss_set_tile(c, t);
+    for (int t = own ? kNoTile : 0; t < kNumTiles; ++t) {
+      rc = select_tile(c, t);
       if (rc) return rc;
       double ms[5];
       rc = ss_time_passes(c, 2, ms);  // warm-up
       if (rc) return rc;
       rc = ss_time_passes(c, n_steps, ms);
       if (rc) return rc;
-      if (ms_out) ms_out[p * kNumTiles + t] = ms[4];
+      if (ms_out && t >= 0) ms_out[p * kNumTiles + t] = ms[4];
       if (ms[4] < best_ms) {
         best_ms = ms[4];
         best_t = t;
@@ -1676,10 +1711,11 @@ int ss_autotune(ss_ctx* c, int n_steps, double* ms_out) {
   }
   rc = ss_set_plan(c, best_p);
   if (rc) return rc;
-  rc = ss_set_tile(c, best_t);
+  rc = select_tile(c, best_t);
   if (rc) return rc;
+  if (ms_out && best_t == kNoTile) ms_out[best_p * kNumTiles + c->tile] = best_ms;
   tune_store(c, best_p, best_t);
-  return reset_state(c) ? SS_EHIP : best_t;
+  return reset_state(c) ? SS_EHIP : c->tile;
 }
 
 int ss_get_tile(ss_ctx* c) { return c ? c->tile : SS_EINVAL; }
@@ -1808,8 +1844,9 @@ int ctx_shape(const ss_ctx* c, int* Nx, int* Ny, int* theory) {
 
 struct ss_batch {
   int theory, dtype, C, n;
-  int tile;   // as selected
-  int shape;  // the compiled shape it stands for
+  int tile;       // as selected, or kDefaultTile
+  bool selected;  // a tile was (ss_batch_set_tile, SS_TILE, the autotuner): it is the shape
+  int shape;      // the compiled shape that runs
   int plan;   // SS_PLAN_*; the fused pass runs on tiles 0 and 1 only (see batch_fused)
   int integ;  // SS_INTEG_*
   hipStream_t stream;
@@ -1885,13 +1922,14 @@ BatchInst<T> batch_inst_of(const ss_ctx* c, int unit0, int nunits) {
 // Workgroups of a batch launch (persistent, at most 8 per CU).
 int batch_nlaunch(const ss_batch* b) { return (int)std::min<long>(round_up(b->nunits_total, 8), kMaxGroups); }
 
-// The compiled shape behind tile 0 of a batch: 64 x 8 sites in FP64, where RK4's fused
+// The shape of a batch where no tile is selected: 64 x 8 sites in FP64, where RK4's fused
 // pass runs on nothing else (64 members: 474 us per step, in stages on 64 x 16 639;
 // gradient flow 107 / 116), and for the one-pass integrators (256 members FP32: velocity
 // Verlet 336 / 380 us per step, gradient flow 180 / 190; the same bits). RK4 in FP32 keeps
 // 64 x 16 (749 / 768).
 int batch_shape(const ss_batch* b) {
-  return b->tile == 0 && (b->dtype == SS_F64 || b->integ != SS_INTEG_RK4) ? 1 : b->tile;
+  if (b->selected) return b->tile;
+  return b->dtype == SS_F64 || b->integ != SS_INTEG_RK4 ? 1 : 0;
 }
 
 // (Re)build, for the batch's tile shape, the per-member tile and unit counts,
@@ -1910,6 +1948,7 @@ int batch_build_tables(ss_batch* b) {
   for (int i = 0; i < b->n; ++i) {
     ss_ctx* c = b->members[i];
     c->tile = b->tile;
+    c->selected = b->selected;
     c->shape = b->shape;
     set_tiles(c->L, c->Nx, c->Ny, b->shape);
     b->ntiles_of[i] = c->L.ntx * c->L.nty;
@@ -2157,6 +2196,7 @@ int ss_batch_create(const char* theory, int n, const ss_instance* inst, int dtyp
   b->C = b->theory == SS_THEORY_AH ? 4 : 3;
   b->n = n;
   b->tile = kDefaultTile;
+  b->selected = false;
   b->plan = SS_PLAN_FUSED;
   b->integ = SS_INTEG_RK4;
   b->stream = (hipStream_t)stream;
@@ -2205,7 +2245,10 @@ int ss_batch_create(const char* theory, int n, const ss_instance* inst, int dtyp
   }
   if (const char* env = std::getenv("SS_TILE")) {
     const int tl = std::atoi(env);
-    if (tl >= 0 && tl < kNumTiles) b->tile = tl;
+    if (tl >= 0 && tl < kNumTiles) {
+      b->tile = tl;
+      b->selected = true;
+    }
   }
   rc = batch_build_tables(b);
   if (rc) {
@@ -2240,7 +2283,13 @@ int ss_batch_set_tile(ss_batch* b, int tile) {
   if (tile < 0 || tile >= kNumTiles) return fail(SS_EINVAL, "tile index out of range");
   SS_HIP(hipStreamSynchronize(b->stream));
   b->tile = tile;
+  b->selected = true;
   return batch_build_tables(b);
+}
+
+int ss_batch_get_shape(ss_batch* b, int* tx, int* ty, int* ry) {
+  if (!b) return fail(SS_EINVAL, "batch is NULL");
+  return shape_of(b->shape, tx, ty, ry);
 }
 
 int ss_batch_set_plan(ss_batch* b, int plan) {

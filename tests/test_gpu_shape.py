@@ -1,0 +1,105 @@
+"""The shape that a context or a batch runs: a selected tile is the shape that it is reported as, at
+every lattice size; while none is selected the default rule's applies (include/ss.h)."""
+import numpy as np
+import pytest
+
+from paper_2603_24370_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+AH = "abelian_higgs"
+
+
+@pytest.fixture(scope="module")
+def ss():
+    import torch
+    assert torch.cuda.is_available()
+    import paper_2603_24370_amd as m
+    m.lib()
+    return m
+
+
+def _np(t):
+    return t.double().cpu().numpy()
+
+
+# lattices on which the default rule has 64 x 4, 64 x 8 and 64 x 16 sites
+@pytest.mark.parametrize("dtype,Nx,Ny,default", [("f64", 150, 37, (64, 4, 1)), ("f32", 150, 37, (64, 8, 2)),
+                                                 ("f64", 700, 573, (64, 8, 2)), ("f32", 555, 230, (64, 16, 2))])
+@pytest.mark.parametrize("integ", ["vv", "rk4"])
+def test_a_selected_tile_is_the_shape_that_runs(ss, orc, dtype, Nx, Ny, default, integ):
+    h, n = 0.2, 2
+    f = I.ah_vortex_ansatz(Nx, Ny, h, [(0.4, -0.3)]) + I.noise(7, 4, Nx, Ny, 1e-3)
+    if dtype == "f32":
+        f = f.astype(np.float32).astype(np.float64)
+    phi_r = orc.flow(AH, f, np.zeros_like(f), h, [1.0], n, scheme=integ)[0]
+    rel = 1e-11 if dtype == "f64" else 1e-5
+    print(f"[case] selected tiles {dtype} {integ} {Nx}x{Ny}", flush=True)
+    s = ss.Solver(AH, Nx, Ny, h, [1.0], dtype=dtype)
+    s.set_integrator(integ)
+    assert ss.ss_get_shape(s.ctx) == default and ss.ss_get_tile(s.ctx) == 0
+    for tile in range(ss.ss_tile_count()):
+        s.set_tile(tile)
+        s.set_integrator(integ)  # a selected tile stays
+        assert ss.ss_get_shape(s.ctx) == ss.ss_tile_shape(tile) and ss.ss_get_tile(s.ctx) == tile
+        s.set_field(f)
+        s.flow_step(n)
+        assert np.abs(_np(s.get_field()) - phi_r).max() <= rel * np.abs(phi_r).max(), tile
+    s.close()
+
+
+def test_the_environment_selects_tile_zero_as_well(ss, monkeypatch):
+    monkeypatch.setenv("SS_TILE", "0")
+    s = ss.Solver(AH, 64, 64, 0.2, [1.0], dtype="f64")
+    B = ss.Batch(AH, [(64, 64, 0.2, [1.0])], dtype="f64")
+    assert ss.ss_get_shape(s.ctx) == ss.ss_batch_get_shape(B.batch) == ss.ss_tile_shape(0) == (64, 16, 2)
+    B.close()
+    s.close()
+
+
+@pytest.mark.parametrize("dtype,integ,default", [("f64", "rk4", (64, 8, 2)), ("f32", "vv", (64, 8, 2)),
+                                                 ("f32", "rk4", (64, 16, 2))])
+def test_a_batch_runs_its_selected_tile(ss, orc, dtype, integ, default):
+    sizes, h, n = [(9, 65), (131, 37)], 0.2, 2
+    rel = 1e-11 if dtype == "f64" else 1e-5
+    print(f"[case] batch selected tiles {dtype} {integ}", flush=True)
+    fields = [I.ah_vortex_ansatz(nx, ny, h, [(0.1, -0.1)]) + I.noise(3, 4, nx, ny, 1e-3) for nx, ny in sizes]
+    if dtype == "f32":
+        fields = [f.astype(np.float32).astype(np.float64) for f in fields]
+    refs = [orc.flow(AH, f, np.zeros_like(f), h, [1.0], n, scheme=integ)[0] for f in fields]
+    B = ss.Batch(AH, [(nx, ny, h, [1.0]) for nx, ny in sizes], dtype=dtype)
+    B.set_integrator(integ)
+    assert ss.ss_batch_get_shape(B.batch) == default
+    for tile in range(ss.ss_tile_count()):
+        B.set_tile(tile)
+        B.set_integrator(integ)
+        assert ss.ss_batch_get_shape(B.batch) == ss.ss_tile_shape(tile)
+        for m, f in zip(B.members, fields):
+            m.set_field(f)
+        B.flow_step(n)
+        for m, r in zip(B.members, refs):
+            assert np.abs(_np(m.get_field()) - r).max() <= rel * np.abs(r).max(), tile
+    B.close()
+
+
+def test_autotune_keeps_the_unselected_shape_where_it_is_the_fastest(ss, tmp_path, monkeypatch):
+    """64 x 4 sites are none of the tiles: the tuner times them as well, and its file holds -1 for them."""
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("SS_AUTOTUNE_CACHE", str(cache))
+    s = ss.Solver(AH, 128, 128, 0.1, [1.0], dtype="f64")
+    s.set_integrator("vv")
+    best, plan, ms = s.autotune(3)
+    timed = [m for row in ms for m in row if m > 0]
+    stored = int(cache.read_text().split()[-1])
+    assert ms[plan][best] == min(timed) and len(timed) == 2 * ss.ss_tile_count()
+    assert ss.ss_get_shape(s.ctx) == ((64, 4, 1) if stored == -1 else ss.ss_tile_shape(stored))
+    assert ss.ss_get_tile(s.ctx) == best == max(stored, 0)
+    s.close()
+    key = cache.read_text().split()[:-1]
+    for tile in (-1, 0):
+        cache.write_text(" ".join(key + [str(tile)]) + "\n")
+        s = ss.Solver(AH, 128, 128, 0.1, [1.0], dtype="f64")
+        s.set_integrator("vv")
+        s.set_tile(2)
+        assert s.autotune(3)[0] == 0 == ss.ss_get_tile(s.ctx)
+        assert ss.ss_get_shape(s.ctx) == ((64, 4, 1) if tile == -1 else (64, 16, 2))
+        s.close()
