@@ -147,8 +147,10 @@ __global__ void __launch_bounds__(256) bec_stage(Bufs<T> B, Coeffs cf, Link link
   const int cur = uniform(int(hd.step & 1));
   T cv, ca;
   stage_coeffs<T, PASS>((T)cf.dt, PASS == kVVA && hd.arrest != 0, cv, ca);
-  T* __restrict__ phc = cur ? B.phi[1] : B.phi[0];
-  const T* __restrict__ ph = (PASS == kEval && src != nullptr) ? src : phc;
+  // phc is ph but for an evaluation of src: a site is read through the one and written
+  // through the other, so neither is __restrict__
+  T* phc = cur ? B.phi[1] : B.phi[0];
+  const T* ph = (PASS == kEval && src != nullptr) ? src : phc;
   T* __restrict__ vv = cur ? B.vel[1] : B.vel[0];
   // one-pass integrators: the current field's force in the buffer of the step's parity
   const T* __restrict__ aa = cur ? B.a2 : B.a1;
