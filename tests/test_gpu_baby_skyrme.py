@@ -98,6 +98,33 @@ def test_flow_tracks_the_oracle(ss, orc, dtype, how):
     s.close()
 
 
+# more than 128 tiles of 64 x 16 sites, where the default shape is 64 x 16 (555 x 230: 135
+# tiles; 1291 x 623: 819, so units of several tiles), and 64 x 8 in FP64 from 400000 sites
+@pytest.mark.parametrize("dtype,Nx,Ny,shape", [("f32", 555, 230, (64, 16, 2)), ("f64", 555, 230, (64, 16, 2)),
+                                               ("f32", 1291, 623, (64, 16, 2)), ("f64", 1291, 311, (64, 8, 2))])
+@pytest.mark.parametrize("integ", ["rk4", "vv", "gf"])
+def test_flow_on_larger_lattices(ss, orc, dtype, Nx, Ny, shape, integ):
+    """The default plan and shape, every site against the oracle (tolerances of the module)."""
+    h, n = 0.2, 3
+    print(f"[case] baby skyrme larger {integ} {dtype} {Nx}x{Ny}", flush=True)
+    f = _field(Nx, Ny, h, seed=Nx + Ny)
+    if dtype == "f32":
+        f = f.astype(np.float32).astype(np.float64)
+    s = ss.Solver(BS, Nx, Ny, h, P, dtype=dtype)
+    s.set_integrator(integ)
+    assert ss.ss_get_shape(s.ctx) == shape
+    s.set_field(f)
+    info = s.flow_step(n)
+    phi, vel = (_np(x) for x in s.get_field(velocity=True))
+    phi_r, v_r, E_r, na_r = orc.flow(BS, f, np.zeros_like(f), h, P, n, scheme=integ)
+    rel = 1e-11 if dtype == "f64" else 1e-5
+    assert np.abs(phi - phi_r).max() <= rel * np.abs(phi_r).max()
+    assert np.abs(vel - v_r).max() <= rel * max(np.abs(phi_r).max(), 1.0)
+    assert info["step"] == n and info["n_arrests"] == na_r
+    assert info["energy"] == pytest.approx(orc.energy(BS, phi, h, P), rel=1e-12)
+    s.close()
+
+
 def test_minimise_and_observables(ss, orc):
     """A baby skyrmion relaxed to ||G||_inf < 1e-5 in FP64 under velocity Verlet:
     the stop step equals the oracle's; the relaxed field has Berg-Luescher charge

@@ -167,6 +167,47 @@ def test_demag_flow_tracks_the_oracle(ss, orc, how):
     s.close()
 
 
+@pytest.mark.parametrize("dtype,how", [("f32", "vv"), ("f64", "vv"), ("f32", "rk4"), ("f64", "gf")])
+def test_demag_flow_on_more_tiles(ss, orc, dtype, how):
+    """132 tiles of 64 x 16 sites, where the stage passes run on that shape (and the solver
+    on 129 x 4 tiles of 16 x 16): with converged solves the oracle's flow, FP64 to 1e-9, FP32
+    to 1e-5 (rounding of the stored fields)."""
+    Nx, Ny, h, n = 2050, 57, 0.15, 2
+    print(f"[case] demag flow {how} {dtype} {Nx}x{Ny}", flush=True)
+    f = _anti(Nx, Ny, h, seed=11)
+    if dtype == "f32":
+        f = f.astype(np.float32).astype(np.float64)
+    s = _solver(ss, Nx, Ny, h, dtype, "heusler", True)
+    s.set_integrator(how)
+    assert ss.ss_get_shape(s.ctx) == (64, 16, 2)
+    s.set_demag_iters(30, 40)
+    s.set_field(f)
+    info = s.flow_step(n)
+    phi, vel = (_np(x) for x in s.get_field(velocity=True))
+    p = _oracle_params("heusler", True)
+    phi_r, v_r, _, na_r = orc.flow(CMX, f, np.zeros_like(f), h, p, n, scheme=how)
+    tol = 1e-9 if dtype == "f64" else 1e-5
+    assert np.abs(phi - phi_r).max() <= tol
+    assert np.abs(vel - v_r).max() <= tol
+    assert info["step"] == n and info["n_arrests"] == na_r
+    s.close()
+
+
+def test_demag_with_more_tiles_than_workgroups(ss, orc):
+    """2052 tiles of 16 x 16 sites: some of a launch's 2048 workgroups take a second one."""
+    Nx, Ny, h = 8201, 61, 0.15
+    print(f"[case] demag energy_grad f64 {Nx}x{Ny}", flush=True)
+    f = _anti(Nx, Ny, h, seed=12)
+    s = _solver(ss, Nx, Ny, h, "f64", "heusler", True)
+    s.set_field(f)
+    E, _, G = s.energy_grad()
+    p = _oracle_params("heusler", True)
+    G_ref = -orc.acceleration(CMX, f, h, p)
+    assert np.abs(_np(G) - G_ref).max() <= 1e-9 * np.abs(G_ref).max()
+    assert E == pytest.approx(orc.energy(CMX, f, h, p), rel=1e-11, abs=1e-12)
+    s.close()
+
+
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
 def test_warm_started_solves_track_the_converged_flow(ss, orc, dtype):
     """With the default two iterations per stage point (warm-started from the last
