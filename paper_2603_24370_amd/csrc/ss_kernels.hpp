@@ -1079,12 +1079,15 @@ __device__ __forceinline__ void finalise_status(DevStatus* st, double E, double 
 // launch that needs the status sums them in a fixed order (Link).
 // Waves per SIMD a stage pass is compiled for. The Abelian-Higgs one-pass
 // integrators in FP32 on two-row tiles are held to 128 VGPRs (four waves; 160
-// uncapped), so that two 512-thread workgroups share a CU, without spills; the
-// chiral magnet and four-row tiles would spill under that cap, and the other
-// passes fit it uncapped.
+// uncapped), so that two 512-thread workgroups share a CU, without spills; so is
+// the chiral magnet's start of a velocity Verlet run, which a batch's kernel
+// otherwise holds in 134 (256 members of 256^2 on 64 x 8 sites 370 us, 292 now; on
+// 64 x 16 451, 305). Four-row tiles and the chiral magnet's other one-pass
+// integrators would spill under that cap, and the other passes fit it uncapped.
 template <class T, int TH, int PASS, int RY>
 struct StageWaves {
-  static constexpr int value = (sizeof(T) == 4 && TH == 0 && RY == 2 && (advances_first(PASS) || PASS == kGD)) ? 4 : 1;
+  static constexpr bool cap = TH == kAH ? advances_first(PASS) || PASS == kGD : TH == kCM && PASS == kVVStart;
+  static constexpr int value = sizeof(T) == 4 && RY == 2 && cap ? 4 : 1;
 };
 
 // The status a pass starts from. An evaluation reads the current field's parity

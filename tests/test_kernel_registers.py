@@ -1,0 +1,53 @@
+"""Registers of the compiled lattice passes, from the metadata of the built library: where two
+workgroups of 512 threads (or four of 256) are meant to share a CU, a kernel holds 128 at most."""
+import os
+import re
+import shutil
+import struct
+import subprocess
+
+import pytest
+
+READELF = next((c for c in ("/opt/rocm/llvm/bin/llvm-readelf", shutil.which("llvm-readelf")) if c and os.path.exists(c)),
+               None)
+MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+def _code_objects(path):
+    """The device ELF images of a library: one bundle per source file, its entries (offset, size, target)."""
+    data = open(path, "rb").read()
+    for m in re.finditer(re.escape(MAGIC), data):
+        at = m.start() + len(MAGIC)
+        n, = struct.unpack_from("<Q", data, at)
+        if n > 8:
+            continue  # the text, not a bundle
+        at += 8
+        for _ in range(n):
+            off, size, idlen = struct.unpack_from("<QQQ", data, at)
+            target = data[at + 24:at + 24 + idlen].decode()
+            at += 24 + idlen
+            if "gfx950" in target and size:
+                yield data[m.start() + off:m.start() + off + size]
+
+
+def _registers(tmp_path):
+    import paper_2603_24370_amd as ss
+    ss.lib()
+    from paper_2603_24370_amd import build as b
+    out = {}
+    for k, image in enumerate(_code_objects(b.LIB)):
+        p = tmp_path / f"{k}.elf"
+        p.write_bytes(image)
+        notes = subprocess.run([READELF, "--notes", str(p)], capture_output=True, text=True, check=True).stdout
+        for kernel in notes.split("- .agpr_count:")[1:]:
+            name = re.search(r"\.name:\s+(\S+)", kernel).group(1)
+            out[name] = int(re.search(r"\.vgpr_count:\s+(\d+)", kernel).group(1))
+    return out
+
+
+@pytest.mark.skipif(READELF is None, reason="needs llvm-readelf")
+def test_a_batch_keeps_four_waves_per_simd(tmp_path):
+    """The FP32 passes of a batch on its default shapes (64 x 16 and 64 x 8 sites, two rows per thread)."""
+    regs = {n: v for n, v in _registers(tmp_path).items() if re.match(r"_ZN2ss10batch_passIfLi\d+ELi\d+ELi64ELi(16|8)ELi2EE", n)}
+    assert len(regs) == 2 * 2 * 11  # theories, shapes, passes
+    assert {n: v for n, v in regs.items() if v > 128} == {}
