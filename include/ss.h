@@ -511,7 +511,8 @@ int ss_batch_get_shape(ss_batch* batch, int* tx, int* ty, int* ry);
  * runs on 64 x 16 or 64 x 8 sites in FP32 and on 64 x 8 in FP64, i.e. tile 0 or 1;
  * with any other shape the batch runs separate stage passes. While no tile is
  * selected a batch runs on 64 x 8 sites in FP64 and with the one-pass integrators, on
- * 64 x 16 with RK4 in FP32 (ss_batch_get_shape). */
+ * 64 x 16 with RK4 in FP32 and with the chiral magnet's velocity Verlet in FP32 in
+ * batches of less than 4096 tiles of that shape (ss_batch_get_shape). */
 int ss_batch_set_plan(ss_batch* batch, int plan);
 int ss_batch_get_plan(ss_batch* batch);
 /* Integrator of the batch's steps (SS_INTEG_*, default SS_INTEG_RK4; Sec. 3.2),

@@ -1922,14 +1922,28 @@ BatchInst<T> batch_inst_of(const ss_ctx* c, int unit0, int nunits) {
 // Workgroups of a batch launch (persistent, at most 8 per CU).
 int batch_nlaunch(const ss_batch* b) { return (int)std::min<long>(round_up(b->nunits_total, 8), kMaxGroups); }
 
-// The shape of a batch where no tile is selected: 64 x 8 sites in FP64, where RK4's fused
-// pass runs on nothing else (64 members: 474 us per step, in stages on 64 x 16 639;
-// gradient flow 107 / 116), and for the one-pass integrators (256 members FP32: velocity
-// Verlet 336 / 380 us per step, gradient flow 180 / 190; the same bits). RK4 in FP32 keeps
-// 64 x 16 (749 / 768).
+// The shape of a batch where no tile is selected (us per step on 64 x 8 / 64 x 16 sites):
+//  - 64 x 8 in FP64, where RK4's fused pass runs on nothing else (64 members: 474, in
+//    stages on 64 x 16 639; gradient flow 107 / 116);
+//  - 64 x 8 for the one-pass integrators in FP32 (256 members: velocity Verlet 336 / 380,
+//    gradient flow 180 / 190; the same bits), but for the chiral magnet's velocity Verlet
+//    in batches of less than kWideBatch tiles of 64 x 16, where the last round of 64 x 8
+//    workgroups is the emptier one: 4 members of 512^2 (1024 tiles) 33.5 / 32.0, 2 of
+//    1024^2 (2048) 59.8 / 56.8, 48 of 200^2 (2496) 70.5 / 68.3, 120 of 24 to 300 sites a
+//    side (3394) 96.8 / 93.7; above, 64 of 256^2 (4096) 102.9 / 107.8, 300 of 128^2 (4800)
+//    129 / 137;
+//  - 64 x 16 for RK4 in FP32, the faster one for batches of that size (4 members of 512^2
+//    65.3 / 60.9, 64 of 128^2 65.4 / 62.5) but not for large ones (64 of 256^2 207 / 219,
+//    256 of 256^2 777 / 838), which the autotuner finds.
+constexpr long kWideBatch = 4096;
 int batch_shape(const ss_batch* b) {
   if (b->selected) return b->tile;
-  return b->dtype == SS_F64 || b->integ != SS_INTEG_RK4 ? 1 : 0;
+  if (b->dtype == SS_F64) return 1;
+  if (b->integ == SS_INTEG_RK4) return 0;
+  if (b->theory != SS_THEORY_CM || b->integ != SS_INTEG_VV) return 1;
+  long tiles = 0;
+  for (const ss_ctx* c : b->members) tiles += (long)((c->Nx + 63) / 64) * ((c->Ny + 15) / 16);
+  return tiles >= kWideBatch ? 1 : 0;
 }
 
 // (Re)build, for the batch's tile shape, the per-member tile and unit counts,

@@ -103,3 +103,28 @@ def test_autotune_keeps_the_unselected_shape_where_it_is_the_fastest(ss, tmp_pat
         assert s.autotune(3)[0] == 0 == ss.ss_get_tile(s.ctx)
         assert ss.ss_get_shape(s.ctx) == ((64, 4, 1) if tile == -1 else (64, 16, 2))
         s.close()
+
+
+# the chiral magnet's velocity Verlet in FP32: 64 x 16 below 4096 tiles of that shape
+@pytest.mark.parametrize("dtype,integ,members,default", [("f32", "vv", 2, (64, 16, 2)), ("f32", "vv", 32, (64, 8, 2)),
+                                                         ("f32", "vv", 31, (64, 16, 2)), ("f32", "gf", 2, (64, 8, 2)),
+                                                         ("f64", "vv", 2, (64, 8, 2))])
+def test_a_chiral_magnet_batch_runs_the_faster_shape(ss, orc, dtype, integ, members, default):
+    h, n, par = 0.2, 2, [1.0, 1.0, 0.1, 0.6]
+    sizes = [(131, 37)] + [(64, 2048)] * (members - 1) + [(64, 16 * (128 - 9))]  # 9 tiles, 128 each, 119
+    rel = 1e-11 if dtype == "f64" else 1e-5
+    print(f"[case] chiral magnet batch {dtype} {integ} {members}", flush=True)
+    f = I.renormalise_interior(I.cm_skyrmion_ansatz(131, 37, h, R=1.0) + I.noise(3, 3, 131, 37, 1e-3))
+    if dtype == "f32":
+        f = f.astype(np.float32).astype(np.float64)
+    ref = orc.flow("chiral_magnet", f, np.zeros_like(f), h, par, n, scheme=integ)[0]
+    B = ss.Batch("chiral_magnet", [(nx, ny, h, par) for nx, ny in sizes], dtype=dtype)
+    assert ss.ss_batch_get_shape(B.batch) == ((64, 16, 2) if dtype == "f32" else (64, 8, 2))  # RK4
+    B.set_integrator(integ)
+    assert ss.ss_batch_get_shape(B.batch) == default
+    B.members[0].set_field(f)
+    for m in B.members[1:]:
+        m.init_skyrmion(R=1.0)
+    B.flow_step(n)
+    assert np.abs(_np(B.members[0].get_field()) - ref).max() <= rel * np.abs(ref).max()
+    B.close()
