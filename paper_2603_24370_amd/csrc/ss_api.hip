@@ -460,9 +460,9 @@ void launch_lattice_pass(const ss_ctx* c, PassArgs<T> a, Run& r, hipStream_t s) 
   int groups = c->L.nlaunch;  // workgroups launched = partials written
   if (c->grad_mode == SS_GRAD_EXACT) {
     // exact-gradient passes: one tile shape (64 x 16), the layout of tile 0
-    if (c->theory == SS_THEORY_AH) launch_exact<T, kAH, PASS>(a, groups, s);
-    else if (c->theory == SS_THEORY_CM) launch_exact<T, kCM, PASS>(a, groups, s);
-    else launch_exact<T, kBS, PASS>(a, groups, s);
+    if (c->theory == SS_THEORY_AH) groups = launch_exact<T, kAH, PASS>(a, groups, s);
+    else if (c->theory == SS_THEORY_CM) groups = launch_exact<T, kCM, PASS>(a, groups, s);
+    else groups = launch_exact<T, kBS, PASS>(a, groups, s);
   } else {
     int tile = c->shape;
     if constexpr (fixed_tile(PASS)) {

@@ -55,9 +55,9 @@ inline int choose_seg(int ntx, int nty, int groups) {
 template <class T, int TH, int PASS>
 int launch_tiled(int tile, const PassArgs<T>& a, int nlaunch, hipStream_t s);
 
-// A pass of the exact-gradient form.
+// A pass of the exact-gradient form, likewise.
 template <class T, int TH, int PASS>
-void launch_exact(const PassArgs<T>& a, int groups, hipStream_t s);
+int launch_exact(const PassArgs<T>& a, int nlaunch, hipStream_t s);
 
 // Fused stages 2-4 on the layout of tile 0 (FP32 only) or 1.
 template <class T, int TH>

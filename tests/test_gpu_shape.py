@@ -128,3 +128,35 @@ def test_a_chiral_magnet_batch_runs_the_faster_shape(ss, orc, dtype, integ, memb
     B.flow_step(n)
     assert np.abs(_np(B.members[0].get_field()) - ref).max() <= rel * np.abs(ref).max()
     B.close()
+
+
+# more tiles than the workgroups of an exact-gradient pass: 16 x 36 and 21 x 65 of 64 x 16 sites
+@pytest.mark.parametrize("dtype,Nx,Ny", [("f64", 1021, 571), ("f32", 1291, 1033)])
+@pytest.mark.parametrize("integ", ["rk4", "vv", "gf"])
+@pytest.mark.parametrize("theory", [AH, "chiral_magnet"])
+def test_exact_gradient_flow_of_several_tiles_per_workgroup(ss, orc, theory, integ, dtype, Nx, Ny):
+    h, n = 0.17, 3
+    par = [1.0] if theory == AH else [1.0, 1.0, 0.1, 0.6]
+    print(f"[case] exact several tiles {theory} {integ} {dtype} {Nx}x{Ny}", flush=True)
+    if theory == AH:
+        f = I.ah_vortex_ansatz(Nx, Ny, h, [(3.4, -2.3)]) + I.noise(7, 4, Nx, Ny, 1e-3)
+    else:
+        f = I.renormalise_interior(I.cm_skyrmion_ansatz(Nx, Ny, h, R=4.0) + I.noise(7, 3, Nx, Ny, 1e-3))
+    if dtype == "f32":
+        f = f.astype(np.float32).astype(np.float64)
+    phi_r, v_r, E_r, na_r = orc.flow(theory, f, np.zeros_like(f), h, par, n, scheme=integ, mode=orc.GRAD_EXACT)
+    rel = 1e-11 if dtype == "f64" else 1e-5
+    s = ss.Solver(theory, Nx, Ny, h, par, dtype=dtype, grad_mode=ss.SS_GRAD_EXACT)
+    s.set_integrator(integ)
+    s.set_field(f)
+    info = s.flow_step(n)
+    phi, vel = (_np(x) for x in s.get_field(velocity=True))
+    assert np.abs(phi - phi_r).max() <= rel * np.abs(phi_r).max()
+    assert np.abs(vel - v_r).max() <= rel * max(np.abs(phi_r).max(), 1.0)
+    assert info["step"] == n and info["n_arrests"] == na_r
+    assert info["energy"] == pytest.approx(orc.energy(theory, phi, h, par), rel=1e-12)
+    # a relaxation that stops there leaves the field as its later passes found it
+    s.set_field(f)
+    s.minimise(grad_tol=0.0, max_steps=n)
+    assert np.array_equal(_np(s.get_field()), phi)
+    s.close()
