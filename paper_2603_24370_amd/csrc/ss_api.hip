@@ -466,8 +466,10 @@ void launch_lattice_pass(const ss_ctx* c, PassArgs<T> a, Run& r, hipStream_t s) 
   } else {
     int tile = c->shape;
     if constexpr (fixed_tile(PASS)) {
-      // once per run, or after an arrest: tile 0 whatever the context's tile
-      tile = sizeof(T) == 8 && small_lattice(c->Nx, c->Ny) ? kSmallShape : 0;
+      // once per run, or after an arrest: tile 0 whatever the context's tile, and 64 x 4
+      // in FP64 on small lattices while none is selected (64 x 4 rounds otherwise: a run
+      // on a selected tile has the bits of a batch's member on that tile)
+      tile = sizeof(T) == 8 && !c->selected && small_lattice(c->Nx, c->Ny) ? kSmallShape : 0;
       Layout L = c->L;
       set_tiles(L, c->Nx, c->Ny, tile);
       a.ntx = L.ntx;

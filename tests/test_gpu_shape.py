@@ -160,3 +160,40 @@ def test_exact_gradient_flow_of_several_tiles_per_workgroup(ss, orc, theory, int
     s.minimise(grad_tol=0.0, max_steps=n)
     assert np.array_equal(_np(s.get_field()), phi)
     s.close()
+
+
+@pytest.mark.parametrize("theory", [AH, "chiral_magnet"])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("integ,plan,tiles", [("vv", 1, (0, 1)), ("gf", 1, (0, 1, 2, 3)), ("rk4", 0, (0, 1, 2, 3))])
+def test_a_member_and_a_lone_lattice_on_a_selected_tile_are_the_same_bits(ss, theory, dtype, integ, plan, tiles):
+    """Stage passes and one-pass integrators (a batch runs velocity Verlet's half-step form)."""
+    h, n, sizes = 0.2, 12, [(64, 64), (129, 70), (300, 260), (700, 400)]
+    par = [1.3] if theory == AH else [1.0, 1.0, 0.1, 0.6]
+    print(f"[case] member and lone lattice {theory} {dtype} {integ}", flush=True)
+
+    def start(s, nx, ny):
+        if theory == AH:
+            s.init_vortices([(0.03 * nx, 0.1), (-0.03 * nx, -0.02 * ny)], seed=3, noise_amp=1e-3)
+        else:
+            s.init_skyrmion(R=min(nx, ny) * h / 8, seed=3, noise_amp=1e-3)
+
+    B = ss.Batch(theory, [(nx, ny, h, par) for nx, ny in sizes], dtype=dtype)
+    B.set_integrator(integ)
+    B.set_plan(plan)
+    for tile in tiles:
+        B.set_tile(tile)
+        for m, (nx, ny) in zip(B.members, sizes):
+            start(m, nx, ny)
+        B.flow_step(n)
+        for m, (nx, ny) in zip(B.members, sizes):
+            s = ss.Solver(theory, nx, ny, h, par, dtype=dtype)
+            s.set_integrator(integ)
+            s.set_plan(plan)
+            s.set_vv_form("half_step")
+            s.set_tile(tile)
+            start(s, nx, ny)
+            s.flow_step(n)
+            for a, b in zip(m.get_field(velocity=True), s.get_field(velocity=True)):
+                assert np.array_equal(_np(a), _np(b)), (tile, nx, ny)
+            s.close()
+    B.close()
