@@ -490,9 +490,14 @@ void launch_lattice_pass(const ss_ctx* c, PassArgs<T> a, Run& r, hipStream_t s) 
 }
 
 // Fused stages 2-4 run on 64 x 16 tiles (tile 0) or 64 x 8 tiles (tile 1), two
-// rows per thread. FP32 follows the context's tile when it is one of these two
-// (so the autotuner can pick either) and uses 64 x 16 otherwise; FP64 always
-// uses 64 x 8 (its LDS planes are twice as large).
+// rows per thread; FP64 always uses 64 x 8 (its LDS planes are twice as large). FP32
+// follows the selected tile where it is one of these two and runs on 64 x 16 otherwise, and
+// while none is selected: the faster one up to some 10^6 sites, where the ring of 64 x 8
+// tiles costs more than their third workgroup per CU hides, but not above, where the
+// autotuner picks 64 x 8. us per step on 64 x 16 / 64 x 8, Abelian Higgs 512^2 18.5 /
+// 20.0, 1024^2 49.7 / 50.4, 2048^2 172 / 161, 4096^2 680 / 619; chiral magnet 18.6 / 20.5,
+// 43.8 / 45.9, 148 / 144, 568 / 538; baby Skyrme 21.2 / 24.1, 54.6 / 57.3, 191 / 185,
+// 736 / 696.
 template <class T>
 int fused_layout_tile(int tile) {
   if (sizeof(T) == 8) return 1;

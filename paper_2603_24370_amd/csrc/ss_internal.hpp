@@ -32,8 +32,8 @@ struct DevStatus {
   int nonfinite;         // non-finite count of the last test
   int window;
   int minimise;          // 1: the arrest pass applies the stop rules
-  unsigned counter;      // last-block counter of the arrest pass
-  unsigned counter_obs;  // last-block counter of the observable passes
+  unsigned counter;      // these two are always 0: places in the checkpoint blob, which
+  unsigned counter_obs;  // holds this struct
   int fresh;             // set when a run is armed: its first test is of the field
                          // the last run ended on (or a fresh one), whose arrest is decided
   double e_target;       // minimise stops once E <= e_target (-inf: never)

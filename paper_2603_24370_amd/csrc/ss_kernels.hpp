@@ -1059,7 +1059,6 @@ __device__ __forceinline__ void tile_body_exact(const InstView<T>& V, int cur, b
 // (thread 0 of the finalising workgroup). E is already multiplied by h^2.
 template <int PASS>
 __device__ __forceinline__ void finalise_status(DevStatus* st, double E, double gmax, int nfin) {
-  st->counter = 0u;
   if (PASS == kEval) {
     st->eval_E = E;
     st->eval_gmax = gmax;
@@ -1181,8 +1180,10 @@ static __global__ void __launch_bounds__(256) settle_status(Link link, double h)
 // apart from the loads and each other, and the LDS holds three stage points. (With
 // phi, v, a1 and a2 staged, and S3 and S4 formed from them between barriers, 4096^2
 // Abelian Higgs FP32 took 768 us per step, now 673; 1024^2 56.6, now 50.7; chiral magnet
-// 54.6, now 44.6.) What bounds it is its registers: one 512-thread workgroup to a CU, at
-// 229 per lane; capped at 168 or 128 for more, it spills and takes twice as long.
+// 54.6, now 44.6.) What bounds it is its registers: at 129 to 168 per lane in FP32 a CU
+// holds one 512-thread workgroup of a 64 x 16 tile, or three of 256 threads on 64 x 8 (137
+// to 167); capped at 128 for two, the Abelian Higgs pass on 64 x 16 spills and takes twice
+// as long. In FP64 a CU holds one workgroup of 256 threads, two of the chiral magnet's.
 
 // Jets of one site from an LDS plane with row length LX, arithmetic as column_jets.
 template <class T, int LX, bool MIXED>
@@ -1471,9 +1472,9 @@ __device__ __forceinline__ void tile_body_fused(const InstView<T>& V, int cur, b
   __syncthreads();
 }
 
-// Waves per SIMD the fused pass is compiled for. With FP32 fields two
-// workgroups share a CU (LDS), so registers are capped at 256 per lane; with
-// FP64 fields the LDS of one workgroup fills the CU and no cap applies.
+// Waves per SIMD the fused pass is compiled for: two in FP32, that is at most 256 VGPRs
+// per lane, which it uses 129 to 168 of (see above); no cap in FP64, whose Abelian Higgs
+// and baby Skyrme passes take all 256.
 template <class T>
 struct FusedWaves {
   static constexpr int value = sizeof(T) == 4 ? 2 : 1;

@@ -246,12 +246,6 @@ def main(argv=None):
             "ratio": round((rs["read_GB"] + rs["write_GB"]) / (rs["alg_read_GB"] + rs["alg_write_GB"]), 3),
             "kernel": rs["kernel"]}
 
-    fin = stats.get("ss::pass_finalise<0>")
-    if fin is not None:
-        md += ["", "Each reducing pass is followed by `ss::pass_finalise<PASS>` (one workgroup summing the "
-               "workgroup", f"partials and updating the status): {float(fin['AverageNs']) / 1e3:.1f} us per call "
-               f"({int(fin['Calls'])} calls of the energy pass in the stats run), included in the P1 time that",
-               "`bench.py` reports through `ss_time_passes`."]
     with open(args.out_md, "w") as fh:
         fh.write("\n".join(md) + "\n")
     rec = {"kernel_source": bench.kernel_source_hash(), "scale": {"FETCH_SIZE": fs, "WRITE_SIZE": ws},
