@@ -101,10 +101,11 @@ def restart_summary(stats_dirs, F, W, fs, ws):
     idle = [x for x in durs if x <= 0.2 * max(durs)]
     fv, wv = F[k]["FETCH_SIZE"], W[k]["WRITE_SIZE"]
     rd = wr = None  # no arrest in the counter runs: no working dispatch to read
-    if max(fv) > 0 and max(wv) > 0:
+    alg = SITES * C * ELEM / 1e9
+    # (a dispatch that returns at once has read the pending test's partials)
+    if min(fs * max(fv), ws * max(wv)) * KIB / 1e9 > 0.2 * alg:
         rd = fs * statistics.median([v for v in fv if v > 0.2 * max(fv)]) * KIB / 1e9
         wr = ws * statistics.median([v for v in wv if v > 0.2 * max(wv)]) * KIB / 1e9
-    alg = SITES * C * ELEM / 1e9
     return {"kernel": k, "dispatches": len(durs), "working": len(work), "us_working": statistics.mean(work),
             "us_idle": statistics.mean(idle) if idle else 0.0, "read_GB": rd, "write_GB": wr, "alg_read_GB": alg,
             "alg_write_GB": alg}

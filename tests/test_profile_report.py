@@ -56,3 +56,23 @@ def test_traffic_is_scaled_by_the_copy_and_matches_the_algorithmic_bytes(tmp_pat
     assert t["ratio"] == pytest.approx((rd + wr) / fused_alg, abs=1e-3)
     text = md.read_text()
     assert "P234 (tile 64x16, 2 rows/thread; chosen)" in text and "600.0" in text
+
+
+@pytest.mark.parametrize("arrest", [False, True])
+def test_restart_traffic_is_that_of_a_dispatch_that_worked(tmp_path, arrest):
+    """The others read the pending test's partials (some 50 KB) and return."""
+    k = R.kernel_name("VVR", 0)
+    kib = R.SITES * R.C * R.ELEM / 1024
+    F = {k: {"FETCH_SIZE": [24.0, kib / 2 if arrest else 24.0, 24.0]}}
+    W = {k: {"WRITE_SIZE": [0.1, kib if arrest else 0.1, 0.1]}}
+    with open(tmp_path / "run_kernel_trace.csv", "w", newline="") as fh:
+        w = csv.DictWriter(fh, fieldnames=["Kernel_Name", "Start_Timestamp", "End_Timestamp"])
+        w.writeheader()
+        for us in (4, 120, 4):
+            w.writerow({"Kernel_Name": f"void {k}(int)", "Start_Timestamp": 0, "End_Timestamp": 1000 * us})
+    r = R.restart_summary([str(tmp_path)], F, W, 2.0, 1.0)
+    assert r["working"] == 1 and r["us_working"] == 120 and r["us_idle"] == 4
+    if arrest:
+        assert r["read_GB"] == pytest.approx(r["alg_read_GB"]) and r["write_GB"] == pytest.approx(r["alg_write_GB"])
+    else:
+        assert r["read_GB"] is None and r["write_GB"] is None
