@@ -259,3 +259,20 @@ def test_default_tile_follows_the_integrator(ss, theory, dtype, integ):
         assert (a - b).abs().max() <= rel * b.abs().max(), (nx, ny)
         s.close()
     B.close()
+
+
+@pytest.mark.parametrize("n", [1, 2])
+@pytest.mark.parametrize("integ", ["rk4", "vv", "gf"])
+def test_step_information_is_each_members_own(ss, integ, n):
+    """A lone member's is read without the launch that gathers several."""
+    insts = _members(0, n, sides=[40, 71])
+    B = ss.Batch(AH, [(m.Nx, m.Ny, m.h, m.params) for m in insts], dtype="f64")
+    B.set_integrator(integ)
+    for m, mem in zip(insts, B.members):
+        mem.set_field(m.field())
+    infos = B.flow_step(3)
+    assert [i["step"] for i in infos] == [3] * n and infos == [mem.info() for mem in B.members]
+    rc, infos = B.minimise(grad_tol=0.0, max_steps=9)
+    for i, mem in zip(infos, B.members):
+        assert i["reason"] == "max_steps" and {k: i[k] for k in mem.info()} == mem.info()
+    B.close()
