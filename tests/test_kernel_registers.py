@@ -41,13 +41,23 @@ def _registers(tmp_path):
         notes = subprocess.run([READELF, "--notes", str(p)], capture_output=True, text=True, check=True).stdout
         for kernel in notes.split("- .agpr_count:")[1:]:
             name = re.search(r"\.name:\s+(\S+)", kernel).group(1)
-            out[name] = int(re.search(r"\.vgpr_count:\s+(\d+)", kernel).group(1))
+            out[name] = tuple(int(re.search(rf"\.{k}:\s+(\d+)", kernel).group(1)) for k in ("vgpr_count", "vgpr_spill_count"))
     return out
 
 
 @pytest.mark.skipif(READELF is None, reason="needs llvm-readelf")
 def test_a_batch_keeps_four_waves_per_simd(tmp_path):
     """The FP32 passes of a batch on its default shapes (64 x 16 and 64 x 8 sites, two rows per thread)."""
-    regs = {n: v for n, v in _registers(tmp_path).items() if re.match(r"_ZN2ss10batch_passIfLi\d+ELi\d+ELi64ELi(16|8)ELi2EE", n)}
+    regs = {n: v for n, (v, _) in _registers(tmp_path).items() if re.match(r"_ZN2ss10batch_passIfLi\d+ELi\d+ELi64ELi(16|8)ELi2EE", n)}
     assert len(regs) == 2 * 2 * 11  # theories, shapes, passes
     assert {n: v for n, v in regs.items() if v > 128} == {}
+
+
+# Abelian Higgs passes on tall tiles, and the registers that they spilled before their rows
+# went on scalar bases
+@pytest.mark.parametrize("kernel,spills", [("stage_passIdLi0ELi2ELi64ELi32ELi4EE", 25),
+                                           ("stage_passIdLi0ELi3ELi64ELi32ELi4EE", 57)])
+@pytest.mark.skipif(READELF is None, reason="needs llvm-readelf")
+def test_tall_tiles_spill_no_more_than_they_need(kernel, spills, tmp_path):
+    (name, (_, n)), = ((k, v) for k, v in _registers(tmp_path).items() if kernel in k)
+    assert n <= spills, name
