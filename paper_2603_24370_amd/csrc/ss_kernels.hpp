@@ -1618,8 +1618,13 @@ __attribute__((amdgpu_waves_per_eu(StageWaves<T, TH, PASS, RY>::value))) batch_p
     const bool arrest = uses_arrest(PASS) ? (uniform(st->arrest) != 0) : false;
     // The Abelian Higgs passes hold the descriptor, which the tiles' stores may alias
     // (256 members FP32, velocity Verlet on 64 x 8: 351 us per step, 336 held); in the
-    // chiral magnet's FP32 passes that costs a wave per SIMD (385, 432).
-    typedef typename Held<TH == kAH, InstView<T>>::type View;
+    // chiral magnet's FP32 passes that costs a wave per SIMD (385, 432), on 64 x 16 in FP32
+    // velocity Verlet spills for it (8 members of 512^2 59.7 us per step held, 55.1) and the
+    // separate stages are no faster (162, 155), on 64 x 32 in FP64 all passes spill more
+    // (RK4 in stages 1.03 times the time before any were held, 0.98 without).
+    constexpr bool kHold = TH == kAH && !(sizeof(T) == 8 && TY == 32) &&
+                           !(sizeof(T) == 4 && TY == 16 && RY == 2 && (PASS == kVV || STAGED));
+    typedef typename Held<kHold, InstView<T>>::type View;
     View V = I.V;
     double e_acc = 0.0, g_acc = 0.0;
     int nf = 0;

@@ -53,11 +53,14 @@ def test_a_batch_keeps_four_waves_per_simd(tmp_path):
     assert {n: v for n, v in regs.items() if v > 128} == {}
 
 
-# Abelian Higgs passes on tall tiles, and the registers that they spilled before their rows
-# went on scalar bases
+# Abelian Higgs passes, and the registers that they spilled before their rows went on scalar
+# bases and a batch's descriptors were held in registers
 @pytest.mark.parametrize("kernel,spills", [("stage_passIdLi0ELi2ELi64ELi32ELi4EE", 25),
-                                           ("stage_passIdLi0ELi3ELi64ELi32ELi4EE", 57)])
+                                           ("stage_passIdLi0ELi3ELi64ELi32ELi4EE", 57),
+                                           ("batch_passIfLi0ELi7ELi64ELi16ELi2EE", 5),
+                                           ("batch_passIdLi0ELi2ELi64ELi32ELi4EE", 25),
+                                           ("batch_passIdLi0ELi3ELi64ELi32ELi4EE", 69)])
 @pytest.mark.skipif(READELF is None, reason="needs llvm-readelf")
-def test_tall_tiles_spill_no_more_than_they_need(kernel, spills, tmp_path):
+def test_passes_spill_no_more_than_they_need(kernel, spills, tmp_path):
     (name, (_, n)), = ((k, v) for k, v in _registers(tmp_path).items() if kernel in k)
     assert n <= spills, name
